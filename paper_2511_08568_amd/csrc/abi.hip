@@ -312,8 +312,7 @@ struct recmg_cache {
     hipStream_t fwd_stream = nullptr, plc_stream = nullptr;
     bool fwd_ev = false, plc_ev = false;  // the events below were recorded
     hipEvent_t ev_src = nullptr;   // latest forward: after its dedup, probe, sources and coverage
-    hipEvent_t ev_pool = nullptr;  // latest forward: after its pooled kernel
-    hipEvent_t ev_fwd = nullptr;   // latest forward: after all its kernels
+    hipEvent_t ev_fwd = nullptr;   // latest forward: after all its kernels (the pooled kernel, or a few us later)
     hipEvent_t ev_plc = nullptr;   // latest placement: after all its kernels but the fill
     hipEvent_t ev_fill[2] = {nullptr, nullptr};  // fill of the latest placement of each parity
     bool fill_rec[2] = {false, false};
@@ -365,7 +364,7 @@ struct recmg_cache {
     // Every event the handle created, also when init stops half way.  The
     // caller of delete has synchronised (or nothing was enqueued).
     ~recmg_cache() {
-        for (hipEvent_t e : {ev_src, ev_pool, ev_fwd, ev_plc, ev_fill[0], ev_fill[1], ev_ready, ev_copied, ev_np})
+        for (hipEvent_t e : {ev_src, ev_fwd, ev_plc, ev_fill[0], ev_fill[1], ev_ready, ev_copied, ev_np})
             if (e) (void)hipEventDestroy(e);
         for (const Mark &m : marks) {
             if (m.a) (void)hipEventDestroy(m.a);
@@ -657,7 +656,7 @@ int32_t early_gather(recmg_cache_t *c, hipStream_t cs) {
 // stream; the compute stream waits for the copies.  The zero-copy tables'
 // misses are fetched by the kernel, launched once the host has read what it
 // needs (so that its waits do not wait for the kernel), beside the gather.
-int32_t staged_fetch(recmg_cache_t *c, hipStream_t s) {
+int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
     const int T = c->T;
     HIP_TRY(hipMemcpyAsync(c->h_st.data(), c->g.st, sizeof(TState) * T, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(c->h_tstart.data(), c->g.tstart, 8 * (T + 1), hipMemcpyDeviceToHost, s));
@@ -667,7 +666,7 @@ int32_t staged_fetch(recmg_cache_t *c, hipStream_t s) {
     auto zero_copy_fetch = [&]() -> int32_t {
         if (c->has_zc) {
             DispatchTimer dt(c, RECMG_STAGE_FWD_FETCH, true);
-            launch_fetch(c->g, s, dt.a, dt.b);
+            launch_fetch(c->g, log_slot, s, dt.a, dt.b);
             dt.issued();
         }
         return RECMG_OK;
@@ -1029,7 +1028,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     HIP_TRY(hipDeviceSynchronize());
 
     c->copy_stream = static_cast<hipStream_t>(cfg->copy_stream);
-    for (hipEvent_t *e : {&c->ev_src, &c->ev_pool, &c->ev_fwd, &c->ev_plc, &c->ev_fill[0], &c->ev_fill[1]})
+    for (hipEvent_t *e : {&c->ev_src, &c->ev_fwd, &c->ev_plc, &c->ev_fill[0], &c->ev_fill[1]})
         HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
     if (c->has_staged) {
         char *hs = static_cast<char *>(cfg->host_staging);
@@ -1104,11 +1103,11 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
 
     {
         StageTimer tm(c, RECMG_STAGE_PLC_CLASSIFY, s);
-        launch_plc_prep(g, prefetch_offsets, num_prefetch, p.have_fwd, s);
+        if (num_prefetch == 0) launch_plc_prep(g, prefetch_offsets, num_prefetch, p.have_fwd, s);
         if (p.prio && cache_bits && c->have_fwd) launch_plc_bits(g, cache_bits, c->last_n, s);
         if (p.lfu && c->have_fwd) launch_plc_freq(g, c->last_n, s);
         if (num_prefetch > 0) {
-            launch_mark(g, prefetch_rows, g.pstart, num_prefetch, s);
+            launch_mark_prefetch(g, prefetch_rows, prefetch_offsets, num_prefetch, p.have_fwd, s);
             launch_dedup(g, EMIT_PREFETCH,
                          reinterpret_cast<int32_t *>(reinterpret_cast<char *>(g.st) + offsetof(TState, pcount)),
                          (int)(sizeof(TState) / 4), 0, c->max_nblk, s);
@@ -1162,7 +1161,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // placement on a stream of its own overlaps the previous fill); that
     // forward's pooled kernel waits for it.
     if (fs != s) HIP_TRY(hipStreamWaitEvent(fs, c->ev_plc, 0));
-    if (c->fwd_ev && c->fwd_stream != fs) HIP_TRY(hipStreamWaitEvent(fs, c->ev_pool, 0));
+    if (c->fwd_ev && c->fwd_stream != fs) HIP_TRY(hipStreamWaitEvent(fs, c->ev_fwd, 0));
     // The previous placement's fill may still write slots this placement has
     // just freed and handed to other rows.  On one fill stream the two fills
     // run in order; on different ones (no copy stream, placements on
@@ -1244,17 +1243,19 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
     const int32_t stamp = (int32_t)c->forwards;
     c->cur ^= 1;  // the other staging buffer: a pending fill may still read this one
     c->g.staging = c->stage[c->cur];
+    const int64_t log_slot = c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1;
     {
         StageTimer tm(c, RECMG_STAGE_FWD_DEDUP, s);
-        launch_fwd_prep(g, offsets, (int32_t)B, n, s);
-        if (n > 0) {
-            launch_mark(g, indices, g.tstart, n, s);
+        const bool small = n > 0 && small_batch(c->T, n, c->max_nblk);
+        if (small) launch_fwd_small(g, indices, offsets, (int32_t)B, n, stamp, c->plc_np > 0, c->max_nblk, s);
+        else if (n == 0) launch_fwd_prep(g, offsets, (int32_t)B, n, s);
+        else {
+            launch_mark_forward(g, indices, offsets, (int32_t)B, n, s);
             launch_dedup(g, EMIT_FORWARD,
                          reinterpret_cast<int32_t *>(reinterpret_cast<char *>(g.st) + offsetof(TState, ucount)),
                          (int)(sizeof(TState) / 4), stamp, c->max_nblk, s);
-            launch_fwd_probe(g, stamp, n, s);
+            launch_fwd_probe(g, stamp, n, std::max<int64_t>(c->plc_np, 0), s);
             launch_fwd_src(g, indices, n, s);
-            if (c->plc_np >= 0) launch_fwd_cover(g, stamp, c->plc_np, s);
         }
     }
     HIP_TRY(hipEventRecord(c->ev_src, s));  // a placement on another stream may start here
@@ -1262,9 +1263,9 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
         StageTimer tm(c, RECMG_STAGE_FWD_FETCH, s);
         if (!c->has_staged) {
             DispatchTimer dt(c, RECMG_STAGE_FWD_FETCH, true);
-            launch_fetch(g, s, dt.a, dt.b);
+            launch_fetch(g, log_slot, s, dt.a, dt.b);
             dt.issued();
-        } else if ((rc = staged_fetch(c, s))) {  // launches the zero-copy tables' fetch too
+        } else if ((rc = staged_fetch(c, log_slot, s))) {  // launches the zero-copy tables' fetch too
             return rc;
         }
     }
@@ -1289,9 +1290,9 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
                     (int)c->pool_launches.size(), a, b, s);
         if (a) c->marks.push_back({RECMG_STAGE_FWD_POOL, a, b});
     }
-    HIP_TRY(hipEventRecord(c->ev_pool, s));  // the next fill may overwrite slots from here on
-    launch_fwd_finalize(g, c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1, s);
-    HIP_TRY(hipEventRecord(c->ev_fwd, s));
+    // the fetch has published the counters; a forward without one does it here
+    if (n == 0 || !c->has_zc) launch_fwd_finalize(g, log_slot, s);
+    HIP_TRY(hipEventRecord(c->ev_fwd, s));  // the next fill may overwrite slots, the next forward the batch's arrays
     HIP_TRY(hipGetLastError());
     guard.done = true;
     c->forwards++;

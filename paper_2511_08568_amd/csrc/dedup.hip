@@ -93,56 +93,87 @@ __global__ void __launch_bounds__(kBlock) k_mark(DGlobal g, const int32_t *__res
     }
 }
 
-constexpr int kOwnThreads = 1024, kOwnUnroll = 8;
+constexpr int kOwnThreads = 1024;
 static_assert(kOwnSliceWords * 32 == 1 << 20, "a slice holds 2^20 bitmap positions");
 static_assert(kOwnSliceBlocks <= kOwnThreads && kOwnSliceWords % kWordsPerBlock == 0, "slice = whole bitmap blocks");
 
-// Block (slice, table) of the LDS marking: grid (g.own_slices, T); blocks of
-// tables that are not owned, and slices past a table's bitmap, exit at once.
-// Writes the slice's non-zero words into the (all-zero) bitmap and blocksum of
-// each of its bitmap blocks.  Range errors are raised by slice 0 only.
+// The first kernel of a forward's or a placement's dedup.  Block (slice, table)
+// of a grid (slices, T).  Slice 0 of every table checks the call's offsets and
+// sets up the table's state (forward_prep / placement_prep); each block of an
+// owned table then marks its slice in LDS: the slice's non-zero words go to the
+// (all-zero) bitmap and the popcount of each of its bitmap blocks to blocksum.
+// Blocks of other tables, and slices past a table's bitmap, end there.
+// `offs`: bag offsets with B per table, or the prefetch list's with B = 1.  A
+// block whose own range is malformed raises the error and reads no id; range
+// errors of ids are raised by slice 0 only.
+// A block reads its ids 16 bytes per lane, four loads in flight, with 32-bit
+// offsets: on 26 tables of 123,000 ids each (one slice per table, so 26 blocks)
+// it is bound by the instructions per id on those CUs.
+template <int MODE>
 __global__ void __launch_bounds__(kOwnThreads) k_mark_own(DGlobal g, const int32_t *__restrict__ keys,
-                                                          const int64_t *__restrict__ starts) {
+                                                          const int64_t *__restrict__ offs, int32_t B, int64_t n,
+                                                          int32_t have_fwd) {
     __shared__ uint4 s_bm[kOwnSliceWords / 4];
     __shared__ int s_cnt[kOwnSliceBlocks];
     __shared__ int s_err;
     const int t = blockIdx.y, sl = blockIdx.x;
     const DTable &tb = g.tabs[t];
     const int nblk = tb.bm_nblk;
-    if (!owns_bitmap(nblk) || sl * kOwnSliceBlocks >= nblk) return;  // block-uniform
-    // the error word is read once: slice 0 of another table may set it meanwhile,
-    // and the waves of the block must agree before its barriers
+    const bool mark = owns_bitmap(nblk) && sl * kOwnSliceBlocks < nblk;  // block-uniform
+    if (!mark && sl) return;
+    // the error word is read once: another block may set it meanwhile, and the
+    // waves of the block must agree before its barriers
     if (threadIdx.x == 0) s_err = *g.err;
+    const int64_t lo = offs[(int64_t)t * B], hi = offs[(int64_t)(t + 1) * B];
+    if (sl == 0) {
+        if (MODE == EMIT_FORWARD) forward_prep(g, t, offs, B, n);
+        else placement_prep(g, t, offs, n, have_fwd);
+    }
+    if (!mark) return;  // block-uniform
     const int sblk = nblk - sl * kOwnSliceBlocks < kOwnSliceBlocks ? nblk - sl * kOwnSliceBlocks : kOwnSliceBlocks;
     const int nq = sblk * (kWordsPerBlock / 4);  // uint4 words of the slice
     for (int k = threadIdx.x; k < nq; k += kOwnThreads) s_bm[k] = make_uint4(0u, 0u, 0u, 0u);
     if (threadIdx.x < kOwnSliceBlocks) s_cnt[threadIdx.x] = 0;
     __syncthreads();
-    if (s_err) return;  // block-uniform
+    if (s_err || lo < 0 || hi < lo || hi > n) return;  // block-uniform; forward_prep / placement_prep raise the latter
     uint32_t *bm = reinterpret_cast<uint32_t *>(s_bm);
-    const int64_t lo = starts[t], hi = starts[t + 1];
-    const int64_t rows = tb.rows;
+    const uint32_t rows = (uint32_t)tb.rows;  // < 2^31
     const int32_t ns = tb.nsets, qb = tb.qbits;
-    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += (int64_t)kOwnThreads * kOwnUnroll) {
-        int32_t r[kOwnUnroll];
-#pragma unroll
-        for (int u = 0; u < kOwnUnroll; ++u) {
-            const int64_t i = i0 + (int64_t)u * kOwnThreads;
-            r[u] = i < hi ? keys[i] : 0;
+    bool bad = false;
+    auto mark_id = [&](uint32_t r) {
+        if (r >= rows) {  // negative ids too
+            bad = true;
+            return;
         }
+        const uint32_t pos = bm_pos(ns, qb, (int32_t)r);
+        if ((int)(pos >> 20) != sl) return;  // the position's slice
+        const uint32_t w = (pos >> 5) & (kOwnSliceWords - 1), bit = 1u << (pos & 31);
+        if (!(bm[w] & bit)) atomicOr(&bm[w], bit);
+    };
+    // ids before the first 16-byte boundary, whole 16-byte groups, the rest
+    const uint32_t cnt = (uint32_t)(hi - lo);
+    const int32_t *ids = keys + lo;
+    uint32_t head = (uint32_t)((16 - (reinterpret_cast<uintptr_t>(ids) & 15)) & 15) / 4;
+    if (head > cnt) head = cnt;
+    const uint32_t nv = (cnt - head) / 4, tail0 = head + 4 * nv;
+    constexpr uint32_t kV = 4;
+    for (uint32_t v0 = threadIdx.x; v0 < nv; v0 += kV * kOwnThreads) {
+        uint4 v[kV];
 #pragma unroll
-        for (int u = 0; u < kOwnUnroll; ++u) {
-            if (i0 + (int64_t)u * kOwnThreads >= hi) continue;
-            if (r[u] < 0 || (int64_t)r[u] >= rows) {
-                if (sl == 0) atomicOr(g.err, ERR_RANGE);
-                continue;
+        for (uint32_t u = 0; u < kV; ++u)
+            if (v0 + u * kOwnThreads < nv) v[u] = gload16(ids + head + 4 * (v0 + u * kOwnThreads));
+#pragma unroll
+        for (uint32_t u = 0; u < kV; ++u)
+            if (v0 + u * kOwnThreads < nv) {
+                mark_id(v[u].x);
+                mark_id(v[u].y);
+                mark_id(v[u].z);
+                mark_id(v[u].w);
             }
-            const uint32_t pos = bm_pos(ns, qb, r[u]);
-            if ((int)(pos >> 20) != sl) continue;  // the position's slice
-            const uint32_t w = (pos >> 5) & (kOwnSliceWords - 1), bit = 1u << (pos & 31);
-            if (!(bm[w] & bit)) atomicOr(&bm[w], bit);
-        }
     }
+    const uint32_t rest = head + (cnt - tail0);  // at most 6
+    if (threadIdx.x < rest) mark_id((uint32_t)ids[threadIdx.x < head ? threadIdx.x : tail0 + threadIdx.x - head]);
+    if (bad && sl == 0) atomicOr(g.err, ERR_RANGE);
     __syncthreads();
     uint4 *gbm = reinterpret_cast<uint4 *>(tb.bitmap + (int64_t)sl * kOwnSliceWords);
     for (int k = threadIdx.x; k < nq; k += kOwnThreads) {
@@ -169,9 +200,13 @@ __global__ void __launch_bounds__(kBlock) k_mark_resident(DGlobal g) {
     }
 }
 
+// The table of bitmap block blk (T <= blockDim.x): every table's bounds are
+// tested at once, where a binary search would chain its loads.  Ends with a
+// barrier.
 __device__ __forceinline__ int block_table(const DGlobal &g, int blk) {
     __shared__ int s_t;
-    if (threadIdx.x == 0) s_t = find_seg32(g.bm_block_start, g.T, blk);
+    const int t = threadIdx.x;
+    if (t < g.T && g.bm_block_start[t] <= blk && blk < g.bm_block_start[t + 1]) s_t = t;
     __syncthreads();
     return s_t;
 }
@@ -189,9 +224,9 @@ __global__ void __launch_bounds__(kBlock) k_bm_count(DGlobal g) {
     if (threadIdx.x == 0) g.blocksum[blk] = s;
 }
 
-// One block per table: exclusive scan of the table's block counts.
-// counts[t * count_stride] receives the table's total.
-__global__ void __launch_bounds__(1024) k_bm_scan(DGlobal g, int32_t *counts, int count_stride) {
+// One block per table: exclusive scan of the table's block counts (for tables
+// of more blocks than k_bm_emit adds up by itself).
+__global__ void __launch_bounds__(1024) k_bm_scan(DGlobal g) {
     if (*g.err) return;
     __shared__ int tmp[16];
     const int t = blockIdx.x;
@@ -205,90 +240,48 @@ __global__ void __launch_bounds__(1024) k_bm_scan(DGlobal g, int32_t *counts, in
         if (k < nb) g.blockoff[b0 + k] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) counts[(int64_t)t * count_stride] = carry;
 }
 
-// Write the distinct ids in ascending order (U, PU or the resident dump).
-template <int MODE>
-__global__ void __launch_bounds__(kBlock) k_bm_emit(DGlobal g, int32_t stamp) {
+// Write the distinct ids in ascending order (U, PU or the resident dump), one
+// bitmap word per thread.  SCANNED: the block's first rank comes from k_bm_scan;
+// else the block adds up the counts of the table's blocks before it (at most
+// kEmitThreads), which costs less than a kernel between marking and emitting.
+// The table's last block writes its total to counts[t * count_stride]; a block
+// without a set bit ends before it reads its words.
+constexpr int kEmitThreads = kWordsPerBlock;
+template <int MODE, bool SCANNED>
+__global__ void __launch_bounds__(kEmitThreads) k_bm_emit(DGlobal g, int32_t *counts, int count_stride, int32_t stamp) {
     if (*g.err) return;
     __shared__ int tmp[16];
     const int blk = blockIdx.x;
     const int t = block_table(g, blk);
     const DTable &tb = g.tabs[t];
-    const int64_t wbase = (int64_t)(blk - tb.bm_block0) * kWordsPerBlock + threadIdx.x * kWordsPerThread;
-    const uint4 w4 = *reinterpret_cast<const uint4 *>(tb.bitmap + wbase);
-    const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
-    const int cnt = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
+    const int b0 = tb.bm_block0, own = g.blocksum[blk];
+    int first;
+    if (SCANNED) first = g.blockoff[blk];
+    else first = block_sum((int)threadIdx.x < blk - b0 ? g.blocksum[b0 + threadIdx.x] : 0, tmp);
+    if (threadIdx.x == 0 && blk == b0 + tb.bm_nblk - 1) counts[(int64_t)t * count_stride] = first + own;
+    if (own == 0) return;  // block-uniform
+    const int64_t word = (int64_t)(blk - b0) * kWordsPerBlock + threadIdx.x;
+    uint32_t *bmw = tb.bitmap + word;
+    uint32_t bits = *bmw;
+    int32_t *out;
+    if (MODE == EMIT_FORWARD) out = g.U + g.tstart[t];
+    else if (MODE == EMIT_PREFETCH) out = g.PU + g.pstart[t];
+    else out = g.dump + tb.cap_off;
+    const int32_t nsets = tb.nsets, qbits = tb.qbits;
+    uint4 *rank = tb.rank + word;
     int tot;
-    const int first = g.blockoff[blk] + block_excl_scan(cnt, tmp, &tot);
-    if (tot == 0) return;  // block-uniform
-    int32_t *out;
-    if (MODE == EMIT_FORWARD) out = g.U + g.tstart[t];
-    else if (MODE == EMIT_PREFETCH) out = g.PU + g.pstart[t];
-    else out = g.dump + tb.cap_off;
-    int u = first;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t bits = w[q];
-        if (!bits) continue;
-        const int64_t word = wbase + q;
-        if (MODE == EMIT_FORWARD) tb.rank[word] = make_uint4((uint32_t)u, bits, (uint32_t)stamp, 0u);
-        tb.bitmap[word] = 0;
-        while (bits) {
-            const int b = __ffs(bits) - 1;
-            bits &= bits - 1;
-            const uint32_t pos = (uint32_t)(word * 32 + b);
-            out[u++] = MODE == EMIT_DUMP ? (int32_t)pos : bm_row(tb, pos);
-        }
+    int u = first + block_excl_scan(__popc(bits), tmp, &tot);
+    if (!bits) return;
+    if (MODE == EMIT_FORWARD) *rank = make_uint4((uint32_t)u, bits, (uint32_t)stamp, 0u);
+    *bmw = 0;
+    while (bits) {
+        const int b = __ffs(bits) - 1;
+        bits &= bits - 1;
+        const uint32_t pos = (uint32_t)(word * 32 + b);
+        out[u++] = MODE == EMIT_DUMP ? (int32_t)pos : bm_row(nsets, qbits, pos);
     }
-}
-
-// Small tables: count, scan and emit in one kernel, one block of 1024 threads
-// per table walking its bitmap 4096 words at a time (the three-kernel form
-// costs two more launches, which dominate when a table's bitmap is a few
-// blocks: configuration 1 has four).
-constexpr int kFusedThreads = 1024, kFusedWords = kFusedThreads * kWordsPerThread;
-
-template <int MODE>
-__global__ void __launch_bounds__(kFusedThreads) k_bm_fused(DGlobal g, int32_t *counts, int count_stride,
-                                                           int32_t stamp) {
-    if (*g.err) return;
-    __shared__ int tmp[16];
-    const int t = blockIdx.x;
-    const DTable &tb = g.tabs[t];
-    int32_t *out;
-    if (MODE == EMIT_FORWARD) out = g.U + g.tstart[t];
-    else if (MODE == EMIT_PREFETCH) out = g.PU + g.pstart[t];
-    else out = g.dump + tb.cap_off;
-    int base = 0;  // distinct ids of the words before this pass
-    for (int64_t w0 = 0; w0 < tb.bm_words; w0 += kFusedWords) {
-        const int64_t wbase = w0 + threadIdx.x * kWordsPerThread;
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if (wbase < tb.bm_words) {  // bm_words is a multiple of kWordsPerBlock, so four words are present
-            const uint4 w4 = *reinterpret_cast<const uint4 *>(tb.bitmap + wbase);
-            w[0] = w4.x, w[1] = w4.y, w[2] = w4.z, w[3] = w4.w;
-        }
-        const int cnt = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
-        int tot;
-        int u = base + block_excl_scan(cnt, tmp, &tot);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t bits = w[q];
-            if (!bits) continue;
-            const int64_t word = wbase + q;
-            if (MODE == EMIT_FORWARD) tb.rank[word] = make_uint4((uint32_t)u, bits, (uint32_t)stamp, 0u);
-            tb.bitmap[word] = 0;
-            while (bits) {
-                const int b = __ffs(bits) - 1;
-                bits &= bits - 1;
-                const uint32_t pos = (uint32_t)(word * 32 + b);
-                out[u++] = MODE == EMIT_DUMP ? (int32_t)pos : bm_row(tb, pos);
-            }
-        }
-        base += tot;
-    }
-    if (threadIdx.x == 0) counts[(int64_t)t * count_stride] = base;
 }
 
 // ------------------------------------------------------------------- launchers
@@ -300,10 +293,24 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
     return (unsigned)b;
 }
 
-void launch_mark(const DGlobal &g, const int32_t *keys, const int64_t *starts, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    if (g.own_tables > 0) k_mark_own<<<dim3((unsigned)g.own_slices, (unsigned)g.T), kOwnThreads, 0, s>>>(g, keys, starts);
+// One kernel does it where every table is marked in LDS; larger tables' ids
+// are marked by k_mark, from the starts that it has written.
+template <int MODE>
+static void mark(const DGlobal &g, const int32_t *keys, const int64_t *offs, int32_t B, int64_t n, int32_t have_fwd,
+                 const int64_t *starts, hipStream_t s) {
+    const unsigned slices = g.own_slices > 0 ? (unsigned)g.own_slices : 1u;
+    k_mark_own<MODE><<<dim3(slices, (unsigned)g.T), kOwnThreads, 0, s>>>(g, keys, offs, B, n, have_fwd);
     if (g.own_tables < g.T) k_mark<<<grid_for(n, kBlock * 8, 4096), kBlock, 0, s>>>(g, keys, starts, n);
+}
+
+void launch_mark_forward(const DGlobal &g, const int32_t *indices, const int64_t *offsets, int32_t B, int64_t n,
+                         hipStream_t s) {
+    mark<EMIT_FORWARD>(g, indices, offsets, B, n, 0, g.tstart, s);
+}
+
+void launch_mark_prefetch(const DGlobal &g, const int32_t *rows, const int64_t *poff, int64_t np, int32_t have_fwd,
+                          hipStream_t s) {
+    mark<EMIT_PREFETCH>(g, rows, poff, 1, np, have_fwd, g.pstart, s);
 }
 
 void launch_mark_resident(const DGlobal &g, int32_t max_cap, hipStream_t s) {
@@ -314,18 +321,22 @@ void launch_mark_resident(const DGlobal &g, int32_t max_cap, hipStream_t s) {
 
 void launch_dedup(const DGlobal &g, int mode, int32_t *counts, int count_stride, int32_t stamp, int32_t max_nblk,
                   hipStream_t s) {
-    if (max_nblk <= kFusedMaxBlocks) {
-        if (mode == EMIT_FORWARD) k_bm_fused<EMIT_FORWARD><<<g.T, kFusedThreads, 0, s>>>(g, counts, count_stride, stamp);
-        else if (mode == EMIT_PREFETCH) k_bm_fused<EMIT_PREFETCH><<<g.T, kFusedThreads, 0, s>>>(g, counts, count_stride, stamp);
-        else k_bm_fused<EMIT_DUMP><<<g.T, kFusedThreads, 0, s>>>(g, counts, count_stride, stamp);
-        return;
-    }
     // k_mark_own has counted the owned tables' blocks (not those of the resident dump)
     if (mode == EMIT_DUMP || g.own_tables < g.T) k_bm_count<<<g.total_bm_blocks, kBlock, 0, s>>>(g);
-    k_bm_scan<<<g.T, 1024, 0, s>>>(g, counts, count_stride);
-    if (mode == EMIT_FORWARD) k_bm_emit<EMIT_FORWARD><<<g.total_bm_blocks, kBlock, 0, s>>>(g, stamp);
-    else if (mode == EMIT_PREFETCH) k_bm_emit<EMIT_PREFETCH><<<g.total_bm_blocks, kBlock, 0, s>>>(g, stamp);
-    else k_bm_emit<EMIT_DUMP><<<g.total_bm_blocks, kBlock, 0, s>>>(g, stamp);
+    const bool scanned = max_nblk > kEmitThreads;
+    if (scanned) k_bm_scan<<<g.T, 1024, 0, s>>>(g);
+    const dim3 grid((unsigned)g.total_bm_blocks), blk(kEmitThreads);
+#define RECMG_EMIT(M)                                                                        \
+    if (scanned) k_bm_emit<M, true><<<grid, blk, 0, s>>>(g, counts, count_stride, stamp);    \
+    else k_bm_emit<M, false><<<grid, blk, 0, s>>>(g, counts, count_stride, stamp);
+    if (mode == EMIT_FORWARD) {
+        RECMG_EMIT(EMIT_FORWARD)
+    } else if (mode == EMIT_PREFETCH) {
+        RECMG_EMIT(EMIT_PREFETCH)
+    } else {
+        RECMG_EMIT(EMIT_DUMP)
+    }
+#undef RECMG_EMIT
 }
 
 }  // namespace recmg

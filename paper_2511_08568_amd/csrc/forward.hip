@@ -1,15 +1,19 @@
 // Forward of one batch: pooled embedding-bag lookup over the two-tier store.
 //
 // Order of work on the stream (dedup and probe live in dedup.hip):
-//   k_fwd_prep   validate bag offsets, record each table's index range
-//   k_mark / count / scan / emit(FORWARD)   distinct rows, sorted; map probe
+//   k_mark_own (and k_mark), k_bm_emit   bag offsets checked, each table's
+//                index range recorded, distinct rows sorted
+//   k_fwd_probe  map probe of the distinct rows, prefetch coverage
 //   k_fwd_src    per index: where its row lives (slot or staging row, and
 //                that row's device address), through the rank of the row
 //                among the distinct rows
 //   k_fetch      ZERO_COPY: copy each distinct missing row once from pinned
-//                host memory to HBM staging (GPU reads over the host link)
+//                host memory to HBM staging (GPU reads over the host link); its
+//                last block publishes the counters (k_fwd_finalize where no
+//                fetch is launched)
 //   k_pool       per bag, sum of its rows in fp32 (Sec. II, pooling by sum)
-//   k_fwd_finalize  publish the counters
+// A forward of few ids per table runs the part before the fetch in one kernel
+// (k_fwd_small, small.hip).
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -18,121 +22,138 @@
 
 namespace recmg {
 
+// A forward of no indices: offsets checked, counters zero (one block per table;
+// other forwards do this in the first kernel of their dedup).
 __global__ void __launch_bounds__(kBlock) k_fwd_prep(DGlobal g, const int64_t *__restrict__ offsets, int32_t B,
                                                      int64_t n) {
-    const int64_t nb = (int64_t)g.T * B;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nb && offsets[i] > offsets[i + 1]) atomicOr(g.err, ERR_OFFSETS);
-    if (i == 0 && (offsets[0] != 0 || offsets[nb] != n)) atomicOr(g.err, ERR_OFFSETS);
-    if (i <= g.T) g.tstart[i] = offsets[i * (int64_t)B];
-    if (i < g.T) {
-        TState &st = g.st[i];
-        st.ucount = 0;
-        st.mcount = 0;
-        st.hits = 0;
-        st.hits_pf = 0;
-        st.covered = 0;
-    }
-}
-
-// Coverage (Eq. coverage): how many distinct rows of the last placement's
-// prefetch list (PU, still in place) this batch touches.  A row is in the
-// batch iff its rank word carries this forward's stamp and its bit.
-__global__ void __launch_bounds__(kBlock) k_fwd_cover(DGlobal g, int32_t stamp, int64_t np) {
-    if (*g.err) return;
-    __shared__ int64_t s_pstart[RECMG_MAX_TABLES + 1];
-    __shared__ int32_t s_pc[RECMG_MAX_TABLES];
-    __shared__ int s_cov[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
-        s_pstart[t] = g.pstart[t];
-        if (t < g.T) {
-            s_pc[t] = g.st[t].pcount;
-            s_cov[t] = 0;
-        }
-    }
-    __syncthreads();
-    int64_t lo, hi;
-    block_share(np, &lo, &hi);
-    for (int64_t base = lo; base < hi; base += blockDim.x) {  // block-uniform
-        const int64_t i = base + threadIdx.x;
-        int t = 0;
-        bool hit = false;
-        if (i < hi) {
-            t = find_seg(s_pstart, g.T, i);
-            if (i - s_pstart[t] < s_pc[t]) {
-                const DTable &tb = g.tabs[t];
-                const uint32_t pos = bm_pos(tb, g.PU[i]);
-                const uint4 rk = tb.rank[pos >> 5];
-                hit = (int32_t)rk.z == stamp && (rk.y & (1u << (pos & 31)));
-            }
-        }
-        wave_count_lds(hit, t, s_cov);  // counts only
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x)
-        if (s_cov[t]) atomicAdd(&g.st[t].covered, s_cov[t]);
+    forward_prep(g, blockIdx.x, offsets, B, n);
 }
 
 // Cache probe of every distinct row (row -> slot map, or a scan of the row's
-// set in a set-associative table): hits are stamped and
-// counted, misses are numbered (their staging row).  One thread per slot of
-// the index space; table t's distinct rows occupy [tstart[t], + ucount).
-__global__ void __launch_bounds__(kBlock) k_fwd_probe(DGlobal g, int32_t stamp, int64_t n) {
+// set in a set-associative table): hits are stamped and counted, misses are
+// numbered (their staging row).  The tables' distinct rows are laid end to end
+// and dealt to the blocks in contiguous shares, so no block is spent on the
+// repeats of the index space; a thread takes kProbe rows per round with the
+// first probes of all of them in flight, and a round reserves its misses with
+// one atomic per table (every wave's atomics queued on the state's few lines).
+// Then coverage (Eq. coverage): how many distinct rows of the last placement's
+// prefetch list (PU, still in place) this batch touches: a row is in the batch
+// iff its rank word carries this forward's stamp and its bit.
+constexpr int kProbe = 4;
+__global__ void __launch_bounds__(kBlock) k_fwd_probe(DGlobal g, int32_t stamp, int cover) {
     if (*g.err) return;
-    __shared__ int64_t s_start[RECMG_MAX_TABLES + 1];
-    __shared__ int32_t s_uc[RECMG_MAX_TABLES];
-    __shared__ int s_hits[RECMG_MAX_TABLES], s_hits_pf[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
-        s_start[t] = g.tstart[t];
-        if (t < g.T) {
-            s_uc[t] = g.st[t].ucount;
-            s_hits[t] = 0;
-            s_hits_pf[t] = 0;
-        }
+    __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
+    __shared__ int64_t s_ts[RECMG_MAX_TABLES];
+    __shared__ int s_hits[RECMG_MAX_TABLES], s_hits_pf[RECMG_MAX_TABLES], s_miss[RECMG_MAX_TABLES];
+    __shared__ int tmp[16];
+    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
+        s_hits[t] = s_hits_pf[t] = s_miss[t] = 0;
+        s_ts[t] = g.tstart[t];
     }
-    __syncthreads();
-    int32_t *mcount0 = &g.st[0].mcount;
-    const int stride_st = (int)(sizeof(TState) / 4);
-    int64_t lo, hi;
-    block_share(n, &lo, &hi);
-    for (int64_t base = lo; base < hi; base += blockDim.x) {  // block-uniform
-        const int64_t i = base + threadIdx.x;
-        int t = 0;
-        bool miss = false, valid = false, hit = false, hit_pf = false;
-        int32_t row = 0;
-        if (i < hi) {
-            t = find_seg(s_start, g.T, i);
-            valid = i - s_start[t] < s_uc[t];
+    const int32_t n = lay_tables(g.T, [&](int t) { return g.st[t].ucount; }, s_pre, tmp);
+    constexpr int kRound = kProbe * kBlock;
+    int32_t lo, hi;
+    round_share(n, kRound, &lo, &hi);
+    for (int32_t base = lo; base < hi; base += kRound) {  // block-uniform
+        int t[kProbe];
+        int32_t row[kProbe], m[kProbe];
+        int64_t at[kProbe];
+        bool in[kProbe];
+        int tt = find_seg32(s_pre, g.T, base);  // tables of a round are few: walk on from its first
+#pragma unroll
+        for (int q = 0; q < kProbe; ++q) {
+            const int32_t i = base + q * kBlock + (int32_t)threadIdx.x;
+            in[q] = i < hi;
+            if (in[q])
+                while (i >= s_pre[tt + 1]) ++tt;
+            t[q] = tt;
+            at[q] = s_ts[tt] + (i - s_pre[tt]);
+            row[q] = in[q] ? g.U[at[q]] : 0;
         }
-        if (valid) {
-            const DTable &tb = g.tabs[t];
-            row = g.U[i];
-            const int32_t slot = find_slot(tb, row);
-            if (slot >= 0) {
-                g.slotU[i] = slot;
-                tb.slot_touch[slot] = stamp;
-                hit = true;
-                hit_pf = (tb.slot_flags[slot] & F_PF) != 0;
+        const int t0 = __builtin_amdgcn_readfirstlane(t[0]);
+        // rows of one table (nearly every wave): its descriptor is read once,
+        // through scalar loads
+        auto probe = [&](auto one_tag) {
+            constexpr bool ONE = decltype(one_tag)::value;
+            auto tab = [&](int q) -> const DTable & { return g.tabs[ONE ? t0 : t[q]]; };
+            int32_t slot[kProbe];
+            if (ONE && !g.tabs[t0].ways) {
+                map_find_n<kProbe>(g.tabs[t0], row, in, slot);
             } else {
-                miss = true;
+#pragma unroll
+                for (int q = 0; q < kProbe; ++q) slot[q] = in[q] ? find_slot(tab(q), row[q]) : -1;
             }
+            uint32_t fl[kProbe];
+#pragma unroll
+            for (int q = 0; q < kProbe; ++q) fl[q] = in[q] && slot[q] >= 0 ? gload4(tab(q).slot_flags + slot[q]) : 0u;
+#pragma unroll
+            for (int q = 0; q < kProbe; ++q) {
+                const int k = ONE ? t0 : t[q];
+                const bool hit = in[q] && slot[q] >= 0;
+                if (hit) {
+                    g.slotU[at[q]] = slot[q];
+                    tab(q).slot_touch[slot[q]] = stamp;
+                }
+                wave_count_lds(hit, k, s_hits);  // counts only
+                wave_count_lds(hit && (fl[q] & F_PF) != 0, k, s_hits_pf);
+                m[q] = wave_append(in[q] && !hit, k, s_miss, 1);
+            }
+        };
+        if (__ballot(t[0] != t0 || t[kProbe - 1] != t0) == 0) probe(std::true_type{});
+        else probe(std::false_type{});
+        __syncthreads();
+        for (int k = threadIdx.x; k < g.T; k += blockDim.x)  // counts -> first miss number of this round
+            if (s_miss[k]) s_miss[k] = atomicAdd(&g.st[k].mcount, s_miss[k]);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kProbe; ++q) {
+            if (m[q] < 0) continue;
+            m[q] += s_miss[t[q]];
+            const int64_t a = s_ts[t[q]] + m[q];
+            g.slotU[at[q]] = -(m[q] + 1);
+            g.M[a] = row[q];
+            g.mflags[a] = 0;
+            g.mcbit[a] = 0;
         }
-        wave_count_lds(hit, t, s_hits);  // counts only
-        wave_count_lds(hit_pf, t, s_hits_pf);
-        const int32_t m = wave_append(miss, t, mcount0, stride_st);
-        if (miss) {
-            const int64_t at = s_start[t] + m;
-            g.slotU[i] = -(m + 1);
-            g.M[at] = row;
-            g.mflags[at] = 0;
-            g.mcbit[at] = 0;
-        }
+        __syncthreads();
+        for (int k = threadIdx.x; k < g.T; k += blockDim.x) s_miss[k] = 0;
+        __syncthreads();
     }
-    __syncthreads();
     for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
         if (s_hits[t]) atomicAdd(&g.st[t].hits, s_hits[t]);
         if (s_hits_pf[t]) atomicAdd(&g.st[t].hits_pf, s_hits_pf[t]);
     }
+    if (!cover) return;
+    __syncthreads();
+    int *s_cov = s_hits;
+    for (int t = threadIdx.x; t < g.T; t += blockDim.x) s_cov[t] = 0;
+    const int32_t np = lay_tables(g.T, [&](int t) { return g.st[t].pcount; }, s_pre, tmp);
+    round_share(np, kRound, &lo, &hi);
+    for (int32_t base = lo; base < hi; base += kRound) {
+        int tt = find_seg32(s_pre, g.T, base);
+        int t[kProbe];
+        uint4 rk[kProbe];
+        uint32_t pos[kProbe];
+#pragma unroll
+        for (int q = 0; q < kProbe; ++q) {
+            const int32_t i = base + q * kBlock + (int32_t)threadIdx.x;
+            rk[q] = make_uint4(0u, 0u, 0u, 0u);
+            pos[q] = 0;
+            if (i < hi) {
+                while (i >= s_pre[tt + 1]) ++tt;
+                const DTable &tb = g.tabs[tt];
+                pos[q] = bm_pos(tb, g.PU[g.pstart[tt] + (i - s_pre[tt])]);
+                rk[q] = gload16(tb.rank + (pos[q] >> 5));
+            }
+            t[q] = tt;
+        }
+#pragma unroll
+        for (int q = 0; q < kProbe; ++q)  // counts only (no bit is set in a lane past the end)
+            wave_count_lds((int32_t)rk[q].z == stamp && (rk[q].y >> (pos[q] & 31) & 1u), t[q], s_cov);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < g.T; t += blockDim.x)
+        if (s_cov[t]) atomicAdd(&g.st[t].covered, s_cov[t]);
 }
 
 // inverse map and data location of every index
@@ -153,16 +174,66 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
         }
     }
     __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int t = find_seg(s_start, g.T, i);
-        const uint32_t pos = bm_pos(s_ns[t], s_qb[t], indices[i]);
-        const uint4 rk = s_rank[t][pos >> 5];
-        const int32_t u = (int32_t)rk.x + __popc(rk.y & ((1u << (pos & 31)) - 1u));
-        const int32_t sl = g.slotU[s_start[t] + u];
-        g.src[i] = sl;
-        g.raddr[i] = sl >= 0 ? (uint64_t)(s_pool[t] + (int64_t)sl * s_rb[t])
-                             : (uint64_t)(g.staging + (s_start[t] - (int64_t)sl - 1) * g.stage_stride);
+    // contiguous shares: a block meets one or two tables
+    int64_t lo, hi;
+    block_share(n, &lo, &hi);
+    if (lo >= hi) return;
+    int t = find_seg(s_start, g.T, lo);
+    constexpr int Q = 4;
+    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += Q * kBlock) {
+        int tq[Q];
+        uint32_t pos[Q];
+        uint4 rk[Q];
+        int32_t sl[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t i = i0 + q * kBlock;
+            if (i >= hi) break;
+            while (i >= s_start[t + 1]) ++t;
+            tq[q] = t;
+            pos[q] = bm_pos(s_ns[t], s_qb[t], indices[i]);
+            rk[q] = gload16(s_rank[t] + (pos[q] >> 5));
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (i0 + q * kBlock >= hi) break;
+            const int32_t u = (int32_t)rk[q].x + __popc(rk[q].y & ((1u << (pos[q] & 31)) - 1u));
+            sl[q] = g.slotU[s_start[tq[q]] + u];
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t i = i0 + q * kBlock;
+            if (i >= hi) break;
+            const int k = tq[q];
+            g.src[i] = sl[q];
+            g.raddr[i] = sl[q] >= 0 ? (uint64_t)(s_pool[k] + (int64_t)sl[q] * s_rb[k])
+                                    : (uint64_t)(g.staging + (s_start[k] - (int64_t)sl[q] - 1) * g.stage_stride);
+        }
+    }
+}
+
+// Publishes the forward's counters; log_slot >= 0: also as that call's record
+// of the stats log (the placement group of the record stays zero).
+__device__ __forceinline__ void publish_forward(const DGlobal &g, int64_t log_slot) {
+    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
+        TState &st = g.st[t];
+        const DTable &tb = g.tabs[t];
+        int64_t v[kFwdStats];
+        v[0] = g.tstart[t + 1] - g.tstart[t];
+        v[1] = st.ucount;
+        v[2] = st.hits;
+        v[3] = st.hits_pf;
+        v[4] = st.mcount;
+        v[5] = (int64_t)st.mcount * tb.row_bytes;
+        v[6] = st.covered;
+        for (int k = 0; k < kFwdStats; ++k) {
+            st.last[k] = v[k];
+            st.total[k] += v[k];
+        }
+        if (log_slot >= 0) {
+            int64_t *rec = g.stat_log + (log_slot * g.T + t) * (kNumStats + 1);
+            for (int k = 0; k <= kNumStats; ++k) rec[k] = k < kFwdStats ? v[k] : 0;
+        }
     }
 }
 
@@ -170,14 +241,22 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
 
 // ZERO_COPY miss fetch: each distinct miss of a zero-copy table is read once
 // from pinned host memory (device-visible mapping) and written to its staging
-// row (STAGED tables' misses are staged by the host).
-__global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g) {
+// row (STAGED tables' misses are staged by the host).  The grid's last block
+// publishes the forward's counters, which are complete before this kernel
+// starts: that costs no launch of its own (k_fwd_finalize took 3.4 us and a
+// dispatch after the pooled kernel of every forward).
+__global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot) {
     if (*g.err) return;
+    const int64_t nb = (int64_t)gridDim.x - 1;
+    if ((int64_t)blockIdx.x == nb) {  // block-uniform
+        publish_forward(g, log_slot);
+        return;
+    }
     __shared__ int32_t s_cnt[RECMG_MAX_TABLES];
     for (int t = threadIdx.x; t < g.T; t += blockDim.x) s_cnt[t] = g.tabs[t].staged ? 0 : g.st[t].mcount;
     __syncthreads();
     copy_flat(
-        g, s_cnt, gridDim.x,
+        g, s_cnt, nb,
         [&](int t, const DTable &tb, int64_t j) {
             return tb.host + (int64_t)g.M[g.tstart[t] + j] * tb.row_bytes;
         },
@@ -712,30 +791,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC
     else pool_wave_v<DT, LW, R>(raddr, ob, nbags, D, ob_out);
 }
 
-// Publishes the forward's counters; log_slot >= 0: also as that call's record
-// of the stats log (the placement group of the record stays zero).
+// The counters of a forward that fetches nothing from the host itself (no
+// indices, or every table STAGED).
 __global__ void k_fwd_finalize(DGlobal g, int64_t log_slot) {
     if (*g.err) return;
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        TState &st = g.st[t];
-        const DTable &tb = g.tabs[t];
-        int64_t v[kFwdStats];
-        v[0] = g.tstart[t + 1] - g.tstart[t];
-        v[1] = st.ucount;
-        v[2] = st.hits;
-        v[3] = st.hits_pf;
-        v[4] = st.mcount;
-        v[5] = (int64_t)st.mcount * tb.row_bytes;
-        v[6] = st.covered;
-        for (int k = 0; k < kFwdStats; ++k) {
-            st.last[k] = v[k];
-            st.total[k] += v[k];
-        }
-        if (log_slot >= 0) {
-            int64_t *rec = g.stat_log + (log_slot * g.T + t) * (kNumStats + 1);
-            for (int k = 0; k <= kNumStats; ++k) rec[k] = k < kFwdStats ? v[k] : 0;
-        }
-    }
+    publish_forward(g, log_slot);
 }
 
 // ----------------------------------------------------------------- launchers
@@ -748,18 +808,13 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
 }
 
 void launch_fwd_prep(const DGlobal &g, const int64_t *offsets, int32_t B, int64_t n, hipStream_t s) {
-    const int64_t items = ((int64_t)g.T * B + 1) > (g.T + 1) ? ((int64_t)g.T * B + 1) : (g.T + 1);
-    k_fwd_prep<<<(unsigned)((items + kBlock - 1) / kBlock), kBlock, 0, s>>>(g, offsets, B, n);
+    k_fwd_prep<<<g.T, kBlock, 0, s>>>(g, offsets, B, n);
 }
 
-void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    k_fwd_probe<<<grid_for(n, kBlock, 8192), kBlock, 0, s>>>(g, stamp, n);
-}
-
-void launch_fwd_cover(const DGlobal &g, int32_t stamp, int64_t np, hipStream_t s) {
-    if (np <= 0) return;
-    k_fwd_cover<<<grid_for(np, kBlock, 4096), kBlock, 0, s>>>(g, stamp, np);
+void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, int64_t np, hipStream_t s) {
+    // the distinct rows are at most n, often a fraction of it: one round per
+    // block if all ids were distinct, up to 8 blocks per CU
+    k_fwd_probe<<<grid_for(n > np ? n : np, kBlock * kProbe, 2048), kBlock, 0, s>>>(g, stamp, np > 0 ? 1 : 0);
 }
 
 void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStream_t s) {
@@ -776,9 +831,10 @@ void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStre
 // (the next placement runs beside it).  Measured on configuration 3 (64-256
 // blocks): 96 is best with 32-way sets (k_sa_place's critical path runs
 // alongside), within 1% of the best without prefetch and on configuration 5.
-void launch_fetch(const DGlobal &g, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    if (ev0 || ev1) hipExtLaunchKernelGGL(k_fetch, dim3(RECMG_FETCH_BLOCKS), dim3(kBlock), 0, s, ev0, ev1, 0, g);
-    else k_fetch<<<RECMG_FETCH_BLOCKS, kBlock, 0, s>>>(g);
+void launch_fetch(const DGlobal &g, int64_t log_slot, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const dim3 grid(RECMG_FETCH_BLOCKS + 1);  // the last block publishes the counters
+    if (ev0 || ev1) hipExtLaunchKernelGGL(k_fetch, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, log_slot);
+    else k_fetch<<<grid, kBlock, 0, s>>>(g, log_slot);
 }
 
 int pool_kind(int dtype, int vec, int wlw, int wr) {

@@ -12,22 +12,28 @@ constexpr int64_t kTinyItems = 16384;
 static inline int items_per_thread(int64_t n, int big) { return n <= kTinyItems ? 1 : big; }
 
 // dedup.hip
-void launch_mark(const DGlobal &g, const int32_t *keys, const int64_t *starts, int64_t n, hipStream_t s);
+// the start of a forward / placement (offsets checked, state set up) and the marking of its ids
+void launch_mark_forward(const DGlobal &g, const int32_t *indices, const int64_t *offsets, int32_t B, int64_t n,
+                         hipStream_t s);
+void launch_mark_prefetch(const DGlobal &g, const int32_t *rows, const int64_t *poff, int64_t np, int32_t have_fwd,
+                          hipStream_t s);
 void launch_mark_resident(const DGlobal &g, int32_t max_cap, hipStream_t s);
 enum { EMIT_FORWARD = 0, EMIT_PREFETCH = 1, EMIT_DUMP = 2 };
 // mode: where the sorted distinct ids go (U of a forward, PU of a placement, the resident dump);
-// max_nblk: the most bitmap blocks of any table (at most kFusedMaxBlocks: one kernel does it all)
-constexpr int kFusedMaxBlocks = 8;
+// max_nblk: the most bitmap blocks of any table
 void launch_dedup(const DGlobal &g, int mode, int32_t *counts, int count_stride, int32_t stamp, int32_t max_nblk,
                   hipStream_t s);
 
 // forward.hip
 void launch_fwd_prep(const DGlobal &g, const int64_t *offsets, int32_t B, int64_t n, hipStream_t s);
-void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, hipStream_t s);
+// np: prefetch ids of the placement just before this forward (0: none)
+void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, int64_t np, hipStream_t s);
 void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStream_t s);
-void launch_fwd_cover(const DGlobal &g, int32_t stamp, int64_t np, hipStream_t s);
+// fetch, and the forward's counters published by a block of its own (log_slot:
+// record of this call in the stats log, or -1).
 // ev0 / ev1 (may be null): recorded by the dispatch itself around the kernel
-void launch_fetch(const DGlobal &g, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_fetch(const DGlobal &g, int64_t log_slot, hipStream_t s, hipEvent_t ev0 = nullptr,
+                  hipEvent_t ev1 = nullptr);
 // Pooled-sum kernels: kinds [0, kPoolKindsGroup) are the group-per-bag kernel
 // (dtype * 2 + vec), the rest the wave-per-bag kernel per (dtype, wlw, wr).
 constexpr int kPoolKindsGroup = 6, kPoolKinds = kPoolKindsGroup + 15;
@@ -42,8 +48,14 @@ struct PoolLaunch {
 void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out, const int32_t *bstart,
                  const int32_t *btab, int32_t nt, const PoolLaunch *ls, int nl, hipEvent_t ev0, hipEvent_t ev1,
                  hipStream_t s);
-// log_slot: record of this call in the stats log, or -1
+// the counters alone, for a forward that launches no fetch
 void launch_fwd_finalize(const DGlobal &g, int64_t log_slot, hipStream_t s);
+
+// small.hip: forwards of few ids per table, one block per table.
+// max_nblk: the most bitmap blocks of any table; cover: a placement came just before
+bool small_batch(int32_t T, int64_t n, int32_t max_nblk);
+void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *offsets, int32_t B, int64_t n,
+                      int32_t stamp, bool cover, int32_t max_nblk, hipStream_t s);
 
 // placement.hip
 void launch_plc_prep(const DGlobal &g, const int64_t *poff, int64_t np, int32_t have_fwd, hipStream_t s);

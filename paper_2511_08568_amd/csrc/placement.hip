@@ -30,33 +30,10 @@
 
 namespace recmg {
 
+// The start of a placement with an empty prefetch list (others start in the
+// first kernel of the list's dedup): one block per table.
 __global__ void k_plc_prep(DGlobal g, const int64_t *__restrict__ poff, int64_t np, int32_t have_fwd) {
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
-        const int64_t v = poff[t];
-        g.pstart[t] = v;
-        // table t's fill list lives at ftstart[t] + pstart[t] and holds at most
-        // (its last-batch indices) + (its prefetch ids) entries
-        g.ftstart[t] = have_fwd ? g.tstart[t] : 0;
-        if (t < g.T && v > poff[t + 1]) atomicOr(g.err, ERR_OFFSETS);
-        if ((t == 0 && v != 0) || (t == g.T && v != np)) atomicOr(g.err, ERR_OFFSETS);
-        if (t < g.T) {
-            TState &st = g.st[t];
-            st.pcount = 0;
-            st.npcount = 0;
-            st.popped = 0;
-            st.p_res = 0;
-            st.evicted = 0;
-            st.adm_miss = 0;
-            st.p_fill = 0;
-            st.p_drop = 0;
-            st.m_drop = 0;
-            st.z1_keys = 0;
-            st.pend_keep = 0;
-            // set-associative tables and resident rings update the digest by
-            // the rows that come and go
-            st.digest_acc = (g.tabs[t].ways || g.tabs[t].ring_cap) ? st.digest : 0ull;
-        }
-    }
+    placement_prep(g, blockIdx.x, poff, np, have_fwd);
 }
 
 // Caching bits of the last batch, OR-ed per row into a byte of the slot (hit)
@@ -821,7 +798,7 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
 }
 
 void launch_plc_prep(const DGlobal &g, const int64_t *poff, int64_t np, int32_t have_fwd, hipStream_t s) {
-    k_plc_prep<<<1, kBlock, 0, s>>>(g, poff, np, have_fwd);
+    k_plc_prep<<<g.T, 64, 0, s>>>(g, poff, np, have_fwd);
 }
 
 void launch_plc_bits(const DGlobal &g, const uint8_t *bits, int64_t n_last, hipStream_t s) {

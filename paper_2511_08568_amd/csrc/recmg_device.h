@@ -262,6 +262,35 @@ __device__ __forceinline__ int32_t map_find(const DTable &tb, int32_t row) {
     return -1;
 }
 
+// Slots (or -1) of the Q rows with `want`: the first probes of all of them are
+// in flight together, so a thread with several rows waits for one round trip
+// where map_find's loop waits for one per row (the map is at most half full of
+// live and deleted entries, and most rows are settled by their first probe).
+template <int Q>
+__device__ __forceinline__ void map_find_n(const DTable &tb, const int32_t (&row)[Q], const bool (&want)[Q],
+                                           int32_t (&slot)[Q]) {
+    const int32_t mask = tb.map_mask;
+    uint32_t i[Q];
+    int2 e[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        i[q] = hash_row(row[q]) & (uint32_t)mask;
+        e[q] = want[q] ? gload_int2(tb.map + i[q]) : make_int2(kEmpty, -1);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        slot[q] = -1;
+        for (int32_t n = 0; n <= mask && e[q].x != kEmpty; ++n) {
+            if (e[q].x == row[q]) {
+                slot[q] = e[q].y;
+                break;
+            }
+            i[q] = (i[q] + 1) & (uint32_t)mask;
+            e[q] = gload_int2(tb.map + i[q]);
+        }
+    }
+}
+
 // The map holds at most Cap live rows in >= 4 Cap entries, and is rebuilt when
 // deleted entries pass a quarter of it, so at least half of it stays empty.
 
@@ -307,10 +336,11 @@ __device__ __forceinline__ uint32_t bm_pos(int32_t nsets, int32_t qbits, int32_t
     return ((u % n) << qbits) | (u / n);
 }
 __device__ __forceinline__ uint32_t bm_pos(const DTable &tb, int32_t r) { return bm_pos(tb.nsets, tb.qbits, r); }
-__device__ __forceinline__ int32_t bm_row(const DTable &tb, uint32_t pos) {
-    if (!tb.nsets) return (int32_t)pos;
-    return (int32_t)((pos & ((1u << tb.qbits) - 1u)) * (uint32_t)tb.nsets + (pos >> tb.qbits));
+__device__ __forceinline__ int32_t bm_row(int32_t nsets, int32_t qbits, uint32_t pos) {
+    if (!nsets) return (int32_t)pos;
+    return (int32_t)((pos & ((1u << qbits) - 1u)) * (uint32_t)nsets + (pos >> qbits));
 }
+__device__ __forceinline__ int32_t bm_row(const DTable &tb, uint32_t pos) { return bm_row(tb.nsets, tb.qbits, pos); }
 
 // Slot of `row` in its set, or -1.
 __device__ __forceinline__ int32_t set_find(const DTable &tb, int32_t row) {
@@ -318,6 +348,29 @@ __device__ __forceinline__ int32_t set_find(const DTable &tb, int32_t row) {
     for (int32_t k = 0; k < tb.ways; ++k)
         if ((int32_t)gload4(tb.slot_row + base + k) == row) return base + k;
     return -1;
+}
+
+// The same with the set's rows read 16 bytes at a time, four loads in flight
+// (W a multiple of 4, so that a set starts on a 16-byte boundary): for a batch
+// that leaves most of the chip idle the chain of loads is what counts.
+__device__ __forceinline__ int32_t set_find_wide(const DTable &tb, int32_t row) {
+    const int32_t W = tb.ways, base = (int32_t)((uint32_t)row % (uint32_t)tb.nsets) * W;
+    if (W & 3) return set_find(tb, row);
+    int32_t slot = -1;
+    for (int32_t k = 0; k < W && slot < 0; k += 16) {
+        uint4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = k + 4 * q < W ? gload16(tb.slot_row + base + k + 4 * q) : make_uint4(~0u, ~0u, ~0u, ~0u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if ((int32_t)w[x] == row) slot = base + k + 4 * q + x;
+        }
+    }
+    return slot;
 }
 
 __device__ __forceinline__ int32_t find_slot(const DTable &tb, int32_t row) {
@@ -456,6 +509,29 @@ __device__ __forceinline__ void block_share(int64_t n, int64_t *lo, int64_t *hi)
     *hi = *lo + per < n ? *lo + per : n;
 }
 
+// Per-table counts laid end to end: s_pre[t] = first item of table t, s_pre[T]
+// the total, which is returned.  blockDim.x >= T; every thread calls; ends with
+// a barrier.
+template <class Count>
+__device__ __forceinline__ int32_t lay_tables(int T, Count count, int32_t *s_pre, int *tmp) {
+    const int t = threadIdx.x;
+    int tot;
+    const int ex = block_excl_scan(t < T ? (int)count(t) : 0, tmp, &tot);
+    if (t < T) s_pre[t] = ex;
+    if (t == 0) s_pre[T] = tot;
+    __syncthreads();
+    return tot;
+}
+
+// This block's share [*lo, *hi) of n items laid end to end, a whole number of
+// rounds of `round` items (contiguous, as in block_share).
+__device__ __forceinline__ void round_share(int32_t n, int round, int32_t *lo, int32_t *hi) {
+    const int64_t per = (((int64_t)n + gridDim.x - 1) / gridDim.x + round - 1) / round * round;
+    const int64_t a = per * blockIdx.x, b = a + per;
+    *lo = (int32_t)(a < n ? a : n);
+    *hi = (int32_t)(b < n ? b : n);
+}
+
 // Count the lanes with `want` into their own table's LDS counter, one LDS
 // atomic per table present in the wave.  Counts that only add up go through
 // LDS and reach the table's state once per block: a global atomic from every
@@ -514,6 +590,61 @@ __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) {
 
 __device__ __forceinline__ float f16_to_f32(uint32_t bits16) {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
+}
+
+// Start of a forward for table t, by one block: bag offsets checked, the
+// table's index range and counters set.  Every thread of the block calls.
+__device__ __forceinline__ void forward_prep(const DGlobal &g, int t, const int64_t *__restrict__ offsets, int32_t B,
+                                             int64_t n) {
+    const int64_t *ob = offsets + (int64_t)t * B;
+    bool bad = false;
+    for (int32_t j = threadIdx.x; j < B; j += blockDim.x) bad |= ob[j] > ob[j + 1];
+    if (threadIdx.x == 0) {
+        const int64_t lo = ob[0], hi = ob[B];
+        // the last two hold in every table of a well-formed call
+        bad |= (t == 0 && lo != 0) || (t == g.T - 1 && hi != n) || lo < 0 || hi > n;
+        g.tstart[t] = lo;
+        if (t == g.T - 1) g.tstart[g.T] = hi;
+        TState &st = g.st[t];
+        st.ucount = 0;
+        st.mcount = 0;
+        st.hits = 0;
+        st.hits_pf = 0;
+        st.covered = 0;
+    }
+    if (bad) atomicOr(g.err, ERR_OFFSETS);
+}
+
+// Start of a placement for table t, by thread 0 of one block: the prefetch
+// list's offsets checked, the table's range and accumulators set.
+__device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const int64_t *__restrict__ poff, int64_t np,
+                                               int32_t have_fwd) {
+    if (threadIdx.x != 0) return;
+    const int64_t v = poff[t], e = poff[t + 1];
+    if (v > e || v < 0 || e > np || (t == 0 && v != 0) || (t == g.T - 1 && e != np)) atomicOr(g.err, ERR_OFFSETS);
+    g.pstart[t] = v;
+    // table t's fill list lives at ftstart[t] + pstart[t] and holds at most
+    // (its last-batch indices) + (its prefetch ids) entries
+    g.ftstart[t] = have_fwd ? g.tstart[t] : 0;
+    if (t == g.T - 1) {
+        g.pstart[g.T] = e;
+        g.ftstart[g.T] = have_fwd ? g.tstart[g.T] : 0;
+    }
+    TState &st = g.st[t];
+    st.pcount = 0;
+    st.npcount = 0;
+    st.popped = 0;
+    st.p_res = 0;
+    st.evicted = 0;
+    st.adm_miss = 0;
+    st.p_fill = 0;
+    st.p_drop = 0;
+    st.m_drop = 0;
+    st.z1_keys = 0;
+    st.pend_keep = 0;
+    // set-associative tables and resident rings update the digest by the rows
+    // that come and go
+    st.digest_acc = (g.tabs[t].ways || g.tabs[t].ring_cap) ? st.digest : 0ull;
 }
 
 // Copy `count[t]` rows of every table in 16/4/2-byte units, the tables' work
