@@ -291,7 +291,7 @@ struct recmg_cache {
     Layout L;
     DGlobal g{};
     std::vector<const char *> host;  // host tables (host pointers)
-    int32_t max_cap = 0, max_map = 0, max_units = 0, rowbits = 1, nsa = 0, max_nblk = 0;
+    int32_t max_cap = 0, max_units = 0, rowbits = 1, nsa = 0, max_nblk = 0;
     int64_t sa_blocks = 0;   // blocks of the set-associative placement kernel
     int64_t sa_blocks1 = 0;  // the first of them, over the tables of one set per wave
     int64_t sa_max_blocks = 0;  // the most blocks of one table
@@ -960,7 +960,6 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
         out_off += ge.dim;
         cap_off += ge.cap;
         c->max_cap = std::max(c->max_cap, ge.cap);
-        c->max_map = (int32_t)std::max<int64_t>(c->max_map, ge.map_cap);
         c->max_units = std::max(c->max_units, ge.row_bytes / ge.copy_unit);
         c->max_rows = std::max(c->max_rows, ge.rows);
         c->max_nblk = std::max(c->max_nblk, ge.bm_nblk);
@@ -1101,11 +1100,21 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     if (p.total_bits < 1) p.total_bits = 1;
     p.passes = (p.total_bits + kRadixBits - 1) / kRadixBits;
 
-    {
+    const int64_t last_n = c->have_fwd ? c->last_n : 0;
+    const int64_t log_slot = c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1;
+    const int32_t max_fa_cap = c->has_fa ? c->max_cap : 0;
+    // Small batches: one kernel for all but the sets, and the fill beside the
+    // published counters on this stream (a fill of some hundred rows takes a few
+    // microseconds, the waits of another stream for it longer).
+    const bool small = !c->has_staged && small_placement(c->T, last_n, num_prefetch, c->max_nblk, max_fa_cap);
+    if (small) {
+        StageTimer tm(c, RECMG_STAGE_PLC_APPLY, s);
+        launch_plc_small(g, p, prefetch_rows, prefetch_offsets, num_prefetch, cache_bits, q, c->max_nblk, s);
+    } else {
         StageTimer tm(c, RECMG_STAGE_PLC_CLASSIFY, s);
         if (num_prefetch == 0) launch_plc_prep(g, prefetch_offsets, num_prefetch, p.have_fwd, s);
-        if (p.prio && cache_bits && c->have_fwd) launch_plc_bits(g, cache_bits, c->last_n, s);
-        if (p.lfu && c->have_fwd) launch_plc_freq(g, c->last_n, s);
+        if (p.prio && cache_bits && c->have_fwd) launch_plc_bits(g, cache_bits, last_n, s);
+        if (p.lfu && c->have_fwd) launch_plc_freq(g, last_n, s);
         if (num_prefetch > 0) {
             launch_mark_prefetch(g, prefetch_rows, prefetch_offsets, num_prefetch, p.have_fwd, s);
             launch_dedup(g, EMIT_PREFETCH,
@@ -1116,7 +1125,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     }
     // fully associative STAGED tables: their new prefetch candidates go to the
     // host now, so that it gathers their rows while the GPU ranks (early_gather)
-    const bool early = c->has_staged_fa && num_prefetch > 0;
+    const bool early = c->has_staged_fa && num_prefetch > 0;  // never with `small`
     if (early) {
         HIP_TRY(hipMemcpyAsync(c->he_st, g.st, sizeof(TState) * c->T, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipMemcpyAsync(c->he_pstart, g.pstart, 8 * (c->T + 1), hipMemcpyDeviceToHost, s));
@@ -1124,30 +1133,32 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
         HIP_TRY(hipMemcpyAsync(c->he_err, g.err, 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipEventRecord(c->ev_np, s));
     }
-    const int64_t cand = (c->have_fwd ? c->last_n : 0) + num_prefetch;
+    const int64_t cand = last_n + num_prefetch;
     const int64_t per_table = c->max_cap + (cand + c->T - 1) / c->T;
     const int64_t cand_grid = std::min<int64_t>(std::max<int64_t>(cand / c->T, 1024), cand + 1);
     // resident rings: a table's zones hold its pending rows (at most the last
     // placement's prefetch rows) and the last batch's distinct rows
-    const int64_t ring_items = ((c->have_fwd ? c->last_n : 0) + c->plc_np_last + num_prefetch + c->T - 1) / c->T;
-    if (c->has_fa) {
+    const int64_t ring_items = (last_n + c->plc_np_last + num_prefetch + c->T - 1) / c->T;
+    if (c->has_fa && !small) {
         StageTimer tm(c, RECMG_STAGE_PLC_RANK, s);
         if (c->has_scan_fa) launch_plc_rank(g, p, per_table, s);
         if (c->has_ring) launch_ring_rank(g, p, ring_items, s);
     }
     {
         StageTimer tm(c, RECMG_STAGE_PLC_APPLY, s);
-        if (c->has_scan_fa) launch_plc_evict(g, p, c->max_cap, s);
-        if (c->has_ring) launch_ring_evict(g, p, ring_items, c->max_ring_chunks, s);
-        if (c->has_fa) launch_plc_admit(g, p, c->max_cap, c->max_map, cand_grid, s);
-        if (c->has_ring) launch_ring_store(g, p, ring_items, c->max_cap, q, s);
+        if (!small) {
+            if (c->has_scan_fa) launch_plc_evict(g, p, c->max_cap, s);
+            if (c->has_ring) launch_ring_evict(g, p, ring_items, c->max_ring_chunks, s);
+            if (c->has_fa) launch_plc_admit(g, p, cand_grid, s);
+            if (c->has_ring) launch_ring_store(g, p, ring_items, c->max_cap, q, s);
+        }
         if (c->has_sa)
-            launch_sa_place(g, p, c->have_fwd ? c->last_n : 0, num_prefetch, c->nsa, c->sa_blocks1, c->sa_blocks,
-                            c->sa_max_blocks, s);
+            launch_sa_place(g, p, last_n, num_prefetch, c->nsa, c->sa_blocks1, c->sa_blocks, c->sa_max_blocks, !small, s);
     }
-    launch_plc_finalize(g, fdesc, c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1, s);
-    HIP_TRY(hipEventRecord(c->ev_plc, s));
-    hipStream_t fs = c->copy_stream ? c->copy_stream : s;
+    const int32_t end_nsa = c->sa_max_blocks <= kSaSumInEnd ? c->nsa : 0;
+    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, s);
+    if (!small) HIP_TRY(hipEventRecord(c->ev_plc, s));
+    hipStream_t fs = c->copy_stream && !small ? c->copy_stream : s;
     if (early) {
         // the host gathers while the kernels above run; the copies go on the
         // fill stream ahead of the fill (the last fill to read fstage has
@@ -1168,7 +1179,16 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // different streams) this fill waits for it, and so does every forward
     // that waits for this fill.
     if (c->fill_rec[q ^ 1] && c->fill_stream[q ^ 1] != fs) HIP_TRY(hipStreamWaitEvent(fs, c->ev_fill[q ^ 1], 0));
-    {
+    if (small) {
+        StageTimer tm(c, RECMG_STAGE_PLC_FILL, s);
+        DispatchTimer dt(c, RECMG_STAGE_PLC_FILL, true);
+        launch_plc_end(g, nullptr, log_slot, true, max_fa_cap, end_nsa, s, dt.a, dt.b);
+        dt.issued();
+        // calls on other streams that wait for the placement wait for its fill too
+        HIP_TRY(hipEventRecord(c->ev_plc, s));
+        c->fill_rec[q] = false;
+        c->fill_last = -1;
+    } else {
         StageTimer tm(c, RECMG_STAGE_PLC_FILL, fs);
         // Zero-copy tables' rows are read from the host by the kernel, at
         // once (beside the host gather of the STAGED tables' rows); STAGED
@@ -1180,11 +1200,11 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
             launch_plc_fill(g, fdesc, FILL_STAGED, fs, c->has_zc ? nullptr : dt.a, dt.b);
         }
         dt.issued();
+        HIP_TRY(hipEventRecord(c->ev_fill[q], fs));
+        c->fill_rec[q] = true;
+        c->fill_stream[q] = fs;
+        c->fill_last = q;
     }
-    HIP_TRY(hipEventRecord(c->ev_fill[q], fs));
-    c->fill_rec[q] = true;
-    c->fill_stream[q] = fs;
-    c->fill_last = q;
     HIP_TRY(hipGetLastError());
     guard.done = true;
     c->placements++;

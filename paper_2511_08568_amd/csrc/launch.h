@@ -57,6 +57,12 @@ bool small_batch(int32_t T, int64_t n, int32_t max_nblk);
 void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *offsets, int32_t B, int64_t n,
                       int32_t stamp, bool cover, int32_t max_nblk, hipStream_t s);
 
+// a placement's kernels up to (not with) launch_sa_place and launch_plc_end; last_n: ids of
+// the last forward (0: none), max_fa_cap: the most slots of a fully associative table
+bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap);
+void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,
+                      const uint8_t *bits, int wr, int32_t max_nblk, hipStream_t s);
+
 // placement.hip
 void launch_plc_prep(const DGlobal &g, const int64_t *poff, int64_t np, int32_t have_fwd, hipStream_t s);
 void launch_plc_bits(const DGlobal &g, const uint8_t *bits, int64_t n_last, hipStream_t s);
@@ -66,17 +72,20 @@ void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, hipSt
 // block per table ranks it whole
 constexpr int64_t kRankSmallItems = 1 << 16;
 void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, hipStream_t s);
-// evict (tables ranked by radix select), then map upkeep and admission (every
-// fully associative table)
+// evict (tables ranked by radix select), admission (every fully associative table)
 void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, hipStream_t s);
-void launch_plc_admit(const DGlobal &g, const PlcParams &p, int32_t max_cap, int32_t max_map, int64_t cand_bound,
-                      hipStream_t s);
-// fdesc: this placement's fill descriptor, [T][4] int64 (written by finalize, read by fill);
+void launch_plc_admit(const DGlobal &g, const PlcParams &p, int64_t cand_bound, hipStream_t s);
+// fdesc: this placement's fill descriptor, [T][4] int64 (written by the end, read by fill);
 // phase: the tables whose rows this launch copies, by miss mode
 enum { FILL_ZERO_COPY = 1, FILL_STAGED = 2 };
 void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStream_t s, hipEvent_t ev0 = nullptr,
                      hipEvent_t ev1 = nullptr);
-void launch_plc_finalize(const DGlobal &g, int64_t *fdesc, int64_t log_slot, hipStream_t s);
+// the end of a placement: counters published, cleared maps refilled (max_fa_cap:
+// the most slots of a fully associative table, 0 if there is none), the blocks'
+// counts of nsa set-associative tables added up (0: done by launch_sa_place);
+// fill: the zero-copy fill too, else its descriptor is written to fdesc
+void launch_plc_end(const DGlobal &g, int64_t *fdesc, int64_t log_slot, bool fill, int32_t max_fa_cap, int32_t nsa,
+                    hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_init_state(const DGlobal &g, int32_t max_cap, hipStream_t s);
 
 // ring.hip: LRU_BATCH placement of tables with a resident ring (ring_cap > 0).
@@ -91,6 +100,7 @@ void launch_ring_store(const DGlobal &g, const PlcParams &p, int64_t item_bound,
 
 // setassoc.hip: placement of the set-associative tables (nu: index space of
 // the last forward's distinct rows, np: of this placement's prefetch rows;
+// heads: k_sa_heads too (else k_plc_small has found the segments);
 // nsa tables, fewest sets first; blocks = sa_bstart[nsa], the first blocks1 of
 // them over tables of one set per wave), kSaWaves * sa_sets_per_wave(ways,
 // nsets) sets per block of a table
@@ -99,8 +109,11 @@ constexpr int kSaWaves = 16, kSaBlock = 64 * kSaWaves;
 // wave and the sets are many (few events each); one where sets take many events
 constexpr int64_t kSaPairMinSets = 16384;
 constexpr int sa_sets_per_wave(int ways, int64_t nsets) { return ways <= 32 && nsets >= kSaPairMinSets ? 2 : 1; }
-// max_blocks: the most blocks of one table (sizes the per-table sum of the blocks' counts)
+// max_blocks: the most blocks of one table; up to kSaSumInEnd the end of the
+// placement adds up the blocks' counts (one block per table, a few microseconds;
+// a launch of its own costs as much)
+constexpr int64_t kSaSumInEnd = 1024;
 void launch_sa_place(const DGlobal &g, const PlcParams &p, int64_t nu, int64_t np, int32_t nsa, int64_t blocks1,
-                     int64_t blocks, int64_t max_blocks, hipStream_t s);
+                     int64_t blocks, int64_t max_blocks, bool heads, hipStream_t s);
 
 }  // namespace recmg

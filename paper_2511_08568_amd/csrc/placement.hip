@@ -23,10 +23,11 @@
 // EMIT_PREFETCH visitor (dedup.hip), k_plc_update (scores + histogram of
 // pass 0), k_plc_pick, { k_plc_select (histogram of pass 1..), k_plc_pick }*,
 // k_plc_evict, k_map_clear / k_map_refill (rebuild
-// when deleted entries pile up), k_plc_admit, k_plc_fill, k_plc_finalize.
+// when deleted entries pile up), k_plc_admit, k_plc_fill, k_plc_end.
 #include <hip/hip_ext.h>
 
 #include "launch.h"
+#include "placement_device.h"
 
 namespace recmg {
 
@@ -141,24 +142,6 @@ __global__ void __launch_bounds__(kBlock) k_plc_classify(DGlobal g, int32_t last
 
 // ----------------------------------------------------------------- ranking
 
-__device__ __forceinline__ int pass_shift(const PlcParams &p, int pass) { return kRadixBits * (p.passes - 1 - pass); }
-__device__ __forceinline__ int pass_width(const PlcParams &p, int pass) {
-    return pass == 0 ? p.total_bits - kRadixBits * (p.passes - 1) : kRadixBits;
-}
-
-// Histogram increment, aggregated over the wave for the first active lane's
-// bin: the keys of one table bunch up in few digits (LRU scores are batch
-// numbers), and 64 lanes adding 1 to one LDS word would serialise.
-__device__ __forceinline__ void hist_add(int *h, bool active, uint32_t bin) {
-    const uint64_t act = __ballot(active);
-    if (act == 0) return;
-    const int lead = __ffsll((unsigned long long)act) - 1;
-    const uint32_t b0 = (uint32_t)__shfl((int)bin, lead);
-    const uint64_t same = __ballot(active && bin == b0);
-    if ((int)(threadIdx.x & 63) == lead) atomicAdd(&h[b0], __popcll(same));
-    if (active && bin != b0) atomicAdd(&h[bin], 1);
-}
-
 // Merge the block's histogram into the table's global one (non-zero bins).
 // No fence and no "last block" here: on this GPU an agent-scope fence writes
 // back the XCD's whole L2, and a histogram kernel has many blocks; the digit
@@ -167,42 +150,6 @@ __device__ __forceinline__ void hist_merge(const DGlobal &g, int t, const int *s
     int *gh = g.hist + (int64_t)t * kRadix;
     for (int b = threadIdx.x; b < kRadix; b += blockDim.x)
         if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
-}
-
-// The digit of one pass from a table's histogram in LDS: bins are taken from
-// the top until `need` keys are covered; the bin reached (*digit) extends the
-// threshold prefix and the keys still needed inside it (*rest) carry over to
-// the next pass.  Every thread of the block calls; blockDim.x divides kRadix;
-// the results are valid in every thread.
-__device__ __forceinline__ void pick_digit(const int *s_hist, int need, int *tmp, int *digit, int *rest) {
-    __shared__ int s_digit, s_rest;
-    // thread k owns bin group (groups - 1 - k), so an exclusive scan gives the
-    // keys in the groups above
-    if (threadIdx.x == 0) {  // a histogram short of `need` (never, when the counts hold) keeps digit 0
-        s_digit = 0;
-        s_rest = need;
-    }
-    const int per = kRadix / (int)blockDim.x;
-    const int grp = (int)blockDim.x - 1 - (int)threadIdx.x;
-    int cs = 0;
-    for (int b = 0; b < per; ++b) cs += s_hist[grp * per + b];
-    int tot;
-    const int above = block_excl_scan(cs, tmp, &tot);
-    if (above < need && above + cs >= need) {
-        int cum = above;
-        for (int b = grp * per + per - 1; b >= grp * per; --b) {
-            if (cum + s_hist[b] >= need) {
-                s_digit = b;
-                s_rest = need - cum;
-                break;
-            }
-            cum += s_hist[b];
-        }
-    }
-    __syncthreads();
-    *digit = s_digit;
-    *rest = s_rest;
-    __syncthreads();
 }
 
 // One block per table: the digit of this pass from the table's global
@@ -229,93 +176,6 @@ __global__ void __launch_bounds__(kBlock) k_plc_pick(DGlobal g, PlcParams p, int
     }
 }
 
-// The scans over every slot (score update, select passes, evict) take four
-// consecutive slots per thread with 16-byte loads issued together: with one
-// slot per thread and a score load that waited for the row load, they were
-// bound by load latency (configuration 4's 78 million slots: about 1 TB/s).
-// Slots [k0, k0 + 4) of a table, absent ones (k >= cap) reading row -1.
-__device__ __forceinline__ void slot_quad(const int32_t *a, int64_t k0, int64_t cap, int32_t fill, int32_t (&v)[4]) {
-    if (k0 + 3 < cap) {
-        const uint4 w = gload16(a + k0);
-        v[0] = (int32_t)w.x, v[1] = (int32_t)w.y, v[2] = (int32_t)w.z, v[3] = (int32_t)w.w;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = k0 + i < cap ? (int32_t)gload4(a + k0 + i) : fill;
-    }
-}
-
-// Scores of every candidate of table t (written back) and, when `sel`, the
-// histogram of the first select pass, over items tid, tid + stride, ...
-// (stride a multiple of 64: hist_add is wave-wide).
-__device__ __forceinline__ void update_items(const DGlobal &g, const PlcParams &p, const DTable &tb, const Counts &c,
-                                             int t, int *s_hist, bool sel, int64_t tid, int64_t stride) {
-    const int64_t ts = g.tstart[t], ps = g.pstart[t];
-    const int shift = pass_shift(p, 0);
-    const uint32_t dmask = (1u << pass_width(p, 0)) - 1u;
-    const int64_t cap = c.cap;
-    // resident slots, four per thread; every lane runs the same number of
-    // iterations (hist_add is wave-wide)
-    const int64_t ngrp = (cap + 3) / 4, ngrp_r = (ngrp + 63) & ~(int64_t)63;
-    for (int64_t q = tid; q < ngrp_r; q += stride) {
-        const int64_t k0 = 4 * q;
-        const int64_t lim = q < ngrp ? cap : 0;  // lanes past the last group see no slot
-        int32_t row[4], sc[4], fl[4], tch[4];
-        slot_quad(tb.slot_row, k0, lim, -1, row);
-        slot_quad(tb.slot_score, k0, lim, 0, sc);
-        slot_quad(reinterpret_cast<const int32_t *>(tb.slot_flags), k0, lim, 0, fl);
-        slot_quad(tb.slot_touch, k0, lim, -1, tch);
-        uint32_t cbw = 0;
-        if (k0 + 3 < lim) cbw = gload4(tb.slot_cbit + k0);
-        else
-            for (int i = 0; i < 4; ++i)
-                if (k0 + i < lim) cbw |= (uint32_t)tb.slot_cbit[k0 + i] << (8 * i);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t k = k0 + i;
-            const int32_t r = row[i];
-            int32_t s = sc[i];
-            uint32_t f = (uint32_t)fl[i];
-            const int cb = (int)((cbw >> (8 * i)) & 0xffu);
-            if (k < lim) {
-                if (p.prio) s = s > 0 ? s - 1 : 0;
-                if (r >= 0 && tch[i] == p.last_stamp) {
-                    f &= ~F_PF;
-                    s = touch_score(p, tb, r, cb);
-                }
-                if ((f & F_INP) && s < p.pscore) s = p.pscore;
-                // written back only where they change (most slots keep both)
-                if (r >= 0 && s != sc[i]) tb.slot_score[k] = s;
-                if (r >= 0 && (f & ~F_INP) != (uint32_t)fl[i]) tb.slot_flags[k] = f & ~F_INP;
-            }
-            if (sel) hist_add(s_hist, k < lim && r >= 0, (uint32_t)(make_key(s, r < 0 ? 0 : r, p.rowbits) >> shift) & dmask);
-        }
-        if (cbw) {  // caching bits are zero between placements
-            if (k0 + 3 < lim) *reinterpret_cast<uint32_t *>(tb.slot_cbit + k0) = 0u;
-            else
-                for (int i = 0; i < 4; ++i)
-                    if (k0 + i < lim && ((cbw >> (8 * i)) & 0xffu)) tb.slot_cbit[k0 + i] = 0;
-        }
-    }
-    // candidates: the last batch's misses, then new prefetch rows
-    const int64_t nc = (int64_t)c.nm + c.nnp, nc_r = (nc + 63) & ~(int64_t)63;
-    for (int64_t k = tid; k < nc_r; k += stride) {
-        int32_t row = -1, s = 0;
-        if (k >= nc) {
-        } else if (k < c.nm) {
-            const int64_t m = ts + k;
-            row = g.M[m];
-            const uint32_t f = g.mflags[m];
-            s = touch_score(p, tb, row, g.mcbit[m]);
-            if ((f & F_INP) && s < p.pscore) s = p.pscore;
-            g.mscore[m] = s;
-        } else {
-            row = g.NP[ps + (k - c.nm)];
-            s = new_prefetch_score(p, tb, row);
-        }
-        if (sel) hist_add(s_hist, row >= 0, (uint32_t)(make_key(s, row < 0 ? 0 : row, p.rowbits) >> shift) & dmask);
-    }
-}
-
 // Scores of every candidate (written back) and the first select pass.
 __global__ void __launch_bounds__(kBlock) k_plc_update(DGlobal g, PlcParams p) {
     if (*g.err) return;
@@ -335,54 +195,9 @@ __global__ void __launch_bounds__(kBlock) k_plc_update(DGlobal g, PlcParams p) {
         for (int b = threadIdx.x; b < kRadix; b += blockDim.x) s_hist[b] = 0;
     __syncthreads();
     update_items(g, p, tb, c, t, s_hist, sel, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
-                 (int64_t)gridDim.x * blockDim.x);
+                 (int64_t)gridDim.x * blockDim.x, FlagInp());
     __syncthreads();
     if (sel) hist_merge(g, t, s_hist);
-}
-
-// Key of candidate k (k < nm: a miss of the last batch; else a new prefetch row).
-__device__ __forceinline__ uint64_t cand_key(const DGlobal &g, const DTable &tb, const Counts &c, const PlcParams &p,
-                                             int64_t ts, int64_t ps, int64_t k) {
-    int32_t row, s;
-    if (k < c.nm) {
-        const int64_t m = ts + k;
-        row = g.M[m];
-        s = g.mscore[m];
-    } else {
-        row = g.NP[ps + (k - c.nm)];
-        s = new_prefetch_score(p, tb, row);
-    }
-    return make_key(s, row, p.rowbits);
-}
-
-// Histogram of pass `pass` over the keys of table t whose higher digits equal
-// `prefix`, over items tid, tid + stride, ... (stride a multiple of 64).
-__device__ __forceinline__ void select_items(const DGlobal &g, const PlcParams &p, const DTable &tb, const Counts &c,
-                                             int t, int *s_hist, int pass, uint64_t prefix, int64_t tid,
-                                             int64_t stride) {
-    const int64_t ts = g.tstart[t], ps = g.pstart[t];
-    const int shift = pass_shift(p, pass);
-    const int64_t cap = c.cap;
-    const int64_t ngrp = (cap + 3) / 4, ngrp_r = (ngrp + 63) & ~(int64_t)63;
-    for (int64_t q = tid; q < ngrp_r; q += stride) {
-        const int64_t k0 = 4 * q;
-        const int64_t lim = q < ngrp ? cap : 0;
-        int32_t row[4], sc[4];
-        slot_quad(tb.slot_row, k0, lim, -1, row);
-        slot_quad(tb.slot_score, k0, lim, 0, sc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint64_t key = make_key(sc[i], row[i] < 0 ? 0 : row[i], p.rowbits);
-            const bool in = row[i] >= 0 && (key >> (shift + kRadixBits)) == prefix;
-            hist_add(s_hist, in, (uint32_t)(key >> shift) & (kRadix - 1));
-        }
-    }
-    const int64_t nc = (int64_t)c.nm + c.nnp, nc_r = (nc + 63) & ~(int64_t)63;
-    for (int64_t k = tid; k < nc_r; k += stride) {
-        const uint64_t key = k < nc ? cand_key(g, tb, c, p, ts, ps, k) : 0;
-        const bool in = k < nc && (key >> (shift + kRadixBits)) == prefix;
-        hist_add(s_hist, in, (uint32_t)(key >> shift) & (kRadix - 1));
-    }
 }
 
 __global__ void __launch_bounds__(kBlock) k_plc_select(DGlobal g, PlcParams p, int pass) {
@@ -418,30 +233,8 @@ __global__ void __launch_bounds__(kRankSmallThreads) k_plc_rank_small(DGlobal g,
         st.plc_nm = c.nm;
     }
     if (tb.ways) return;
-    const bool sel = c.mode == SEL_SELECT;
-    for (int b = threadIdx.x; b < kRadix; b += blockDim.x) s_hist[b] = 0;
-    __syncthreads();
-    update_items(g, p, tb, c, t, s_hist, sel, threadIdx.x, blockDim.x);
-    __syncthreads();  // also makes the scores written above visible to the block
-    if (!sel) return;
-    uint64_t prefix = 0;
-    int need = c.keep;
-    for (int pass = 0; pass < p.passes; ++pass) {
-        if (pass > 0) {
-            for (int b = threadIdx.x; b < kRadix; b += blockDim.x) s_hist[b] = 0;
-            __syncthreads();
-            select_items(g, p, tb, c, t, s_hist, pass, prefix, threadIdx.x, blockDim.x);
-            __syncthreads();
-        }
-        int digit, rest;
-        pick_digit(s_hist, need, tmp, &digit, &rest);
-        prefix = pass == 0 ? (uint64_t)digit : ((prefix << kRadixBits) | (uint64_t)digit);
-        need = rest;
-    }
-    if (threadIdx.x == 0) {
-        st.prefix = prefix;
-        st.need = need;
-    }
+    const uint64_t thr = rank_block(g, p, tb, c, t, s_hist, tmp, FlagInp());
+    if (threadIdx.x == 0 && c.mode == SEL_SELECT) st.prefix = thr;
 }
 
 // ----------------------------------------------------------------- evict / admit
@@ -484,6 +277,8 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p) {
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
     };
+    const bool reb = st.rebuild != 0;
+    if (reb) map_clear_share(tb, blockIdx.x, gridDim.x);
     int nev = 0;
     unsigned long long dig = 0;
     const int64_t cap = tb.cap;
@@ -505,7 +300,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p) {
                     dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[i]);
                 } else {
                     ev = true;
-                    map_delete(tb, row[i]);
+                    if (!reb) map_delete(tb, row[i]);
                     tb.slot_row[k] = -1;
                     tb.slot_flags[k] = 0;
                 }
@@ -528,37 +323,8 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p) {
     if ((threadIdx.x & 63) == 0 && d) atomicAdd(&st.digest_acc, d);
     if (threadIdx.x == 0 && e) {
         atomicAdd(&st.evicted, e);
-        atomicAdd(&st.tomb, e);
+        if (!reb) atomicAdd(&st.tomb, e);
     }
-}
-
-// Rebuild the map when deleted entries exceed 1/4 of it: clear it here and
-// re-insert the surviving residents in k_map_refill.
-__global__ void __launch_bounds__(kBlock) k_map_clear(DGlobal g) {
-    if (*g.err) return;
-    const int t = blockIdx.y;
-    const DTable &tb = g.tabs[t];
-    if (tb.ways) return;
-    TState &st = g.st[t];
-    const int64_t mcap = (int64_t)tb.map_mask + 1;
-    if ((int64_t)st.tomb * 4 <= mcap) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < mcap; i += (int64_t)gridDim.x * blockDim.x)
-        tb.map[i] = make_int2(kEmpty, -1);
-    if (blockIdx.x == 0 && threadIdx.x == 0) st.rebuild = 1;
-}
-
-__global__ void __launch_bounds__(kBlock) k_map_refill(DGlobal g) {
-    if (*g.err) return;
-    const int t = blockIdx.y;
-    const DTable &tb = g.tabs[t];
-    if (tb.ways) return;
-    TState &st = g.st[t];
-    if (!st.rebuild) return;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < tb.cap; k += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t row = tb.slot_row[k];
-        if (row >= 0) map_insert(tb, row, (int32_t)k);
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) st.tomb = 0;
 }
 
 __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
@@ -572,6 +338,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
     const Counts c = table_counts(tb, st, p);
     const int mode = st.sel_mode;
     const uint64_t thr = st.prefix;
+    const bool reb = st.rebuild != 0;  // k_plc_end inserts every resident
     const int32_t top = st.free_top;
     const int64_t ts = g.ftstart[t], ps = g.pstart[t];
     const int64_t items = (int64_t)c.nm + c.nnp;
@@ -611,10 +378,10 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
             if (adm) {
                 slot = tb.free_stack[fi];
                 tb.slot_row[slot] = row;
-                tb.slot_score[slot] = s;
+                if (!tb.ring_cap) tb.slot_score[slot] = s;  // a ring's order holds its scores
                 tb.slot_flags[slot] = inp ? F_PF : 0u;
                 tb.slot_touch[slot] = -1;
-                n_reuse += map_insert(tb, row, slot);
+                if (!reb) n_reuse += map_insert(tb, row, slot);
                 // the fill list: admitted row j of this table, its source and
                 // slot: a miss's staging row; a prefetch row's host row, or for
                 // a STAGED table the staged row of its candidate (the host
@@ -648,25 +415,15 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
     }
 }
 
-// Copy admitted rows into their slots: misses from HBM staging, prefetch
-// fills from pinned host memory over the host link (ZERO_COPY tables) or from
-// rows the host staged and copied in (STAGED tables).  One launch per miss
-// mode present (phase): the zero-copy tables' at once, the STAGED tables'
-// after the host has staged their rows.  May run on a side stream,
-// concurrently with the next forward and with the next placement: it reads
-// only its own placement's fill list and descriptor (both double-buffered, see
-// k_plc_finalize) and the staging buffer of the forward before that placement,
-// which the next forward does not use.
-__global__ void __launch_bounds__(kBlock) k_plc_fill(DGlobal g, const int64_t *__restrict__ fdesc, int phase) {
-    if (*g.err) return;
-    // the blocks that copy: zero-copy fills as many as k_plc_finalize chose
-    // (fdesc[3]), HBM-to-HBM copies of STAGED rows the whole grid
-    const int64_t nb = phase == FILL_STAGED ? (int64_t)gridDim.x
-                       : fdesc[3] < 1 ? 1 : fdesc[3] > (int64_t)gridDim.x ? (int64_t)gridDim.x : fdesc[3];
-    if ((int64_t)blockIdx.x >= nb) return;  // block-uniform
+// The fill by the first nb blocks of a grid: first_of(t), count_of(t) give
+// table t's entries in the fill list, miss0_of(t) the base of its admitted
+// misses in staging.
+template <class First, class Count, class Miss0>
+__device__ __forceinline__ void fill_rows(const DGlobal &g, int phase, int64_t nb, First first_of, Count count_of,
+                                          Miss0 miss0_of) {
     __shared__ int32_t s_cnt[RECMG_MAX_TABLES];
     for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        const int64_t base = fdesc[4 * t], n = fdesc[4 * t + 1];
+        const int64_t base = first_of(t), n = count_of(t);
         const bool mine = (g.tabs[t].staged != 0) == (phase == FILL_STAGED);
         // admit wrote entries [base, base + n) and checked them against fill_cap
         s_cnt[t] = (mine && base >= 0 && n >= 0 && base + n <= g.fill_cap) ? (int32_t)n : 0;
@@ -676,12 +433,91 @@ __global__ void __launch_bounds__(kBlock) k_plc_fill(DGlobal g, const int64_t *_
     copy_flat(
         g, s_cnt, nb,
         [&](int t, const DTable &tb, int64_t j) -> const char * {
-            const int32_t src = g.fill_src[fdesc[4 * t] + j];
-            if (src >= 0) return g.staging + (fdesc[4 * t + 2] + src) * g.stage_stride;  // admitted miss
+            const int32_t src = g.fill_src[first_of(t) + j];
+            if (src >= 0) return g.staging + (miss0_of(t) + src) * g.stage_stride;  // admitted miss
             return tb.staged ? g.fstage + (int64_t)(-src - 1) * g.stage_stride  // prefetch row, host-staged
                              : tb.host + (int64_t)(-src - 1) * tb.row_bytes;    // prefetch row, zero-copy
         },
-        [&](int t, const DTable &tb, int64_t j) { return tb.pool + (int64_t)g.fill_slot[fdesc[4 * t] + j] * tb.row_bytes; });
+        [&](int t, const DTable &tb, int64_t j) { return tb.pool + (int64_t)g.fill_slot[first_of(t) + j] * tb.row_bytes; });
+}
+
+// Publishes table t's counters and moves its state past this placement; one
+// thread.  log_slot >= 0: the counters also go to that call's record of the
+// stats log (the forward group of the record stays zero).
+__device__ __forceinline__ void publish_placement(const DGlobal &g, int t, int64_t *fdesc, int64_t log_slot) {
+    TState &st = g.st[t];
+    const DTable &tb = g.tabs[t];
+    if (fdesc) {
+        fdesc[4 * t] = g.ftstart[t] + g.pstart[t];
+        fdesc[4 * t + 1] = st.popped;
+        fdesc[4 * t + 2] = g.ftstart[t];
+    }
+    int32_t n_res = st.n_res;
+    if (!tb.ways) {  // set-associative tables count residents as they place
+        const int32_t top = st.free_top - st.popped;  // popped stays: the fill may still read it
+        st.free_top = top;
+        n_res = tb.cap - top;
+        st.n_res = n_res;
+        const int32_t tomb = st.rebuild ? 0 : st.tomb;
+        st.tomb = tomb;
+        st.rebuild_next = (int64_t)tomb * 4 > (int64_t)tb.map_mask + 1 ? 1u : 0u;
+    }
+    if (tb.ring_cap) {  // the ring's new front and back, the new pending list
+        int32_t head;
+        if (st.r_compact) {  // the live entries moved to the front of the other buffer
+            st.r_buf ^= 1;
+            st.r_tail = 0;
+            head = st.r_moved + st.z1_len;
+            st.r_compact = 0;
+        } else {
+            st.r_tail = st.r_cut;
+            head = st.r_head + st.z1_len;
+        }
+        st.r_head = head;
+        st.pend_n = st.pcount;
+        st.pend_off = g.pstart[t];
+        if (st.r_valid + st.pend_keep != n_res || head > tb.ring_cap) atomicOr(g.err, ERR_INTERNAL);
+    }
+    int64_t v[kPlcStats];
+    v[0] = st.evicted;
+    v[1] = st.adm_miss;
+    v[2] = st.p_fill;
+    v[3] = st.p_res;
+    v[4] = st.p_drop;
+    v[5] = st.m_drop;
+    v[6] = n_res;
+    v[7] = (int64_t)st.p_fill * tb.row_bytes;
+    v[8] = st.pcount;
+    for (int k = 0; k < kPlcStats; ++k) {
+        st.last[kFwdStats + k] = v[k];
+        st.total[kFwdStats + k] += v[k];
+    }
+    st.digest = st.digest_acc;
+    if (log_slot >= 0) {
+        int64_t *rec = g.stat_log + (log_slot * g.T + t) * (kNumStats + 1);
+        for (int k = 0; k < kNumStats; ++k) rec[k] = k < kFwdStats ? 0 : v[k - kFwdStats];
+        rec[kNumStats] = (int64_t)st.digest_acc;
+    }
+}
+
+// Copy admitted rows into their slots: misses from HBM staging, prefetch
+// fills from pinned host memory over the host link (ZERO_COPY tables) or from
+// rows the host staged and copied in (STAGED tables).  One launch per miss
+// mode present (phase): the zero-copy tables' at once, the STAGED tables'
+// after the host has staged their rows.  May run on a side stream,
+// concurrently with the next forward and with the next placement: it reads
+// only its own placement's fill list and descriptor (both double-buffered, see
+// k_plc_end) and the staging buffer of the forward before that placement,
+// which the next forward does not use.
+__global__ void __launch_bounds__(kBlock) k_plc_fill(DGlobal g, const int64_t *__restrict__ fdesc, int phase) {
+    if (*g.err) return;
+    // the blocks that copy: zero-copy fills as many as k_plc_end chose
+    // (fdesc[3]), HBM-to-HBM copies of STAGED rows the whole grid
+    const int64_t nb = phase == FILL_STAGED ? (int64_t)gridDim.x
+                       : fdesc[3] < 1 ? 1 : fdesc[3] > (int64_t)gridDim.x ? (int64_t)gridDim.x : fdesc[3];
+    if ((int64_t)blockIdx.x >= nb) return;  // block-uniform
+    fill_rows(g, phase, nb, [&](int t) { return fdesc[4 * t]; }, [&](int t) { return fdesc[4 * t + 1]; },
+              [&](int t) { return fdesc[4 * t + 2]; });
 }
 
 #ifndef RECMG_FILL_BLOCKS
@@ -704,79 +540,53 @@ constexpr int kFillGridBlocks = RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_SHARED
                                     : (RECMG_FILL_BLOCKS_SHARED > RECMG_FILL_BLOCKS_BIG ? RECMG_FILL_BLOCKS_SHARED
                                                                                        : RECMG_FILL_BLOCKS_BIG);
 
-// Publishes the counters and writes the fill descriptor of this placement
-// (per table: first fill-list entry, entry count, base of its admitted misses
-// in staging), which the fill reads instead of state the next placement resets.
-// fdesc[3] (a spare word of table 0's entry) is the number of blocks the fill
-// copies with: zero-copy fills take more when the last forward fetched at
-// least 1 MB on demand, since the next forward's fetch will then share the
-// host link (with fewer waves of its own the fill gets less of it), more
-// still when it fetched at least 256 MB (the two then hold the link for tens
-// of milliseconds, and the kernels beside them are a small part of the step),
-// and fewer when the fill has the link to itself, so that it takes no more
-// CUs than it needs from the kernels beside it.
-// log_slot >= 0: the counters also go to that call's record of the stats log
-// (the forward group of the record stays zero).
-__global__ void k_plc_finalize(DGlobal g, int64_t *fdesc, int64_t log_slot) {
-    if (*g.err) return;  // one block; nothing sets the word while it runs
-    __shared__ unsigned long long s_mbytes;  // bytes of the last forward's on-demand misses
-    if (threadIdx.x == 0) s_mbytes = 0;
-    __syncthreads();
-    unsigned long long mb = 0;
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x)
-        mb += (unsigned long long)(g.st[t].mcount > 0 ? g.st[t].mcount : 0) * (unsigned long long)g.tabs[t].row_bytes;
-    if (mb) atomicAdd(&s_mbytes, mb);
-    __syncthreads();
-    if (threadIdx.x == 0)
-        fdesc[3] = s_mbytes >= kBigFetchBytes      ? RECMG_FILL_BLOCKS_BIG
-                   : s_mbytes >= kSharedFetchBytes ? RECMG_FILL_BLOCKS_SHARED
-                                                   : RECMG_FILL_BLOCKS;
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        TState &st = g.st[t];
-        const DTable &tb = g.tabs[t];
-        fdesc[4 * t] = g.ftstart[t] + g.pstart[t];
-        fdesc[4 * t + 1] = st.popped;
-        fdesc[4 * t + 2] = g.ftstart[t];
-        if (!tb.ways) {  // set-associative tables count residents as they place
-            st.free_top -= st.popped;  // popped stays: the fill may still read it
-            st.n_res = tb.cap - st.free_top;
-        }
-        if (tb.ring_cap) {  // the ring's new front and back, the new pending list
-            if (st.r_compact) {  // the live entries moved to the front of the other buffer
-                st.r_buf ^= 1;
-                st.r_tail = 0;
-                st.r_head = st.r_moved + st.z1_len;
-                st.r_compact = 0;
-            } else {
-                st.r_tail = st.r_cut;
-                st.r_head += st.z1_len;
-            }
-            st.pend_n = st.pcount;
-            st.pend_off = g.pstart[t];
-            if (st.r_valid + st.pend_keep != st.n_res || st.r_head > tb.ring_cap) atomicOr(g.err, ERR_INTERNAL);
-        }
-        st.rebuild = 0;
-        int64_t v[kPlcStats];
-        v[0] = st.evicted;
-        v[1] = st.adm_miss;
-        v[2] = st.p_fill;
-        v[3] = st.p_res;
-        v[4] = st.p_drop;
-        v[5] = st.m_drop;
-        v[6] = st.n_res;
-        v[7] = (int64_t)st.p_fill * tb.row_bytes;
-        v[8] = st.pcount;
-        for (int k = 0; k < kPlcStats; ++k) {
-            st.last[kFwdStats + k] = v[k];
-            st.total[kFwdStats + k] += v[k];
-        }
-        st.digest = st.digest_acc;
-        if (log_slot >= 0) {
-            int64_t *rec = g.stat_log + (log_slot * g.T + t) * (kNumStats + 1);
-            for (int k = 0; k < kNumStats; ++k) rec[k] = k < kFwdStats ? 0 : v[k - kFwdStats];
-            rec[kNumStats] = (int64_t)st.digest_acc;
-        }
+// The end of a placement.  Blocks by role:
+//   [0, nfill)         the fill, where it runs with the placement (small batches:
+//                      see recmg_apply_placement); else nfill = 0
+//   [nfill, + T)       table blockIdx.x - nfill: a set-associative table's counts
+//                      added up (sa_sum), its counters published, its fill
+//                      descriptor written (fdesc, where the fill runs apart)
+//   the rest           the maps that this placement cleared, refilled
+// fdesc (per table: first fill-list entry, entry count, base of its admitted
+// misses in staging) is what a fill on another stream reads instead of state
+// the next placement resets.  fdesc[3] (a spare word of table 0's entry) is the
+// number of blocks such a fill copies with: zero-copy fills take more when the
+// last forward fetched at least 1 MB on demand, since the next forward's fetch
+// will then share the host link (with fewer waves of its own the fill gets less
+// of it), more still when it fetched at least 256 MB (the two then hold the
+// link for tens of milliseconds, and the kernels beside them are a small part
+// of the step), and fewer when the fill has the link to itself, so that it
+// takes no more CUs than it needs from the kernels beside it.
+__global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, int64_t log_slot, int32_t nfill,
+                                                    int32_t nsa) {
+    if (*g.err) return;  // set by earlier kernels only, but for broken ring counts (below)
+    __shared__ long long tmp[16];
+    if ((int)blockIdx.x < nfill) {  // block-uniform, as the other roles
+        fill_rows(g, FILL_ZERO_COPY, nfill, [&](int t) { return g.ftstart[t] + g.pstart[t]; },
+                  [&](int t) { return (int64_t)g.st[t].popped; }, [&](int t) { return g.ftstart[t]; });
+        return;
     }
+    const int r = (int)blockIdx.x - nfill;
+    if (r >= g.T) {
+        const int nb = (int)gridDim.x - nfill - g.T;
+        for (int t = 0; t < g.T; ++t)
+            if (g.st[t].rebuild) map_refill_share(g.tabs[t], r - g.T, nb);
+        return;
+    }
+    if (nsa > 0 && g.tabs[r].ways) sa_sum_table(g, r, nsa, tmp);
+    if (r == 0 && fdesc) {
+        long long mb = 0, tot;  // bytes of the last forward's on-demand misses
+        if ((int)threadIdx.x < g.T) {
+            const int32_t m = g.st[threadIdx.x].mcount;
+            mb = (long long)(m > 0 ? m : 0) * g.tabs[threadIdx.x].row_bytes;
+        }
+        (void)block_excl_scan64(mb, tmp, &tot);
+        if (threadIdx.x == 0)
+            fdesc[3] = (unsigned long long)tot >= kBigFetchBytes      ? RECMG_FILL_BLOCKS_BIG
+                       : (unsigned long long)tot >= kSharedFetchBytes ? RECMG_FILL_BLOCKS_SHARED
+                                                                      : RECMG_FILL_BLOCKS;
+    }
+    if (threadIdx.x == 0) publish_placement(g, r, fdesc, log_slot);
 }
 
 // Initial state: every slot free, the free stack handing out slot 0 first.
@@ -839,10 +649,7 @@ void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, hip
     k_plc_evict<<<dim3(grid_for(max_cap, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g, p);
 }
 
-void launch_plc_admit(const DGlobal &g, const PlcParams &p, int32_t max_cap, int32_t max_map, int64_t cand_bound,
-                      hipStream_t s) {
-    k_map_clear<<<dim3(grid_for(max_map, kBlock * 8, 2048), g.T), kBlock, 0, s>>>(g);
-    k_map_refill<<<dim3(grid_for(max_cap, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g);
+void launch_plc_admit(const DGlobal &g, const PlcParams &p, int64_t cand_bound, hipStream_t s) {
     k_plc_admit<<<dim3(grid_for(cand_bound, kBlock * items_per_thread(cand_bound, 4), 2048), g.T), kBlock, 0, s>>>(g, p);
 }
 
@@ -860,15 +667,20 @@ void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStrea
     // (85 MB), and 256 blocks gave +4% (512: -6%).  On configuration 5 the
     // fetch moves about 750 MB per batch beside a 3.8 GB fill, and 512 blocks
     // gave +2.7% against 256 (768 and 1024: the same as 512).  The grid holds
-    // the largest count; k_plc_finalize writes how many of its blocks copy.
+    // the largest count; k_plc_end writes how many of its blocks copy.
     // STAGED fills copy within HBM and take a full grid.
     const int blocks = phase == FILL_STAGED ? kStagedFillBlocks : kFillGridBlocks;
     if (ev0 || ev1) hipExtLaunchKernelGGL(k_plc_fill, dim3(blocks), dim3(kBlock), 0, s, ev0, ev1, 0, g, fdesc, phase);
     else k_plc_fill<<<blocks, kBlock, 0, s>>>(g, fdesc, phase);
 }
 
-void launch_plc_finalize(const DGlobal &g, int64_t *fdesc, int64_t log_slot, hipStream_t s) {
-    k_plc_finalize<<<1, kBlock, 0, s>>>(g, fdesc, log_slot);
+void launch_plc_end(const DGlobal &g, int64_t *fdesc, int64_t log_slot, bool fill, int32_t max_fa_cap, int32_t nsa,
+                    hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    const int32_t nfill = fill ? RECMG_FILL_BLOCKS : 0;
+    const unsigned refill = max_fa_cap > 0 ? grid_for(max_fa_cap, kBlock * 4, 256) : 0;
+    const dim3 grid((unsigned)nfill + (unsigned)g.T + refill);
+    if (ev0 || ev1) hipExtLaunchKernelGGL(k_plc_end, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, fdesc, log_slot, nfill, nsa);
+    else k_plc_end<<<grid, kBlock, 0, s>>>(g, fdesc, log_slot, nfill, nsa);
 }
 
 void launch_init_state(const DGlobal &g, int32_t max_cap, hipStream_t s) {

@@ -116,7 +116,7 @@ struct TState {
     int32_t n_res, free_top, popped, tomb;
     int32_t rebuild, sel_mode, need, plc_nm;  // plc_nm: misses the current placement ranks
     uint64_t prefix;  // radix-select prefix; the threshold key after the last pass
-    uint32_t pad0;
+    uint32_t rebuild_next;  // rebuild of the next placement: deleted entries passed a quarter of the map
     int32_t covered;  // accumulator: distinct prefetch rows of the last placement found in this batch
     // accumulators of the call in flight
     int32_t hits, hits_pf, p_res, evicted, adm_miss, p_fill, p_drop, m_drop;
@@ -291,28 +291,32 @@ __device__ __forceinline__ void map_find_n(const DTable &tb, const int32_t (&row
     }
 }
 
-// The map holds at most Cap live rows in >= 4 Cap entries, and is rebuilt when
-// deleted entries pass a quarter of it, so at least half of it stays empty.
+// The map holds at most Cap live rows in >= 4 Cap entries, and is rebuilt in the
+// placement after the one whose deleted entries passed a quarter of it (at most
+// Cap more by then), so at least a quarter of it stays empty.
 
 // Insert a row known to be absent.  Concurrent inserts of distinct rows are
-// safe; no lookup may run concurrently.  Returns 1 if a deleted entry was reused.
+// safe; no lookup may run concurrently.  Returns 1 if a deleted entry was
+// reused.  An entry (key, slot) is taken whole by one 64-bit compare-and-swap,
+// tried on the empty value first: mostly one memory operation per insert.
 __device__ __forceinline__ int map_insert(const DTable &tb, int32_t row, int32_t slot) {
     const int32_t mask = tb.map_mask;
+    const unsigned long long mine = ((unsigned long long)(uint32_t)slot << 32) | (uint32_t)row;
     uint32_t i = hash_row(row) & (uint32_t)mask;
     for (int32_t n = 0; n <= mask; ++n) {
-        int32_t k = tb.map[i].x;  // may be stale (L1); the CAS result is not
-        while (k == kEmpty || k == kTomb) {
-            const int32_t prev = atomicCAS(&tb.map[i].x, k, row);
-            if (prev == k) {
-                tb.map[i].y = slot;
-                return k == kTomb;
-            }
-            k = prev;  // lost the entry to another insert
+        unsigned long long cur = ~0ull;  // an empty entry: key -1, slot -1
+        for (;;) {
+            const unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long *>(tb.map + i), cur, mine);
+            const int32_t k = (int32_t)(uint32_t)prev;
+            if (prev == cur) return k == kTomb;
+            if (k != kEmpty && k != kTomb) break;  // taken by another row
+            cur = prev;  // a deleted entry (with its old slot)
         }
         i = (i + 1) & (uint32_t)mask;
     }
     return 0;
 }
+static_assert(kEmpty == -1, "an empty map entry is all ones");
 
 // Delete a present row (distinct rows may be deleted concurrently).
 __device__ __forceinline__ void map_delete(const DTable &tb, int32_t row) {
@@ -631,6 +635,7 @@ __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const in
         g.ftstart[g.T] = have_fwd ? g.tstart[g.T] : 0;
     }
     TState &st = g.st[t];
+    st.rebuild = (int32_t)st.rebuild_next;
     st.pcount = 0;
     st.npcount = 0;
     st.popped = 0;

@@ -38,16 +38,11 @@
 #include <algorithm>
 
 #include "launch.h"
+#include "placement_device.h"
 
 namespace recmg {
 
-constexpr int kRingThreads = 1024;  // one-block-per-table kernels: one entry of a chunk per thread
-static_assert(kRingThreads == kRingChunk, "the cut takes a chunk's entries one per thread");
 constexpr int kRingEvictBuf = 2048;
-
-__device__ __forceinline__ bool ring_live(const DTable &tb, int32_t slot, int32_t e) {
-    return slot >= 0 && slot < tb.cap && tb.slot_pos[slot] == e;
-}
 
 // First index of a[0, n) (ascending) holding a value >= v, or > v if upper.
 __device__ __forceinline__ int32_t ring_bound(const int32_t *a, int32_t n, int32_t v, bool upper) {
@@ -61,13 +56,6 @@ __device__ __forceinline__ int32_t ring_bound(const int32_t *a, int32_t n, int32
     return lo;
 }
 
-// Table t's zone Z1: entries [pend_off + tstart[t], + z1_len) of g.zone.
-// Tables' regions are disjoint: pend_off and tstart partition the prefetch
-// and index spaces, and z1_len = pend_n + (last forward's distinct rows).
-__device__ __forceinline__ int2 *ring_zone(const DGlobal &g, const TState &st, int t) {
-    return g.zone + st.pend_off + g.tstart[t];
-}
-
 // One pass over the pending rows, the last batch's distinct rows and the
 // prefetch list:
 //  * Z1 by merging two ascending lists: pending entry i lands at i + (U rows
@@ -76,7 +64,7 @@ __device__ __forceinline__ int2 *ring_zone(const DGlobal &g, const TState &st, i
 //    a hole.  A key is a pending row neither touched nor named again, a hit or
 //    miss the list does not name (F_INP, set by classification).
 //  * new scores: hits take the touch score, or pscore if the list names them
-//    (and lose F_PF); the list's untouched residents take pscore.  Their ring
+//    (and lose F_PF); the list's untouched residents take pscore.  So their ring
 //    entries go stale (slot_pos = -1).  F_INP stays until the append.
 //  * the misses' scores, which admission reads.
 // A thread reads a pending row's flags only if the batch did not touch it,
@@ -100,7 +88,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st.z1_len = n1;
     int keys = 0, stale = 0;
     for (int32_t j = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); j < n; j += (int32_t)(gridDim.x * blockDim.x)) {
-        int32_t sl = -1, s = 0;  // a resident whose score changes, and its new score
+        int32_t sl = -1;  // a resident whose score changes (the ring's order holds the scores, no slot does)
         if (j < n1) {
             int32_t row, at, ref = kRingHole;
             if (j < pn) {
@@ -118,7 +106,6 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
                     const bool inp = (f & F_INP) != 0;
                     if (!inp) ref = h;
                     sl = h;
-                    s = inp ? p.pscore : p.lru_touch;
                     if (f & F_PF) tb.slot_flags[h] = f & ~F_PF;
                 } else {
                     const int32_t m = -h - 1;
@@ -131,13 +118,9 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
             keys += ref != kRingHole ? 1 : 0;
         } else {
             const int32_t v = g.puref[ps + (j - n1)];
-            if (v >= 0 && tb.slot_touch[v] != p.last_stamp) {  // touched: its hit entry scored it
-                sl = v;
-                s = p.pscore;
-            }
+            if (v >= 0 && tb.slot_touch[v] != p.last_stamp) sl = v;  // touched: its hit entry took care of it
         }
         if (sl >= 0) {
-            tb.slot_score[sl] = s;
             const int32_t e = tb.slot_pos[sl];
             if (e >= 0) {  // pending rows have no ring entry
                 tb.slot_pos[sl] = -1;
@@ -153,130 +136,26 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
     }
 }
 
-// One block per table: where the D keys to drop end.  Sets sel_mode and the
-// threshold key (st.prefix) that admission applies to the candidates, the
-// ring's cut, whether Z1/Z2 residents are evicted, and whether the live
-// entries after the cut move to the front of the other buffer (when this
-// placement's run would not fit behind them), with each chunk's first new
-// index.
+// One block per table: ring_cut, kept in the table's state for the kernels
+// that apply it.
 __global__ void __launch_bounds__(kRingThreads) k_ring_cut(DGlobal g, PlcParams p) {
     if (*g.err) return;
     __shared__ int tmp[16];
-    __shared__ int32_t s_at, s_rest;
     const int t = blockIdx.x;
     const DTable &tb = g.tabs[t];
     if (!tb.ring_cap) return;
     TState &st = g.st[t];
     const Counts c = table_counts(tb, st, p);
-    const int64_t nk = (int64_t)st.n_res + c.nm + c.nnp;
-    const int64_t drop = nk - c.keep;
-    const int32_t nold = st.r_valid, z1 = st.z1_keys, z2 = st.pcount;
-    const int32_t head = st.r_head, tail = st.r_tail;
-    const int32_t *ring = tb.ring[st.r_buf];
-    const int32_t *rcnt = tb.rcnt[st.r_buf];
-    const int32_t nch = (int32_t)(((int64_t)head + kRingChunk - 1) / kRingChunk);
-    bool bad = nold < 0 || (int64_t)nold + z1 + z2 != nk;  // every key sits in the ring, Z1 or Z2
-    int32_t mode = c.mode, cut = tail, zev = 0, cut_live = 0;  // cut_live: live entries of cut's chunk before it
-    uint64_t thr = make_key(p.lru_touch, 0, p.rowbits);  // below every key of Z1 and Z2
-    if (!bad && drop > 0 && drop <= nold) {
-        // the drop-th live entry from the front: whole chunks by their counts,
-        // then the entries of the chunk that reaches it
-        mode = SEL_SELECT;
-        int32_t need = (int32_t)drop, cc = -1;
-        for (int32_t base = tail / kRingChunk; base < nch; base += kRingThreads) {
-            const int32_t ch = base + (int32_t)threadIdx.x;
-            const int v = ch < nch ? rcnt[ch] : 0;
-            int tot;
-            const int ex = block_excl_scan(v, tmp, &tot);
-            if (need <= tot) {  // block-uniform
-                if (ex < need && ex + v >= need) {
-                    s_at = ch;
-                    s_rest = need - ex;
-                }
-                __syncthreads();
-                cc = s_at;
-                need = s_rest;
-                __syncthreads();  // read before s_at is reused below
-                break;
-            }
-            need -= tot;
-        }
-        if (cc < 0) {
-            bad = true;
-        } else {
-            const int32_t e = cc * kRingChunk + (int32_t)threadIdx.x;
-            const bool live = e >= tail && e < head && ring_live(tb, ring[e], e);
-            if (threadIdx.x == 0) s_at = -1;
-            int tot;
-            const int ex = block_excl_scan(live ? 1 : 0, tmp, &tot);  // its barriers order s_at's reset
-            if (live && ex + 1 == need) s_at = e + 1;
-            __syncthreads();
-            cut = s_at;
-            if (cut < 0) bad = true;
-            else if (cut / kRingChunk == cc) cut_live = need;
-        }
-    } else if (!bad && drop > nold) {
-        // the whole ring goes; the threshold is the key of rank r of Z1, or of
-        // rank r - |Z1| of Z2 (every prefetch row is a key)
-        cut = head;
-        zev = 1;
-        const int32_t r = (int32_t)(drop - nold);
-        if (r < z1) {
-            const int2 *z = ring_zone(g, st, t);
-            const int32_t n = st.z1_len;
-            int32_t want = r;
-            if (threadIdx.x == 0) s_at = -1;
-            __syncthreads();
-            for (int32_t base = 0; base < n; base += kRingThreads) {
-                const int32_t j = base + (int32_t)threadIdx.x;
-                const int2 zr = j < n ? z[j] : make_int2(kRingHole, 0);
-                const bool key = zr.x != kRingHole;
-                int tot;
-                const int ex = block_excl_scan(key ? 1 : 0, tmp, &tot);
-                if (want < tot) {  // block-uniform
-                    if (key && ex == want) s_at = zr.y;
-                    __syncthreads();
-                    break;
-                }
-                want -= tot;
-            }
-            if (s_at < 0) bad = true;
-            thr = make_key(p.lru_touch, s_at < 0 ? 0 : s_at, p.rowbits);
-            mode = SEL_SELECT;
-        } else if (r - z1 < z2) {
-            thr = make_key(p.pscore, g.PU[g.pstart[t] + (r - z1)], p.rowbits);
-            mode = SEL_SELECT;
-        } else {
-            mode = SEL_NONE;
-        }
-    } else if (!bad) {
-        mode = SEL_ALL;  // nothing to drop
-    }
-    const int32_t moved = bad ? 0 : (int32_t)(drop <= 0 ? nold : drop <= nold ? nold - drop : 0);
-    const bool compact = (int64_t)head + st.z1_len > tb.ring_cap;
-    if (compact && moved > 0) {
-        // first new index of each chunk from cut's on: its live entries at or after the cut
-        int32_t run = 0;
-        const int32_t c0 = cut / kRingChunk;
-        for (int32_t base = c0; base < nch; base += kRingThreads) {
-            const int32_t ch = base + (int32_t)threadIdx.x;
-            const int v = ch < nch ? rcnt[ch] - (ch == c0 ? cut_live : 0) : 0;
-            int tot;
-            const int ex = block_excl_scan(v, tmp, &tot);
-            if (ch < nch) tb.roff[ch] = run + ex;
-            run += tot;
-        }
-        if (run != moved) bad = true;
-    }
+    const RingCut o = ring_cut(g, p, t, tb, st, c, st.r_valid, st.z1_keys, st.z1_len, st.pcount, tmp);
     if (threadIdx.x == 0) {
-        if (bad) atomicOr(g.err, ERR_INTERNAL);
-        st.sel_mode = mode;
-        st.prefix = thr;
+        if (o.bad) atomicOr(g.err, ERR_INTERNAL);
+        st.sel_mode = o.mode;
+        st.prefix = o.thr;
         st.plc_nm = c.nm;
-        st.r_cut = cut;
-        st.r_zevict = zev;
-        st.r_compact = compact ? 1 : 0;
-        st.r_moved = moved;
+        st.r_cut = o.cut;
+        st.r_zevict = o.zev;
+        st.r_compact = o.compact ? 1 : 0;
+        st.r_moved = o.moved;
     }
 }
 
@@ -313,13 +192,15 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
     };
+    const bool reb = st.rebuild != 0;
+    if (reb) map_clear_share(tb, blockIdx.x, gridDim.x);
     int nev = 0, nring = 0;
     unsigned long long dig = 0;
     // frees slot sl (when ev) and lists it; every lane of the wave calls
     auto evict = [&](bool ev, int32_t sl) {
         if (ev) {
             const int32_t row = tb.slot_row[sl];
-            map_delete(tb, row);
+            if (!reb) map_delete(tb, row);
             tb.slot_row[sl] = -1;
             tb.slot_flags[sl] = 0;
             tb.slot_pos[sl] = -1;
@@ -410,7 +291,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
     if (threadIdx.x == 0) {
         if (e) {
             atomicAdd(&st.evicted, e);
-            atomicAdd(&st.tomb, e);
+            if (!reb) atomicAdd(&st.tomb, e);
         }
         if (er) atomicSub(&st.r_valid, er);
     }

@@ -32,6 +32,7 @@
 #include <algorithm>
 
 #include "launch.h"
+#include "placement_device.h"
 
 namespace recmg {
 
@@ -415,42 +416,13 @@ __global__ void __launch_bounds__(kSaBlock) k_sa_place(DGlobal g, PlcParams p, i
     }
 }
 
-// The placement blocks' records added to their tables' counters: blockIdx.x
-// is the table (in sa_btab order), blockIdx.y one of gridDim.y slices of its
-// blocks; one atomic per counter per slice.
-__global__ void __launch_bounds__(1024) k_sa_sum(DGlobal g, int32_t nsa) {
+// The records of a table with many placement blocks, added up by slices:
+// blockIdx.x is the table (in sa_btab order), blockIdx.y one of gridDim.y slices
+// of its blocks (tables of few blocks: one block of k_plc_end).
+__global__ void __launch_bounds__(1024) k_sa_sum(DGlobal g) {
     if (*g.err) return;
     __shared__ long long tmp[16];
-    __shared__ unsigned long long s_dig[16];
-    const int kt = blockIdx.x;
-    TState &st = g.st[g.sa_btab[kt]];
-    const int32_t b0 = g.sa_bstart[kt], b1 = g.sa_bstart[kt + 1];
-    long long v[7] = {0, 0, 0, 0, 0, 0, 0};
-    unsigned long long dg = 0;  // digests add modulo 2^64
-    for (int32_t b = b0 + (int32_t)(blockIdx.y * blockDim.x + threadIdx.x); b < b1;
-         b += (int32_t)(gridDim.y * blockDim.x)) {
-#pragma unroll
-        for (int k = 0; k < 7; ++k) v[k] += g.sa_part[(int64_t)b * 8 + k];
-        dg += (unsigned long long)g.sa_part[(int64_t)b * 8 + 7];
-    }
-    long long tot[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) (void)block_excl_scan64(v[k], tmp, &tot[k]);
-    dg = wave_sum64(dg);
-    if ((threadIdx.x & 63) == 0) s_dig[threadIdx.x >> 6] = dg;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long d = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) d += s_dig[w];
-        if (tot[0]) atomicAdd(&st.evicted, (int32_t)tot[0]);
-        if (tot[1]) atomicAdd(&st.adm_miss, (int32_t)tot[1]);
-        if (tot[2]) atomicAdd(&st.p_fill, (int32_t)tot[2]);
-        if (tot[3]) atomicAdd(&st.p_drop, (int32_t)tot[3]);
-        if (tot[4]) atomicAdd(&st.m_drop, (int32_t)tot[4]);
-        if (tot[5]) atomicAdd(&st.n_res, (int32_t)tot[5]);
-        if (tot[6]) atomicAdd(&st.p_res, (int32_t)tot[6]);
-        if (d) atomicAdd(&st.digest_acc, d);
-    }
+    sa_sum_records(g, blockIdx.x, blockIdx.y, gridDim.y, tmp);
 }
 
 static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
@@ -461,14 +433,16 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
 }
 
 void launch_sa_place(const DGlobal &g, const PlcParams &p, int64_t nu, int64_t np, int32_t nsa, int64_t blocks1,
-                     int64_t blocks, int64_t max_blocks, hipStream_t s) {
-    if (nu + np > 0) k_sa_heads<<<grid_for(nu + np, kBlock, 8192), kBlock, 0, s>>>(g, nu, np, p.have_fwd, p.last_stamp);
+                     int64_t blocks, int64_t max_blocks, bool heads, hipStream_t s) {
+    if (heads && nu + np > 0) k_sa_heads<<<grid_for(nu + np, kBlock, 8192), kBlock, 0, s>>>(g, nu, np, p.have_fwd, p.last_stamp);
     // tables of one set per wave come first (fewest sets), then those of two
     if (blocks1 > 0) k_sa_place<1><<<(unsigned)blocks1, kSaBlock, 0, s>>>(g, p, nsa, 0);
     if (blocks > blocks1) k_sa_place<2><<<(unsigned)(blocks - blocks1), kSaBlock, 0, s>>>(g, p, nsa, (int32_t)blocks1);
     // slices: about 4,096 records each for the table with the most blocks
-    const unsigned slices = (unsigned)std::min<int64_t>(32, std::max<int64_t>(1, (max_blocks + 4095) / 4096));
-    k_sa_sum<<<dim3(nsa, slices), 1024, 0, s>>>(g, nsa);
+    if (max_blocks > kSaSumInEnd) {
+        const unsigned slices = (unsigned)std::min<int64_t>(32, (max_blocks + 4095) / 4096);
+        k_sa_sum<<<dim3(nsa, slices), 1024, 0, s>>>(g);
+    }
 }
 
 }  // namespace recmg

@@ -7,6 +7,7 @@
 // so the presence bitmap, its prefix sums and every counter stay in LDS, and
 // what passes from step to step costs a barrier instead of a launch.
 #include "launch.h"
+#include "placement_device.h"
 
 namespace recmg {
 
@@ -270,9 +271,494 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(DGlobal g, const in
     }
 }
 
+// ----------------------------------------------------------------- placement
+
+// Block totals of a count held per thread, one LDS atomic per wave.
+__device__ __forceinline__ void lds_sum(int v, int *counter) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0 && v) atomicAdd(counter, v);
+}
+
+// Everything of a placement but the sets of set-associative tables, the fill
+// and the published counters, for one table per block.  Same results as the
+// general sequence (placement.hip, ring.hip, k_sa_heads); what k_plc_end reads
+// from the table's state is written once, by thread 0, at the end.
+//   all tables   list offsets checked, caching bits or batch counts of the last
+//                batch, set(P) sorted (PU)
+//   set-assoc.   each set's event segments and the prefetch rows' staging rows
+//                (then k_sa_place plays the sets)
+//   others       classification of PU; ranking: the radix select of rank_block,
+//                or the resident ring's cut; eviction; admission; the ring's run
+//                and pending list
+// The ring's zone Z1 (keys of the touch score in row order) comes from the same
+// kind of LDS bitmap as the dedup: its rows are marked, and a row's place is its
+// rank.  So Z1 has no holes here, and no row is searched for in the other list.
+// P's bitmap answers whether a row is named, so no slot or miss is flagged.
+// What bounds it is the one CU's rate of scattered accesses (some 10 ns each),
+// so each step makes as few per row as it can.
+template <int NB>
+__global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParams p, const int32_t *__restrict__ rows,
+                                                             const int64_t *__restrict__ poff, int64_t np,
+                                                             const uint8_t *__restrict__ bits, int wr) {
+    enum { C_PRES, C_NP, C_STALE, C_EV, C_RING_EV, C_POP, C_ADM, C_FILL, C_PDROP, C_MDROP, C_REUSE, C_RUN, C_KEEP, C_N };
+    __shared__ LdsBitmap<NB> bm, bz;  // the rows of P; the rows of Z1 (or the ranking's histogram)
+    __shared__ int tmp[16];
+    __shared__ int s_c[C_N];
+    __shared__ int s_err, s_bad_id;
+    __shared__ unsigned long long s_dig;
+    static_assert(sizeof(bz.w4) >= kRadix * sizeof(int), "the ranking's histogram takes a bitmap's place");
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const DTable tb = g.tabs[t];
+    TState &st = g.st[t];
+    if (tid == 0) {
+        s_err = *g.err;  // read once: another block may set it meanwhile
+        s_bad_id = 0;
+        s_dig = 0;
+    }
+    if (tid < C_N) s_c[tid] = 0;
+    const int nw = tb.bm_words;
+    bm.clear(nw);
+    const int64_t lo = poff[t], hi = poff[t + 1];
+    __syncthreads();
+    if (s_err) return;  // block-uniform
+    if (lo < 0 || hi < lo || hi > np || (t == 0 && lo != 0) || (t == g.T - 1 && hi != np)) {  // block-uniform
+        if (tid == 0) atomicOr(g.err, ERR_OFFSETS);
+        return;
+    }
+    const int64_t ts = g.tstart[t], te = g.tstart[t + 1], fts = p.have_fwd ? ts : 0;
+    const int32_t nu = p.have_fwd ? st.ucount : 0, nm = p.have_fwd ? st.mcount : 0;
+    const int32_t n_res = st.n_res;
+    const bool reb = st.rebuild_next != 0;
+    if (tid == 0) {
+        g.pstart[t] = lo;
+        g.ftstart[t] = fts;
+        if (t == g.T - 1) {
+            g.pstart[g.T] = hi;
+            g.ftstart[g.T] = p.have_fwd ? te : 0;
+        }
+    }
+    if (p.prio && bits && p.have_fwd) {
+        // OR of the caching bits per row; every writer stores the same value
+        for (int64_t i = ts + tid; i < te; i += kSmallThreads) {
+            if (!bits[i]) continue;
+            const int32_t s = g.src[i];
+            uint8_t *f = s >= 0 ? tb.slot_cbit + s : g.mcbit + ts + (-(int64_t)s - 1);
+            if (!*f) *f = 1;
+        }
+    }
+    if (p.lfu)
+        for (int32_t u = tid; u < nu; u += kSmallThreads) tb.freq[g.U[ts + u]] += 1;  // distinct rows
+    if (!mark_ids(bm, tb, rows, lo, hi)) s_bad_id = 1;
+    __syncthreads();
+    if (s_bad_id) {  // block-uniform
+        if (tid == 0) atomicOr(g.err, ERR_RANGE);
+        return;
+    }
+    const int32_t pc = bm.scan(nw, tmp);
+    int32_t *PU = g.PU + lo;
+    bm.each_word(nw, [&](int w, uint32_t b, int u) {
+        while (b) {
+            const int k = __ffs(b) - 1;
+            b &= b - 1;
+            PU[u++] = bm_row(tb, (uint32_t)(w * 32 + k));
+        }
+    });
+    __syncthreads();
+    // place of a row among the last batch's distinct rows, or -1 (its rank word
+    // carries the batch's stamp and the row's bit)
+    auto in_batch = [&](uint4 rk, uint32_t pos) -> int32_t {
+        const uint32_t bit = 1u << (pos & 31);
+        return (int32_t)rk.z == p.last_stamp && (rk.y & bit) ? (int32_t)rk.x + __popc(rk.y & (bit - 1u)) : -1;
+    };
+    if (tb.ways) {  // block-uniform
+        const uint32_t ns = (uint32_t)tb.nsets;
+        int *seg = reinterpret_cast<int *>(tb.seg);
+        auto bounds = [&](const int32_t *list, int32_t n, int32_t k, int field) {
+            const uint32_t set = (uint32_t)list[k] % ns;
+            if (k == 0 || (uint32_t)list[k - 1] % ns != set) seg[4 * (int64_t)set + field] = k;
+            if (k + 1 == n || (uint32_t)list[k + 1] % ns != set) seg[4 * (int64_t)set + field + 1] = k + 1;
+        };
+        for (int32_t u = tid; u < nu; u += kSmallThreads) bounds(g.U + ts, nu, u, 0);
+        for (int32_t i = tid; i < pc; i += kSmallThreads) {
+            bounds(PU, pc, i, 2);
+            int32_t from = -1;  // its staging row if the last batch missed it
+            if (p.have_fwd) {
+                const uint32_t pos = bm_pos(tb, PU[i]);
+                const int32_t u = in_batch(gload16(tb.rank + (pos >> 5)), pos);
+                const int32_t su = u >= 0 ? g.slotU[ts + u] : 0;
+                if (su < 0) from = -su - 1;
+            }
+            g.pfrom[lo + i] = from;
+        }
+        if (tid == 0) {
+            st.pcount = pc;
+            st.npcount = st.popped = st.p_res = st.evicted = st.adm_miss = st.p_fill = st.p_drop = st.m_drop = 0;
+            st.digest_acc = st.digest;
+        }
+        return;
+    }
+    // ---- classification of the prefetch rows: resident, missed, or new
+    constexpr int Q = 4;
+    for (int32_t u0 = 0; u0 < pc; u0 += Q * kSmallThreads) {  // block-uniform
+        int32_t row[Q], slot[Q];
+        uint4 rk[Q];
+        bool in[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int32_t u = u0 + q * kSmallThreads + tid;
+            in[q] = u < pc;
+            row[q] = in[q] ? PU[u] : 0;
+        }
+        map_find_n<Q>(tb, row, in, slot);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            rk[q] = in[q] && slot[q] < 0 ? gload16(tb.rank + ((uint32_t)row[q] >> 5)) : make_uint4(0u, 0u, ~0u, 0u);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (u0 + q * kSmallThreads >= pc) break;  // block-uniform
+            const int32_t u = u0 + q * kSmallThreads + tid;
+            const bool res = in[q] && slot[q] >= 0;
+            bool fresh = false;
+            int32_t ref = slot[q];
+            if (!res && in[q]) {
+                const int32_t k = p.have_fwd ? in_batch(rk[q], (uint32_t)row[q]) : -1;
+                if (k >= 0) {
+                    ref = ring_ref_miss(-g.slotU[ts + k] - 1);
+                } else {
+                    fresh = true;
+                }
+            }
+            lds_count(res, &s_c[C_PRES]);
+            const int k = lds_append(fresh, &s_c[C_NP]);
+            if (fresh) {
+                g.NP[lo + k] = row[q];
+                ref = ring_ref_new(k);
+            }
+            if (in[q]) g.puref[lo + u] = ref;
+        }
+    }
+    __syncthreads();
+    Counts c;
+    c.cap = tb.cap;
+    c.nm = nm;
+    c.nnp = s_c[C_NP];
+    const int64_t nk = (int64_t)n_res + c.nm + c.nnp;
+    c.keep = (int32_t)(nk < c.cap ? nk : c.cap);
+    c.mode = nk <= c.cap ? SEL_ALL : (c.keep == 0 ? SEL_NONE : SEL_SELECT);
+    const int32_t top0 = st.free_top;
+    const bool ring = tb.ring_cap != 0;
+    if (reb) map_clear_share(tb, 0, 1);  // no lookup follows; k_plc_end inserts every resident
+    unsigned long long dig = 0;  // this thread's share of the digest (ring: of its change)
+    // frees slot sl of row r (when ev); every lane of the wave calls.  Its row
+    // and flags are cleared after admission, if no admitted row takes the slot.
+    auto evict = [&](bool ev, int32_t sl, int32_t r) {
+        const int at = top0 + lds_append(ev, &s_c[C_EV]);
+        if (!ev) return;
+        if (!reb) map_delete(tb, r);
+        if (at < tb.cap) tb.free_stack[at] = sl;
+        else atomicOr(g.err, ERR_INTERNAL);
+    };
+    auto named = [&](int32_t r, uint32_t) { return bm.test((uint32_t)r); };  // r in P
+    int32_t mode = c.mode;
+    uint64_t thr = 0;
+    RingCut cut{};
+    int32_t z1 = 0, r_valid = 0;
+    int2 *z = nullptr;
+    if (!ring) {
+        // ---- scores of every slot and candidate, the threshold, eviction
+        thr = rank_block(g, p, tb, c, t, reinterpret_cast<int *>(bz.w4), tmp, named);
+        const int32_t ngrp = (tb.cap + 3) / 4;
+        for (int32_t q0 = 0; q0 < ngrp; q0 += kSmallThreads) {  // block-uniform
+            const int32_t k0 = 4 * (q0 + tid), lim = q0 + tid < ngrp ? tb.cap : 0;
+            int32_t row[4], sc[4];
+            slot_quad(tb.slot_row, k0, lim, -1, row);
+            slot_quad(tb.slot_score, k0, lim, 0, sc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool live = row[i] >= 0;
+                const bool keep = live && kept(mode, make_key(sc[i], row[i], p.rowbits), thr);
+                if (keep) dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[i]);
+                evict(live && !keep, k0 + i, row[i]);
+            }
+        }
+        __syncthreads();
+    } else {
+        // ---- new scores of the touched and named rows, Z1
+        const int32_t pn = st.pend_n;
+        const bool pb = st.pend_buf != 0, rb = st.r_buf != 0;
+        const int32_t *prow = (pb ? g.pend_row[1] : g.pend_row[0]) + st.pend_off;
+        const int32_t *pslot = (pb ? g.pend_slot[1] : g.pend_slot[0]) + st.pend_off;
+        const int32_t *urow = g.U + ts;
+        int32_t *rcnt = rb ? tb.rcnt[1] : tb.rcnt[0], *rcnt2 = rb ? tb.rcnt[0] : tb.rcnt[1];
+        z = ring_zone(g, st, t);
+        bz.clear(nw);
+        __syncthreads();
+        int stale = 0;
+        auto unring = [&](int32_t sl) {  // its score changes: its ring entry, if it has one, goes stale
+            const int32_t e = tb.slot_pos[sl];
+            if (e >= 0) {
+                tb.slot_pos[sl] = -1;
+                atomicSub(&rcnt[e / kRingChunk], 1);
+                ++stale;
+            }
+        };
+        // pending rows neither touched nor named again
+        for (int32_t j = tid; j < pn; j += kSmallThreads) {
+            const int32_t q = pslot[j], r = prow[j];
+            if (q >= 0 && q < tb.cap && !named(r, 0) && tb.slot_touch[q] != p.last_stamp) bz.set((uint32_t)r);
+        }
+        for (int32_t u = tid; u < nu; u += kSmallThreads) {
+            const int32_t h = g.slotU[ts + u], r = urow[u];
+            if (!named(r, 0)) bz.set((uint32_t)r);
+            if (h >= 0) {
+                const uint32_t f = tb.slot_flags[h];
+                unring(h);
+                if (f & F_PF) tb.slot_flags[h] = f & ~F_PF;
+            }
+        }
+        for (int32_t i = tid; i < pc; i += kSmallThreads) {
+            const int32_t v = g.puref[lo + i];
+            if (v >= 0 && tb.slot_touch[v] != p.last_stamp) unring(v);  // touched: done above
+        }
+        lds_sum(stale, &s_c[C_STALE]);
+        __syncthreads();
+        z1 = bz.scan(nw, tmp);
+        // a pending row the batch touched has the batch's entry, of the same slot
+        for (int32_t j = tid; j < pn; j += kSmallThreads) {
+            const int32_t q = pslot[j], r = prow[j];
+            if (q >= 0 && q < tb.cap && bz.test((uint32_t)r)) z[bz.rank((uint32_t)r)] = make_int2(q, r);
+        }
+        for (int32_t u = tid; u < nu; u += kSmallThreads) {
+            const int32_t r = urow[u], h = g.slotU[ts + u];
+            if (bz.test((uint32_t)r)) z[bz.rank((uint32_t)r)] = make_int2(h >= 0 ? h : ring_ref_miss(-h - 1), r);
+        }
+        __syncthreads();
+        // ---- the cut, eviction from the ring's front, compaction
+        r_valid = st.r_valid - s_c[C_STALE];
+        cut = ring_cut(g, p, t, tb, st, c, r_valid, z1, z1, pc, tmp);
+        if (cut.bad) {  // block-uniform; never expected
+            if (tid == 0) atomicOr(g.err, ERR_INTERNAL);
+            return;
+        }
+        mode = cut.mode;
+        thr = cut.thr;
+        const int32_t tail = st.r_tail, head = st.r_head;
+        const int32_t *ringb = rb ? tb.ring[1] : tb.ring[0];
+        int32_t *dst = rb ? tb.ring[0] : tb.ring[1];
+        const int32_t hi_ch = cut.compact && cut.moved > 0 ? (int32_t)(((int64_t)head + kRingChunk - 1) / kRingChunk)
+                              : cut.cut > tail             ? (cut.cut - 1) / kRingChunk + 1
+                                                           : 0;
+        int32_t run = 0;  // entries moved so far
+        for (int32_t ch = tail / kRingChunk; ch < hi_ch; ++ch) {
+            const int32_t e = ch * kRingChunk + tid;
+            const int32_t sl = (int32_t)gload4(ringb + e);
+            const bool live = e >= tail && e < head && ring_live(tb, sl, e);
+            const bool ev = live && e < cut.cut, mv = live && !ev && cut.compact;
+            const int32_t r = ev ? tb.slot_row[sl] : 0;
+            const int before = s_c[C_EV];
+            __syncthreads();  // every thread has read it
+            evict(ev, sl, r);
+            if (ev) {
+                tb.slot_pos[sl] = -1;
+                dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r);
+            }
+            int tot;
+            const int at = run + block_excl_scan(mv ? 1 : 0, tmp, &tot);
+            if (mv) {
+                if (at < cut.moved) dst[at] = sl;
+                else atomicOr(g.err, ERR_INTERNAL);  // counts and entries disagree (never expected)
+            }
+            run += tot;
+            if (tid == 0) {
+                const int n = s_c[C_EV] - before;
+                if (n) rcnt[ch] -= n;
+                s_c[C_RING_EV] += n;
+            }
+            __syncthreads();
+        }
+        if (cut.zev) {  // Z1 and Z2 residents below the threshold
+            const int32_t n = z1 + pc;
+            for (int32_t b0 = 0; b0 < n; b0 += kSmallThreads) {  // block-uniform
+                const int32_t k = b0 + tid;
+                int32_t sl = -1, r = 0;
+                if (k < z1) {
+                    const int2 zr = z[k];
+                    r = zr.y;
+                    if (zr.x >= 0 && !kept(mode, make_key(p.lru_touch, r, p.rowbits), thr)) sl = zr.x;
+                } else if (k < n) {
+                    const int32_t v = g.puref[lo + (k - z1)];
+                    r = PU[k - z1];
+                    if (v >= 0 && !kept(mode, make_key(p.pscore, r, p.rowbits), thr)) sl = v;
+                }
+                evict(sl >= 0, sl, r);
+                if (sl >= 0) {
+                    tb.slot_pos[sl] = -1;
+                    dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r);
+                }
+            }
+        }
+        __syncthreads();
+        if (cut.compact) {  // moved slots learn their new index once no entry is tested any more
+            for (int32_t k = tid; k < cut.moved; k += kSmallThreads) {
+                const int32_t sl = dst[k];
+                if (sl >= 0 && sl < tb.cap) tb.slot_pos[sl] = k;
+                else atomicOr(g.err, ERR_INTERNAL);
+            }
+            for (int32_t ch = tid; ch < tb.ring_cap / kRingChunk; ch += kSmallThreads) {
+                const int64_t left = (int64_t)cut.moved - (int64_t)ch * kRingChunk;
+                rcnt2[ch] = left <= 0 ? 0 : left >= kRingChunk ? kRingChunk : (int32_t)left;
+            }
+            __syncthreads();
+        }
+    }
+    // ---- admission
+    const int32_t nev = s_c[C_EV], top = top0 + nev;
+    const int32_t items = c.nm + c.nnp;
+    int n_adm = 0, n_fill = 0, n_pdrop = 0, n_mdrop = 0, n_reuse = 0;
+    for (int32_t b0 = 0; b0 < items; b0 += kSmallThreads) {  // block-uniform
+        const int32_t k = b0 + tid;
+        bool adm = false, inp = false;
+        const bool is_miss = k < c.nm;
+        int32_t row = 0, s = 0;
+        if (k < items) {
+            if (is_miss) {
+                row = g.M[ts + k];
+                inp = named(row, 0);
+                s = ring ? (inp ? p.pscore : p.lru_touch) : g.mscore[ts + k];
+            } else {
+                row = g.NP[lo + (k - c.nm)];
+                s = new_prefetch_score(p, tb, row);
+                inp = true;
+            }
+            adm = kept(mode, make_key(s, row, p.rowbits), thr);
+        }
+        const int32_t at = lds_append(adm, &s_c[C_POP]);
+        if (k >= items) continue;
+        int32_t slot = -1;
+        const int32_t fi = top - 1 - at;
+        const int64_t fj = fts + lo + at;  // this row's entry in the fill list
+        if (adm) {
+            if (fi >= 0 && fi < tb.cap && fj >= 0 && fj < g.fill_cap) slot = tb.free_stack[fi];
+            if ((uint32_t)slot >= (uint32_t)tb.cap) {
+                atomicOr(g.err, ERR_INTERNAL);
+                adm = false;
+            }
+        }
+        if (!adm) {
+            n_mdrop += is_miss ? 1 : 0;
+            n_pdrop += inp ? 1 : 0;
+            continue;
+        }
+        // (the slot's touch stamp, of a forward before this placement, is older
+        // than any a later placement asks for)
+        tb.slot_row[slot] = row;
+        if (!ring) tb.slot_score[slot] = s;
+        tb.slot_flags[slot] = inp ? F_PF : 0u;
+        if (!reb) n_reuse += map_insert(tb, row, slot);
+        g.fill_src[fj] = is_miss ? k : -(row + 1);
+        g.fill_slot[fj] = slot;
+        if (ring) {
+            if (is_miss) g.mslot[ts + k] = slot;
+            else g.npslot[lo + (k - c.nm)] = slot;
+        }
+        dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row);
+        if (is_miss) ++n_adm;
+        else ++n_fill;
+    }
+    lds_sum(n_adm, &s_c[C_ADM]);
+    lds_sum(n_fill, &s_c[C_FILL]);
+    lds_sum(n_pdrop, &s_c[C_PDROP]);
+    lds_sum(n_mdrop, &s_c[C_MDROP]);
+    lds_sum(n_reuse, &s_c[C_REUSE]);
+    dig = wave_sum64(dig);
+    if ((tid & 63) == 0 && dig) atomicAdd(&s_dig, dig);
+    __syncthreads();
+    for (int32_t j = top0 + tid; j < top - s_c[C_POP]; j += kSmallThreads) {  // freed and not taken again
+        const int32_t sl = tb.free_stack[j];
+        tb.slot_row[sl] = -1;
+        tb.slot_flags[sl] = 0;
+    }
+    // ---- the ring's new run and pending list
+    if (ring) {
+        const bool buf1 = (st.r_buf != 0) != cut.compact;
+        const int32_t head = cut.compact ? cut.moved : st.r_head;
+        int32_t *ringb = buf1 ? tb.ring[1] : tb.ring[0], *rcnt = buf1 ? tb.rcnt[1] : tb.rcnt[0];
+        if ((int64_t)head + z1 > tb.ring_cap) {  // block-uniform; compaction made room, never expected
+            if (tid == 0) atomicOr(g.err, ERR_INTERNAL);
+            return;
+        }
+        for (int32_t j0 = 0; j0 < z1; j0 += kSmallThreads) {  // block-uniform
+            const int32_t j = j0 + tid, e = head + j;
+            int32_t sl = kRingHole;
+            if (j < z1) {
+                const int2 zr = z[j];
+                if (kept(mode, make_key(p.lru_touch, zr.y, p.rowbits), thr)) sl = zr.x >= 0 ? zr.x : g.mslot[ts + (-1 - zr.x)];
+                if (sl != kRingHole && (sl < 0 || sl >= tb.cap)) {
+                    atomicOr(g.err, ERR_INTERNAL);
+                    sl = kRingHole;
+                }
+                ringb[e] = sl;
+                if (sl != kRingHole) tb.slot_pos[sl] = e;
+            }
+            const bool live = sl != kRingHole;
+            lds_count(live, &s_c[C_RUN]);
+            // live entries of the wave's two chunks at most
+            const int32_t c0 = __builtin_amdgcn_readfirstlane(e) / kRingChunk;
+            const uint64_t m0 = __ballot(live && e / kRingChunk == c0), m1 = __ballot(live && e / kRingChunk != c0);
+            if ((tid & 63) == 0) {
+                if (m0) atomicAdd(&rcnt[c0], (int)__popcll(m0));
+                if (m1) atomicAdd(&rcnt[c0 + 1], (int)__popcll(m1));
+            }
+        }
+        int32_t *nrow = (wr ? g.pend_row[1] : g.pend_row[0]) + lo, *nslot = (wr ? g.pend_slot[1] : g.pend_slot[0]) + lo;
+        int keepn = 0;
+        for (int32_t i = tid; i < pc; i += kSmallThreads) {
+            const int32_t row = PU[i], v = g.puref[lo + i];
+            int32_t sl = -1;
+            if (kept(mode, make_key(p.pscore, row, p.rowbits), thr)) {
+                if (v >= 0) {
+                    sl = v;
+                } else {
+                    sl = v > kRingNewBase ? g.mslot[ts + (-1 - v)] : g.npslot[lo + (kRingNewBase - v)];
+                }
+            }
+            nrow[i] = row;
+            nslot[i] = sl;
+            keepn += sl >= 0 ? 1 : 0;
+        }
+        lds_sum(keepn, &s_c[C_KEEP]);
+        __syncthreads();
+    }
+    if (tid == 0) {
+        st.pcount = pc;
+        st.npcount = c.nnp;
+        st.popped = s_c[C_POP];
+        st.p_res = s_c[C_PRES];
+        st.evicted = nev;
+        st.adm_miss = s_c[C_ADM];
+        st.p_fill = s_c[C_FILL];
+        st.p_drop = s_c[C_PDROP];
+        st.m_drop = s_c[C_MDROP];
+        st.free_top = top;
+        st.rebuild = reb ? 1 : 0;
+        if (!reb) st.tomb += nev - s_c[C_REUSE];
+        st.digest_acc = (ring ? st.digest : 0ull) + s_dig;
+        if (ring) {
+            st.r_valid = r_valid - s_c[C_RING_EV] + s_c[C_RUN];
+            st.r_cut = cut.cut;
+            st.r_compact = cut.compact ? 1 : 0;
+            st.r_moved = cut.moved;
+            st.z1_len = z1;
+            st.pend_keep = s_c[C_KEEP];
+            st.pend_buf = wr;
+        }
+    }
+}
+
 // ----------------------------------------------------------------- launchers
 
 constexpr int kSmallBlocksLow = 8, kSmallBlocksHigh = kOwnSliceBlocks;  // bitmap blocks: 32 and 128 KiB of LDS
+constexpr int kSmallBlocksPlc = 16;  // a placement's two bitmaps
 
 // Where one block per table is the faster form.  It saves the launches of three
 // kernels, about 12 us per forward, and pays for doing a table's work on one
@@ -295,6 +781,31 @@ void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *o
         k_fwd_small<kSmallBlocksLow><<<g.T, kSmallThreads, 0, s>>>(g, indices, offsets, B, n, stamp, cover ? 1 : 0);
     else
         k_fwd_small<kSmallBlocksHigh><<<g.T, kSmallThreads, 0, s>>>(g, indices, offsets, B, n, stamp, cover ? 1 : 0);
+}
+
+// The same for a placement, by the mean of its two lists (the last batch's ids,
+// the prefetch ids).  It saves eight to eleven launches, 60 .. 100 us: steps of 1
+// and 8 tables of 20,000 and 200,000 rows, cached tenth, take 52 .. 79 us at 300
+// ids per table where the general sequence takes 98 .. 157, 69 .. 116 against
+// 116 .. 207 at 2,500, and about the same at 6,000 in 8 tables.  A table's rows
+// cost its CU more here than in a forward, so the total that bounds the loss
+// of a batch with nearly all ids in one table is half as large; tables with
+// more slots than one block ranks take the general sequence too.
+#ifndef RECMG_SMALL_PLC_MAX
+#define RECMG_SMALL_PLC_MAX (RECMG_SMALL_MAX / 2)
+#endif
+bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap) {
+    const int64_t n = (last_n + np + 1) / 2;
+    return last_n + np > 0 && n <= RECMG_SMALL_PLC_MAX && max_nblk <= kSmallBlocksPlc && max_fa_cap <= kRankSmallItems &&
+           small_batch(T, n, max_nblk);
+}
+
+void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,
+                      const uint8_t *bits, int wr, int32_t max_nblk, hipStream_t s) {
+    if (max_nblk <= kSmallBlocksLow)
+        k_plc_small<kSmallBlocksLow><<<g.T, kSmallThreads, 0, s>>>(g, p, rows, poff, np, bits, wr);
+    else
+        k_plc_small<kSmallBlocksPlc><<<g.T, kSmallThreads, 0, s>>>(g, p, rows, poff, np, bits, wr);
 }
 
 }  // namespace recmg
