@@ -235,7 +235,7 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     L->fill_src = take(4 * 2 * (mi + mp));   // two fill lists: a placement's fill may still
     L->fill_slot = take(4 * 2 * (mi + mp));  // read one while the next placement writes the other
     L->fdesc = take(8 * 4 * 2 * (size_t)T);
-    L->hist = take(4 * (size_t)kRadix * T);
+    L->hist = take(4 * (size_t)kRadix * T * kMaxPasses);
     L->dump = take(4 * (size_t)L->sum_cap);
     L->dump_count = take(4 * T);
     L->pool_bstart = take(4 * (T + 1));
@@ -1016,7 +1016,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     HIP_TRY(hipMemsetAsync(ws + L.pstart, 0, 8 * (T + 1), s0));
     HIP_TRY(hipMemsetAsync(ws + L.ftstart, 0, 8 * (T + 1), s0));
     HIP_TRY(hipMemsetAsync(ws + L.err, 0, 4, s0));
-    HIP_TRY(hipMemsetAsync(ws + L.hist, 0, 4 * (size_t)kRadix * T, s0));
+    HIP_TRY(hipMemsetAsync(ws + L.hist, 0, 4 * (size_t)kRadix * T * kMaxPasses, s0));
     HIP_TRY(hipMemcpy(ws + L.tabs, tabs.data(), sizeof(DTable) * T, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ws + L.bm_block_start, bstart.data(), 4 * (T + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ws + L.pool_btab, c->pool_order.data(), 4 * T, hipMemcpyHostToDevice));
@@ -1147,7 +1147,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     {
         StageTimer tm(c, RECMG_STAGE_PLC_APPLY, s);
         if (!small) {
-            if (c->has_scan_fa) launch_plc_evict(g, p, c->max_cap, s);
+            if (c->has_scan_fa) launch_plc_evict(g, p, c->max_cap, per_table, s);
             if (c->has_ring) launch_ring_evict(g, p, ring_items, c->max_ring_chunks, s);
             if (c->has_fa) launch_plc_admit(g, p, cand_grid, s);
             if (c->has_ring) launch_ring_store(g, p, ring_items, c->max_cap, q, s);
@@ -1156,7 +1156,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
             launch_sa_place(g, p, last_n, num_prefetch, c->nsa, c->sa_blocks1, c->sa_blocks, c->sa_max_blocks, !small, s);
     }
     const int32_t end_nsa = c->sa_max_blocks <= kSaSumInEnd ? c->nsa : 0;
-    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, s);
+    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, c->has_scan_fa ? p.passes : 0, s);
     if (!small) HIP_TRY(hipEventRecord(c->ev_plc, s));
     hipStream_t fs = c->copy_stream && !small ? c->copy_stream : s;
     if (early) {
@@ -1182,7 +1182,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     if (small) {
         StageTimer tm(c, RECMG_STAGE_PLC_FILL, s);
         DispatchTimer dt(c, RECMG_STAGE_PLC_FILL, true);
-        launch_plc_end(g, nullptr, log_slot, true, max_fa_cap, end_nsa, s, dt.a, dt.b);
+        launch_plc_end(g, nullptr, log_slot, true, max_fa_cap, end_nsa, 0, s, dt.a, dt.b);
         dt.issued();
         // calls on other streams that wait for the placement wait for its fill too
         HIP_TRY(hipEventRecord(c->ev_plc, s));

@@ -33,127 +33,100 @@ __global__ void __launch_bounds__(kBlock) k_fwd_prep(DGlobal g, const int64_t *_
 // set in a set-associative table): hits are stamped and counted, misses are
 // numbered (their staging row).  The tables' distinct rows are laid end to end
 // and dealt to the blocks in contiguous shares, so no block is spent on the
-// repeats of the index space; a thread takes kProbe rows per round with the
-// first probes of all of them in flight, and a round reserves its misses with
-// one atomic per table (every wave's atomics queued on the state's few lines).
+// repeats of the index space; a round of one row per thread reserves its misses
+// with one atomic per table (an atomic per wave queued on the state's few
+// lines).  Small blocks of one round each: this kernel runs beside the fill,
+// whose host reads hold the L1s of the CUs they run on, and blocks of 1,024
+// threads or of four rows per thread then waited at their barriers for their
+// slowest wave (259 and 293 us on 402,000 rows, 61 with 256 threads).
 // Then coverage (Eq. coverage): how many distinct rows of the last placement's
 // prefetch list (PU, still in place) this batch touches: a row is in the batch
 // iff its rank word carries this forward's stamp and its bit.
-constexpr int kProbe = 4;
-__global__ void __launch_bounds__(kBlock) k_fwd_probe(DGlobal g, int32_t stamp, int cover) {
+constexpr int kProbeRound = 256;
+__global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t stamp, int cover) {
     if (*g.err) return;
     __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ int64_t s_ts[RECMG_MAX_TABLES];
     __shared__ int s_hits[RECMG_MAX_TABLES], s_hits_pf[RECMG_MAX_TABLES], s_miss[RECMG_MAX_TABLES];
     __shared__ int tmp[16];
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        s_hits[t] = s_hits_pf[t] = s_miss[t] = 0;
-        s_ts[t] = g.tstart[t];
+    if ((int)threadIdx.x < g.T) {
+        s_hits[threadIdx.x] = s_hits_pf[threadIdx.x] = s_miss[threadIdx.x] = 0;
+        s_ts[threadIdx.x] = g.tstart[threadIdx.x];
     }
     const int32_t n = lay_tables(g.T, [&](int t) { return g.st[t].ucount; }, s_pre, tmp);
-    constexpr int kRound = kProbe * kBlock;
     int32_t lo, hi;
-    round_share(n, kRound, &lo, &hi);
-    for (int32_t base = lo; base < hi; base += kRound) {  // block-uniform
-        int t[kProbe];
-        int32_t row[kProbe], m[kProbe];
-        int64_t at[kProbe];
-        bool in[kProbe];
-        int tt = find_seg32(s_pre, g.T, base);  // tables of a round are few: walk on from its first
-#pragma unroll
-        for (int q = 0; q < kProbe; ++q) {
-            const int32_t i = base + q * kBlock + (int32_t)threadIdx.x;
-            in[q] = i < hi;
-            if (in[q])
-                while (i >= s_pre[tt + 1]) ++tt;
-            t[q] = tt;
-            at[q] = s_ts[tt] + (i - s_pre[tt]);
-            row[q] = in[q] ? g.U[at[q]] : 0;
-        }
-        const int t0 = __builtin_amdgcn_readfirstlane(t[0]);
-        // rows of one table (nearly every wave): its descriptor is read once,
-        // through scalar loads
-        auto probe = [&](auto one_tag) {
-            constexpr bool ONE = decltype(one_tag)::value;
-            auto tab = [&](int q) -> const DTable & { return g.tabs[ONE ? t0 : t[q]]; };
-            int32_t slot[kProbe];
-            if (ONE && !g.tabs[t0].ways) {
-                map_find_n<kProbe>(g.tabs[t0], row, in, slot);
-            } else {
-#pragma unroll
-                for (int q = 0; q < kProbe; ++q) slot[q] = in[q] ? find_slot(tab(q), row[q]) : -1;
-            }
-            uint32_t fl[kProbe];
-#pragma unroll
-            for (int q = 0; q < kProbe; ++q) fl[q] = in[q] && slot[q] >= 0 ? gload4(tab(q).slot_flags + slot[q]) : 0u;
-#pragma unroll
-            for (int q = 0; q < kProbe; ++q) {
-                const int k = ONE ? t0 : t[q];
-                const bool hit = in[q] && slot[q] >= 0;
+    round_share(n, kProbeRound, &lo, &hi);
+    for (int32_t base = lo; base < hi; base += kProbeRound) {  // block-uniform
+        const int32_t i = base + (int32_t)threadIdx.x;
+        const bool in = i < hi;
+        int t = find_seg32(s_pre, g.T, in ? i : base);
+        int64_t at = 0;
+        int32_t row = 0, m = -1;
+        // rows of one table (nearly every wave): its descriptor is read through scalar loads
+        auto probe = [&](const DTable &tb) {
+            at = s_ts[t] + (i - s_pre[t]);
+            bool hit = false, pf = false;
+            if (in) {
+                row = g.U[at];
+                const int32_t slot = find_slot(tb, row);
+                hit = slot >= 0;
                 if (hit) {
-                    g.slotU[at[q]] = slot[q];
-                    tab(q).slot_touch[slot[q]] = stamp;
+                    g.slotU[at] = slot;
+                    tb.slot_touch[slot] = stamp;
+                    pf = (tb.slot_flags[slot] & F_PF) != 0;
                 }
-                wave_count_lds(hit, k, s_hits);  // counts only
-                wave_count_lds(hit && (fl[q] & F_PF) != 0, k, s_hits_pf);
-                m[q] = wave_append(in[q] && !hit, k, s_miss, 1);
             }
+            wave_count_lds(hit, t, s_hits);  // counts only
+            wave_count_lds(pf, t, s_hits_pf);
+            m = wave_append(in && !hit, t, s_miss, 1);
         };
-        if (__ballot(t[0] != t0 || t[kProbe - 1] != t0) == 0) probe(std::true_type{});
-        else probe(std::false_type{});
+        const int t0 = __builtin_amdgcn_readfirstlane(t);
+        if (__ballot(t != t0) == 0) probe(g.tabs[t0]);
+        else probe(g.tabs[t]);
         __syncthreads();
-        for (int k = threadIdx.x; k < g.T; k += blockDim.x)  // counts -> first miss number of this round
-            if (s_miss[k]) s_miss[k] = atomicAdd(&g.st[k].mcount, s_miss[k]);
+        int *cnt = s_miss + threadIdx.x;  // counts -> first miss number of this round
+        if ((int)threadIdx.x < g.T && *cnt) *cnt = atomicAdd(&g.st[threadIdx.x].mcount, *cnt);
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kProbe; ++q) {
-            if (m[q] < 0) continue;
-            m[q] += s_miss[t[q]];
-            const int64_t a = s_ts[t[q]] + m[q];
-            g.slotU[at[q]] = -(m[q] + 1);
-            g.M[a] = row[q];
+        if (m >= 0) {
+            m += s_miss[t];
+            const int64_t a = s_ts[t] + m;
+            g.slotU[at] = -(m + 1);
+            g.M[a] = row;
             g.mflags[a] = 0;
             g.mcbit[a] = 0;
         }
         __syncthreads();
-        for (int k = threadIdx.x; k < g.T; k += blockDim.x) s_miss[k] = 0;
+        if ((int)threadIdx.x < g.T) *cnt = 0;
         __syncthreads();
     }
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        if (s_hits[t]) atomicAdd(&g.st[t].hits, s_hits[t]);
-        if (s_hits_pf[t]) atomicAdd(&g.st[t].hits_pf, s_hits_pf[t]);
+    if ((int)threadIdx.x < g.T) {
+        if (s_hits[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].hits, s_hits[threadIdx.x]);
+        if (s_hits_pf[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].hits_pf, s_hits_pf[threadIdx.x]);
     }
     if (!cover) return;
     __syncthreads();
     int *s_cov = s_hits;
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) s_cov[t] = 0;
+    if ((int)threadIdx.x < g.T) {
+        s_cov[threadIdx.x] = 0;
+        s_ts[threadIdx.x] = g.pstart[threadIdx.x];
+    }
     const int32_t np = lay_tables(g.T, [&](int t) { return g.st[t].pcount; }, s_pre, tmp);
-    round_share(np, kRound, &lo, &hi);
-    for (int32_t base = lo; base < hi; base += kRound) {
-        int tt = find_seg32(s_pre, g.T, base);
-        int t[kProbe];
-        uint4 rk[kProbe];
-        uint32_t pos[kProbe];
-#pragma unroll
-        for (int q = 0; q < kProbe; ++q) {
-            const int32_t i = base + q * kBlock + (int32_t)threadIdx.x;
-            rk[q] = make_uint4(0u, 0u, 0u, 0u);
-            pos[q] = 0;
-            if (i < hi) {
-                while (i >= s_pre[tt + 1]) ++tt;
-                const DTable &tb = g.tabs[tt];
-                pos[q] = bm_pos(tb, g.PU[g.pstart[tt] + (i - s_pre[tt])]);
-                rk[q] = gload16(tb.rank + (pos[q] >> 5));
-            }
-            t[q] = tt;
+    round_share(np, kProbeRound, &lo, &hi);
+    for (int32_t base = lo; base < hi; base += kProbeRound) {
+        const int32_t i = base + (int32_t)threadIdx.x;
+        int t = 0;
+        bool hit = false;
+        if (i < hi) {
+            t = find_seg32(s_pre, g.T, i);
+            const DTable &tb = g.tabs[t];
+            const uint32_t pos = bm_pos(tb, g.PU[s_ts[t] + (i - s_pre[t])]);
+            const uint4 rk = gload16(tb.rank + (pos >> 5));
+            hit = (int32_t)rk.z == stamp && (rk.y >> (pos & 31) & 1u);
         }
-#pragma unroll
-        for (int q = 0; q < kProbe; ++q)  // counts only (no bit is set in a lane past the end)
-            wave_count_lds((int32_t)rk[q].z == stamp && (rk[q].y >> (pos[q] & 31) & 1u), t[q], s_cov);
+        wave_count_lds(hit, t, s_cov);  // counts only
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x)
-        if (s_cov[t]) atomicAdd(&g.st[t].covered, s_cov[t]);
+    if ((int)threadIdx.x < g.T && s_cov[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].covered, s_cov[threadIdx.x]);
 }
 
 // inverse map and data location of every index
@@ -812,9 +785,8 @@ void launch_fwd_prep(const DGlobal &g, const int64_t *offsets, int32_t B, int64_
 }
 
 void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, int64_t np, hipStream_t s) {
-    // the distinct rows are at most n, often a fraction of it: one round per
-    // block if all ids were distinct, up to 8 blocks per CU
-    k_fwd_probe<<<grid_for(n > np ? n : np, kBlock * kProbe, 2048), kBlock, 0, s>>>(g, stamp, np > 0 ? 1 : 0);
+    // one round per block if all ids were distinct
+    k_fwd_probe<<<grid_for(n > np ? n : np, kProbeRound, 8192), kProbeRound, 0, s>>>(g, stamp, np > 0 ? 1 : 0);
 }
 
 void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStream_t s) {

@@ -73,7 +73,7 @@ void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, hipSt
 constexpr int64_t kRankSmallItems = 1 << 16;
 void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, hipStream_t s);
 // evict (tables ranked by radix select), admission (every fully associative table)
-void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, hipStream_t s);
+void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, int64_t item_bound, hipStream_t s);
 void launch_plc_admit(const DGlobal &g, const PlcParams &p, int64_t cand_bound, hipStream_t s);
 // fdesc: this placement's fill descriptor, [T][4] int64 (written by the end, read by fill);
 // phase: the tables whose rows this launch copies, by miss mode
@@ -83,9 +83,10 @@ void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStrea
 // the end of a placement: counters published, cleared maps refilled (max_fa_cap:
 // the most slots of a fully associative table, 0 if there is none), the blocks'
 // counts of nsa set-associative tables added up (0: done by launch_sa_place);
-// fill: the zero-copy fill too, else its descriptor is written to fdesc
+// fill: the zero-copy fill too, else its descriptor is written to fdesc;
+// passes: histograms of the radix select to clear
 void launch_plc_end(const DGlobal &g, int64_t *fdesc, int64_t log_slot, bool fill, int32_t max_fa_cap, int32_t nsa,
-                    hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                    int32_t passes, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_init_state(const DGlobal &g, int32_t max_cap, hipStream_t s);
 
 // ring.hip: LRU_BATCH placement of tables with a resident ring (ring_cap > 0).

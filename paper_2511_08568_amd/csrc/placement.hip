@@ -6,8 +6,8 @@
 // member gets a score (aging, touch, prefetch, below), and the cache keeps the
 // min(Cap, |K|) largest keys (score, row).  Instead of one victim scan per
 // insertion, one radix select per placement finds the threshold key: 11-bit
-// digits from the top, each pass a histogram kernel and a one-block-per-table
-// kernel that picks the digit holding the Cap-th largest key.  Keys are
+// digits from the top, each pass a histogram kernel whose digit, the one holding
+// the Cap-th largest key, the next kernel picks.  Keys are
 // distinct (rows are distinct), so exactly min(Cap, |K|) keys are >= the
 // threshold.
 //
@@ -19,11 +19,13 @@
 //                     touched: caching bit + ES (Alg. 1); prefetched:
 //                     max(score, ES); a touched resident loses its prefetch flag.
 //
-// Kernels on the stream: k_plc_prep, [k_plc_bits], dedup of P with the
-// EMIT_PREFETCH visitor (dedup.hip), k_plc_update (scores + histogram of
-// pass 0), k_plc_pick, { k_plc_select (histogram of pass 1..), k_plc_pick }*,
-// k_plc_evict, k_map_clear / k_map_refill (rebuild
-// when deleted entries pile up), k_plc_admit, k_plc_fill, k_plc_end.
+// Kernels on the stream: [k_plc_bits or k_plc_freq], the dedup of P with the
+// placement's preparation (dedup.hip; k_plc_prep if P is empty), k_plc_classify,
+// k_plc_update (scores + histogram of pass 0), k_plc_select per further pass
+// (which first picks the digit of the pass before), k_plc_evict (which picks the
+// last), k_plc_admit, k_plc_end, k_plc_fill.  A map with too many deleted entries
+// is rebuilt on the way (map_clear_share).  Placements of few rows run all but
+// the end in one kernel (small.hip).
 #include <hip/hip_ext.h>
 
 #include "launch.h"
@@ -74,70 +76,78 @@ __global__ void __launch_bounds__(kBlock) k_plc_freq(DGlobal g, int64_t n) {
 
 // Classify every distinct prefetch row of the fully associative tables (Alg.
 // 1's prefetch loop taken as a set): resident -> flag the slot; missed by the
-// last batch -> flag the miss; otherwise a new candidate, appended to NP.  One
-// thread per slot of the prefetch index space; table t's distinct rows occupy
-// [pstart[t], + pcount).  Set-associative tables play their prefetch rows as
-// events in k_sa_place, which also counts the resident ones.
-__global__ void __launch_bounds__(kBlock) k_plc_classify(DGlobal g, int32_t last_stamp, int64_t np) {
+// last batch -> flag the miss; otherwise a new candidate, appended to NP.  The
+// distinct rows are laid end to end, one per thread and round; a round reserves
+// its new candidates with one atomic per table (one per wave queued on the
+// table states: 1.16 million rows of 4 tables took 300 us, now 190).
+// Set-associative tables play their prefetch rows as events in k_sa_place,
+// which also counts the resident ones.
+__global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last_stamp) {
     if (*g.err) return;
-    __shared__ int64_t s_pstart[RECMG_MAX_TABLES + 1];
-    __shared__ int32_t s_pc[RECMG_MAX_TABLES];
-    __shared__ int s_res[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
-        s_pstart[t] = g.pstart[t];
-        if (t < g.T) {
-            s_pc[t] = g.tabs[t].ways ? 0 : g.st[t].pcount;
-            s_res[t] = 0;
-        }
+    __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
+    __shared__ int64_t s_ps[RECMG_MAX_TABLES];
+    __shared__ int s_res[RECMG_MAX_TABLES], s_new[RECMG_MAX_TABLES];
+    __shared__ int tmp[16];
+    if ((int)threadIdx.x < g.T) {
+        s_res[threadIdx.x] = s_new[threadIdx.x] = 0;
+        s_ps[threadIdx.x] = g.pstart[threadIdx.x];
     }
-    __syncthreads();
-    const int stride_st = (int)(sizeof(TState) / 4);
-    int64_t lo, hi;
-    block_share(np, &lo, &hi);
-    for (int64_t base = lo; base < hi; base += blockDim.x) {  // block-uniform
-        const int64_t i = base + threadIdx.x;
-        int t = 0;
-        bool valid = false, isnew = false, resident = false;
-        int32_t row = 0;
-        if (i < hi) {
-            t = find_seg(s_pstart, g.T, i);
-            valid = i - s_pstart[t] < s_pc[t];
-        }
-        if (valid) {
-            const DTable &tb = g.tabs[t];
-            row = g.PU[i];
-            const int32_t slot = find_slot(tb, row);
-            if (slot >= 0) {
-                // distinct prefetch rows name distinct slots: plain read-modify-write
-                tb.slot_flags[slot] |= F_INP;
-                resident = true;
-                g.puref[i] = slot;
-            } else {
-                // distinct rows of the last batch carry its stamp in the rank word
-                const uint32_t pos = bm_pos(tb, row);
-                const uint4 rk = tb.rank[pos >> 5];
-                const uint32_t bit = 1u << (pos & 31);
-                if ((int32_t)rk.z == last_stamp && (rk.y & bit)) {
-                    const int64_t ts = g.tstart[t];
-                    const int32_t u = (int32_t)rk.x + __popc(rk.y & (bit - 1u));
-                    const int64_t m = -(int64_t)g.slotU[ts + u] - 1;
-                    g.mflags[ts + m] |= F_INP;  // distinct rows, distinct misses
-                    g.puref[i] = ring_ref_miss((int32_t)m);
+    const int32_t n = lay_tables(g.T, [&](int t) { return g.tabs[t].ways ? 0 : g.st[t].pcount; }, s_pre, tmp);
+    int32_t lo, hi;
+    round_share(n, kRound, &lo, &hi);
+    for (int32_t base = lo; base < hi; base += kRound) {  // block-uniform
+        const int32_t i = base + (int32_t)threadIdx.x;
+        const bool in = i < hi;
+        const int t = find_seg32(s_pre, g.T, in ? i : base);
+        int64_t at = 0;
+        int32_t row = 0, k = -1;
+        // rows of one table (nearly every wave): its descriptor is read through scalar loads
+        auto classify = [&](const DTable &tb) {
+            at = s_ps[t] + (i - s_pre[t]);
+            bool isnew = false, resident = false;
+            if (in) {
+                row = g.PU[at];
+                const int32_t slot = map_find(tb, row);
+                if (slot >= 0) {
+                    // distinct prefetch rows name distinct slots: plain read-modify-write
+                    tb.slot_flags[slot] |= F_INP;
+                    resident = true;
+                    g.puref[at] = slot;
                 } else {
-                    isnew = true;
+                    // distinct rows of the last batch carry its stamp in the rank word
+                    const uint4 rk = gload16(tb.rank + ((uint32_t)row >> 5));
+                    const uint32_t bit = 1u << (row & 31);
+                    if ((int32_t)rk.z == last_stamp && (rk.y & bit)) {
+                        const int64_t ts = g.tstart[t];
+                        const int32_t u = (int32_t)rk.x + __popc(rk.y & (bit - 1u));
+                        const int64_t m = -(int64_t)g.slotU[ts + u] - 1;
+                        g.mflags[ts + m] |= F_INP;  // distinct rows, distinct misses
+                        g.puref[at] = ring_ref_miss((int32_t)m);
+                    } else {
+                        isnew = true;
+                    }
                 }
             }
+            wave_count_lds(resident, t, s_res);  // counts only
+            k = wave_append(isnew, t, s_new, 1);
+        };
+        const int t0 = __builtin_amdgcn_readfirstlane(t);
+        if (__ballot(t != t0) == 0) classify(g.tabs[t0]);
+        else classify(g.tabs[t]);
+        __syncthreads();
+        int *cnt = s_new + threadIdx.x;  // counts -> first candidate of this round
+        if ((int)threadIdx.x < g.T && *cnt) *cnt = atomicAdd(&g.st[threadIdx.x].npcount, *cnt);
+        __syncthreads();
+        if (k >= 0) {
+            k += s_new[t];
+            g.NP[s_ps[t] + k] = row;
+            g.puref[at] = ring_ref_new(k);
         }
-        wave_count_lds(resident, t, s_res);  // counts only
-        const int32_t k = wave_append(isnew, t, &g.st[0].npcount, stride_st);
-        if (isnew) {
-            g.NP[s_pstart[t] + k] = row;
-            g.puref[i] = ring_ref_new(k);
-        }
+        __syncthreads();
+        if ((int)threadIdx.x < g.T) *cnt = 0;
+        __syncthreads();
     }
-    __syncthreads();
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x)
-        if (s_res[t]) atomicAdd(&g.st[t].p_res, s_res[t]);
+    if ((int)threadIdx.x < g.T && s_res[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].p_res, s_res[threadIdx.x]);
 }
 
 // ----------------------------------------------------------------- ranking
@@ -145,35 +155,38 @@ __global__ void __launch_bounds__(kBlock) k_plc_classify(DGlobal g, int32_t last
 // Merge the block's histogram into the table's global one (non-zero bins).
 // No fence and no "last block" here: on this GPU an agent-scope fence writes
 // back the XCD's whole L2, and a histogram kernel has many blocks; the digit
-// is picked by k_plc_pick after the kernel boundary instead.
-__device__ __forceinline__ void hist_merge(const DGlobal &g, int t, const int *s_hist) {
-    int *gh = g.hist + (int64_t)t * kRadix;
+// is picked after the kernel boundary instead (pass_threshold).
+__device__ __forceinline__ int *pass_hist(const DGlobal &g, int pass, int t) {
+    return g.hist + ((int64_t)pass * g.T + t) * kRadix;
+}
+__device__ __forceinline__ void hist_merge(const DGlobal &g, int pass, int t, const int *s_hist) {
+    int *gh = pass_hist(g, pass, t);
     for (int b = threadIdx.x; b < kRadix; b += blockDim.x)
         if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
 }
 
-// One block per table: the digit of this pass from the table's global
-// histogram (clearing it for the next pass).
-__global__ void __launch_bounds__(kBlock) k_plc_pick(DGlobal g, PlcParams p, int pass) {
-    if (*g.err) return;
-    __shared__ int s_hist[kRadix];
-    __shared__ int tmp[16];
-    const int t = blockIdx.x;
-    TState &st = g.st[t];
-    if (g.tabs[t].ring_cap || st.sel_mode != SEL_SELECT) return;  // uniform over the block
-    int *gh = g.hist + (int64_t)t * kRadix;
-    for (int b = threadIdx.x; b < kRadix; b += blockDim.x) {
-        s_hist[b] = gh[b];
-        gh[b] = 0;
-    }
+// The threshold prefix after pass `pass`, from the table's finished histogram
+// of that pass: by every block of the kernel that follows, for itself (8 KiB
+// from L2 and a scan, about 2 us beside the block's other loads; a kernel of its
+// own per pass cost 6 to 7 us).  Each pass has its own histogram, so none is
+// cleared here, and writes its result to its own place: block 0 of the table
+// does it for the next pass's kernel, and no block of this kernel reads it.
+// s_hist is used up.  Every thread calls.
+__device__ __forceinline__ uint64_t pass_threshold(const DGlobal &g, TState &st, int t, int pass, int keep, int *s_hist,
+                                                   int *tmp) {
+    const int *gh = pass_hist(g, pass, t);
+    for (int b = threadIdx.x; b < kRadix; b += blockDim.x) s_hist[b] = gh[b];
+    const int need = pass == 0 ? keep : st.pass_need[pass - 1];
+    const uint64_t before = pass == 0 ? 0 : st.pass_prefix[pass - 1] << kRadixBits;
     __syncthreads();
-    const int need = pass == 0 ? table_counts(g.tabs[t], st, p).keep : st.need;
     int digit, rest;
     pick_digit(s_hist, need, tmp, &digit, &rest);
-    if (threadIdx.x == 0) {
-        st.prefix = pass == 0 ? (uint64_t)digit : ((st.prefix << kRadixBits) | (uint64_t)digit);
-        st.need = rest;
+    const uint64_t prefix = before | (uint64_t)digit;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st.pass_prefix[pass] = prefix;
+        st.pass_need[pass] = rest;
     }
+    return prefix;
 }
 
 // Scores of every candidate (written back) and the first select pass.
@@ -197,7 +210,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_update(DGlobal g, PlcParams p) {
     update_items(g, p, tb, c, t, s_hist, sel, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
                  (int64_t)gridDim.x * blockDim.x, FlagInp());
     __syncthreads();
-    if (sel) hist_merge(g, t, s_hist);
+    if (sel) hist_merge(g, 0, t, s_hist);
 }
 
 __global__ void __launch_bounds__(kBlock) k_plc_select(DGlobal g, PlcParams p, int pass) {
@@ -208,12 +221,14 @@ __global__ void __launch_bounds__(kBlock) k_plc_select(DGlobal g, PlcParams p, i
     TState &st = g.st[t];
     if (tb.ring_cap || st.sel_mode != SEL_SELECT) return;  // uniform over the table's blocks
     const Counts c = table_counts(tb, st, p);
+    __shared__ int tmp[16];
+    const uint64_t prefix = pass_threshold(g, st, t, pass - 1, c.keep, s_hist, tmp);
     for (int b = threadIdx.x; b < kRadix; b += blockDim.x) s_hist[b] = 0;
     __syncthreads();
-    select_items(g, p, tb, c, t, s_hist, pass, st.prefix, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
+    select_items(g, p, tb, c, t, s_hist, pass, prefix, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
                  (int64_t)gridDim.x * blockDim.x);
     __syncthreads();
-    hist_merge(g, t, s_hist);
+    hist_merge(g, pass, t, s_hist);
 }
 
 // Small tables: the whole ranking of a table in one block (scores, then every
@@ -247,17 +262,27 @@ __global__ void __launch_bounds__(kRankSmallThreads) k_plc_rank_small(DGlobal g,
 // numbers are not observable.
 constexpr int kEvictBuf = 2048;
 
-__global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p) {
+// last_pass: the radix select's last pass, whose digit gives the threshold key
+// (-1: k_plc_rank_small has found it).
+__global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p, int last_pass) {
     if (block_err(g)) return;
     __shared__ int tmp[16];
     __shared__ int s_base, s_n;
     __shared__ int32_t s_free[kEvictBuf];
+    static_assert(kEvictBuf >= kRadix, "the last pass's histogram takes the buffer's place first");
     const int t = blockIdx.y;
     const DTable &tb = g.tabs[t];
     if (tb.ways || tb.ring_cap) return;
     TState &st = g.st[t];
     const int mode = st.sel_mode;
-    const uint64_t thr = st.prefix;
+    uint64_t thr = 0;
+    if (mode == SEL_SELECT) {  // block-uniform
+        if (last_pass < 0) thr = st.prefix;
+        else {
+            thr = pass_threshold(g, st, t, last_pass, table_counts(tb, st, p).keep, s_free, tmp);
+            if (blockIdx.x == 0 && threadIdx.x == 0) st.prefix = thr;  // for admission
+        }
+    }
     const int lane = threadIdx.x & 63;
     if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
@@ -380,7 +405,8 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
                 tb.slot_row[slot] = row;
                 if (!tb.ring_cap) tb.slot_score[slot] = s;  // a ring's order holds its scores
                 tb.slot_flags[slot] = inp ? F_PF : 0u;
-                tb.slot_touch[slot] = -1;
+                // (the slot's touch stamp, of a forward before this placement,
+                // is older than any a later placement asks for)
                 if (!reb) n_reuse += map_insert(tb, row, slot);
                 // the fill list: admitted row j of this table, its source and
                 // slot: a miss's staging row; a prefetch row's host row, or for
@@ -557,8 +583,9 @@ constexpr int kFillGridBlocks = RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_SHARED
 // link for tens of milliseconds, and the kernels beside them are a small part
 // of the step), and fewer when the fill has the link to itself, so that it
 // takes no more CUs than it needs from the kernels beside it.
+// Table blocks also clear the radix select's histograms.
 __global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, int64_t log_slot, int32_t nfill,
-                                                    int32_t nsa) {
+                                                    int32_t nsa, int32_t passes) {
     if (*g.err) return;  // set by earlier kernels only, but for broken ring counts (below)
     __shared__ long long tmp[16];
     if ((int)blockIdx.x < nfill) {  // block-uniform, as the other roles
@@ -569,11 +596,18 @@ __global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, i
     const int r = (int)blockIdx.x - nfill;
     if (r >= g.T) {
         const int nb = (int)gridDim.x - nfill - g.T;
+        const bool mine = (int)threadIdx.x < g.T && g.st[threadIdx.x].rebuild != 0;
+        if (!__syncthreads_or(mine)) return;
         for (int t = 0; t < g.T; ++t)
             if (g.st[t].rebuild) map_refill_share(g.tabs[t], r - g.T, nb);
         return;
     }
     if (nsa > 0 && g.tabs[r].ways) sa_sum_table(g, r, nsa, tmp);
+    if (passes > 0 && g.st[r].sel_mode == SEL_SELECT && !g.tabs[r].ways && !g.tabs[r].ring_cap)
+        for (int k = 0; k < passes; ++k) {
+            int *h = pass_hist(g, k, r);
+            for (int b = threadIdx.x; b < kRadix; b += blockDim.x) h[b] = 0;
+        }
     if (r == 0 && fdesc) {
         long long mb = 0, tot;  // bytes of the last forward's on-demand misses
         if ((int)threadIdx.x < g.T) {
@@ -623,11 +657,13 @@ void launch_plc_freq(const DGlobal &g, int64_t n_last, hipStream_t s) {
 
 void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, hipStream_t s) {
     if (np <= 0) return;
-    k_plc_classify<<<grid_for(np, kBlock, 8192), kBlock, 0, s>>>(g, last_stamp, np);
+    k_plc_classify<<<grid_for(np, kRound, 1024), kRound, 0, s>>>(g, last_stamp);
 }
 
+bool rank_in_block(int64_t item_bound) { return item_bound <= kRankSmallItems; }
+
 void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, hipStream_t s) {
-    if (item_bound <= kRankSmallItems) {  // a table's slots and candidates fit one block's loop
+    if (rank_in_block(item_bound)) {  // a table's slots and candidates fit one block's loop
         k_plc_rank_small<<<g.T, kRankSmallThreads, 0, s>>>(g, p);
         return;
     }
@@ -638,15 +674,12 @@ void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, h
 #endif
     const dim3 grid(grid_for(item_bound, kBlock * RECMG_RANK_IPT, 512), g.T);
     k_plc_update<<<grid, kBlock, 0, s>>>(g, p);
-    k_plc_pick<<<g.T, kBlock, 0, s>>>(g, p, 0);
-    for (int pass = 1; pass < p.passes; ++pass) {
-        k_plc_select<<<grid, kBlock, 0, s>>>(g, p, pass);
-        k_plc_pick<<<g.T, kBlock, 0, s>>>(g, p, pass);
-    }
+    for (int pass = 1; pass < p.passes; ++pass) k_plc_select<<<grid, kBlock, 0, s>>>(g, p, pass);
 }
 
-void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, hipStream_t s) {
-    k_plc_evict<<<dim3(grid_for(max_cap, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g, p);
+void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, int64_t item_bound, hipStream_t s) {
+    const int last = rank_in_block(item_bound) ? -1 : p.passes - 1;
+    k_plc_evict<<<dim3(grid_for(max_cap, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g, p, last);
 }
 
 void launch_plc_admit(const DGlobal &g, const PlcParams &p, int64_t cand_bound, hipStream_t s) {
@@ -675,12 +708,12 @@ void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStrea
 }
 
 void launch_plc_end(const DGlobal &g, int64_t *fdesc, int64_t log_slot, bool fill, int32_t max_fa_cap, int32_t nsa,
-                    hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                    int32_t passes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const int32_t nfill = fill ? RECMG_FILL_BLOCKS : 0;
     const unsigned refill = max_fa_cap > 0 ? grid_for(max_fa_cap, kBlock * 4, 256) : 0;
     const dim3 grid((unsigned)nfill + (unsigned)g.T + refill);
-    if (ev0 || ev1) hipExtLaunchKernelGGL(k_plc_end, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, fdesc, log_slot, nfill, nsa);
-    else k_plc_end<<<grid, kBlock, 0, s>>>(g, fdesc, log_slot, nfill, nsa);
+    if (ev0 || ev1) hipExtLaunchKernelGGL(k_plc_end, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, fdesc, log_slot, nfill, nsa, passes);
+    else k_plc_end<<<grid, kBlock, 0, s>>>(g, fdesc, log_slot, nfill, nsa, passes);
 }
 
 void launch_init_state(const DGlobal &g, int32_t max_cap, hipStream_t s) {

@@ -25,6 +25,8 @@ constexpr int kOwnMaxSlices = RECMG_OWN_MAX_SLICES;
 __host__ __device__ constexpr bool owns_bitmap(int32_t bm_nblk) { return bm_nblk <= kOwnMaxSlices * kOwnSliceBlocks; }
 constexpr int kRadixBits = 11;                      // radix-select digit
 constexpr int kRadix = 1 << kRadixBits;
+constexpr int kMaxPasses = 6;                       // a key has at most 32 + 31 bits
+static_assert(kMaxPasses * kRadixBits >= 63, "passes for the longest key");
 constexpr int32_t kEmpty = -1;                      // map key of a never-used entry
 constexpr int32_t kTomb = -2;                       // map key of a deleted entry
 constexpr int32_t kPending = INT32_MIN;             // probe result before miss numbering
@@ -114,8 +116,12 @@ struct TState {
     int32_t pcount;   // distinct prefetch rows of the current placement
     int32_t npcount;  // prefetch rows neither resident nor missed (in NP)
     int32_t n_res, free_top, popped, tomb;
-    int32_t rebuild, sel_mode, need, plc_nm;  // plc_nm: misses the current placement ranks
-    uint64_t prefix;  // radix-select prefix; the threshold key after the last pass
+    int32_t rebuild, sel_mode, free0, plc_nm;  // plc_nm: misses the current placement ranks;
+                                               // free0: free_top as the placement began
+    uint64_t prefix;  // the threshold key that the radix select (or the ring's cut) found
+    // radix select: the prefix and the keys still wanted after each pass
+    uint64_t pass_prefix[kMaxPasses];
+    int32_t pass_need[kMaxPasses];
     uint32_t rebuild_next;  // rebuild of the next placement: deleted entries passed a quarter of the map
     int32_t covered;  // accumulator: distinct prefetch rows of the last placement found in this batch
     // accumulators of the call in flight
@@ -159,7 +165,7 @@ struct DGlobal {
     int32_t *fill_src;        // [max_indices + max_prefetch] admitted row's source: staging row (>= 0)
                               // or -(host row + 1); table t at ftstart[t] + pstart[t]
     int32_t *fill_slot;       // [max_indices + max_prefetch] its slot
-    int32_t *hist;            // [T][kRadix]
+    int32_t *hist;            // [kMaxPasses][T][kRadix], zero between placements
     int32_t *dump;            // [sum cap] sorted resident rows
     int32_t *dump_count;      // [T]
     char *staging;            // [max_indices][stage_stride] miss rows of the latest forward
@@ -527,6 +533,9 @@ __device__ __forceinline__ int32_t lay_tables(int T, Count count, int32_t *s_pre
     return tot;
 }
 
+// Threads of the kernels that take such items, one per thread and round.
+constexpr int kRound = 1024;
+
 // This block's share [*lo, *hi) of n items laid end to end, a whole number of
 // rounds of `round` items (contiguous, as in block_share).
 __device__ __forceinline__ void round_share(int32_t n, int round, int32_t *lo, int32_t *hi) {
@@ -636,6 +645,7 @@ __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const in
     }
     TState &st = g.st[t];
     st.rebuild = (int32_t)st.rebuild_next;
+    st.free0 = st.free_top;
     st.pcount = 0;
     st.npcount = 0;
     st.popped = 0;

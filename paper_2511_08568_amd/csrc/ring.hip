@@ -87,7 +87,8 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
     const int32_t n1 = pn + nu, n = n1 + st.pcount;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.z1_len = n1;
     int keys = 0, stale = 0;
-    for (int32_t j = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); j < n; j += (int32_t)(gridDim.x * blockDim.x)) {
+    for (int32_t j0 = (int32_t)(blockIdx.x * blockDim.x); j0 < n; j0 += (int32_t)(gridDim.x * blockDim.x)) {  // block-uniform
+        const int32_t j = j0 + (int32_t)threadIdx.x;
         int32_t sl = -1;  // a resident whose score changes (the ring's order holds the scores, no slot does)
         if (j < n1) {
             int32_t row, at, ref = kRingHole;
@@ -116,18 +117,17 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
             }
             z[at] = make_int2(ref, row);
             keys += ref != kRingHole ? 1 : 0;
-        } else {
+        } else if (j < n) {
             const int32_t v = g.puref[ps + (j - n1)];
             if (v >= 0 && tb.slot_touch[v] != p.last_stamp) sl = v;  // touched: its hit entry took care of it
         }
-        if (sl >= 0) {
-            const int32_t e = tb.slot_pos[sl];
-            if (e >= 0) {  // pending rows have no ring entry
-                tb.slot_pos[sl] = -1;
-                atomicSub(&rcnt[e / kRingChunk], 1);
-                ++stale;
-            }
+        int32_t e = -1;
+        if (sl >= 0) e = tb.slot_pos[sl];
+        if (e >= 0) {  // pending rows have no ring entry
+            tb.slot_pos[sl] = -1;
+            ++stale;
         }
+        chunk_sub(e >= 0, e / kRingChunk, rcnt);
     }
     const int k = block_sum(keys, tmp), ns = block_sum(stale, tmp);
     if (threadIdx.x == 0) {
@@ -198,11 +198,9 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
     unsigned long long dig = 0;
     // frees slot sl (when ev) and lists it; every lane of the wave calls
     auto evict = [&](bool ev, int32_t sl) {
-        if (ev) {
+        if (ev) {  // its row and flags: k_ring_append, unless an admitted row takes the slot
             const int32_t row = tb.slot_row[sl];
             if (!reb) map_delete(tb, row);
-            tb.slot_row[sl] = -1;
-            tb.slot_flags[sl] = 0;
             tb.slot_pos[sl] = -1;
             dig += mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)row);
             ++nev;
@@ -329,6 +327,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, 
     }
     const int2 *z = ring_zone(g, st, t);
     if (n1 > 0) {
+        int added = 0;
         const int32_t c1 = (head + n1 - 1) / kRingChunk;
         for (int32_t ch = head / kRingChunk + (int32_t)blockIdx.x; ch <= c1; ch += (int32_t)gridDim.x) {
             int add = 0;
@@ -351,11 +350,18 @@ __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, 
                 }
             }
             const int an = block_sum(add, tmp);
-            if (threadIdx.x == 0 && an) {
-                atomicAdd(&tb.rcnt[buf][ch], an);
-                atomicAdd(&st.r_valid, an);
-            }
+            if (threadIdx.x == 0 && an) atomicAdd(&tb.rcnt[buf][ch], an);
+            added += an;
         }
+        if (threadIdx.x == 0 && added) atomicAdd(&st.r_valid, added);
+    }
+    // slots freed and not taken again (the free stack's new entries below its
+    // new top); in a full cache in steady state there are none
+    const int32_t left = st.free_top - st.popped;
+    for (int32_t k = st.free0 + (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); k < left; k += (int32_t)(gridDim.x * blockDim.x)) {
+        const int32_t sl = tb.free_stack[k];
+        tb.slot_row[sl] = -1;
+        tb.slot_flags[sl] = 0;
     }
     int keepn = 0;
     int32_t *prow = g.pend_row[wr] + ps, *pslot = g.pend_slot[wr] + ps;

@@ -495,30 +495,35 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         __syncthreads();
         int stale = 0;
         auto unring = [&](int32_t sl) {  // its score changes: its ring entry, if it has one, goes stale
-            const int32_t e = tb.slot_pos[sl];
+            const int32_t e = sl >= 0 ? tb.slot_pos[sl] : -1;
             if (e >= 0) {
                 tb.slot_pos[sl] = -1;
-                atomicSub(&rcnt[e / kRingChunk], 1);
                 ++stale;
             }
+            chunk_sub(e >= 0, e / kRingChunk, rcnt);  // every lane of the wave calls
         };
         // pending rows neither touched nor named again
         for (int32_t j = tid; j < pn; j += kSmallThreads) {
             const int32_t q = pslot[j], r = prow[j];
             if (q >= 0 && q < tb.cap && !named(r, 0) && tb.slot_touch[q] != p.last_stamp) bz.set((uint32_t)r);
         }
-        for (int32_t u = tid; u < nu; u += kSmallThreads) {
-            const int32_t h = g.slotU[ts + u], r = urow[u];
-            if (!named(r, 0)) bz.set((uint32_t)r);
-            if (h >= 0) {
-                const uint32_t f = tb.slot_flags[h];
-                unring(h);
+        for (int32_t u0 = 0; u0 < nu; u0 += kSmallThreads) {  // block-uniform
+            const int32_t u = u0 + tid;
+            int32_t h = -1;
+            if (u < nu) {
+                const int32_t r = urow[u];
+                h = g.slotU[ts + u];
+                if (!named(r, 0)) bz.set((uint32_t)r);
+                const uint32_t f = h >= 0 ? tb.slot_flags[h] : 0u;
                 if (f & F_PF) tb.slot_flags[h] = f & ~F_PF;
             }
+            unring(h);
         }
-        for (int32_t i = tid; i < pc; i += kSmallThreads) {
-            const int32_t v = g.puref[lo + i];
-            if (v >= 0 && tb.slot_touch[v] != p.last_stamp) unring(v);  // touched: done above
+        for (int32_t i0 = 0; i0 < pc; i0 += kSmallThreads) {  // block-uniform
+            const int32_t i = i0 + tid;
+            int32_t v = i < pc ? g.puref[lo + i] : -1;
+            if (v >= 0 && tb.slot_touch[v] == p.last_stamp) v = -1;  // touched: done above
+            unring(v);
         }
         lds_sum(stale, &s_c[C_STALE]);
         __syncthreads();
