@@ -225,11 +225,8 @@ __global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot) {
         publish_forward(g, log_slot);
         return;
     }
-    __shared__ int32_t s_cnt[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) s_cnt[t] = g.tabs[t].staged ? 0 : g.st[t].mcount;
-    __syncthreads();
     copy_flat(
-        g, s_cnt, nb,
+        g, [&](int t) { return g.tabs[t].staged ? 0 : g.st[t].mcount; }, nb,
         [&](int t, const DTable &tb, int64_t j) {
             return tb.host + (int64_t)g.M[g.tstart[t] + j] * tb.row_bytes;
         },

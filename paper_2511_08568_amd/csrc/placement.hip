@@ -447,17 +447,15 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
 template <class First, class Count, class Miss0>
 __device__ __forceinline__ void fill_rows(const DGlobal &g, int phase, int64_t nb, First first_of, Count count_of,
                                           Miss0 miss0_of) {
-    __shared__ int32_t s_cnt[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t < g.T; t += blockDim.x) {
-        const int64_t base = first_of(t), n = count_of(t);
-        const bool mine = (g.tabs[t].staged != 0) == (phase == FILL_STAGED);
-        // admit wrote entries [base, base + n) and checked them against fill_cap
-        s_cnt[t] = (mine && base >= 0 && n >= 0 && base + n <= g.fill_cap) ? (int32_t)n : 0;
-    }
-    __syncthreads();
-    // entries were checked where admit and the set-associative placement wrote them
+    // admit and the set-associative placement checked the entries that they wrote
     copy_flat(
-        g, s_cnt, nb,
+        g,
+        [&](int t) {
+            const int64_t base = first_of(t), n = count_of(t);
+            const bool mine = (g.tabs[t].staged != 0) == (phase == FILL_STAGED);
+            return mine && base >= 0 && n >= 0 && base + n <= g.fill_cap ? (int32_t)n : 0;
+        },
+        nb,
         [&](int t, const DTable &tb, int64_t j) -> const char * {
             const int32_t src = g.fill_src[first_of(t) + j];
             if (src >= 0) return g.staging + (miss0_of(t) + src) * g.stage_stride;  // admitted miss

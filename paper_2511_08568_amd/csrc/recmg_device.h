@@ -305,22 +305,52 @@ __device__ __forceinline__ void map_find_n(const DTable &tb, const int32_t (&row
 // safe; no lookup may run concurrently.  Returns 1 if a deleted entry was
 // reused.  An entry (key, slot) is taken whole by one 64-bit compare-and-swap,
 // tried on the empty value first: mostly one memory operation per insert.
-__device__ __forceinline__ int map_insert(const DTable &tb, int32_t row, int32_t slot) {
+__device__ __forceinline__ unsigned long long map_entry(int32_t row, int32_t slot) {
+    return ((unsigned long long)(uint32_t)slot << 32) | (uint32_t)row;
+}
+// goes on from entry i, whose compare-and-swap of the empty value returned prev
+__device__ __forceinline__ int map_insert_from(const DTable &tb, uint32_t i, unsigned long long prev,
+                                               unsigned long long mine) {
     const int32_t mask = tb.map_mask;
-    const unsigned long long mine = ((unsigned long long)(uint32_t)slot << 32) | (uint32_t)row;
-    uint32_t i = hash_row(row) & (uint32_t)mask;
-    for (int32_t n = 0; n <= mask; ++n) {
-        unsigned long long cur = ~0ull;  // an empty entry: key -1, slot -1
-        for (;;) {
-            const unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long *>(tb.map + i), cur, mine);
-            const int32_t k = (int32_t)(uint32_t)prev;
-            if (prev == cur) return k == kTomb;
-            if (k != kEmpty && k != kTomb) break;  // taken by another row
+    unsigned long long cur = ~0ull;  // an empty entry: key -1, slot -1
+    for (int32_t n = 0; n <= mask;) {
+        const int32_t k = (int32_t)(uint32_t)prev;
+        if (prev == cur) return k == kTomb;
+        if (k == kEmpty || k == kTomb) {
             cur = prev;  // a deleted entry (with its old slot)
+        } else {  // taken by another row
+            i = (i + 1) & (uint32_t)mask;
+            cur = ~0ull;
+            ++n;
         }
-        i = (i + 1) & (uint32_t)mask;
+        prev = atomicCAS(reinterpret_cast<unsigned long long *>(tb.map + i), cur, mine);
     }
     return 0;
+}
+__device__ __forceinline__ int map_insert(const DTable &tb, int32_t row, int32_t slot) {
+    const uint32_t i = hash_row(row) & (uint32_t)tb.map_mask;
+    const unsigned long long mine = map_entry(row, slot);
+    return map_insert_from(tb, i, atomicCAS(reinterpret_cast<unsigned long long *>(tb.map + i), ~0ull, mine), mine);
+}
+// The same for the Q rows with `want`, their first attempts in flight together;
+// the number of deleted entries reused.
+template <int Q>
+__device__ __forceinline__ int map_insert_n(const DTable &tb, const int32_t (&row)[Q], const int32_t (&slot)[Q],
+                                            const bool (&want)[Q]) {
+    unsigned long long prev[Q];
+    int reused = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        prev[q] = ~0ull;
+        if (want[q])
+            prev[q] = atomicCAS(reinterpret_cast<unsigned long long *>(tb.map + (hash_row(row[q]) & (uint32_t)tb.map_mask)),
+                                ~0ull, map_entry(row[q], slot[q]));
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (want[q] && prev[q] != ~0ull)
+            reused += map_insert_from(tb, hash_row(row[q]) & (uint32_t)tb.map_mask, prev[q], map_entry(row[q], slot[q]));
+    return reused;
 }
 static_assert(kEmpty == -1, "an empty map entry is all ones");
 
@@ -337,6 +367,29 @@ __device__ __forceinline__ void map_delete(const DTable &tb, int32_t row) {
         if (k == kEmpty) return;
         i = (i + 1) & (uint32_t)mask;
     }
+}
+
+// The same for the Q rows with `want`, their first probes in flight together.
+template <int Q>
+__device__ __forceinline__ void map_delete_n(const DTable &tb, const int32_t (&row)[Q], const bool (&want)[Q]) {
+    const int32_t mask = tb.map_mask;
+    uint32_t i[Q];
+    int32_t k[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        i[q] = hash_row(row[q]) & (uint32_t)mask;
+        k[q] = want[q] ? (int32_t)gload4(&tb.map[i[q]].x) : kEmpty;
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        for (int32_t n = 0; n <= mask && k[q] != kEmpty; ++n) {
+            if (k[q] == row[q]) {
+                tb.map[i[q]].x = kTomb;
+                break;
+            }
+            i[q] = (i[q] + 1) & (uint32_t)mask;
+            k[q] = (int32_t)gload4(&tb.map[i[q]].x);
+        }
 }
 
 // Bitmap position of row r (see DTable::qbits) and its inverse.
@@ -662,19 +715,18 @@ __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const in
     st.digest_acc = (g.tabs[t].ways || g.tabs[t].ring_cap) ? st.digest : 0ull;
 }
 
-// Copy `count[t]` rows of every table in 16/4/2-byte units, the tables' work
+// Copy count_of(t) rows of every table in 16/4/2-byte units, the tables' work
 // laid end to end so every table gets its share of the first `nblocks` blocks
 // of the grid (the others copy nothing).  src_of / dst_of give the byte
 // addresses of item j of table t.
-template <class Src, class Dst>
-__device__ __forceinline__ void copy_flat(const DGlobal &g, const int32_t *count, int64_t nblocks, Src src_of,
-                                          Dst dst_of) {
+template <class Count, class Src, class Dst>
+__device__ __forceinline__ void copy_flat(const DGlobal &g, Count count_of, int64_t nblocks, Src src_of, Dst dst_of) {
     __shared__ int64_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ long long tmp[16];
     // per-table unit counts, scanned (T <= 256 = blockDim)
     long long mine = 0;
     const int t0 = threadIdx.x;
-    if (t0 < g.T) mine = (long long)count[t0] * (g.tabs[t0].row_bytes / g.tabs[t0].copy_unit);
+    if (t0 < g.T) mine = (long long)count_of(t0) * (g.tabs[t0].row_bytes / g.tabs[t0].copy_unit);
     long long tot;
     const long long ex = block_excl_scan64(mine, tmp, &tot);
     if (t0 < g.T) s_pre[t0] = ex;

@@ -303,7 +303,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     enum { C_PRES, C_NP, C_STALE, C_EV, C_RING_EV, C_POP, C_ADM, C_FILL, C_PDROP, C_MDROP, C_REUSE, C_RUN, C_KEEP, C_N };
     __shared__ LdsBitmap<NB> bm, bz;  // the rows of P; the rows of Z1 (or the ranking's histogram)
     __shared__ int tmp[16];
-    __shared__ int s_c[C_N];
+    constexpr int Q = 4;  // items per thread whose loads are in flight together
+    __shared__ int s_c[C_N], s_ch[Q];
     __shared__ int s_err, s_bad_id;
     __shared__ unsigned long long s_dig;
     static_assert(sizeof(bz.w4) >= kRadix * sizeof(int), "the ranking's histogram takes a bitmap's place");
@@ -316,6 +317,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         s_dig = 0;
     }
     if (tid < C_N) s_c[tid] = 0;
+    if (tid < Q) s_ch[tid] = 0;
     const int nw = tb.bm_words;
     bm.clear(nw);
     const int64_t lo = poff[t], hi = poff[t + 1];
@@ -398,7 +400,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         return;
     }
     // ---- classification of the prefetch rows: resident, missed, or new
-    constexpr int Q = 4;
     for (int32_t u0 = 0; u0 < pc; u0 += Q * kSmallThreads) {  // block-uniform
         int32_t row[Q], slot[Q];
         uint4 rk[Q];
@@ -449,14 +450,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     const bool ring = tb.ring_cap != 0;
     if (reb) map_clear_share(tb, 0, 1);  // no lookup follows; k_plc_end inserts every resident
     unsigned long long dig = 0;  // this thread's share of the digest (ring: of its change)
-    // frees slot sl of row r (when ev); every lane of the wave calls.  Its row
-    // and flags are cleared after admission, if no admitted row takes the slot.
-    auto evict = [&](bool ev, int32_t sl, int32_t r) {
-        const int at = top0 + lds_append(ev, &s_c[C_EV]);
-        if (!ev) return;
-        if (!reb) map_delete(tb, r);
-        if (at < tb.cap) tb.free_stack[at] = sl;
-        else atomicOr(g.err, ERR_INTERNAL);
+    // frees Q slots sl of rows r (where ev); every lane of the wave calls.  Their
+    // rows and flags are cleared after admission, if no admitted row takes the slot.
+    auto evict = [&](const bool (&ev)[Q], const int32_t (&sl)[Q], const int32_t (&r)[Q]) {
+        if (!reb) map_delete_n<Q>(tb, r, ev);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int at = top0 + lds_append(ev[q], &s_c[C_EV]);
+            if (!ev[q]) continue;
+            if (at < tb.cap) tb.free_stack[at] = sl[q];
+            else atomicOr(g.err, ERR_INTERNAL);
+        }
     };
     auto named = [&](int32_t r, uint32_t) { return bm.test((uint32_t)r); };  // r in P
     int32_t mode = c.mode;
@@ -473,13 +477,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
             int32_t row[4], sc[4];
             slot_quad(tb.slot_row, k0, lim, -1, row);
             slot_quad(tb.slot_score, k0, lim, 0, sc);
+            bool ev[Q];
+            int32_t sl[Q];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const bool live = row[i] >= 0;
                 const bool keep = live && kept(mode, make_key(sc[i], row[i], p.rowbits), thr);
                 if (keep) dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[i]);
-                evict(live && !keep, k0 + i, row[i]);
+                ev[i] = live && !keep;
+                sl[i] = k0 + i;
             }
+            evict(ev, sl, row);
         }
         __syncthreads();
     } else {
@@ -494,36 +502,61 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         bz.clear(nw);
         __syncthreads();
         int stale = 0;
-        auto unring = [&](int32_t sl) {  // its score changes: its ring entry, if it has one, goes stale
-            const int32_t e = sl >= 0 ? tb.slot_pos[sl] : -1;
-            if (e >= 0) {
-                tb.slot_pos[sl] = -1;
-                ++stale;
+        // the ring entries e of slots sl, whose scores change, go stale (-1: none);
+        // every lane of the wave calls
+        auto unring = [&](const int32_t (&sl)[Q], const int32_t (&e)[Q]) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (e[q] >= 0) {
+                    tb.slot_pos[sl[q]] = -1;
+                    ++stale;
+                }
+                chunk_sub(e[q] >= 0, e[q] / kRingChunk, rcnt);
             }
-            chunk_sub(e >= 0, e / kRingChunk, rcnt);  // every lane of the wave calls
         };
         // pending rows neither touched nor named again
         for (int32_t j = tid; j < pn; j += kSmallThreads) {
             const int32_t q = pslot[j], r = prow[j];
             if (q >= 0 && q < tb.cap && !named(r, 0) && tb.slot_touch[q] != p.last_stamp) bz.set((uint32_t)r);
         }
-        for (int32_t u0 = 0; u0 < nu; u0 += kSmallThreads) {  // block-uniform
-            const int32_t u = u0 + tid;
-            int32_t h = -1;
-            if (u < nu) {
-                const int32_t r = urow[u];
-                h = g.slotU[ts + u];
-                if (!named(r, 0)) bz.set((uint32_t)r);
-                const uint32_t f = h >= 0 ? tb.slot_flags[h] : 0u;
-                if (f & F_PF) tb.slot_flags[h] = f & ~F_PF;
+        for (int32_t u0 = 0; u0 < nu; u0 += Q * kSmallThreads) {  // block-uniform
+            int32_t h[Q], e[Q];
+            uint32_t f[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int32_t u = u0 + q * kSmallThreads + tid;
+                h[q] = u < nu ? (int32_t)gload4(g.slotU + ts + u) : -1;
+                if (u < nu) {
+                    const int32_t r = (int32_t)gload4(urow + u);
+                    if (!named(r, 0)) bz.set((uint32_t)r);
+                }
             }
-            unring(h);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                f[q] = h[q] >= 0 ? gload4(tb.slot_flags + h[q]) : 0u;
+                e[q] = h[q] >= 0 ? (int32_t)gload4(tb.slot_pos + h[q]) : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (f[q] & F_PF) tb.slot_flags[h[q]] = f[q] & ~F_PF;
+            unring(h, e);
         }
-        for (int32_t i0 = 0; i0 < pc; i0 += kSmallThreads) {  // block-uniform
-            const int32_t i = i0 + tid;
-            int32_t v = i < pc ? g.puref[lo + i] : -1;
-            if (v >= 0 && tb.slot_touch[v] == p.last_stamp) v = -1;  // touched: done above
-            unring(v);
+        for (int32_t i0 = 0; i0 < pc; i0 += Q * kSmallThreads) {  // block-uniform
+            int32_t v[Q], e[Q], tch[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int32_t i = i0 + q * kSmallThreads + tid;
+                v[q] = i < pc ? (int32_t)gload4(g.puref + lo + i) : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                tch[q] = v[q] >= 0 ? (int32_t)gload4(tb.slot_touch + v[q]) : 0;
+                e[q] = v[q] >= 0 ? (int32_t)gload4(tb.slot_pos + v[q]) : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (tch[q] == p.last_stamp) e[q] = -1;  // touched: done above
+            unring(v, e);
         }
         lds_sum(stale, &s_c[C_STALE]);
         __syncthreads();
@@ -554,52 +587,76 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
                               : cut.cut > tail             ? (cut.cut - 1) / kRingChunk + 1
                                                            : 0;
         int32_t run = 0;  // entries moved so far
-        for (int32_t ch = tail / kRingChunk; ch < hi_ch; ++ch) {
-            const int32_t e = ch * kRingChunk + tid;
-            const int32_t sl = (int32_t)gload4(ringb + e);
-            const bool live = e >= tail && e < head && ring_live(tb, sl, e);
-            const bool ev = live && e < cut.cut, mv = live && !ev && cut.compact;
-            const int32_t r = ev ? tb.slot_row[sl] : 0;
-            const int before = s_c[C_EV];
-            __syncthreads();  // every thread has read it
+        // Q chunks at a time, their loads in flight together
+        for (int32_t ch = tail / kRingChunk; ch < hi_ch; ch += Q) {
+            int32_t sl[Q], r[Q], pos[Q];
+            bool ev[Q], mv[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) sl[q] = ch + q < hi_ch ? (int32_t)gload4(ringb + (ch + q) * kRingChunk + tid) : -1;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const bool ok = sl[q] >= 0 && sl[q] < tb.cap;
+                pos[q] = ok ? (int32_t)gload4(tb.slot_pos + sl[q]) : -1;
+                r[q] = ok ? (int32_t)gload4(tb.slot_row + sl[q]) : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int32_t e = (ch + q) * kRingChunk + tid;
+                const bool live = e >= tail && e < head && pos[q] == e;
+                ev[q] = live && e < cut.cut;
+                mv[q] = live && !ev[q] && cut.compact;
+                if (ev[q]) {
+                    tb.slot_pos[sl[q]] = -1;
+                    dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r[q]);
+                }
+                lds_count(ev[q], &s_ch[q]);
+            }
             evict(ev, sl, r);
-            if (ev) {
-                tb.slot_pos[sl] = -1;
-                dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r);
+            if (cut.compact) {  // block-uniform
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    int tot;
+                    const int at = run + block_excl_scan(mv[q] ? 1 : 0, tmp, &tot);
+                    if (mv[q]) {
+                        if (at < cut.moved) dst[at] = sl[q];
+                        else atomicOr(g.err, ERR_INTERNAL);  // counts and entries disagree (never expected)
+                    }
+                    run += tot;
+                }
             }
-            int tot;
-            const int at = run + block_excl_scan(mv ? 1 : 0, tmp, &tot);
-            if (mv) {
-                if (at < cut.moved) dst[at] = sl;
-                else atomicOr(g.err, ERR_INTERNAL);  // counts and entries disagree (never expected)
-            }
-            run += tot;
-            if (tid == 0) {
-                const int n = s_c[C_EV] - before;
-                if (n) rcnt[ch] -= n;
-                s_c[C_RING_EV] += n;
+            __syncthreads();
+            if (tid < Q && s_ch[tid]) {
+                rcnt[ch + tid] -= s_ch[tid];
+                atomicAdd(&s_c[C_RING_EV], s_ch[tid]);
+                s_ch[tid] = 0;
             }
             __syncthreads();
         }
         if (cut.zev) {  // Z1 and Z2 residents below the threshold
             const int32_t n = z1 + pc;
-            for (int32_t b0 = 0; b0 < n; b0 += kSmallThreads) {  // block-uniform
-                const int32_t k = b0 + tid;
-                int32_t sl = -1, r = 0;
-                if (k < z1) {
-                    const int2 zr = z[k];
-                    r = zr.y;
-                    if (zr.x >= 0 && !kept(mode, make_key(p.lru_touch, r, p.rowbits), thr)) sl = zr.x;
-                } else if (k < n) {
-                    const int32_t v = g.puref[lo + (k - z1)];
-                    r = PU[k - z1];
-                    if (v >= 0 && !kept(mode, make_key(p.pscore, r, p.rowbits), thr)) sl = v;
+            for (int32_t b0 = 0; b0 < n; b0 += Q * kSmallThreads) {  // block-uniform
+                int32_t sl[Q], r[Q];
+                bool ev[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int32_t k = b0 + q * kSmallThreads + tid;
+                    sl[q] = -1, r[q] = 0;
+                    if (k < z1) {
+                        const int2 zr = z[k];
+                        r[q] = zr.y;
+                        if (zr.x >= 0 && !kept(mode, make_key(p.lru_touch, zr.y, p.rowbits), thr)) sl[q] = zr.x;
+                    } else if (k < n) {
+                        const int32_t v = g.puref[lo + (k - z1)];
+                        r[q] = PU[k - z1];
+                        if (v >= 0 && !kept(mode, make_key(p.pscore, r[q], p.rowbits), thr)) sl[q] = v;
+                    }
+                    ev[q] = sl[q] >= 0;
+                    if (ev[q]) {
+                        tb.slot_pos[sl[q]] = -1;
+                        dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r[q]);
+                    }
                 }
-                evict(sl >= 0, sl, r);
-                if (sl >= 0) {
-                    tb.slot_pos[sl] = -1;
-                    dig -= mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r);
-                }
+                evict(ev, sl, r);
             }
         }
         __syncthreads();
@@ -620,55 +677,65 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     const int32_t nev = s_c[C_EV], top = top0 + nev;
     const int32_t items = c.nm + c.nnp;
     int n_adm = 0, n_fill = 0, n_pdrop = 0, n_mdrop = 0, n_reuse = 0;
-    for (int32_t b0 = 0; b0 < items; b0 += kSmallThreads) {  // block-uniform
-        const int32_t k = b0 + tid;
-        bool adm = false, inp = false;
-        const bool is_miss = k < c.nm;
-        int32_t row = 0, s = 0;
-        if (k < items) {
-            if (is_miss) {
-                row = g.M[ts + k];
-                inp = named(row, 0);
-                s = ring ? (inp ? p.pscore : p.lru_touch) : g.mscore[ts + k];
-            } else {
-                row = g.NP[lo + (k - c.nm)];
-                s = new_prefetch_score(p, tb, row);
-                inp = true;
+    for (int32_t b0 = 0; b0 < items; b0 += Q * kSmallThreads) {  // block-uniform
+        int32_t row[Q], sc[Q], slot[Q], at[Q];
+        bool adm[Q], inp[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int32_t k = b0 + q * kSmallThreads + tid;
+            row[q] = sc[q] = 0;
+            if (k < c.nm) {
+                row[q] = (int32_t)gload4(g.M + ts + k);
+                if (!ring) sc[q] = (int32_t)gload4(g.mscore + ts + k);
+            } else if (k < items) {
+                row[q] = (int32_t)gload4(g.NP + lo + (k - c.nm));
             }
-            adm = kept(mode, make_key(s, row, p.rowbits), thr);
         }
-        const int32_t at = lds_append(adm, &s_c[C_POP]);
-        if (k >= items) continue;
-        int32_t slot = -1;
-        const int32_t fi = top - 1 - at;
-        const int64_t fj = fts + lo + at;  // this row's entry in the fill list
-        if (adm) {
-            if (fi >= 0 && fi < tb.cap && fj >= 0 && fj < g.fill_cap) slot = tb.free_stack[fi];
-            if ((uint32_t)slot >= (uint32_t)tb.cap) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int32_t k = b0 + q * kSmallThreads + tid;
+            inp[q] = k >= c.nm || named(row[q], 0);
+            if (k >= c.nm) sc[q] = k < items ? new_prefetch_score(p, tb, row[q]) : 0;
+            else if (ring) sc[q] = inp[q] ? p.pscore : p.lru_touch;
+            adm[q] = k < items && kept(mode, make_key(sc[q], row[q], p.rowbits), thr);
+            at[q] = lds_append(adm[q], &s_c[C_POP]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int32_t fi = top - 1 - at[q];
+            const int64_t fj = fts + lo + at[q];  // this row's entry in the fill list
+            slot[q] = adm[q] && fi >= 0 && fi < tb.cap && fj >= 0 && fj < g.fill_cap ? (int32_t)gload4(tb.free_stack + fi) : -1;
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int32_t k = b0 + q * kSmallThreads + tid;
+            const bool is_miss = k < c.nm;
+            if (adm[q] && (uint32_t)slot[q] >= (uint32_t)tb.cap) {
                 atomicOr(g.err, ERR_INTERNAL);
-                adm = false;
+                adm[q] = false;
             }
+            if (!adm[q]) {
+                n_mdrop += is_miss ? 1 : 0;
+                n_pdrop += k < items && inp[q] ? 1 : 0;
+                continue;
+            }
+            // (the slot's touch stamp, of a forward before this placement, is older
+            // than any a later placement asks for)
+            tb.slot_row[slot[q]] = row[q];
+            if (!ring) tb.slot_score[slot[q]] = sc[q];
+            tb.slot_flags[slot[q]] = inp[q] ? F_PF : 0u;
+            const int64_t fj = fts + lo + at[q];
+            g.fill_src[fj] = is_miss ? k : -(row[q] + 1);
+            g.fill_slot[fj] = slot[q];
+            if (ring) {
+                if (is_miss) g.mslot[ts + k] = slot[q];
+                else g.npslot[lo + (k - c.nm)] = slot[q];
+            }
+            dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[q]);
+            if (is_miss) ++n_adm;
+            else ++n_fill;
         }
-        if (!adm) {
-            n_mdrop += is_miss ? 1 : 0;
-            n_pdrop += inp ? 1 : 0;
-            continue;
-        }
-        // (the slot's touch stamp, of a forward before this placement, is older
-        // than any a later placement asks for)
-        tb.slot_row[slot] = row;
-        if (!ring) tb.slot_score[slot] = s;
-        tb.slot_flags[slot] = inp ? F_PF : 0u;
-        if (!reb) n_reuse += map_insert(tb, row, slot);
-        g.fill_src[fj] = is_miss ? k : -(row + 1);
-        g.fill_slot[fj] = slot;
-        if (ring) {
-            if (is_miss) g.mslot[ts + k] = slot;
-            else g.npslot[lo + (k - c.nm)] = slot;
-        }
-        dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row);
-        if (is_miss) ++n_adm;
-        else ++n_fill;
+        if (!reb) n_reuse += map_insert_n<Q>(tb, row, slot, adm);
     }
     lds_sum(n_adm, &s_c[C_ADM]);
     lds_sum(n_fill, &s_c[C_FILL]);
