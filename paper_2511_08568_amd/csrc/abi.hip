@@ -75,7 +75,8 @@ struct Layout {
     size_t fstage = 0;
     size_t puref = 0, zone = 0, mslot = 0, npslot = 0, pend_row[2] = {0, 0}, pend_slot[2] = {0, 0};
     // pinned host staging (STAGED): miss ids, miss rows, fill sources, prefetch rows
-    size_t h_mrows = 0, h_rows = 0, h_fsrc = 0, h_frows = 0, h_np = 0, h_early = 0;
+    size_t h_mrows = 0, h_rows = 0, h_fsrc = 0, h_frows = 0, h_np = 0, h_back = 0;
+    size_t back_bytes = 0;  // st .. ftstart
     size_t staging[2] = {0, 0};
     int64_t stage_stride = 0, sum_cap = 0;
     int32_t total_bm_blocks = 0;
@@ -215,13 +216,16 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     }
     const size_t mi = (size_t)cfg->max_indices, mp = (size_t)cfg->max_prefetch;
     L->tabs = take(sizeof(DTable) * T);
+    // what the host reads back, side by side: one copy brings all of it
     L->st = take(sizeof(TState) * T);
     L->err = take(4);
+    L->tstart = take(8 * (T + 1));
+    L->pstart = take(8 * (T + 1));
+    L->ftstart = take(8 * (T + 1));
+    L->back_bytes = off - L->st;
     L->bm_block_start = take(4 * (T + 1));
     L->blocksum = take(4 * (size_t)L->total_bm_blocks);
     L->blockoff = take(4 * (size_t)L->total_bm_blocks);
-    L->tstart = take(8 * (T + 1));
-    L->pstart = take(8 * (T + 1));
     L->src = take(4 * mi);
     L->raddr = take(8 * (mi + kRaddrPad));  // blocks of row addresses are read past the end
     L->U = take(4 * mi);
@@ -240,7 +244,6 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     L->dump_count = take(4 * T);
     L->pool_bstart = take(4 * (T + 1));
     L->pool_btab = take(4 * T);
-    L->ftstart = take(8 * (T + 1));
     L->stat_log = take((size_t)cfg->stats_log_calls * T * sizeof(recmg_table_stats_t));
     L->sa_bstart = take(4 * (T + 1));
     L->sa_btab = take(4 * T);
@@ -275,7 +278,7 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
         L->h_fsrc = htake(4 * (mi + mp));
         L->h_frows = htake(mp * (size_t)L->stage_stride);
         L->h_np = htake(4 * mp);
-        L->h_early = htake(sizeof(TState) * T + 8 * (T + 1) + 8);
+        L->h_back = htake(L->back_bytes);
         L->host_total = h;
     }
 }
@@ -311,6 +314,8 @@ struct recmg_cache {
     // needs from the latest call of the other kind through these events.
     hipStream_t fwd_stream = nullptr, plc_stream = nullptr;
     bool fwd_ev = false, plc_ev = false;  // the events below were recorded
+    bool own_stream = false;  // some placement came on another stream than the forward before it
+    bool src_rec = false;     // ev_src was recorded by the latest forward
     hipEvent_t ev_src = nullptr;   // latest forward: after its dedup, probe, sources and coverage
     hipEvent_t ev_fwd = nullptr;   // latest forward: after all its kernels (the pooled kernel, or a few us later)
     hipEvent_t ev_plc = nullptr;   // latest placement: after all its kernels but the fill
@@ -337,19 +342,13 @@ struct recmg_cache {
     hipEvent_t ev_ready = nullptr, ev_copied = nullptr;
     hipEvent_t ev_np = nullptr;  // a placement's new prefetch candidates have reached the host
     int32_t *h_np = nullptr;     // those candidates (NP), for the early gather
-    // pinned copies made with them: table states, prefetch list starts, error word
-    TState *he_st = nullptr;
-    int64_t *he_pstart = nullptr;
-    int32_t *he_err = nullptr;
+    char *h_back = nullptr;      // pinned copy of the workspace's st .. ftstart (see Back)
     bool has_staged_fa = false;  // STAGED fully associative tables with slots (gathered early)
     bool has_staged_sa = false;  // STAGED set-associative tables (gathered after their placement)
     int32_t *h_mrows = nullptr;
     char *h_rows = nullptr;
     int32_t *h_fsrc = nullptr;  // fill sources of a placement, rewritten to staged rows
     char *h_frows = nullptr;    // prefetch rows gathered on the host
-    std::vector<int64_t> h_pstart, h_ftstart;
-    std::vector<TState> h_st;
-    std::vector<int64_t> h_tstart;
     // stage timing: 0 off, 1 the pooled kernel only, 2 every stage
     int32_t timing = 0;
     struct Mark {
@@ -467,12 +466,33 @@ struct EnqueueGuard {
 
 // Waits for every stream the handle's calls used.
 hipError_t sync_all(recmg_cache_t *c) {
-    hipError_t e = hipStreamSynchronize(c->last_stream);
-    if (e == hipSuccess && c->fwd_ev) e = hipStreamSynchronize(c->fwd_stream);
-    if (e == hipSuccess && c->plc_ev) e = hipStreamSynchronize(c->plc_stream);
-    if (e == hipSuccess && c->copy_stream) e = hipStreamSynchronize(c->copy_stream);
+    const hipStream_t last = c->last_stream;
+    hipError_t e = hipStreamSynchronize(last);
+    if (e == hipSuccess && c->fwd_ev && c->fwd_stream != last) e = hipStreamSynchronize(c->fwd_stream);
+    if (e == hipSuccess && c->plc_ev && c->plc_stream != last) e = hipStreamSynchronize(c->plc_stream);
+    if (e == hipSuccess && c->copy_stream && c->copy_stream != last) e = hipStreamSynchronize(c->copy_stream);
     if (e == hipSuccess) c->fill_last = -1;
     return e;
+}
+
+// A host copy of the table states, the error word and the list starts, which
+// lie side by side in the workspace: one copy brings them all (a copy of a few
+// bytes costs its 5 to 10 us whatever its size).
+struct Back {
+    const TState *st;
+    const int64_t *tstart, *pstart, *ftstart;
+    int32_t err;
+    Back(const Layout &L, const char *host)
+        : st(reinterpret_cast<const TState *>(host)),
+          tstart(reinterpret_cast<const int64_t *>(host + (L.tstart - L.st))),
+          pstart(reinterpret_cast<const int64_t *>(host + (L.pstart - L.st))),
+          ftstart(reinterpret_cast<const int64_t *>(host + (L.ftstart - L.st))),
+          err(*reinterpret_cast<const int32_t *>(host + (L.err - L.st))) {}
+};
+
+// Enqueues that copy into the handle's pinned buffer (STAGED handles).
+hipError_t copy_back(recmg_cache_t *c, hipStream_t s) {
+    return hipMemcpyAsync(c->h_back, c->g.st, c->L.back_bytes, hipMemcpyDeviceToHost, s);
 }
 
 int32_t set_device(recmg_cache_t *c) {
@@ -548,20 +568,17 @@ int32_t gather_and_copy(const std::vector<int64_t> &n, Work work, Copy copy) {
 // and the fill kernel (launched by the caller on cs) copies rows into slots.
 int32_t staged_fill(recmg_cache_t *c, hipStream_t s, hipStream_t cs) {
     const int T = c->T;
-    HIP_TRY(hipMemcpyAsync(c->h_st.data(), c->g.st, sizeof(TState) * T, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(c->h_pstart.data(), c->g.pstart, 8 * (T + 1), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(c->h_ftstart.data(), c->g.ftstart, 8 * (T + 1), hipMemcpyDeviceToHost, s));
-    int32_t err = 0;
-    HIP_TRY(hipMemcpyAsync(&err, c->g.err, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(copy_back(c, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (err) return RECMG_OK;
+    const Back back(c->L, c->h_back);
+    if (back.err) return RECMG_OK;
     std::vector<int64_t> base(T), nfill(T, 0);
     int64_t total = 0;
     for (int t = 0; t < T; ++t) {
-        base[t] = c->h_ftstart[t] + c->h_pstart[t];
+        base[t] = back.ftstart[t] + back.pstart[t];
         // zero-copy tables' fills read the host themselves; fully associative
         // STAGED tables' prefetch rows were gathered early (early_gather)
-        nfill[t] = c->geo[t].staged && c->geo[t].ways ? c->h_st[t].popped : 0;
+        nfill[t] = c->geo[t].staged && c->geo[t].ways ? back.st[t].popped : 0;
         if (base[t] < 0 || nfill[t] < 0 || base[t] + nfill[t] > c->g.fill_cap)
             return fail(RECMG_E_STATE, "fill list outside its buffer");
         if (nfill[t])
@@ -583,11 +600,11 @@ int32_t staged_fill(recmg_cache_t *c, hipStream_t s, hipStream_t cs) {
             for (int64_t j = k * kChunk; j < std::min(nfill[t], (k + 1) * kChunk); ++j) cnt += c->h_fsrc[base[t] + j] < 0;
             kbase[t][k + 1] = kbase[t][k] + cnt;
         }
-        if (kbase[t][nck] > c->h_pstart[t + 1] - c->h_pstart[t])
+        if (kbase[t][nck] > back.pstart[t + 1] - back.pstart[t])
             return fail(RECMG_E_STATE, "staged fills exceed the list");
     }
     auto work = [&](int t, int64_t lo, int64_t hi) {
-        const int64_t rb = c->geo[t].row_bytes, p0 = c->h_pstart[t];
+        const int64_t rb = c->geo[t].row_bytes, p0 = back.pstart[t];
         int64_t k = kbase[t][lo / kChunk];
         for (int64_t j = lo; j < hi; ++j) {
             if (j + kAhead < hi && c->h_fsrc[base[t] + j + kAhead] < 0)
@@ -604,7 +621,7 @@ int32_t staged_fill(recmg_cache_t *c, hipStream_t s, hipStream_t cs) {
         HIP_TRY(hipMemcpyAsync(c->g.fill_src + base[t] + lo, c->h_fsrc + base[t] + lo, 4 * (size_t)(hi - lo),
                                hipMemcpyHostToDevice, cs));
         const int64_t k0 = kbase[t][lo / kChunk], k1 = kbase[t][(hi + kChunk - 1) / kChunk];
-        const int64_t r0 = c->h_pstart[t] + k0;
+        const int64_t r0 = back.pstart[t] + k0;
         if (k1 > k0)
             HIP_TRY(hipMemcpyAsync(c->g.fstage + r0 * stride, c->h_frows + r0 * stride, (size_t)((k1 - k0) * stride),
                                    hipMemcpyHostToDevice, cs));
@@ -624,13 +641,14 @@ int32_t staged_fill(recmg_cache_t *c, hipStream_t s, hipStream_t cs) {
 int32_t early_gather(recmg_cache_t *c, hipStream_t cs) {
     const int T = c->T;
     HIP_TRY(hipEventSynchronize(c->ev_np));
-    if (*c->he_err) return RECMG_OK;  // the device flag already disables the rest
-    const int64_t *ps = c->he_pstart;
+    const Back back(c->L, c->h_back);
+    if (back.err) return RECMG_OK;  // the device flag already disables the rest
+    const int64_t *ps = back.pstart;
     std::vector<int64_t> n(T, 0);
     for (int t = 0; t < T; ++t) {
         const Geom &ge = c->geo[t];
         if (!ge.staged || ge.ways || ge.cap == 0) continue;
-        n[t] = c->he_st[t].npcount;
+        n[t] = back.st[t].npcount;
         if (n[t] < 0 || ps[t] < 0 || ps[t] + n[t] > ps[t + 1] || ps[t + 1] > c->cfg.max_prefetch)
             return fail(RECMG_E_STATE, "prefetch candidates outside their list");
     }
@@ -658,11 +676,10 @@ int32_t early_gather(recmg_cache_t *c, hipStream_t cs) {
 // needs (so that its waits do not wait for the kernel), beside the gather.
 int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
     const int T = c->T;
-    HIP_TRY(hipMemcpyAsync(c->h_st.data(), c->g.st, sizeof(TState) * T, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(c->h_tstart.data(), c->g.tstart, 8 * (T + 1), hipMemcpyDeviceToHost, s));
-    int32_t err = 0;
-    HIP_TRY(hipMemcpyAsync(&err, c->g.err, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(copy_back(c, s));
     HIP_TRY(hipStreamSynchronize(s));
+    const Back back(c->L, c->h_back);
+    int32_t err = back.err;
     auto zero_copy_fetch = [&]() -> int32_t {
         if (c->has_zc) {
             DispatchTimer dt(c, RECMG_STAGE_FWD_FETCH, true);
@@ -675,9 +692,9 @@ int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
     std::vector<int64_t> nm(T);
     int64_t total = 0;
     for (int t = 0; t < T; ++t) {
-        nm[t] = c->geo[t].staged ? c->h_st[t].mcount : 0;
+        nm[t] = c->geo[t].staged ? back.st[t].mcount : 0;
         if (nm[t])
-            HIP_TRY(hipMemcpyAsync(c->h_mrows + c->h_tstart[t], c->g.M + c->h_tstart[t], 4 * (size_t)nm[t],
+            HIP_TRY(hipMemcpyAsync(c->h_mrows + back.tstart[t], c->g.M + back.tstart[t], 4 * (size_t)nm[t],
                                    hipMemcpyDeviceToHost, s));
         total += nm[t];
     }
@@ -691,14 +708,14 @@ int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
     }
     if ((err = zero_copy_fetch())) return err;
     auto work = [&](int t, int64_t lo, int64_t hi) {
-        const int64_t ts = c->h_tstart[t], rb = c->geo[t].row_bytes;
+        const int64_t ts = back.tstart[t], rb = c->geo[t].row_bytes;
         for (int64_t m = lo; m < hi; ++m) {
             if (m + kAhead < hi) prefetch_row(c->host[t] + (int64_t)c->h_mrows[ts + m + kAhead] * rb, rb);
             std::memcpy(c->h_rows + (ts + m) * stride, c->host[t] + (int64_t)c->h_mrows[ts + m] * rb, (size_t)rb);
         }
     };
     auto copy = [&](int t, int64_t lo, int64_t hi) -> int32_t {
-        const int64_t r0 = c->h_tstart[t] + lo;
+        const int64_t r0 = back.tstart[t] + lo;
         HIP_TRY(hipMemcpyAsync(c->g.staging + r0 * stride, c->h_rows + r0 * stride, (size_t)((hi - lo) * stride),
                                hipMemcpyHostToDevice, cs));
         return RECMG_OK;
@@ -1036,17 +1053,11 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
         c->h_fsrc = reinterpret_cast<int32_t *>(hs + L.h_fsrc);
         c->h_frows = hs + L.h_frows;
         c->h_np = reinterpret_cast<int32_t *>(hs + L.h_np);
-        c->he_st = reinterpret_cast<TState *>(hs + L.h_early);
-        c->he_pstart = reinterpret_cast<int64_t *>(hs + L.h_early + sizeof(TState) * T);
-        c->he_err = reinterpret_cast<int32_t *>(hs + L.h_early + sizeof(TState) * T + 8 * (T + 1));
-        c->h_pstart.resize(T + 1);
-        c->h_ftstart.resize(T + 1);
+        c->h_back = hs + L.h_back;
         HIP_TRY(hipEventCreateWithFlags(&c->ev_ready, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_copied, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_np, hipEventDisableTiming));
     }
-    c->h_st.resize(T);
-    c->h_tstart.resize(T + 1);
     *out = c.release();
     g_last_error.clear();
     return RECMG_OK;
@@ -1073,7 +1084,10 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     EnqueueGuard guard(c);
     // what this placement reads from calls on other streams: the latest
     // forward's distinct rows, misses and sources; the latest placement's state
-    if (c->fwd_ev && c->fwd_stream != s) HIP_TRY(hipStreamWaitEvent(s, c->ev_src, 0));
+    if (c->fwd_ev && c->fwd_stream != s) {
+        HIP_TRY(hipStreamWaitEvent(s, c->src_rec ? c->ev_src : c->ev_fwd, 0));
+        c->own_stream = true;
+    }
     if (c->plc_ev && c->plc_stream != s) HIP_TRY(hipStreamWaitEvent(s, c->ev_plc, 0));
     const int q = (int)(c->placements & 1);
     if (c->fill_rec[q]) HIP_TRY(hipStreamWaitEvent(s, c->ev_fill[q], 0));  // it read this parity's fill list
@@ -1127,10 +1141,8 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // host now, so that it gathers their rows while the GPU ranks (early_gather)
     const bool early = c->has_staged_fa && num_prefetch > 0;  // never with `small`
     if (early) {
-        HIP_TRY(hipMemcpyAsync(c->he_st, g.st, sizeof(TState) * c->T, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(c->he_pstart, g.pstart, 8 * (c->T + 1), hipMemcpyDeviceToHost, s));
+        HIP_TRY(copy_back(c, s));
         HIP_TRY(hipMemcpyAsync(c->h_np, g.NP, 4 * (size_t)num_prefetch, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(c->he_err, g.err, 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipEventRecord(c->ev_np, s));
     }
     const int64_t cand = last_n + num_prefetch;
@@ -1278,7 +1290,10 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
             launch_fwd_src(g, indices, n, s);
         }
     }
-    HIP_TRY(hipEventRecord(c->ev_src, s));  // a placement on another stream may start here
+    // a placement on another stream may start here (recorded once placements
+    // have come on one: elsewhere it is a command of every forward for nothing)
+    c->src_rec = c->own_stream;
+    if (c->src_rec) HIP_TRY(hipEventRecord(c->ev_src, s));
     if (n > 0) {
         StageTimer tm(c, RECMG_STAGE_FWD_FETCH, s);
         if (!c->has_staged) {
@@ -1336,10 +1351,11 @@ int32_t recmg_stats(recmg_cache_t *c, recmg_table_stats_t *last, recmg_table_sta
     hipStream_t s = c->last_stream;
     HIP_TRY(sync_all(c));
     const int T = c->T;
-    std::vector<TState> st(T);
-    int32_t err = 0;
-    HIP_TRY(hipMemcpy(st.data(), c->g.st, sizeof(TState) * T, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&err, c->g.err, 4, hipMemcpyDeviceToHost));
+    std::vector<char> host(c->L.back_bytes);
+    HIP_TRY(hipMemcpy(host.data(), c->g.st, host.size(), hipMemcpyDeviceToHost));
+    const Back back(c->L, host.data());
+    const TState *st = back.st;
+    const int32_t err = back.err;
     for (int t = 0; t < T; ++t) {
         for (int which = 0; which < 2; ++which) {
             recmg_table_stats_t *o = which == 0 ? last : total;
