@@ -304,7 +304,6 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p, in
     };
     const bool reb = st.rebuild != 0;
     if (reb) map_clear_share(tb, blockIdx.x, gridDim.x);
-    int nev = 0;
     unsigned long long dig = 0;
     const int64_t cap = tb.cap;
     // four slots per thread; a block's iterations are uniform (its barriers)
@@ -316,19 +315,21 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p, in
         int32_t row[4], sc[4];
         slot_quad(tb.slot_row, k0, lim, -1, row);
         slot_quad(tb.slot_score, k0, lim, 0, sc);
+        bool evs[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool keep = row[i] >= 0 && kept(mode, make_key(sc[i], row[i], p.rowbits), thr);
+            if (keep) dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[i]);
+            evs[i] = row[i] >= 0 && !keep;
+        }
+        if (!reb) map_delete_n<4>(tb, row, evs);  // their first probes in flight together
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t k = k0 + i;
-            bool ev = false;
-            if (row[i] >= 0) {
-                if (kept(mode, make_key(sc[i], row[i], p.rowbits), thr)) {
-                    dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[i]);
-                } else {
-                    ev = true;
-                    if (!reb) map_delete(tb, row[i]);
-                    tb.slot_row[k] = -1;
-                    tb.slot_flags[k] = 0;
-                }
+            const bool ev = evs[i];
+            if (ev) {
+                tb.slot_row[k] = -1;
+                tb.slot_flags[k] = 0;
             }
             // append the wave's freed slots to the block's list (one LDS atomic per wave)
             const uint64_t m = __ballot(ev);
@@ -336,22 +337,26 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p, in
             if (lane == 0 && m) wb = atomicAdd(&s_n, __popcll(m));
             wb = __shfl(wb, 0);
             if (ev) s_free[wb + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)k;
-            nev += ev ? 1 : 0;
         }
         __syncthreads();
         if (s_n > kEvictBuf - 4 * (int)blockDim.x) flush();  // room for one more pass of the block
     }
     __syncthreads();
     flush();
-    const int e = block_sum(nev, tmp);
-    const unsigned long long d = wave_sum64(dig);
-    if ((threadIdx.x & 63) == 0 && d) atomicAdd(&st.digest_acc, d);
-    if (threadIdx.x == 0 && e) {
-        atomicAdd(&st.evicted, e);
-        if (!reb) atomicAdd(&st.tomb, e);
-    }
+    __shared__ unsigned long long s_dig[kBlock / 64];
+    const unsigned long long d = block_sum64(dig, s_dig);
+    if (threadIdx.x == 0 && d) atomicAdd(&st.digest_acc, d);
 }
 
+// Candidates kept: slots from the free stack's top, map entries, the fill list.
+// A block takes Q candidates per thread and round with their loads (and first
+// map attempts) in flight together, and reserves its slots with one atomic.
+// Q = 4 where the candidates are many: a chain of five dependent accesses and an
+// atomic per 256 of them took 133 us for 487,000 rows of 4 tables, 71 now.  Q = 1
+// below kAdmitMany per table, where blocks are few (6,600 candidates in each of
+// 13 tables: 16 us, 26 with Q = 4).
+constexpr int64_t kAdmitMany = 65536;
+template <int Q>
 __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
     if (block_err(g)) return;
     __shared__ int tmp[16];
@@ -364,80 +369,92 @@ __global__ void __launch_bounds__(kBlock) k_plc_admit(DGlobal g, PlcParams p) {
     const int mode = st.sel_mode;
     const uint64_t thr = st.prefix;
     const bool reb = st.rebuild != 0;  // k_plc_end inserts every resident
-    const int32_t top = st.free_top;
+    const int32_t top = st.free_top, cap = tb.cap;
     const int64_t ts = g.ftstart[t], ps = g.pstart[t];
     const int64_t items = (int64_t)c.nm + c.nnp;
-    int n_adm_miss = 0, n_fill = 0, n_pdrop = 0, n_mdrop = 0, n_reuse = 0;
+    const bool ring = tb.ring_cap != 0, staged = tb.staged != 0;
+    const int32_t *stack = tb.free_stack;
+    int n_adm_miss = 0, n_pdrop = 0, n_reuse = 0;
     unsigned long long dig = 0;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < items; base += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = base + threadIdx.x;
-        int adm = 0;
-        int32_t row = 0, s = 0;
-        bool is_miss = false, inp = false;
-        if (k < items) {
-            is_miss = k < c.nm;
-            if (is_miss) {
-                row = g.M[ts + k];
-                s = g.mscore[ts + k];
-                inp = (g.mflags[ts + k] & F_INP) != 0;
-            } else {
-                row = g.NP[ps + (k - c.nm)];
-                s = new_prefetch_score(p, tb, row);
-                inp = true;
+    for (int64_t base = (int64_t)blockIdx.x * (Q * kBlock); base < items; base += (int64_t)gridDim.x * (Q * kBlock)) {
+        int32_t row[Q], sc[Q], slot[Q];
+        bool adm[Q], inp[Q];
+        int mine = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t k = base + q * kBlock + threadIdx.x;
+            row[q] = sc[q] = 0;
+            inp[q] = true;
+            if (k < c.nm) {
+                row[q] = (int32_t)gload4(g.M + ts + k);
+                sc[q] = (int32_t)gload4(g.mscore + ts + k);
+                inp[q] = (gload4(g.mflags + ts + k) & F_INP) != 0;
+            } else if (k < items) {
+                row[q] = (int32_t)gload4(g.NP + ps + (k - c.nm));
             }
-            adm = kept(mode, make_key(s, row, p.rowbits), thr) ? 1 : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t k = base + q * kBlock + threadIdx.x;
+            if (k >= c.nm && k < items) sc[q] = new_prefetch_score(p, tb, row[q]);
+            adm[q] = k < items && kept(mode, make_key(sc[q], row[q], p.rowbits), thr);
+            mine += adm[q] ? 1 : 0;
         }
         int tot;
-        const int ex = block_excl_scan(adm, tmp, &tot);
+        const int ex = block_excl_scan(mine, tmp, &tot);
         if (threadIdx.x == 0 && tot) s_base = atomicAdd(&st.popped, tot);
         __syncthreads();
-        if (k < items) {
-            int32_t slot = -1;
-            const int64_t fi = (int64_t)top - 1 - (s_base + ex);
-            const int64_t fj = ts + ps + (s_base + ex);  // this row's entry in the fill list
-            if (adm && (fi < 0 || fi >= tb.cap || (uint32_t)tb.free_stack[fi] >= (uint32_t)tb.cap || fj < 0 ||
-                        fj >= g.fill_cap)) {
-                atomicOr(g.err, ERR_INTERNAL);
-                adm = 0;
-            }
-            if (adm) {
-                slot = tb.free_stack[fi];
-                tb.slot_row[slot] = row;
-                if (!tb.ring_cap) tb.slot_score[slot] = s;  // a ring's order holds its scores
-                tb.slot_flags[slot] = inp ? F_PF : 0u;
-                // (the slot's touch stamp, of a forward before this placement,
-                // is older than any a later placement asks for)
-                if (!reb) n_reuse += map_insert(tb, row, slot);
-                // the fill list: admitted row j of this table, its source and
-                // slot: a miss's staging row; a prefetch row's host row, or for
-                // a STAGED table the staged row of its candidate (the host
-                // gathered NP[ps + i] into row ps + i)
-                g.fill_src[fj] = is_miss ? (int32_t)k : tb.staged ? -(int32_t)(ps + (k - c.nm)) - 1 : -(row + 1);
-                g.fill_slot[fj] = slot;
-                if (tb.ring_cap) {  // where ring.hip finds the admitted rows' slots
-                    if (is_miss) g.mslot[ts + k] = slot;
-                    else g.npslot[ps + (k - c.nm)] = slot;
-                }
-                dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row);
-                if (is_miss) ++n_adm_miss;
-                else ++n_fill;
-            } else {
-                if (is_miss) ++n_mdrop;
-                if (inp) ++n_pdrop;
-            }
+        int32_t at[Q];
+        int nth = s_base + ex;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            at[q] = nth;
+            nth += adm[q] ? 1 : 0;
+            const int64_t fi = (int64_t)top - 1 - at[q], fj = ts + ps + at[q];  // fj: this row's entry in the fill list
+            slot[q] = adm[q] && fi >= 0 && fi < cap && fj >= 0 && fj < g.fill_cap ? (int32_t)gload4(stack + fi) : -1;
         }
-        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t k = base + q * kBlock + threadIdx.x;
+            const bool is_miss = k < c.nm;
+            if (adm[q] && (uint32_t)slot[q] >= (uint32_t)cap) {
+                atomicOr(g.err, ERR_INTERNAL);
+                adm[q] = false;
+            }
+            if (!adm[q]) {
+                n_pdrop += k < items && inp[q] ? 1 : 0;
+                continue;
+            }
+            tb.slot_row[slot[q]] = row[q];
+            if (!ring) tb.slot_score[slot[q]] = sc[q];  // a ring's order holds its scores
+            // (the slot's touch stamp, of a forward before this placement, is
+            // older than any a later placement asks for)
+            tb.slot_flags[slot[q]] = inp[q] ? F_PF : 0u;
+            // the fill list: admitted row j of this table, its source and slot: a
+            // miss's staging row; a prefetch row's host row, or for a STAGED table
+            // the staged row of its candidate (the host gathered NP[ps + i] into
+            // row ps + i)
+            const int64_t fj = ts + ps + at[q];
+            g.fill_src[fj] = is_miss ? (int32_t)k : staged ? -(int32_t)(ps + (k - c.nm)) - 1 : -(row[q] + 1);
+            g.fill_slot[fj] = slot[q];
+            if (ring) {  // where ring.hip finds the admitted rows' slots
+                if (is_miss) g.mslot[ts + k] = slot[q];
+                else g.npslot[ps + (k - c.nm)] = slot[q];
+            }
+            dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[q]);
+            n_adm_miss += is_miss ? 1 : 0;
+        }
+        if (!reb) n_reuse += map_insert_n<Q>(tb, row, slot, adm);
+        __syncthreads();  // before s_base is set again
     }
-    const int a = block_sum(n_adm_miss, tmp), f = block_sum(n_fill, tmp);
-    const int pd = block_sum(n_pdrop, tmp), md = block_sum(n_mdrop, tmp), ru = block_sum(n_reuse, tmp);
-    const unsigned long long d = wave_sum64(dig);
-    if ((threadIdx.x & 63) == 0 && d) atomicAdd(&st.digest_acc, d);
+    const int a = block_sum(n_adm_miss, tmp), pd = block_sum(n_pdrop, tmp), ru = block_sum(n_reuse, tmp);
+    __shared__ unsigned long long s_dig[kBlock / 64];
+    const unsigned long long d = block_sum64(dig, s_dig);
     if (threadIdx.x == 0) {
+        if (d) atomicAdd(&st.digest_acc, d);
         if (a) atomicAdd(&st.adm_miss, a);
-        if (f) atomicAdd(&st.p_fill, f);
         if (pd) atomicAdd(&st.p_drop, pd);
-        if (md) atomicAdd(&st.m_drop, md);
-        if (ru) atomicSub(&st.tomb, ru);
+        if (ru) atomicAdd(&st.reused, ru);
     }
 }
 
@@ -476,13 +493,17 @@ __device__ __forceinline__ void publish_placement(const DGlobal &g, int t, int64
         fdesc[4 * t + 1] = st.popped;
         fdesc[4 * t + 2] = g.ftstart[t];
     }
-    int32_t n_res = st.n_res;
-    if (!tb.ways) {  // set-associative tables count residents as they place
-        const int32_t top = st.free_top - st.popped;  // popped stays: the fill may still read it
+    int32_t n_res = st.n_res, evicted = st.evicted, fill = st.p_fill, m_drop = st.m_drop;
+    const int32_t adm_miss = st.adm_miss;
+    if (!tb.ways) {  // set-associative tables count these as they place
+        const int32_t before = st.free_top, popped = st.popped, top = before - popped;  // popped stays: the fill reads it
+        evicted = before - st.free0;
+        fill = popped - adm_miss;
+        m_drop = st.plc_nm - adm_miss;
         st.free_top = top;
         n_res = tb.cap - top;
         st.n_res = n_res;
-        const int32_t tomb = st.rebuild ? 0 : st.tomb;
+        const int32_t tomb = st.rebuild ? 0 : st.tomb + evicted - st.reused;
         st.tomb = tomb;
         st.rebuild_next = (int64_t)tomb * 4 > (int64_t)tb.map_mask + 1 ? 1u : 0u;
     }
@@ -500,17 +521,20 @@ __device__ __forceinline__ void publish_placement(const DGlobal &g, int t, int64
         st.r_head = head;
         st.pend_n = st.pcount;
         st.pend_off = g.pstart[t];
-        if (st.r_valid + st.pend_keep != n_res || head > tb.ring_cap) atomicOr(g.err, ERR_INTERNAL);
+        const int32_t stale = (int32_t)(uint32_t)st.touched, run = (int32_t)(st.appended >> 32);
+        const int32_t valid = st.r_valid - stale - (evicted - st.z_evicted) + run;
+        st.r_valid = valid;
+        if (valid + (int32_t)(uint32_t)st.appended != n_res || head > tb.ring_cap) atomicOr(g.err, ERR_INTERNAL);
     }
     int64_t v[kPlcStats];
-    v[0] = st.evicted;
-    v[1] = st.adm_miss;
-    v[2] = st.p_fill;
+    v[0] = evicted;
+    v[1] = adm_miss;
+    v[2] = fill;
     v[3] = st.p_res;
     v[4] = st.p_drop;
-    v[5] = st.m_drop;
+    v[5] = m_drop;
     v[6] = n_res;
-    v[7] = (int64_t)st.p_fill * tb.row_bytes;
+    v[7] = (int64_t)fill * tb.row_bytes;
     v[8] = st.pcount;
     for (int k = 0; k < kPlcStats; ++k) {
         st.last[kFwdStats + k] = v[k];
@@ -665,23 +689,27 @@ void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, h
         k_plc_rank_small<<<g.T, kRankSmallThreads, 0, s>>>(g, p);
         return;
     }
-    // few blocks per table: each block merges its non-zero histogram bins
-    // into global memory
-#ifndef RECMG_RANK_IPT
-#define RECMG_RANK_IPT 32
-#endif
-    const dim3 grid(grid_for(item_bound, kBlock * RECMG_RANK_IPT, 512), g.T);
+    // few blocks per table, as each merges its non-zero histogram bins into
+    // global memory: 32 items per thread where that gives some 512 blocks in all,
+    // fewer items where it would leave the chip idle (13 tables of up to 60,000
+    // slots were 117 blocks)
+    const int64_t want = item_bound * g.T / (kBlock * 512) + 1;
+    const int ipt = (int)(want < 4 ? 4 : want > 32 ? 32 : want);
+    const dim3 grid(grid_for(item_bound, kBlock * ipt, 512), g.T);
     k_plc_update<<<grid, kBlock, 0, s>>>(g, p);
     for (int pass = 1; pass < p.passes; ++pass) k_plc_select<<<grid, kBlock, 0, s>>>(g, p, pass);
 }
 
 void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, int64_t item_bound, hipStream_t s) {
     const int last = rank_in_block(item_bound) ? -1 : p.passes - 1;
-    k_plc_evict<<<dim3(grid_for(max_cap, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g, p, last);
+    // each block picks the last digit for itself (2 us), so it takes four rounds
+    // of slots where there are that many
+    k_plc_evict<<<dim3(grid_for(max_cap, kBlock * (max_cap > 1 << 16 ? 16 : 4), 2048), g.T), kBlock, 0, s>>>(g, p, last);
 }
 
 void launch_plc_admit(const DGlobal &g, const PlcParams &p, int64_t cand_bound, hipStream_t s) {
-    k_plc_admit<<<dim3(grid_for(cand_bound, kBlock * items_per_thread(cand_bound, 4), 2048), g.T), kBlock, 0, s>>>(g, p);
+    if (cand_bound > kAdmitMany) k_plc_admit<4><<<dim3(grid_for(cand_bound, kBlock * 4, 2048), g.T), kBlock, 0, s>>>(g, p);
+    else k_plc_admit<1><<<dim3(grid_for(cand_bound, kBlock, 2048), g.T), kBlock, 0, s>>>(g, p);
 }
 
 void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStream_t s, hipEvent_t ev0,

@@ -109,24 +109,22 @@ struct DTable {
     int32_t ring_cap;   // entries per buffer (a multiple of kRingChunk); 0: ranked by radix select
 };
 
-// Mutable per-table state and counters, resident in the workspace.
+// Mutable per-table state and counters, resident in the workspace.  What many
+// blocks of a kernel add to lies apart from what they read, and each kernel's
+// counters on a line of their own: additions to one line queue (some 30 ns each),
+// and a read of that line waits in the same queue.
 struct TState {
-    int32_t ucount;   // distinct rows of the last forward (sorted in U)
-    int32_t mcount;   // misses of the last forward (in M, staged at the same index)
-    int32_t pcount;   // distinct prefetch rows of the current placement
-    int32_t npcount;  // prefetch rows neither resident nor missed (in NP)
-    int32_t n_res, free_top, popped, tomb;
+    // set by one thread or block at a time, read by many
+    alignas(128) int32_t ucount;  // distinct rows of the last forward (sorted in U)
+    int32_t pcount;    // distinct prefetch rows of the current placement
+    int32_t n_res, tomb;
     int32_t rebuild, sel_mode, free0, plc_nm;  // plc_nm: misses the current placement ranks;
                                                // free0: free_top as the placement began
-    uint64_t prefix;  // the threshold key that the radix select (or the ring's cut) found
+    uint32_t rebuild_next;  // rebuild of the next placement: deleted entries passed a quarter of the map
+    uint64_t prefix;        // the threshold key that the radix select (or the ring's cut) found
     // radix select: the prefix and the keys still wanted after each pass
     uint64_t pass_prefix[kMaxPasses];
     int32_t pass_need[kMaxPasses];
-    uint32_t rebuild_next;  // rebuild of the next placement: deleted entries passed a quarter of the map
-    int32_t covered;  // accumulator: distinct prefetch rows of the last placement found in this batch
-    // accumulators of the call in flight
-    int32_t hits, hits_pf, p_res, evicted, adm_miss, p_fill, p_drop, m_drop;
-    unsigned long long digest_acc;
     // resident ring (ring_cap > 0): live entries lie in [r_tail, r_head) of
     // buffer r_buf; r_valid of them are live; this placement evicts the live
     // ones in [r_tail, r_cut).  The rows the last placement's prefetch named
@@ -134,10 +132,27 @@ struct TState {
     // [pend_off, + pend_n) of pend_row / pend_slot[pend_buf], until a placement
     // merges them into the ring with the rows the last batch touched.
     int32_t r_head, r_tail, r_cut, r_valid, r_buf, r_compact, r_zevict, r_moved;
-    int32_t z1_len, z1_keys, pend_n, pend_buf, pend_keep;
+    int32_t z1_len, pend_n, pend_buf;
     int64_t pend_off;
+    // reservations
+    alignas(128) int32_t mcount;   // misses of the last forward (in M, staged at the same index)
+    alignas(128) int32_t npcount;  // prefetch rows neither resident nor missed (in NP)
+    alignas(128) int32_t free_top; // entries of the free stack (evictions push; admissions pop at the end)
+    alignas(128) int32_t popped;   // slots the current placement has taken from it
+    // accumulators of the call in flight
+    alignas(128) int32_t hits;
+    int32_t hits_pf;
+    int32_t covered;  // distinct prefetch rows of the last placement found in this batch
+    alignas(128) unsigned long long touched;   // ring: (keys of Z1) << 32 | entries gone stale
+    alignas(128) unsigned long long appended;  // ring: (entries appended) << 32 | pending rows kept
+    alignas(128) unsigned long long digest_acc;
+    int32_t p_res, adm_miss, p_drop;  // prefetch rows resident; misses admitted; prefetch rows dropped
+    int32_t reused;     // deleted map entries taken by inserts
+    int32_t z_evicted;  // ring: residents evicted from Z1 and Z2, which have no ring entry
+    // set-associative tables' counts (k_sa_sum, k_plc_end)
+    int32_t evicted, p_fill, m_drop;
     // published counters, in recmg_table_stats_t order
-    int64_t last[kNumStats];
+    alignas(128) int64_t last[kNumStats];
     unsigned long long digest;
     int64_t total[kNumStats];
 };
@@ -524,6 +539,19 @@ __device__ __forceinline__ int wave_sum(int v) {
     return v;
 }
 
+// Sum over the block, in thread 0 (tmp: __shared__, blockDim.x / 64 entries).
+// Every thread calls.
+__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v);
+__device__ __forceinline__ unsigned long long block_sum64(unsigned long long v, unsigned long long *tmp) {
+    v = wave_sum64(v);
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
+    __syncthreads();
+    unsigned long long s = 0;
+    if (threadIdx.x == 0)
+        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += tmp[k];
+    return s;
+}
+
 __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -708,8 +736,10 @@ __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const in
     st.p_fill = 0;
     st.p_drop = 0;
     st.m_drop = 0;
-    st.z1_keys = 0;
-    st.pend_keep = 0;
+    st.reused = 0;
+    st.z_evicted = 0;
+    st.touched = 0;
+    st.appended = 0;
     // set-associative tables and resident rings update the digest by the rows
     // that come and go
     st.digest_acc = (g.tabs[t].ways || g.tabs[t].ring_cap) ? st.digest : 0ull;

@@ -44,11 +44,29 @@ namespace recmg {
 
 constexpr int kRingEvictBuf = 2048;
 
-// First index of a[0, n) (ascending) holding a value >= v, or > v if upper.
-__device__ __forceinline__ int32_t ring_bound(const int32_t *a, int32_t n, int32_t v, bool upper) {
-    int32_t lo = 0, hi = n;
+// Merging two ascending lists A and B (an element of A goes before an equal one
+// of B): how many of the first d merged elements are A's.  By one wave: 64
+// probes per step, so three or four dependent loads where a binary search makes
+// eighteen.  Every lane calls and gets the result.
+__device__ __forceinline__ int32_t merge_split(const int32_t *A, int32_t na, const int32_t *B, int32_t nb, int32_t d) {
+    int32_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+    const int lane = threadIdx.x & 63;
+    while (lo < hi) {  // the answer is in [lo, hi]: the first a with A[a] > B[d - 1 - a], or hi
+        const int32_t a = lo + (int32_t)(((int64_t)(hi - lo) * lane) >> 6);
+        const bool more = (int32_t)gload4(A + a) <= (int32_t)gload4(B + (d - 1 - a));  // true up to the answer
+        const int c = __popcll(__ballot(more));
+        const int32_t last = __shfl(a, c > 0 ? c - 1 : 0), next = __shfl(a, c < 64 ? c : 63);
+        if (c < 64) hi = next;
+        if (c > 0) lo = last + 1;
+    }
+    return lo;
+}
+
+// First index of the LDS list a[0, n) (ascending) holding a value >= v, or > v if upper.
+__device__ __forceinline__ int lds_bound(const int32_t *a, int n, int32_t v, bool upper) {
+    int lo = 0, hi = n;
     while (lo < hi) {
-        const int32_t mid = (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
+        const int mid = (lo + hi) >> 1;
         const int32_t x = a[mid];
         if (x < v || (upper && x == v)) lo = mid + 1;
         else hi = mid;
@@ -62,7 +80,11 @@ __device__ __forceinline__ int32_t ring_bound(const int32_t *a, int32_t n, int32
 //    below it), U entry u at u + (pending rows at or below it), so a row in
 //    both (a pending row the batch touched) takes two places, the pending one
 //    a hole.  A key is a pending row neither touched nor named again, a hit or
-//    miss the list does not name (F_INP, set by classification).
+//    miss the list does not name (F_INP, set by classification).  A block takes
+//    tiles of kTile merged entries: the tile's ends in both lists by
+//    merge_split, its rows into LDS, where each finds its place.  (A binary
+//    search in the other list for every row was bound by the number of loads
+//    in flight: 102 us on 290,000 + 170,000 rows in each of 4 tables.)
 //  * new scores: hits take the touch score, or pscore if the list names them
 //    (and lose F_PF); the list's untouched residents take pscore.  So their ring
 //    entries go stale (slot_pos = -1).  F_INP stays until the append.
@@ -70,8 +92,11 @@ __device__ __forceinline__ int32_t ring_bound(const int32_t *a, int32_t n, int32
 // A thread reads a pending row's flags only if the batch did not touch it,
 // and only hit threads write flags (of touched slots), so the reads see
 // settled values.
+constexpr int kTileQ = 4, kTile = kTileQ * kBlock;
 __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
     if (*g.err) return;
+    __shared__ int32_t s_row[kTile];  // the tile's pending rows, then its U rows
+    __shared__ int32_t s_split[2];
     __shared__ int tmp[16];
     const int t = blockIdx.y;
     const DTable &tb = g.tabs[t];
@@ -81,59 +106,111 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
     const int32_t nu = p.have_fwd ? st.ucount : 0, pn = st.pend_n;
     const int32_t *prow = g.pend_row[st.pend_buf] + st.pend_off;
     const int32_t *pslot = g.pend_slot[st.pend_buf] + st.pend_off;
-    const int32_t *urow = g.U + ts;
+    const int32_t *urow = g.U + ts, *uslot = g.slotU + ts;
     int32_t *rcnt = tb.rcnt[st.r_buf];
     int2 *z = ring_zone(g, st, t);
-    const int32_t n1 = pn + nu, n = n1 + st.pcount;
+    const int32_t n1 = pn + nu, np = st.pcount;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.z1_len = n1;
+    const int32_t *touch = tb.slot_touch, *pos = tb.slot_pos;
+    const int32_t cap = tb.cap;
+    const int tid = threadIdx.x, wave = tid >> 6;
     int keys = 0, stale = 0;
-    for (int32_t j0 = (int32_t)(blockIdx.x * blockDim.x); j0 < n; j0 += (int32_t)(gridDim.x * blockDim.x)) {  // block-uniform
-        const int32_t j = j0 + (int32_t)threadIdx.x;
-        int32_t sl = -1;  // a resident whose score changes (the ring's order holds the scores, no slot does)
-        if (j < n1) {
-            int32_t row, at, ref = kRingHole;
-            if (j < pn) {
-                row = prow[j];
-                const int32_t q = pslot[j];
-                at = j + ring_bound(urow, nu, row, false);
-                if (q >= 0 && q < tb.cap && tb.slot_touch[q] != p.last_stamp && !(tb.slot_flags[q] & F_INP)) ref = q;
+    // the ring entries e of slots sl (-1: none) go stale; every lane of the wave calls
+    auto unring = [&](const int32_t (&sl)[kTileQ], const int32_t (&e)[kTileQ]) {
+#pragma unroll
+        for (int q = 0; q < kTileQ; ++q) {
+            if (e[q] >= 0) {  // pending rows have no ring entry
+                tb.slot_pos[sl[q]] = -1;
+                ++stale;
+            }
+            chunk_sub(e[q] >= 0, e[q] / kRingChunk, rcnt);
+        }
+    };
+    const int32_t tiles1 = (n1 + kTile - 1) / kTile, tiles = tiles1 + (np + kTile - 1) / kTile;
+    for (int32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {  // block-uniform
+        int32_t sl[kTileQ], e[kTileQ];  // residents whose score changes, their ring entries
+        if (tile >= tiles1) {           // the prefetch list's residents
+            const int32_t i0 = (tile - tiles1) * kTile;
+            int32_t tch[kTileQ];
+#pragma unroll
+            for (int q = 0; q < kTileQ; ++q) {
+                const int32_t i = i0 + q * kBlock + tid;
+                sl[q] = i < np ? (int32_t)gload4(g.puref + ps + i) : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < kTileQ; ++q) {
+                tch[q] = sl[q] >= 0 ? (int32_t)gload4(touch + sl[q]) : 0;
+                e[q] = sl[q] >= 0 ? (int32_t)gload4(pos + sl[q]) : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < kTileQ; ++q)
+                if (tch[q] == p.last_stamp) e[q] = -1;  // touched: its hit entry takes care of it
+            unring(sl, e);
+            continue;
+        }
+        const int32_t d0 = tile * kTile, d1 = d0 + kTile < n1 ? d0 + kTile : n1;
+        if (wave < 2) {
+            const int32_t a = merge_split(prow, pn, urow, nu, wave == 0 ? d0 : d1);
+            if ((tid & 63) == 0) s_split[wave] = a;
+        }
+        __syncthreads();
+        const int32_t a0 = s_split[0], na = s_split[1] - a0, b0 = d0 - a0, nt = d1 - d0;  // na pending, nt - na of U
+        int32_t row[kTileQ], ref[kTileQ];
+        uint32_t f[kTileQ], mf[kTileQ];
+        int32_t tch[kTileQ];
+#pragma unroll
+        for (int q = 0; q < kTileQ; ++q) {
+            const int32_t k = q * kBlock + tid;
+            row[q] = 0, ref[q] = -1;
+            if (k < na) {
+                row[q] = (int32_t)gload4(prow + a0 + k);
+                ref[q] = (int32_t)gload4(pslot + a0 + k);
+                if (ref[q] >= cap) ref[q] = -1;
+            } else if (k < nt) {
+                row[q] = (int32_t)gload4(urow + b0 + (k - na));
+                ref[q] = (int32_t)gload4(uslot + b0 + (k - na));
+            }
+            if (k < nt) s_row[k] = row[q];
+        }
+#pragma unroll
+        for (int q = 0; q < kTileQ; ++q) {
+            const int32_t k = q * kBlock + tid;
+            const bool slot = k < nt && ref[q] >= 0, hit = slot && k >= na, miss = k >= na && k < nt && !slot;
+            f[q] = slot ? gload4(tb.slot_flags + ref[q]) : 0u;
+            tch[q] = slot && k < na ? (int32_t)gload4(touch + ref[q]) : 0;
+            mf[q] = miss ? gload4(g.mflags + ts + (-ref[q] - 1)) : 0u;
+            sl[q] = hit ? ref[q] : -1;
+            e[q] = hit ? (int32_t)gload4(pos + ref[q]) : -1;
+        }
+        __syncthreads();  // the tile's rows are in LDS
+#pragma unroll
+        for (int q = 0; q < kTileQ; ++q) {
+            const int32_t k = q * kBlock + tid;
+            if (k >= nt) continue;
+            int32_t at, zr = kRingHole;
+            if (k < na) {
+                at = d0 + k + lds_bound(s_row + na, nt - na, row[q], false);
+                if (ref[q] >= 0 && tch[q] != p.last_stamp && !(f[q] & F_INP)) zr = ref[q];
             } else {
-                const int32_t u = j - pn;
-                row = urow[u];
-                const int32_t h = g.slotU[ts + u];
-                at = u + ring_bound(prow, pn, row, true);
-                if (h >= 0) {
-                    const uint32_t f = tb.slot_flags[h];
-                    const bool inp = (f & F_INP) != 0;
-                    if (!inp) ref = h;
-                    sl = h;
-                    if (f & F_PF) tb.slot_flags[h] = f & ~F_PF;
+                at = d0 + (k - na) + lds_bound(s_row, na, row[q], true);
+                if (ref[q] >= 0) {
+                    if (!(f[q] & F_INP)) zr = ref[q];
+                    if (f[q] & F_PF) tb.slot_flags[ref[q]] = f[q] & ~F_PF;
                 } else {
-                    const int32_t m = -h - 1;
-                    const bool inp = (g.mflags[ts + m] & F_INP) != 0;
+                    const int32_t m = -ref[q] - 1;
+                    const bool inp = (mf[q] & F_INP) != 0;
                     g.mscore[ts + m] = inp ? p.pscore : p.lru_touch;
-                    if (!inp) ref = ring_ref_miss(m);
+                    if (!inp) zr = ring_ref_miss(m);
                 }
             }
-            z[at] = make_int2(ref, row);
-            keys += ref != kRingHole ? 1 : 0;
-        } else if (j < n) {
-            const int32_t v = g.puref[ps + (j - n1)];
-            if (v >= 0 && tb.slot_touch[v] != p.last_stamp) sl = v;  // touched: its hit entry took care of it
+            z[at] = make_int2(zr, row[q]);
+            keys += zr != kRingHole ? 1 : 0;
         }
-        int32_t e = -1;
-        if (sl >= 0) e = tb.slot_pos[sl];
-        if (e >= 0) {  // pending rows have no ring entry
-            tb.slot_pos[sl] = -1;
-            ++stale;
-        }
-        chunk_sub(e >= 0, e / kRingChunk, rcnt);
+        unring(sl, e);
+        __syncthreads();  // before the next tile's rows take the LDS
     }
     const int k = block_sum(keys, tmp), ns = block_sum(stale, tmp);
-    if (threadIdx.x == 0) {
-        if (k) atomicAdd(&st.z1_keys, k);
-        if (ns) atomicSub(&st.r_valid, ns);
-    }
+    if (threadIdx.x == 0 && (k | ns)) atomicAdd(&st.touched, ((unsigned long long)k << 32) | (uint32_t)ns);
 }
 
 // One block per table: ring_cut, kept in the table's state for the kernels
@@ -146,7 +223,8 @@ __global__ void __launch_bounds__(kRingThreads) k_ring_cut(DGlobal g, PlcParams 
     if (!tb.ring_cap) return;
     TState &st = g.st[t];
     const Counts c = table_counts(tb, st, p);
-    const RingCut o = ring_cut(g, p, t, tb, st, c, st.r_valid, st.z1_keys, st.z1_len, st.pcount, tmp);
+    const int32_t nold = st.r_valid - (int32_t)(uint32_t)st.touched, z1 = (int32_t)(st.touched >> 32);
+    const RingCut o = ring_cut(g, p, t, tb, st, c, nold, z1, st.z1_len, st.pcount, tmp);
     if (threadIdx.x == 0) {
         if (o.bad) atomicOr(g.err, ERR_INTERNAL);
         st.sel_mode = o.mode;
@@ -196,20 +274,23 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
     if (reb) map_clear_share(tb, blockIdx.x, gridDim.x);
     int nev = 0, nring = 0;
     unsigned long long dig = 0;
-    // frees slot sl (when ev) and lists it; every lane of the wave calls
-    auto evict = [&](bool ev, int32_t sl) {
-        if (ev) {  // its row and flags: k_ring_append, unless an admitted row takes the slot
-            const int32_t row = tb.slot_row[sl];
-            if (!reb) map_delete(tb, row);
-            tb.slot_pos[sl] = -1;
-            dig += mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)row);
+    // frees Q slots sl of rows r (where ev) and lists them; every lane of the wave
+    // calls.  A slot's row and flags: k_ring_append, unless an admitted row takes it.
+    constexpr int Q = 4;
+    auto evict = [&](const bool (&ev)[Q], const int32_t (&sl)[Q], const int32_t (&r)[Q]) {
+        if (!reb) map_delete_n<Q>(tb, r, ev);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint64_t m = __ballot(ev[q]);
+            int wb = 0;
+            if (lane == 0 && m) wb = atomicAdd(&s_n, __popcll(m));
+            wb = __shfl(wb, 0);
+            if (!ev[q]) continue;
+            tb.slot_pos[sl[q]] = -1;
+            dig += mix64(((unsigned long long)t << 40) | (unsigned long long)(uint32_t)r[q]);
             ++nev;
+            s_free[wb + __popcll(m & ((1ull << lane) - 1ull))] = sl[q];
         }
-        const uint64_t m = __ballot(ev);
-        int wb = 0;
-        if (lane == 0 && m) wb = atomicAdd(&s_n, __popcll(m));
-        wb = __shfl(wb, 0);
-        if (ev) s_free[wb + __popcll(m & ((1ull << lane) - 1ull))] = sl;
     };
     const int32_t tail = st.r_tail, cut = st.r_cut, head = st.r_head, moved = st.r_moved;
     const bool compact = st.r_compact != 0;
@@ -223,19 +304,26 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
     for (int32_t ch = tail / kRingChunk + (int32_t)blockIdx.x; ch < hi; ch += (int32_t)gridDim.x) {
         const int32_t e0 = ch * kRingChunk + 4 * (int32_t)threadIdx.x;
         const uint4 v = gload16(ring + e0);
-        const int32_t sl[4] = {(int32_t)v.x, (int32_t)v.y, (int32_t)v.z, (int32_t)v.w};
-        bool mv[4];
+        const int32_t sl[Q] = {(int32_t)v.x, (int32_t)v.y, (int32_t)v.z, (int32_t)v.w};
+        bool mv[Q], ev[Q];
+        int32_t r[Q], ps[Q];
         int here = 0, nmv = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < Q; ++i) {  // eight loads in flight
+            const bool ok = sl[i] >= 0 && sl[i] < tb.cap;
+            ps[i] = ok ? (int32_t)gload4(tb.slot_pos + sl[i]) : -1;
+            r[i] = ok ? (int32_t)gload4(tb.slot_row + sl[i]) : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
             const int32_t e = e0 + i;
-            const bool live = e >= tail && e < head && ring_live(tb, sl[i], e);
-            const bool ev = live && e < cut;
-            mv[i] = live && !ev && compact;
-            evict(ev, sl[i]);
-            here += ev ? 1 : 0;
+            const bool live = e >= tail && e < head && ps[i] == e;
+            ev[i] = live && e < cut;
+            mv[i] = live && !ev[i] && compact;
+            here += ev[i] ? 1 : 0;
             nmv += mv[i] ? 1 : 0;
         }
+        evict(ev, sl, r);
         int tot;
         const int ex = block_excl_scan(nmv, tmp, &tot);
         if (tot) {  // block-uniform; chunks with movers lie at or after the cut's
@@ -266,32 +354,37 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
         const int2 *z = ring_zone(g, st, t);
         const int64_t ps = g.pstart[t];
         const int32_t n1 = st.z1_len, n = n1 + st.pcount;
-        for (int32_t base = (int32_t)(blockIdx.x * blockDim.x); base < n; base += (int32_t)(gridDim.x * blockDim.x)) {
-            const int32_t k = base + (int32_t)threadIdx.x;
-            int32_t sl = -1;
-            if (k < n1) {
-                const int2 zr = z[k];
-                if (zr.x >= 0 && !kept(mode, make_key(p.lru_touch, zr.y, p.rowbits), thr)) sl = zr.x;
-            } else if (k < n) {
-                const int32_t v = g.puref[ps + (k - n1)];
-                if (v >= 0 && !kept(mode, make_key(p.pscore, g.PU[ps + (k - n1)], p.rowbits), thr)) sl = v;
+        for (int32_t base = (int32_t)(blockIdx.x * blockDim.x) * Q; base < n; base += (int32_t)(gridDim.x * blockDim.x) * Q) {
+            int32_t sl[Q], r[Q];
+            bool ev[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int32_t k = base + q * kBlock + (int32_t)threadIdx.x;
+                sl[q] = -1, r[q] = 0;
+                if (k < n1) {
+                    const int2 zr = z[k];
+                    r[q] = zr.y;
+                    if (zr.x >= 0 && !kept(mode, make_key(p.lru_touch, zr.y, p.rowbits), thr)) sl[q] = zr.x;
+                } else if (k < n) {
+                    const int32_t v = g.puref[ps + (k - n1)];
+                    r[q] = g.PU[ps + (k - n1)];
+                    if (v >= 0 && !kept(mode, make_key(p.pscore, r[q], p.rowbits), thr)) sl[q] = v;
+                }
+                ev[q] = sl[q] >= 0;
             }
-            evict(sl >= 0, sl);
+            evict(ev, sl, r);
             __syncthreads();
-            if (s_n > kRingEvictBuf - (int)blockDim.x) flush();
+            if (s_n > kRingEvictBuf - Q * (int)blockDim.x) flush();
         }
     }
     __syncthreads();
     flush();
     const int e = block_sum(nev, tmp), er = block_sum(nring, tmp);
-    const unsigned long long d = wave_sum64(dig);
-    if (lane == 0 && d) atomicAdd(&st.digest_acc, 0ull - d);
+    __shared__ unsigned long long s_dig[kBlock / 64];
+    const unsigned long long d = block_sum64(dig, s_dig);
     if (threadIdx.x == 0) {
-        if (e) {
-            atomicAdd(&st.evicted, e);
-            if (!reb) atomicAdd(&st.tomb, e);
-        }
-        if (er) atomicSub(&st.r_valid, er);
+        if (d) atomicAdd(&st.digest_acc, 0ull - d);
+        if (e != er) atomicAdd(&st.z_evicted, e - er);
     }
 }
 
@@ -326,8 +419,8 @@ __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, 
         }
     }
     const int2 *z = ring_zone(g, st, t);
+    int added = 0;
     if (n1 > 0) {
-        int added = 0;
         const int32_t c1 = (head + n1 - 1) / kRingChunk;
         for (int32_t ch = head / kRingChunk + (int32_t)blockIdx.x; ch <= c1; ch += (int32_t)gridDim.x) {
             int add = 0;
@@ -353,7 +446,6 @@ __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, 
             if (threadIdx.x == 0 && an) atomicAdd(&tb.rcnt[buf][ch], an);
             added += an;
         }
-        if (threadIdx.x == 0 && added) atomicAdd(&st.r_valid, added);
     }
     // slots freed and not taken again (the free stack's new entries below its
     // new top); in a full cache in steady state there are none
@@ -381,7 +473,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, 
         keepn += sl >= 0 ? 1 : 0;
     }
     const int kn = block_sum(keepn, tmp);
-    if (threadIdx.x == 0 && kn) atomicAdd(&st.pend_keep, kn);
+    if (threadIdx.x == 0 && (kn | added)) atomicAdd(&st.appended, ((unsigned long long)added << 32) | (uint32_t)kn);
     if (blockIdx.x == 0 && threadIdx.x == 0) st.pend_buf = wr;
 }
 
@@ -395,14 +487,14 @@ static inline unsigned ring_grid(int64_t n, int per_block, unsigned cap) {
 }
 
 void launch_ring_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, hipStream_t s) {
-    k_ring_touch<<<dim3(ring_grid(item_bound, kBlock * items_per_thread(item_bound, 4), 1024), g.T), kBlock, 0, s>>>(g, p);
+    k_ring_touch<<<dim3(ring_grid(item_bound, kTile, 1024), g.T), kBlock, 0, s>>>(g, p);
     k_ring_cut<<<g.T, kRingThreads, 0, s>>>(g, p);
 }
 
 void launch_ring_evict(const DGlobal &g, const PlcParams &p, int64_t item_bound, int32_t ring_chunks, hipStream_t s) {
     // the cut is typically a few chunks past the front; a compaction walks
     // every chunk, so blocks loop
-    const unsigned gx = std::max(ring_grid(item_bound, kBlock * 4, 256), ring_grid(ring_chunks, 64, 256));
+    const unsigned gx = std::max(ring_grid(item_bound, kBlock * 4, 512), ring_grid(ring_chunks, 64, 256));
     k_ring_evict<<<dim3(gx, g.T), kBlock, 0, s>>>(g, p);
 }
 

@@ -300,7 +300,7 @@ template <int NB>
 __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParams p, const int32_t *__restrict__ rows,
                                                              const int64_t *__restrict__ poff, int64_t np,
                                                              const uint8_t *__restrict__ bits, int wr) {
-    enum { C_PRES, C_NP, C_STALE, C_EV, C_RING_EV, C_POP, C_ADM, C_FILL, C_PDROP, C_MDROP, C_REUSE, C_RUN, C_KEEP, C_N };
+    enum { C_PRES, C_NP, C_STALE, C_EV, C_RING_EV, C_POP, C_ADM, C_PDROP, C_REUSE, C_RUN, C_KEEP, C_N };
     __shared__ LdsBitmap<NB> bm, bz;  // the rows of P; the rows of Z1 (or the ranking's histogram)
     __shared__ int tmp[16];
     constexpr int Q = 4;  // items per thread whose loads are in flight together
@@ -395,6 +395,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         if (tid == 0) {
             st.pcount = pc;
             st.npcount = st.popped = st.p_res = st.evicted = st.adm_miss = st.p_fill = st.p_drop = st.m_drop = 0;
+            st.rebuild = 0;
             st.digest_acc = st.digest;
         }
         return;
@@ -466,7 +467,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     int32_t mode = c.mode;
     uint64_t thr = 0;
     RingCut cut{};
-    int32_t z1 = 0, r_valid = 0;
+    int32_t z1 = 0;
     int2 *z = nullptr;
     if (!ring) {
         // ---- scores of every slot and candidate, the threshold, eviction
@@ -572,8 +573,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         }
         __syncthreads();
         // ---- the cut, eviction from the ring's front, compaction
-        r_valid = st.r_valid - s_c[C_STALE];
-        cut = ring_cut(g, p, t, tb, st, c, r_valid, z1, z1, pc, tmp);
+        cut = ring_cut(g, p, t, tb, st, c, st.r_valid - s_c[C_STALE], z1, z1, pc, tmp);
         if (cut.bad) {  // block-uniform; never expected
             if (tid == 0) atomicOr(g.err, ERR_INTERNAL);
             return;
@@ -676,7 +676,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     // ---- admission
     const int32_t nev = s_c[C_EV], top = top0 + nev;
     const int32_t items = c.nm + c.nnp;
-    int n_adm = 0, n_fill = 0, n_pdrop = 0, n_mdrop = 0, n_reuse = 0;
+    int n_adm = 0, n_pdrop = 0, n_reuse = 0;
     for (int32_t b0 = 0; b0 < items; b0 += Q * kSmallThreads) {  // block-uniform
         int32_t row[Q], sc[Q], slot[Q], at[Q];
         bool adm[Q], inp[Q];
@@ -715,7 +715,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
                 adm[q] = false;
             }
             if (!adm[q]) {
-                n_mdrop += is_miss ? 1 : 0;
                 n_pdrop += k < items && inp[q] ? 1 : 0;
                 continue;
             }
@@ -732,15 +731,12 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
                 else g.npslot[lo + (k - c.nm)] = slot[q];
             }
             dig += mix64(((unsigned long long)t << 40) | (unsigned long long)row[q]);
-            if (is_miss) ++n_adm;
-            else ++n_fill;
+            n_adm += is_miss ? 1 : 0;
         }
         if (!reb) n_reuse += map_insert_n<Q>(tb, row, slot, adm);
     }
     lds_sum(n_adm, &s_c[C_ADM]);
-    lds_sum(n_fill, &s_c[C_FILL]);
     lds_sum(n_pdrop, &s_c[C_PDROP]);
-    lds_sum(n_mdrop, &s_c[C_MDROP]);
     lds_sum(n_reuse, &s_c[C_REUSE]);
     dig = wave_sum64(dig);
     if ((tid & 63) == 0 && dig) atomicAdd(&s_dig, dig);
@@ -806,22 +802,22 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         st.npcount = c.nnp;
         st.popped = s_c[C_POP];
         st.p_res = s_c[C_PRES];
-        st.evicted = nev;
         st.adm_miss = s_c[C_ADM];
-        st.p_fill = s_c[C_FILL];
         st.p_drop = s_c[C_PDROP];
-        st.m_drop = s_c[C_MDROP];
+        st.plc_nm = nm;
+        st.free0 = top0;
         st.free_top = top;
         st.rebuild = reb ? 1 : 0;
-        if (!reb) st.tomb += nev - s_c[C_REUSE];
+        st.reused = s_c[C_REUSE];
         st.digest_acc = (ring ? st.digest : 0ull) + s_dig;
         if (ring) {
-            st.r_valid = r_valid - s_c[C_RING_EV] + s_c[C_RUN];
+            st.touched = (uint32_t)s_c[C_STALE];
+            st.z_evicted = nev - s_c[C_RING_EV];
+            st.appended = ((unsigned long long)s_c[C_RUN] << 32) | (uint32_t)s_c[C_KEEP];
             st.r_cut = cut.cut;
             st.r_compact = cut.compact ? 1 : 0;
             st.r_moved = cut.moved;
             st.z1_len = z1;
-            st.pend_keep = s_c[C_KEEP];
             st.pend_buf = wr;
         }
     }
