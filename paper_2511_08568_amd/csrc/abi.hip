@@ -80,6 +80,8 @@ struct Layout {
     size_t staging[2] = {0, 0};
     int64_t stage_stride = 0, sum_cap = 0;
     int32_t total_bm_blocks = 0;
+    int32_t mark_parts = 1;
+    size_t part_bm = 0;
 };
 
 int32_t check_config(const recmg_config_t *cfg, std::vector<Geom> *geo) {
@@ -261,6 +263,18 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
         L->pend_row[k] = take(any_ring ? 4 * mp : 0);
         L->pend_slot[k] = take(any_ring ? 4 * mp : 0);
     }
+    // parts that many ids may be marked in: as many as keep all slices' blocks
+    // on the chip at once (dedup.hip)
+    int64_t slices = 0;
+    bool all_owned = true;
+    for (const Geom &g : geo) {
+        all_owned = all_owned && owns_bitmap(g.bm_nblk);
+        slices += (g.bm_nblk + kOwnSliceBlocks - 1) / kOwnSliceBlocks;
+    }
+    if (all_owned) L->mark_parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMarkMaxParts, kMarkBlocks / slices));
+    const bool many = std::max(cfg->max_indices, cfg->max_prefetch) / T >= kMarkSplitIds;
+    if (!many) L->mark_parts = 1;
+    L->part_bm = take(L->mark_parts > 1 ? (size_t)L->mark_parts * L->total_bm_blocks * kWordsPerBlock * 4 : 0);
     L->staging[0] = take(mi * (size_t)L->stage_stride);
     L->staging[1] = take(mi * (size_t)L->stage_stride);
     const bool staged = any_staged(geo);
@@ -900,6 +914,8 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     g.total_bm_blocks = L.total_bm_blocks;
     g.own_tables = 0;
     g.own_slices = 0;
+    g.mark_parts = L.mark_parts;
+    g.part_bm = reinterpret_cast<uint32_t *>(ws + L.part_bm);
     g.stat_log = reinterpret_cast<int64_t *>(ws + L.stat_log);
     g.sa_bstart = reinterpret_cast<int32_t *>(ws + L.sa_bstart);
     g.sa_btab = reinterpret_cast<int32_t *>(ws + L.sa_btab);

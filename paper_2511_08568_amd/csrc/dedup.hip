@@ -27,6 +27,8 @@
 // block instead of one per occurrence.  A bitmap word there is shared by blocks
 // on every XCD, so that atomic (and the load before it) is served past the
 // XCD's L2, a cache line per distinct id and block.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace recmg {
@@ -107,8 +109,10 @@ static_assert(kOwnSliceBlocks <= kOwnThreads && kOwnSliceWords % kWordsPerBlock 
 // block whose own range is malformed raises the error and reads no id; range
 // errors of ids are raised by slice 0 only.
 // A block reads its ids 16 bytes per lane, four loads in flight, with 32-bit
-// offsets: on 26 tables of 123,000 ids each (one slice per table, so 26 blocks)
-// it is bound by the instructions per id on those CUs.
+// offsets.  It is bound by the instructions and LDS accesses per id of its CU
+// (26 us for 123,000 ids), so many ids are split over parts: a part's block
+// writes all of its slice's words to its own copy (part_bm), and k_bm_merge puts
+// the copies together and counts them.
 template <int MODE>
 __global__ void __launch_bounds__(kOwnThreads) k_mark_own(DGlobal g, const int32_t *__restrict__ keys,
                                                           const int64_t *__restrict__ offs, int32_t B, int64_t n,
@@ -116,16 +120,16 @@ __global__ void __launch_bounds__(kOwnThreads) k_mark_own(DGlobal g, const int32
     __shared__ uint4 s_bm[kOwnSliceWords / 4];
     __shared__ int s_cnt[kOwnSliceBlocks];
     __shared__ int s_err;
-    const int t = blockIdx.y, sl = blockIdx.x;
+    const int t = blockIdx.y, sl = blockIdx.x, part = blockIdx.z, parts = gridDim.z;
     const DTable &tb = g.tabs[t];
     const int nblk = tb.bm_nblk;
     const bool mark = owns_bitmap(nblk) && sl * kOwnSliceBlocks < nblk;  // block-uniform
-    if (!mark && sl) return;
+    if (!mark && (sl || part)) return;
     // the error word is read once: another block may set it meanwhile, and the
     // waves of the block must agree before its barriers
     if (threadIdx.x == 0) s_err = *g.err;
     const int64_t lo = offs[(int64_t)t * B], hi = offs[(int64_t)(t + 1) * B];
-    if (sl == 0) {
+    if (sl == 0 && part == 0) {
         if (MODE == EMIT_FORWARD) forward_prep(g, t, offs, B, n);
         else placement_prep(g, t, offs, n, have_fwd);
     }
@@ -151,8 +155,9 @@ __global__ void __launch_bounds__(kOwnThreads) k_mark_own(DGlobal g, const int32
         if (!(bm[w] & bit)) atomicOr(&bm[w], bit);
     };
     // ids before the first 16-byte boundary, whole 16-byte groups, the rest
-    const uint32_t cnt = (uint32_t)(hi - lo);
-    const int32_t *ids = keys + lo;
+    const int64_t plo = lo + (hi - lo) * part / parts, phi = lo + (hi - lo) * (part + 1) / parts;
+    const uint32_t cnt = (uint32_t)(phi - plo);
+    const int32_t *ids = keys + plo;
     uint32_t head = (uint32_t)((16 - (reinterpret_cast<uintptr_t>(ids) & 15)) & 15) / 4;
     if (head > cnt) head = cnt;
     const uint32_t nv = (cnt - head) / 4, tail0 = head + 4 * nv;
@@ -175,6 +180,13 @@ __global__ void __launch_bounds__(kOwnThreads) k_mark_own(DGlobal g, const int32
     if (threadIdx.x < rest) mark_id((uint32_t)ids[threadIdx.x < head ? threadIdx.x : tail0 + threadIdx.x - head]);
     if (bad && sl == 0) atomicOr(g.err, ERR_RANGE);
     __syncthreads();
+    if (parts > 1) {  // block-uniform
+        const int64_t words = (int64_t)g.total_bm_blocks * kWordsPerBlock;
+        uint4 *dst = reinterpret_cast<uint4 *>(g.part_bm + part * words + (int64_t)tb.bm_block0 * kWordsPerBlock +
+                                               (int64_t)sl * kOwnSliceWords);
+        for (int k = threadIdx.x; k < nq; k += kOwnThreads) dst[k] = s_bm[k];
+        return;
+    }
     uint4 *gbm = reinterpret_cast<uint4 *>(tb.bitmap + (int64_t)sl * kOwnSliceWords);
     for (int k = threadIdx.x; k < nq; k += kOwnThreads) {
         const uint4 v = s_bm[k];
@@ -221,6 +233,29 @@ __global__ void __launch_bounds__(kBlock) k_bm_count(DGlobal g) {
     const uint4 w = *reinterpret_cast<const uint4 *>(tb.bitmap + w0);
     const int c = __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w);
     const int s = block_sum(c, tmp);
+    if (threadIdx.x == 0) g.blocksum[blk] = s;
+}
+
+// The parts' copies of a bitmap block put together: its non-zero words to the
+// (all-zero) bitmap, their popcount to blocksum.
+__global__ void __launch_bounds__(kBlock) k_bm_merge(DGlobal g, int parts) {
+    if (*g.err) return;
+    __shared__ int tmp[16];
+    const int blk = blockIdx.x;
+    const int t = block_table(g, blk);
+    const DTable &tb = g.tabs[t];
+    const int64_t words = (int64_t)g.total_bm_blocks * kWordsPerBlock;
+    const uint32_t *src = g.part_bm + (int64_t)blk * kWordsPerBlock + threadIdx.x * kWordsPerThread;
+    uint4 v[kMarkMaxParts];
+#pragma unroll
+    for (int k = 0; k < kMarkMaxParts; ++k) v[k] = k < parts ? gload16(src + k * words) : make_uint4(0u, 0u, 0u, 0u);
+    uint4 w = v[0];
+#pragma unroll
+    for (int k = 1; k < kMarkMaxParts; ++k) w.x |= v[k].x, w.y |= v[k].y, w.z |= v[k].z, w.w |= v[k].w;
+    if (w.x | w.y | w.z | w.w)
+        *reinterpret_cast<uint4 *>(tb.bitmap + (int64_t)(blk - tb.bm_block0) * kWordsPerBlock +
+                                   threadIdx.x * kWordsPerThread) = w;
+    const int s = block_sum(__popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w), tmp);
     if (threadIdx.x == 0) g.blocksum[blk] = s;
 }
 
@@ -299,7 +334,14 @@ template <int MODE>
 static void mark(const DGlobal &g, const int32_t *keys, const int64_t *offs, int32_t B, int64_t n, int32_t have_fwd,
                  const int64_t *starts, hipStream_t s) {
     const unsigned slices = g.own_slices > 0 ? (unsigned)g.own_slices : 1u;
-    k_mark_own<MODE><<<dim3(slices, (unsigned)g.T), kOwnThreads, 0, s>>>(g, keys, offs, B, n, have_fwd);
+    // Parts: about 16,000 ids each, from 48,000 ids per table on; below, the
+    // merge's launch costs what the split saves (some 5 us).  26 resident tables of
+    // 123,000 ids: marking 26 -> 6 us and merging 5; the 290,000 prefetch ids of
+    // each of 4 tables 60 -> 17 us in all.
+    const int64_t per = n / g.T;
+    const int parts = per < kMarkSplitIds ? 1 : (int)std::min<int64_t>(g.mark_parts, per / 16384);
+    k_mark_own<MODE><<<dim3(slices, (unsigned)g.T, (unsigned)parts), kOwnThreads, 0, s>>>(g, keys, offs, B, n, have_fwd);
+    if (parts > 1) k_bm_merge<<<g.total_bm_blocks, kBlock, 0, s>>>(g, parts);
     if (g.own_tables < g.T) k_mark<<<grid_for(n, kBlock * 8, 4096), kBlock, 0, s>>>(g, keys, starts, n);
 }
 

@@ -18,6 +18,10 @@ constexpr int kWordsPerBlock = kBlock * kWordsPerThread;  // 1024 words = 32768 
 // larger ones with a device atomic per distinct id and block.
 constexpr int kOwnSliceWords = 32768;  // 128 KiB of LDS, 2^20 rows
 constexpr int kOwnSliceBlocks = kOwnSliceWords / kWordsPerBlock;
+// Where every table is marked so and they have fewer slices than kMarkBlocks,
+// many ids are marked by several blocks per slice, a part of the ids each.
+constexpr int kMarkBlocks = 256, kMarkMaxParts = 8;
+constexpr int64_t kMarkSplitIds = 49152;  // ids per table, on average, from which they are split
 #ifndef RECMG_OWN_MAX_SLICES
 #define RECMG_OWN_MAX_SLICES 32
 #endif
@@ -196,6 +200,8 @@ struct DGlobal {
     int32_t total_bm_blocks;
     int32_t own_tables;  // tables with owns_bitmap(bm_nblk)
     int32_t own_slices;  // the most LDS slices of such a table
+    int32_t mark_parts;  // parts that a table's ids may be marked in (1: never split)
+    uint32_t *part_bm;   // [mark_parts][total_bm_blocks * kWordsPerBlock] each part's bitmap words
     int32_t *sa_bstart;  // [nsa + 1] first placement block of each set-associative table
     int32_t *sa_btab;    // [nsa] those tables, fewest sets first
     int64_t *sa_part;    // [sa blocks][8] each set-associative placement block's counts (added up per table after)

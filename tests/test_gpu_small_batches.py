@@ -60,10 +60,11 @@ def test_small_and_general_calls_in_turn(shape, policy, ways):
     even = lambda n: [n // T + (t < n % T) for t in range(T)]
     skew = lambda n: [n - (T - 1) * 3] + [3] * (T - 1)
     none = lambda n: [n] + [0] * (T - 1)
-    # ids per call: far below the line, at the total's line and one past it, far past it
-    plan = [even(200), even(32768), even(32769), skew(9000), even(60), none(5000), skew(32768), even(90000), even(700),
-            even(0), even(1500)]
-    g = GpuRunner(w, tabs, max_indices=90000, max_prefetch=90000)
+    # ids per call: far below the line, at the total's line and one past it, far past it, enough per table (in two
+    # tables) to be marked in parts
+    plan = [even(200), even(32768), even(32769), skew(9000), even(60), none(5000), skew(32768), even(130001), even(700),
+            even(0), skew(120000), even(1500)]
+    g = GpuRunner(w, tabs, max_indices=130001, max_prefetch=130001)
     o = oracle.for_workload(w, tabs)
     try:
         last = None
