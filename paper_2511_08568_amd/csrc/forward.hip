@@ -761,6 +761,51 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC
     else pool_wave_v<DT, LW, R>(raddr, ob, nbags, D, ob_out);
 }
 
+// The pooled sums of tables of several kinds in one launch: a block takes its
+// table's own form.  For batches of few bags, where a launch per kind leaves most
+// of the chip idle each time (13 tables of five kinds with 1,000 bags each: 29 us
+// in five launches, 15 in one); the registers of the largest form would cost the
+// others waves where there are many.
+template <int DT>
+__device__ __forceinline__ void pool_any(const DGlobal &g, const DTable &tb, int t, int32_t B,
+                                         const int64_t *__restrict__ offsets, const uint64_t *__restrict__ raddr,
+                                         float *__restrict__ out, int blk) {
+    if (!tb.wlw) {
+        if (tb.vec) pool_table<DT, true>(g, tb, t, B, offsets, out, blk);
+        else pool_table<DT, false>(g, tb, t, B, offsets, out, blk);
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int j0 = (blk * (kBlock / 64) + wave) * kWaveBags;
+    if (j0 >= B) return;
+    const int nbags = B - j0 < kWaveBags ? B - j0 : kWaveBags, D = tb.dim;
+    const int64_t *ob = offsets + (int64_t)t * B + j0;
+    float *o = out + (int64_t)B * tb.out_elem_off + (int64_t)j0 * D;
+    if (tb.wlw == 4) pool_wave_v<DT, 4, 4>(raddr, ob, nbags, D, o);
+    else if (tb.wlw == 8) pool_wave_v<DT, 8, 4>(raddr, ob, nbags, D, o);
+    else if (tb.wr == 4) pool_wave_v<DT, 16, 4>(raddr, ob, nbags, D, o);
+    else if (tb.wr == 2) pool_wave_v<DT, 16, 2>(raddr, ob, nbags, D, o);
+    else pool_wave_s<DT, 16>(raddr, ob, nbags, tb.wnch, D, o);
+}
+
+__global__ void __launch_bounds__(kBlock) k_pool_any(DGlobal g, const int64_t *__restrict__ offsets,
+                                                     const uint64_t *__restrict__ raddr, int32_t B,
+                                                     float *__restrict__ out, const int32_t *__restrict__ bstart,
+                                                     const int32_t *__restrict__ btab, int32_t nt, int32_t nblk) {
+    if (*g.err) return;
+    const int lb = xcd_block(nblk);
+    __shared__ int s_k;
+    // (blocks of the tables in btab order; a table without blocks matches none)
+    if ((int)threadIdx.x < nt && bstart[threadIdx.x] <= lb && lb < bstart[threadIdx.x + 1]) s_k = threadIdx.x;
+    __syncthreads();
+    const int k = __builtin_amdgcn_readfirstlane(s_k);
+    const int t = btab[k], blk = lb - bstart[k];
+    const DTable &tb = g.tabs[t];
+    if (tb.dtype == RECMG_F32) pool_any<RECMG_F32>(g, tb, t, B, offsets, raddr, out, blk);
+    else if (tb.dtype == RECMG_F16) pool_any<RECMG_F16>(g, tb, t, B, offsets, raddr, out, blk);
+    else pool_any<RECMG_BF16>(g, tb, t, B, offsets, raddr, out, blk);
+}
+
 // The counters of a forward that fetches nothing from the host itself (no
 // indices, or every table STAGED).
 __global__ void k_fwd_finalize(DGlobal g, int64_t log_slot) {
@@ -812,6 +857,13 @@ int pool_kind(int dtype, int vec, int wlw, int wr) {
     return kPoolKindsGroup + dtype * 5 + v;
 }
 
+// Blocks up to which tables of several kinds share a launch.  12 tables of four
+// kinds, whole forwards: 512 bags each (1,536 blocks) 42 us shared, 57 apart;
+// 2,048 bags (6,144 blocks) 63 and 59; 8,192 bags 162 and 116.
+#ifndef RECMG_POOL_ANY
+#define RECMG_POOL_ANY 3072
+#endif
+
 // ev0 / ev1 (may be null): recorded by the first / last dispatch itself, so
 // they bracket the kernels' execution without the dispatch gap.
 void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out, const int32_t *bstart,
@@ -828,6 +880,16 @@ void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out
     static const KW kw[kPoolKinds - kPoolKindsGroup] = {RECMG_WK(RECMG_F32), RECMG_WK(RECMG_F16),
                                                         RECMG_WK(RECMG_BF16)};
 #undef RECMG_WK
+    int32_t blocks = 0;
+    for (int i = 0; i < nl; ++i) blocks += ls[i].nblk;
+    if (nl > 1 && blocks > 0 && blocks <= RECMG_POOL_ANY) {
+        const dim3 grid((unsigned)blocks), blk(kBlock);
+        const uint64_t *ra = g.raddr;
+        if (ev0 || ev1) hipExtLaunchKernelGGL(k_pool_any, grid, blk, 0, s, ev0, ev1, 0, g, offsets, ra, B, out, bstart, btab,
+                                              nt, blocks);
+        else k_pool_any<<<grid, blk, 0, s>>>(g, offsets, ra, B, out, bstart, btab, nt, blocks);
+        return;
+    }
     int first = -1, last = -1;
     for (int i = 0; i < nl; ++i)
         if (ls[i].nblk > 0) {
