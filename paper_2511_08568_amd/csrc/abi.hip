@@ -69,7 +69,7 @@ struct Layout {
     std::vector<size_t> pool, slot_row, slot_score, slot_flags, slot_touch, slot_cbit, free_stack, map, bitmap, rank,
         seg, freq, slot_pos, ring0, ring1, rcnt0, rcnt1, roff;
     size_t tabs = 0, st = 0, err = 0, bm_block_start = 0, blocksum = 0, blockoff = 0, tstart = 0, pstart = 0;
-    size_t src = 0, raddr = 0, U = 0, slotU = 0, M = 0, mflags = 0, mcbit = 0, mscore = 0, fill_src = 0, fill_slot = 0;
+    size_t src = 0, U = 0, slotU = 0, M = 0, mflags = 0, mcbit = 0, mscore = 0, fill_src = 0, fill_slot = 0;
     size_t NP = 0, PU = 0, hist = 0, dump = 0, dump_count = 0, pool_bstart = 0, pool_btab = 0, ftstart = 0;
     size_t sa_bstart = 0, sa_btab = 0, fdesc = 0, stat_log = 0, pfrom = 0, sa_part = 0;
     size_t fstage = 0;
@@ -228,8 +228,7 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     L->bm_block_start = take(4 * (T + 1));
     L->blocksum = take(4 * (size_t)L->total_bm_blocks);
     L->blockoff = take(4 * (size_t)L->total_bm_blocks);
-    L->src = take(4 * mi);
-    L->raddr = take(8 * (mi + kRaddrPad));  // blocks of row addresses are read past the end
+    L->src = take(4 * (mi + kSrcPad));  // blocks of locations are read past the end
     L->U = take(4 * mi);
     L->slotU = take(4 * mi);
     L->M = take(4 * mi);
@@ -883,7 +882,6 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     g.tstart = reinterpret_cast<int64_t *>(ws + L.tstart);
     g.pstart = reinterpret_cast<int64_t *>(ws + L.pstart);
     g.src = reinterpret_cast<int32_t *>(ws + L.src);
-    g.raddr = reinterpret_cast<uint64_t *>(ws + L.raddr);
     g.U = reinterpret_cast<int32_t *>(ws + L.U);
     g.slotU = reinterpret_cast<int32_t *>(ws + L.slotU);
     g.M = reinterpret_cast<int32_t *>(ws + L.M);

@@ -4,9 +4,8 @@
 //   k_mark_own (and k_mark), k_bm_emit   bag offsets checked, each table's
 //                index range recorded, distinct rows sorted
 //   k_fwd_probe  map probe of the distinct rows, prefetch coverage
-//   k_fwd_src    per index: where its row lives (slot or staging row, and
-//                that row's device address), through the rank of the row
-//                among the distinct rows
+//   k_fwd_src    per index: where its row lives (slot or staging row),
+//                through the rank of the row among the distinct rows
 //   k_fetch      ZERO_COPY: copy each distinct missing row once from pinned
 //                host memory to HBM staging (GPU reads over the host link); its
 //                last block publishes the counters (k_fwd_finalize where no
@@ -129,19 +128,18 @@ __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t st
     if ((int)threadIdx.x < g.T && s_cov[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].covered, s_cov[threadIdx.x]);
 }
 
-// inverse map and data location of every index
+// inverse map: where every index's row lives (slot, or -(miss + 1)).  The pooled
+// kernels make addresses of it themselves: an 8-byte address per index beside
+// the location was 38 MB of the 3.2 million indices' traffic here and there.
 __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__restrict__ indices, int64_t n) {
     if (*g.err) return;
     __shared__ int64_t s_start[RECMG_MAX_TABLES + 1];
     __shared__ const uint4 *s_rank[RECMG_MAX_TABLES];
-    __shared__ const char *s_pool[RECMG_MAX_TABLES];
-    __shared__ int32_t s_rb[RECMG_MAX_TABLES], s_ns[RECMG_MAX_TABLES], s_qb[RECMG_MAX_TABLES];
+    __shared__ int32_t s_ns[RECMG_MAX_TABLES], s_qb[RECMG_MAX_TABLES];
     for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
         s_start[t] = g.tstart[t];
         if (t < g.T) {
             s_rank[t] = g.tabs[t].rank;
-            s_pool[t] = g.tabs[t].pool;
-            s_rb[t] = g.tabs[t].row_bytes;
             s_ns[t] = g.tabs[t].nsets;
             s_qb[t] = g.tabs[t].qbits;
         }
@@ -157,7 +155,6 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
         int tq[Q];
         uint32_t pos[Q];
         uint4 rk[Q];
-        int32_t sl[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int64_t i = i0 + q * kBlock;
@@ -171,16 +168,7 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
         for (int q = 0; q < Q; ++q) {
             if (i0 + q * kBlock >= hi) break;
             const int32_t u = (int32_t)rk[q].x + __popc(rk[q].y & ((1u << (pos[q] & 31)) - 1u));
-            sl[q] = g.slotU[s_start[tq[q]] + u];
-        }
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int64_t i = i0 + q * kBlock;
-            if (i >= hi) break;
-            const int k = tq[q];
-            g.src[i] = sl[q];
-            g.raddr[i] = sl[q] >= 0 ? (uint64_t)(s_pool[k] + (int64_t)sl[q] * s_rb[k])
-                                    : (uint64_t)(g.staging + (s_start[k] - (int64_t)sl[q] - 1) * g.stage_stride);
+            g.src[i0 + q * kBlock] = g.slotU[s_start[tq[q]] + u];
         }
     }
 }
@@ -424,13 +412,13 @@ __global__ void __launch_bounds__(kBlock) k_pool(DGlobal g, const int64_t *__res
 // ------------------------------------------------- wave-per-bag pooled sum
 //
 // One wave sums kWaveBags consecutive bags, one bag at a time.  Each lane
-// adds its LW-byte slice of every row; row addresses come from the per-index
-// array written by k_fwd_src, so the kernel does no slot or staging lookups.
+// adds its LW-byte slice of every row; a row's address comes from its index's
+// location, written by k_fwd_src, so the kernel does no lookups.
 //   R == 1 (rows of 1024 bytes or whole multiples): all lanes read the same
 //     row, so its address is wave-uniform and comes in through scalar loads.
 //   R > 1 (shorter rows): the wave splits into R groups of 64 / R lanes that
 //     read R different rows per load instruction, group h taking the lookups
-//     p with p mod R = h.  Each lane holds one address of a window of 64
+//     p with p mod R = h.  Each lane makes one address of a window of 64
 //     lookups; a ds_bpermute hands every group its row's address.
 // Either way lookup p goes to partial sum p mod 4 and the four are combined
 // as (S0 + S1) + (S2 + S3): a fixed order per bag, whichever tier served a row.
@@ -550,14 +538,33 @@ __device__ __forceinline__ void wave_offsets(int64_t (&offs)[BPW + 1], const int
     for (int b = 0; b <= BPW; ++b) offs[b] = ob[b < nbags ? b : nbags];
 }
 
+// A table's rows: slot s >= 0 in the slot pool, s < 0 staging row -(s + 1).
+struct Rows {
+    uint64_t pool, staging;  // addresses of slot 0 and of the table's first staging row
+    uint32_t row_bytes, stride;
+    __device__ uint64_t at(int32_t s) const {
+        const bool hit = s >= 0;
+        return (hit ? pool : staging) + (uint64_t)(uint32_t)(hit ? s : ~s) * (hit ? row_bytes : stride);
+    }
+};
+__device__ __forceinline__ Rows table_rows(const DGlobal &g, const DTable &tb, int64_t tstart) {
+    Rows r;
+    r.pool = (uint64_t)tb.pool;
+    r.staging = (uint64_t)(g.staging + tstart * g.stage_stride);
+    r.row_bytes = (uint32_t)tb.row_bytes;
+    r.stride = (uint32_t)g.stage_stride;
+    return r;
+}
+
 // R == 1.  Software pipeline: the scalar loads of the next block's U row
-// addresses (this bag's, else the next non-empty bag's first) are in flight
+// locations (this bag's, else the next non-empty bag's first) are in flight
 // while the current block's row loads are.  A block may run past the bag and
-// past the batch (the address array has kRaddrPad entries of padding); such
-// addresses are never dereferenced.
+// past the batch (the location array has kSrcPad entries of padding); the
+// addresses made of such entries are never dereferenced.
 template <int DT, int LW>
-__device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, const int64_t *__restrict__ ob,
-                                            int nbags, int wnch, int D, float *__restrict__ obase) {
+__device__ __forceinline__ void pool_wave_s(const int32_t *__restrict__ src, const Rows rows,
+                                            const int64_t *__restrict__ ob, int nbags, int wnch, int D,
+                                            float *__restrict__ obase) {
     using V = typename WVec<LW>::V;
     constexpr int EB = Elem<DT>::bytes, NE = LW / EB;
     constexpr int U = 8;  // rows in flight per wave (8 KB)
@@ -567,7 +574,7 @@ __device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, 
     wave_offsets<BPW>(offs, ob, nbags);
     for (int ch = 0; ch < wnch; ++ch) {
         const uint32_t eoff = (uint32_t)((ch * 64 + lane) * LW);
-        uint64_t nx[U];
+        int32_t nx[U];
         // first block of the first non-empty bag after bag b (all indices
         // static, so offs and nx stay in scalar registers)
         auto next_bag_addrs = [&](int b) {
@@ -576,7 +583,7 @@ __device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, 
             for (int b2 = 0; b2 < BPW; ++b2)
                 if (b2 > b && !found && b2 < nbags && offs[b2 + 1] > offs[b2]) {
 #pragma unroll
-                    for (int k = 0; k < U; ++k) nx[k] = raddr[offs[b2] + k];
+                    for (int k = 0; k < U; ++k) nx[k] = src[offs[b2] + k];
                     found = true;
                 }
         };
@@ -596,13 +603,13 @@ __device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, 
                 V v[U];
                 const uint32_t eo = opaque(eoff);
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = wload<V>(nx[u], eo);
+                for (int u = 0; u < U; ++u) v[u] = wload<V>(rows.at(nx[u]), eo);
                 // the barrier keeps the next block's scalar loads after the
                 // row loads above, so one block of addresses is live at a time
                 asm volatile("" ::: "memory");
                 if (p + U < n) {
 #pragma unroll
-                    for (int k = 0; k < U; ++k) nx[k] = raddr[a + p + U + k];
+                    for (int k = 0; k < U; ++k) nx[k] = src[a + p + U + k];
                 } else {
                     next_bag_addrs(b);
                 }
@@ -618,7 +625,7 @@ __device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, 
                     if (p + q < n) {
                         const uint32_t eo = opaque(eoff);
 #pragma unroll
-                        for (int u = q; u < q + 4; ++u) v[u] = wload<V>(p + u < n ? nx[u] : nx[q], eo);
+                        for (int u = q; u < q + 4; ++u) v[u] = wload<V>(rows.at(p + u < n ? nx[u] : nx[q]), eo);
                     }
                 asm volatile("" ::: "memory");
                 next_bag_addrs(b);
@@ -637,12 +644,13 @@ __device__ __forceinline__ void pool_wave_s(const uint64_t *__restrict__ raddr, 
 
 // R > 1.  Lane i holds the address of lookup w + i of a window of 64 lookups
 // of the bag starting at w (a whole bag when it has at most 64); the next
-// window (this bag's, else the next non-empty bag's first) is loaded while
-// the current one's rows are read.  Window entries past the bag, and past the
-// batch (kRaddrPad entries of padding), are never dereferenced.
+// window's locations (this bag's, else the next non-empty bag's first) are loaded
+// while the current one's rows are read.  Window entries past the bag, and past
+// the batch (kSrcPad entries of padding), are never dereferenced.
 template <int DT, int LW, int R>
-__device__ __forceinline__ void pool_wave_v(const uint64_t *__restrict__ raddr, const int64_t *__restrict__ ob,
-                                            int nbags, int D, float *__restrict__ obase) {
+__device__ __forceinline__ void pool_wave_v(const int32_t *__restrict__ src, const Rows rows,
+                                            const int64_t *__restrict__ ob, int nbags, int D,
+                                            float *__restrict__ obase) {
     using V = typename WVec<LW>::V;
     constexpr int EB = Elem<DT>::bytes, NE = LW / EB, GL = 64 / R, NA = 4 / R;
     constexpr int U0 = RECMG_WPOOL_KB * 16 / LW;  // load instructions per sub-block (KB of rows in flight)
@@ -654,13 +662,13 @@ __device__ __forceinline__ void pool_wave_v(const uint64_t *__restrict__ raddr, 
     const uint32_t eoff = (uint32_t)(gl * LW);
     int64_t offs[BPW + 1];
     wave_offsets<BPW>(offs, ob, nbags);
-    uint64_t wnext = 0;
+    int32_t wnext = 0;
     auto next_bag_window = [&](int b) {
         bool found = false;
 #pragma unroll
         for (int b2 = 0; b2 < BPW; ++b2)
             if (b2 > b && !found && b2 < nbags && offs[b2 + 1] > offs[b2]) {
-                wnext = RECMG_GLOBAL(uint64_t, raddr + offs[b2] + lane);
+                wnext = RECMG_GLOBAL(int32_t, src + offs[b2] + lane);
                 found = true;
             }
     };
@@ -676,7 +684,7 @@ __device__ __forceinline__ void pool_wave_v(const uint64_t *__restrict__ raddr, 
 #pragma unroll
             for (int x = 0; x < NE; ++x) acc[k][x] = 0.f;
         for (int p = 0; p < n; p += 64) {
-            const uint64_t wcur = wnext;
+            const uint64_t wcur = rows.at(wnext);
             const int m = n - p < 64 ? n - p : 64;  // lookups in this window
             const int wlo = (int)(uint32_t)wcur, whi = (int)(uint32_t)(wcur >> 32);
             // one sub-block of U load instructions; FULL: all UR lookups are
@@ -707,7 +715,7 @@ __device__ __forceinline__ void pool_wave_v(const uint64_t *__restrict__ raddr, 
                 if (s == 0) {
                     // the next window, issued after this sub-block's row loads
                     asm volatile("" ::: "memory");
-                    if (p + 64 < n) wnext = RECMG_GLOBAL(uint64_t, raddr + a + p + 64 + lane);
+                    if (p + 64 < n) wnext = RECMG_GLOBAL(int32_t, src + a + p + 64 + lane);
                     else next_bag_window(b);
                 }
 #pragma unroll
@@ -732,7 +740,7 @@ __device__ __forceinline__ void pool_wave_v(const uint64_t *__restrict__ raddr, 
 // chain of dependent loads, and the search would add four to it).
 template <int DT, int LW, int R>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RECMG_WPOOL_OCC))) k_pool_w(DGlobal g, const int64_t *__restrict__ offsets,
-                                                   const uint64_t *__restrict__ raddr, int32_t B,
+                                                   const int32_t *__restrict__ src, int32_t B,
                                                    float *__restrict__ out, const int32_t *__restrict__ bstart,
                                                    const int32_t *__restrict__ btab, int32_t nt, int32_t boff,
                                                    int32_t nblk, int32_t k0, int32_t nbt) {
@@ -757,8 +765,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC
     const int nbags = B - j0 < kWaveBags ? B - j0 : kWaveBags;
     const int64_t *ob = offsets + (int64_t)t * B + j0;
     float *ob_out = out + ooff + (int64_t)j0 * D;
-    if constexpr (R == 1) pool_wave_s<DT, LW>(raddr, ob, nbags, tb.wnch, D, ob_out);
-    else pool_wave_v<DT, LW, R>(raddr, ob, nbags, D, ob_out);
+    const Rows rows = table_rows(g, tb, offsets[(int64_t)t * B]);
+    if constexpr (R == 1) pool_wave_s<DT, LW>(src, rows, ob, nbags, tb.wnch, D, ob_out);
+    else pool_wave_v<DT, LW, R>(src, rows, ob, nbags, D, ob_out);
 }
 
 // The pooled sums of tables of several kinds in one launch: a block takes its
@@ -768,7 +777,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC
 // others waves where there are many.
 template <int DT>
 __device__ __forceinline__ void pool_any(const DGlobal &g, const DTable &tb, int t, int32_t B,
-                                         const int64_t *__restrict__ offsets, const uint64_t *__restrict__ raddr,
+                                         const int64_t *__restrict__ offsets, const int32_t *__restrict__ src,
                                          float *__restrict__ out, int blk) {
     if (!tb.wlw) {
         if (tb.vec) pool_table<DT, true>(g, tb, t, B, offsets, out, blk);
@@ -781,15 +790,16 @@ __device__ __forceinline__ void pool_any(const DGlobal &g, const DTable &tb, int
     const int nbags = B - j0 < kWaveBags ? B - j0 : kWaveBags, D = tb.dim;
     const int64_t *ob = offsets + (int64_t)t * B + j0;
     float *o = out + (int64_t)B * tb.out_elem_off + (int64_t)j0 * D;
-    if (tb.wlw == 4) pool_wave_v<DT, 4, 4>(raddr, ob, nbags, D, o);
-    else if (tb.wlw == 8) pool_wave_v<DT, 8, 4>(raddr, ob, nbags, D, o);
-    else if (tb.wr == 4) pool_wave_v<DT, 16, 4>(raddr, ob, nbags, D, o);
-    else if (tb.wr == 2) pool_wave_v<DT, 16, 2>(raddr, ob, nbags, D, o);
-    else pool_wave_s<DT, 16>(raddr, ob, nbags, tb.wnch, D, o);
+    const Rows rows = table_rows(g, tb, offsets[(int64_t)t * B]);
+    if (tb.wlw == 4) pool_wave_v<DT, 4, 4>(src, rows, ob, nbags, D, o);
+    else if (tb.wlw == 8) pool_wave_v<DT, 8, 4>(src, rows, ob, nbags, D, o);
+    else if (tb.wr == 4) pool_wave_v<DT, 16, 4>(src, rows, ob, nbags, D, o);
+    else if (tb.wr == 2) pool_wave_v<DT, 16, 2>(src, rows, ob, nbags, D, o);
+    else pool_wave_s<DT, 16>(src, rows, ob, nbags, tb.wnch, D, o);
 }
 
 __global__ void __launch_bounds__(kBlock) k_pool_any(DGlobal g, const int64_t *__restrict__ offsets,
-                                                     const uint64_t *__restrict__ raddr, int32_t B,
+                                                     const int32_t *__restrict__ src, int32_t B,
                                                      float *__restrict__ out, const int32_t *__restrict__ bstart,
                                                      const int32_t *__restrict__ btab, int32_t nt, int32_t nblk) {
     if (*g.err) return;
@@ -801,9 +811,9 @@ __global__ void __launch_bounds__(kBlock) k_pool_any(DGlobal g, const int64_t *_
     const int k = __builtin_amdgcn_readfirstlane(s_k);
     const int t = btab[k], blk = lb - bstart[k];
     const DTable &tb = g.tabs[t];
-    if (tb.dtype == RECMG_F32) pool_any<RECMG_F32>(g, tb, t, B, offsets, raddr, out, blk);
-    else if (tb.dtype == RECMG_F16) pool_any<RECMG_F16>(g, tb, t, B, offsets, raddr, out, blk);
-    else pool_any<RECMG_BF16>(g, tb, t, B, offsets, raddr, out, blk);
+    if (tb.dtype == RECMG_F32) pool_any<RECMG_F32>(g, tb, t, B, offsets, src, out, blk);
+    else if (tb.dtype == RECMG_F16) pool_any<RECMG_F16>(g, tb, t, B, offsets, src, out, blk);
+    else pool_any<RECMG_BF16>(g, tb, t, B, offsets, src, out, blk);
 }
 
 // The counters of a forward that fetches nothing from the host itself (no
@@ -871,7 +881,7 @@ void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out
                  hipStream_t s) {
     using KG = void (*)(DGlobal, const int64_t *, int32_t, float *, const int32_t *, const int32_t *, int32_t,
                         int32_t, int32_t);
-    using KW = void (*)(DGlobal, const int64_t *, const uint64_t *, int32_t, float *, const int32_t *,
+    using KW = void (*)(DGlobal, const int64_t *, const int32_t *, int32_t, float *, const int32_t *,
                         const int32_t *, int32_t, int32_t, int32_t, int32_t, int32_t);
     static const KG kg[kPoolKindsGroup] = {k_pool<RECMG_F32, false>,  k_pool<RECMG_F32, true>,
                                            k_pool<RECMG_F16, false>,  k_pool<RECMG_F16, true>,
@@ -884,7 +894,7 @@ void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out
     for (int i = 0; i < nl; ++i) blocks += ls[i].nblk;
     if (nl > 1 && blocks > 0 && blocks <= RECMG_POOL_ANY) {
         const dim3 grid((unsigned)blocks), blk(kBlock);
-        const uint64_t *ra = g.raddr;
+        const int32_t *ra = g.src;
         if (ev0 || ev1) hipExtLaunchKernelGGL(k_pool_any, grid, blk, 0, s, ev0, ev1, 0, g, offsets, ra, B, out, bstart, btab,
                                               nt, blocks);
         else k_pool_any<<<grid, blk, 0, s>>>(g, offsets, ra, B, out, bstart, btab, nt, blocks);
@@ -908,7 +918,7 @@ void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out
             else k<<<grid, blk, 0, s>>>(g, offsets, B, out, bstart, btab, nt, L.boff, L.nblk);
         } else {
             const KW k = kw[L.kind - kPoolKindsGroup];
-            const uint64_t *ra = g.raddr;
+            const int32_t *ra = g.src;
             if (a || b) hipExtLaunchKernelGGL(k, grid, blk, 0, s, a, b, 0, g, offsets, ra, B, out, bstart, btab, nt,
                                               L.boff, L.nblk, L.k0, L.nbt);
             else k<<<grid, blk, 0, s>>>(g, offsets, ra, B, out, bstart, btab, nt, L.boff, L.nblk, L.k0, L.nbt);

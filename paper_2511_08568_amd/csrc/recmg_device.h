@@ -46,7 +46,7 @@ constexpr int32_t ERR_OFFSETS = 2;
 #define RECMG_WPOOL_BAGS 1
 #endif
 constexpr int kWaveBags = RECMG_WPOOL_BAGS;  // consecutive bags per wave in the wave-per-bag pooled kernel
-constexpr int kRaddrPad = 64;  // entries past the batch in the per-index row-address array (read, never used)
+constexpr int kSrcPad = 64;  // entries past the batch in the per-index location array (read, never used)
 constexpr int32_t ERR_INTERNAL = 4;  // a slot-accounting invariant failed (never expected)
 // int64 counters of recmg_table_stats_t: kFwdStats of a forward, then the placement's
 constexpr int kFwdStats = 7, kPlcStats = 9, kNumStats = kFwdStats + kPlcStats;
@@ -171,8 +171,7 @@ struct DGlobal {
     int32_t *blockoff;        // [total bitmap blocks]
     int64_t *tstart;          // [T+1] first index of each table in the last forward
     int64_t *pstart;          // [T+1] first prefetch id of each table in this placement
-    int32_t *src;             // [max_indices] per access: slot (>= 0) or -(miss + 1)
-    uint64_t *raddr;          // [max_indices] per access: device address of its row (slot or staging)
+    int32_t *src;             // [max_indices + kSrcPad] per access: slot (>= 0) or -(miss + 1)
     int32_t *U;               // [max_indices] sorted distinct rows, table t at tstart[t]
     int32_t *slotU;           // [max_indices] per distinct row: slot or -(miss + 1)
     int32_t *M;               // [max_indices] missed rows, table t at tstart[t]

@@ -137,7 +137,7 @@ __device__ __forceinline__ bool mark_ids(LdsBitmap<NB> &bm, const DTable &tb, co
 
 // Everything of a forward before its miss fetch, for one table per block:
 // bag offsets checked, distinct rows (U, rank words), cache probe, per-index
-// location and row address, prefetch coverage.  Same results as k_fwd_prep,
+// location, prefetch coverage.  Same results as k_fwd_prep,
 // k_mark_own, k_bm_*, k_fwd_probe, k_fwd_src and k_fwd_cover.  A table whose
 // offsets or ids are malformed raises the error word and stops; nothing is
 // published for any table then (the later kernels read the word).
@@ -233,9 +233,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(DGlobal g, const in
         }
     }
     __syncthreads();
-    // location and address of every index
-    const char *pool = tb.pool, *stg = g.staging + lo * g.stage_stride;
-    const int64_t rb = tb.row_bytes, ss = g.stage_stride;
+    // location of every index
     const int32_t ns = tb.nsets, qb = tb.qbits;
     constexpr int kSrc = 4;
     for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += kSrc * kSmallThreads) {
@@ -252,7 +250,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(DGlobal g, const in
             if (r[q] < 0) continue;  // past the table's end (every id was checked above)
             const int64_t i = i0 + q * kSmallThreads;
             g.src[i] = sl[q];
-            g.raddr[i] = (uint64_t)(sl[q] >= 0 ? pool + sl[q] * rb : stg + (-(int64_t)sl[q] - 1) * ss);
         }
     }
     if (cover) {  // distinct rows of the last placement's list that the batch touches
