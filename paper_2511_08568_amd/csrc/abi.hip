@@ -1135,20 +1135,29 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // published counters on this stream (a fill of some hundred rows takes a few
     // microseconds, the waits of another stream for it longer).
     const bool small = !c->has_staged && small_placement(c->T, last_n, num_prefetch, c->max_nblk, max_fa_cap);
+    const uint8_t *last_bits = p.prio ? cache_bits : nullptr;
+    const int64_t want_last = (p.prio && cache_bits) || p.lfu ? last_n : 0;
+    int64_t heads_last = want_last;  // ... of these, what k_sa_heads takes care of
     if (small) {
         StageTimer tm(c, RECMG_STAGE_PLC_APPLY, s);
         launch_plc_small(g, p, prefetch_rows, prefetch_offsets, num_prefetch, cache_bits, q, c->max_nblk, s);
     } else {
         StageTimer tm(c, RECMG_STAGE_PLC_CLASSIFY, s);
-        if (num_prefetch == 0) launch_plc_prep(g, prefetch_offsets, num_prefetch, p.have_fwd, s);
-        if (p.prio && cache_bits && c->have_fwd) launch_plc_bits(g, cache_bits, last_n, s);
-        if (p.lfu && c->have_fwd) launch_plc_freq(g, last_n, s);
         if (num_prefetch > 0) {
             launch_mark_prefetch(g, prefetch_rows, prefetch_offsets, num_prefetch, p.have_fwd, s);
             launch_dedup(g, EMIT_PREFETCH,
                          reinterpret_cast<int32_t *>(reinterpret_cast<char *>(g.st) + offsetof(TState, pcount)),
                          (int)(sizeof(TState) / 4), 0, c->max_nblk, s);
-            launch_plc_classify(g, p.last_stamp, num_prefetch, s);
+        }
+        // the last batch's bits or counts: with the classification, else with
+        // k_sa_heads, else alone
+        if (num_prefetch > 0 && c->has_fa) {
+            launch_plc_classify(g, p.last_stamp, num_prefetch, last_bits, want_last, s);
+            heads_last = 0;
+        } else if (num_prefetch == 0 && c->has_fa) {
+            if (want_last > 0) launch_plc_last(g, prefetch_offsets, num_prefetch, last_bits, want_last, s);
+            else launch_plc_prep(g, prefetch_offsets, num_prefetch, p.have_fwd, s);
+            heads_last = 0;
         }
     }
     // fully associative STAGED tables: their new prefetch candidates go to the
@@ -1179,7 +1188,8 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
             if (c->has_ring) launch_ring_store(g, p, ring_items, c->max_cap, q, s);
         }
         if (c->has_sa)
-            launch_sa_place(g, p, last_n, num_prefetch, c->nsa, c->sa_blocks1, c->sa_blocks, c->sa_max_blocks, !small, s);
+            launch_sa_place(g, p, last_n, num_prefetch, c->nsa, c->sa_blocks1, c->sa_blocks, c->sa_max_blocks, !small,
+                            num_prefetch == 0 && !c->has_fa ? prefetch_offsets : nullptr, last_bits, heads_last, s);
     }
     const int32_t end_nsa = c->sa_max_blocks <= kSaSumInEnd ? c->nsa : 0;
     if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, c->has_scan_fa ? p.passes : 0, s);

@@ -65,9 +65,13 @@ void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows,
 
 // placement.hip
 void launch_plc_prep(const DGlobal &g, const int64_t *poff, int64_t np, int32_t have_fwd, hipStream_t s);
-void launch_plc_bits(const DGlobal &g, const uint8_t *bits, int64_t n_last, hipStream_t s);
-void launch_plc_freq(const DGlobal &g, int64_t n_last, hipStream_t s);
-void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, hipStream_t s);
+// the last batch's caching bits (PRIORITY) or counts (LFU_BATCH, bits = NULL) of
+// last_n indices (0: none) ride with the classification, or with k_sa_heads, or
+// go in a launch of their own with the start of a placement without a list
+void launch_plc_last(const DGlobal &g, const int64_t *poff, int64_t np, const uint8_t *bits, int64_t last_n,
+                     hipStream_t s);
+void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, const uint8_t *bits, int64_t last_n,
+                         hipStream_t s);
 // item_bound: the most slots + candidates of any table; up to kRankSmallItems one
 // block per table ranks it whole
 constexpr int64_t kRankSmallItems = 1 << 16;
@@ -101,7 +105,9 @@ void launch_ring_store(const DGlobal &g, const PlcParams &p, int64_t item_bound,
 
 // setassoc.hip: placement of the set-associative tables (nu: index space of
 // the last forward's distinct rows, np: of this placement's prefetch rows;
-// heads: k_sa_heads too (else k_plc_small has found the segments);
+// heads: k_sa_heads too (else k_plc_small has found the segments), with the
+// placement's start (poff, for an empty prefetch list, else NULL) and the last
+// batch's bits or counts (last_n > 0);
 // nsa tables, fewest sets first; blocks = sa_bstart[nsa], the first blocks1 of
 // them over tables of one set per wave), kSaWaves * sa_sets_per_wave(ways,
 // nsets) sets per block of a table
@@ -115,6 +121,7 @@ constexpr int sa_sets_per_wave(int ways, int64_t nsets) { return ways <= 32 && n
 // a launch of its own costs as much)
 constexpr int64_t kSaSumInEnd = 1024;
 void launch_sa_place(const DGlobal &g, const PlcParams &p, int64_t nu, int64_t np, int32_t nsa, int64_t blocks1,
-                     int64_t blocks, int64_t max_blocks, bool heads, hipStream_t s);
+                     int64_t blocks, int64_t max_blocks, bool heads, const int64_t *poff, const uint8_t *bits, int64_t last_n,
+                     hipStream_t s);
 
 }  // namespace recmg

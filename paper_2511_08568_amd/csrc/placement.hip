@@ -13,14 +13,14 @@
 //
 // Scores:  LRU_BATCH  touched by the last batch: lru_touch; prefetched:
 //                     max(score, pscore) with pscore = lru_touch + 1
-//          LFU_BATCH  every row's score is its batch count (k_plc_freq adds
+//          LFU_BATCH  every row's score is its batch count (last_batch_share adds
 //                     the last batch); a prefetch does not change it
 //          PRIORITY   residents first age by one, saturating at 0 (Alg. 2);
 //                     touched: caching bit + ES (Alg. 1); prefetched:
 //                     max(score, ES); a touched resident loses its prefetch flag.
 //
-// Kernels on the stream: [k_plc_bits or k_plc_freq], the dedup of P with the
-// placement's preparation (dedup.hip; k_plc_prep if P is empty), k_plc_classify,
+// Kernels on the stream: the dedup of P with the placement's preparation
+// (dedup.hip; k_plc_prep or k_plc_last if P is empty), k_plc_classify,
 // k_plc_update (scores + histogram of pass 0), k_plc_select per further pass
 // (which first picks the digit of the pass before), k_plc_evict (which picks the
 // last), k_plc_admit, k_plc_end, k_plc_fill.  A map with too many deleted entries
@@ -39,39 +39,13 @@ __global__ void k_plc_prep(DGlobal g, const int64_t *__restrict__ poff, int64_t 
     placement_prep(g, blockIdx.x, poff, np, have_fwd);
 }
 
-// Caching bits of the last batch, OR-ed per row into a byte of the slot (hit)
-// or of the miss entry.  Every writer stores the same value 1, so plain byte
-// stores suffice (no read-modify-write atomics on popular rows).
-__global__ void __launch_bounds__(kBlock) k_plc_bits(DGlobal g, const uint8_t *__restrict__ bits, int64_t n) {
-    if (*g.err) return;
-    __shared__ int64_t s_start[RECMG_MAX_TABLES + 1];
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) s_start[t] = g.tstart[t];
-    __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        if (!bits[i]) continue;
-        const int t = find_seg(s_start, g.T, i);
-        const int32_t s = g.src[i];
-        uint8_t *f = s >= 0 ? &g.tabs[t].slot_cbit[s] : &g.mcbit[s_start[t] + (-(int64_t)s - 1)];
-        if (!*f) *f = 1;
-    }
-}
-
-// LFU_BATCH: one more batch for every distinct row of the last forward (rows
-// of U are distinct, so plain increments suffice).
-__global__ void __launch_bounds__(kBlock) k_plc_freq(DGlobal g, int64_t n) {
-    if (*g.err) return;
-    __shared__ int64_t s_start[RECMG_MAX_TABLES + 1];
-    __shared__ int32_t s_uc[RECMG_MAX_TABLES];
-    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
-        s_start[t] = g.tstart[t];
-        if (t < g.T) s_uc[t] = g.st[t].ucount;
-    }
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int t = find_seg(s_start, g.T, i);
-        if (i - s_start[t] < s_uc[t]) g.tabs[t].freq[g.U[i]] += 1;
-    }
+// The last batch's bits or counts alone (an empty prefetch list has no kernel
+// for them to ride with), and the placement's start.
+__global__ void __launch_bounds__(kBlock) k_plc_last(DGlobal g, const int64_t *__restrict__ poff, int64_t np,
+                                                     const uint8_t *__restrict__ bits, int64_t n) {
+    const bool err = block_err(g);
+    if ((int)blockIdx.x < g.T) placement_prep(g, blockIdx.x, poff, np, 1);
+    if (!err) last_batch_share(g, bits, n);
 }
 
 // Classify every distinct prefetch row of the fully associative tables (Alg.
@@ -82,7 +56,9 @@ __global__ void __launch_bounds__(kBlock) k_plc_freq(DGlobal g, int64_t n) {
 // table states: 1.16 million rows of 4 tables took 300 us, now 190).
 // Set-associative tables play their prefetch rows as events in k_sa_place,
 // which also counts the resident ones.
-__global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last_stamp) {
+// last_n > 0: then the last batch's bits or counts.
+__global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last_stamp, const uint8_t *__restrict__ bits,
+                                                         int64_t last_n) {
     if (*g.err) return;
     __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ int64_t s_ps[RECMG_MAX_TABLES];
@@ -148,6 +124,7 @@ __global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last
         __syncthreads();
     }
     if ((int)threadIdx.x < g.T && s_res[threadIdx.x]) atomicAdd(&g.st[threadIdx.x].p_res, s_res[threadIdx.x]);
+    if (last_n > 0) last_batch_share(g, bits, last_n);
 }
 
 // ----------------------------------------------------------------- ranking
@@ -667,19 +644,15 @@ void launch_plc_prep(const DGlobal &g, const int64_t *poff, int64_t np, int32_t 
     k_plc_prep<<<g.T, 64, 0, s>>>(g, poff, np, have_fwd);
 }
 
-void launch_plc_bits(const DGlobal &g, const uint8_t *bits, int64_t n_last, hipStream_t s) {
-    if (n_last <= 0) return;
-    k_plc_bits<<<grid_for(n_last, kBlock * 4, 16384), kBlock, 0, s>>>(g, bits, n_last);
+void launch_plc_last(const DGlobal &g, const int64_t *poff, int64_t np, const uint8_t *bits, int64_t last_n,
+                     hipStream_t s) {
+    const unsigned blocks = grid_for(last_n, kBlock * 4, 8192);
+    k_plc_last<<<blocks < (unsigned)g.T ? (unsigned)g.T : blocks, kBlock, 0, s>>>(g, poff, np, bits, last_n);
 }
 
-void launch_plc_freq(const DGlobal &g, int64_t n_last, hipStream_t s) {
-    if (n_last <= 0) return;
-    k_plc_freq<<<grid_for(n_last, kBlock * 4, 8192), kBlock, 0, s>>>(g, n_last);
-}
-
-void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, hipStream_t s) {
-    if (np <= 0) return;
-    k_plc_classify<<<grid_for(np, kRound, 1024), kRound, 0, s>>>(g, last_stamp);
+void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, const uint8_t *bits, int64_t last_n,
+                         hipStream_t s) {
+    k_plc_classify<<<grid_for(np > last_n / 4 ? np : last_n / 4, kRound, 1024), kRound, 0, s>>>(g, last_stamp, bits, last_n);
 }
 
 bool rank_in_block(int64_t item_bound) { return item_bound <= kRankSmallItems; }

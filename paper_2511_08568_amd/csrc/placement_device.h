@@ -229,6 +229,43 @@ __device__ __forceinline__ uint64_t rank_block(const DGlobal &g, const PlcParams
     return prefix;
 }
 
+// ----------------------------------------------------------------- the last batch
+
+// What a placement takes from the last batch besides its misses: PRIORITY the
+// caching bits, OR-ed per row into a byte of the slot (hit) or of the miss entry
+// (every writer stores the same value 1, so plain byte stores suffice, no
+// read-modify-write atomics on popular rows); LFU_BATCH one more batch for every
+// distinct row (rows of U are distinct, so plain increments suffice).  This block's
+// share of n indices; bits: NULL under LFU_BATCH.  It depends on nothing the
+// placement computes and is wanted by its scores only, so it rides with a kernel
+// that comes before them (a kernel of its own took 7 us on a batch of 13,000 ids
+// and 15 us on 1.7 million; a step of 26 32-way LFU tables 182 -> 172 us, of 13
+// ragged PRIORITY tables 257 -> 247).
+__device__ __forceinline__ void last_batch_share(const DGlobal &g, const uint8_t *__restrict__ bits, int64_t n) {
+    __shared__ int64_t s_ts[RECMG_MAX_TABLES + 1];
+    __shared__ int32_t s_uc[RECMG_MAX_TABLES];
+    for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
+        s_ts[t] = g.tstart[t];
+        if (t < g.T) s_uc[t] = g.st[t].ucount;
+    }
+    __syncthreads();
+    int64_t lo, hi;
+    block_share(n, &lo, &hi);
+    if (lo >= hi) return;
+    int t = find_seg(s_ts, g.T, lo);
+    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+        if (bits && !bits[i]) continue;
+        while (i >= s_ts[t + 1]) ++t;
+        if (bits) {
+            const int32_t s = g.src[i];
+            uint8_t *f = s >= 0 ? &g.tabs[t].slot_cbit[s] : &g.mcbit[s_ts[t] + (-(int64_t)s - 1)];
+            if (!*f) *f = 1;
+        } else if (i - s_ts[t] < s_uc[t]) {
+            g.tabs[t].freq[g.U[i]] += 1;
+        }
+    }
+}
+
 // ----------------------------------------------------------------- map upkeep
 
 // A map of many deleted entries is rebuilt in the placement after the one that

@@ -42,9 +42,14 @@ namespace recmg {
 // the begin, a last element the end.  A prefetch row also gets its staging
 // row if the last batch missed it (pfrom): found here, where every row is
 // looked up in parallel, its two dependent loads stay off the sets' chains.
+// poff: the placement starts here (its prefetch list is empty: np = 0), else
+// NULL; last_n > 0: then the last batch's bits or counts.
 __global__ void __launch_bounds__(kBlock) k_sa_heads(DGlobal g, int64_t nu, int64_t np, int32_t have_fwd,
-                                                     int32_t last_stamp) {
-    if (*g.err) return;
+                                                     int32_t last_stamp, const int64_t *__restrict__ poff,
+                                                     const uint8_t *__restrict__ bits, int64_t last_n) {
+    const bool err = block_err(g);
+    if (poff && (int)blockIdx.x < g.T) placement_prep(g, blockIdx.x, poff, np, have_fwd);
+    if (err) return;
     __shared__ int64_t s_ts[RECMG_MAX_TABLES + 1], s_ps[RECMG_MAX_TABLES + 1];
     __shared__ int32_t s_uc[RECMG_MAX_TABLES], s_pc[RECMG_MAX_TABLES];
     for (int t = threadIdx.x; t <= g.T; t += blockDim.x) {
@@ -52,7 +57,7 @@ __global__ void __launch_bounds__(kBlock) k_sa_heads(DGlobal g, int64_t nu, int6
         s_ps[t] = g.pstart[t];
         if (t < g.T) {
             s_uc[t] = have_fwd ? g.st[t].ucount : 0;
-            s_pc[t] = g.st[t].pcount;
+            s_pc[t] = np > 0 ? g.st[t].pcount : 0;
         }
     }
     __syncthreads();
@@ -87,6 +92,7 @@ __global__ void __launch_bounds__(kBlock) k_sa_heads(DGlobal g, int64_t nu, int6
         if (loc == 0 || (uint32_t)list[loc - 1] % ns != set) sg[is_u ? 0 : 2] = (int)loc;
         if (loc + 1 == cnt || (uint32_t)list[loc + 1] % ns != set) sg[is_u ? 1 : 3] = (int)(loc + 1);
     }
+    if (last_n > 0) last_batch_share(g, bits, last_n);
 }
 
 // Minimum of v over each group of HL lanes (HL = 64: the wave, 32: each
@@ -433,8 +439,13 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
 }
 
 void launch_sa_place(const DGlobal &g, const PlcParams &p, int64_t nu, int64_t np, int32_t nsa, int64_t blocks1,
-                     int64_t blocks, int64_t max_blocks, bool heads, hipStream_t s) {
-    if (heads && nu + np > 0) k_sa_heads<<<grid_for(nu + np, kBlock, 8192), kBlock, 0, s>>>(g, nu, np, p.have_fwd, p.last_stamp);
+                     int64_t blocks, int64_t max_blocks, bool heads, const int64_t *poff, const uint8_t *bits, int64_t last_n,
+                     hipStream_t s) {
+    if (heads && (nu + np > 0 || poff)) {
+        const unsigned n = grid_for(nu + np, kBlock, 8192);
+        k_sa_heads<<<poff && n < (unsigned)g.T ? (unsigned)g.T : n, kBlock, 0, s>>>(g, nu, np, p.have_fwd, p.last_stamp,
+                                                                                   poff, bits, last_n);
+    }
     // tables of one set per wave come first (fewest sets), then those of two
     if (blocks1 > 0) k_sa_place<1><<<(unsigned)blocks1, kSaBlock, 0, s>>>(g, p, nsa, 0);
     if (blocks > blocks1) k_sa_place<2><<<(unsigned)(blocks - blocks1), kSaBlock, 0, s>>>(g, p, nsa, (int32_t)blocks1);
