@@ -685,23 +685,27 @@ int32_t early_gather(recmg_cache_t *c, hipStream_t cs) {
 // STAGED miss path: miss ids of the STAGED tables to the host, a parallel
 // host gather into pinned staging overlapped with the copies on the copy
 // stream; the compute stream waits for the copies.  The zero-copy tables'
-// misses are fetched by the kernel, launched once the host has read what it
-// needs (so that its waits do not wait for the kernel), beside the gather.
-int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
+// misses are fetched by the kernel, which also writes the locations of n indices
+// and the counters: launched once the host has read what it needs (so that its
+// waits do not wait for the kernel), beside the gather (in front of the read and
+// behind the pooled kernel the two cost a step of 164,000 indices 6 us).
+int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, const int32_t *indices, int64_t n, hipStream_t s) {
     const int T = c->T;
     HIP_TRY(copy_back(c, s));
     HIP_TRY(hipStreamSynchronize(s));
     const Back back(c->L, c->h_back);
     int32_t err = back.err;
-    auto zero_copy_fetch = [&]() -> int32_t {
+    auto fetch_kernel = [&]() -> int32_t {
         if (c->has_zc) {
             DispatchTimer dt(c, RECMG_STAGE_FWD_FETCH, true);
-            launch_fetch(c->g, log_slot, s, dt.a, dt.b);
+            launch_fetch(c->g, true, log_slot, indices, n, s, dt.a, dt.b);
             dt.issued();
+        } else {
+            launch_fetch(c->g, false, log_slot, indices, n, s);
         }
         return RECMG_OK;
     };
-    if (err) return zero_copy_fetch();  // the device flag already disables the rest
+    if (err) return fetch_kernel();  // the device flag already disables the rest
     std::vector<int64_t> nm(T);
     int64_t total = 0;
     for (int t = 0; t < T; ++t) {
@@ -711,7 +715,7 @@ int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
                                    hipMemcpyDeviceToHost, s));
         total += nm[t];
     }
-    if (total == 0) return zero_copy_fetch();
+    if (total == 0) return fetch_kernel();
     HIP_TRY(hipStreamSynchronize(s));
     const int64_t stride = c->L.stage_stride;
     hipStream_t cs = c->copy_stream ? c->copy_stream : s;
@@ -719,7 +723,7 @@ int32_t staged_fetch(recmg_cache_t *c, int64_t log_slot, hipStream_t s) {
         HIP_TRY(hipEventRecord(c->ev_ready, s));
         HIP_TRY(hipStreamWaitEvent(cs, c->ev_ready, 0));
     }
-    if ((err = zero_copy_fetch())) return err;
+    if ((err = fetch_kernel())) return err;
     auto work = [&](int t, int64_t lo, int64_t hi) {
         const int64_t ts = back.tstart[t], rb = c->geo[t].row_bytes;
         for (int64_t m = lo; m < hi; ++m) {
@@ -1300,6 +1304,7 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
     c->cur ^= 1;  // the other staging buffer: a pending fill may still read this one
     c->g.staging = c->stage[c->cur];
     const int64_t log_slot = c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1;
+    int64_t late_src = 0;
     {
         StageTimer tm(c, RECMG_STAGE_FWD_DEDUP, s);
         const bool small = n > 0 && small_batch(c->T, n, c->max_nblk);
@@ -1311,7 +1316,11 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
                          reinterpret_cast<int32_t *>(reinterpret_cast<char *>(g.st) + offsetof(TState, ucount)),
                          (int)(sizeof(TState) / 4), stamp, c->max_nblk, s);
             launch_fwd_probe(g, stamp, n, std::max<int64_t>(c->plc_np, 0), s);
-            launch_fwd_src(g, indices, n, s);
+            // Where each index's row lies is wanted by the pooled kernel, and by a
+            // placement: with the fetch, unless a placement on another stream
+            // may start before it.
+            if (!c->own_stream) late_src = n;
+            else launch_fwd_src(g, indices, n, s);
         }
     }
     // a placement on another stream may start here (recorded once placements
@@ -1322,9 +1331,9 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
         StageTimer tm(c, RECMG_STAGE_FWD_FETCH, s);
         if (!c->has_staged) {
             DispatchTimer dt(c, RECMG_STAGE_FWD_FETCH, true);
-            launch_fetch(g, log_slot, s, dt.a, dt.b);
+            launch_fetch(g, true, log_slot, indices, late_src, s, dt.a, dt.b);
             dt.issued();
-        } else if ((rc = staged_fetch(c, log_slot, s))) {  // launches the zero-copy tables' fetch too
+        } else if ((rc = staged_fetch(c, log_slot, indices, late_src, s))) {  // launches the zero-copy tables' fetch too
             return rc;
         }
     }
@@ -1350,7 +1359,7 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
         if (a) c->marks.push_back({RECMG_STAGE_FWD_POOL, a, b});
     }
     // the fetch has published the counters; a forward without one does it here
-    if (n == 0 || !c->has_zc) launch_fwd_finalize(g, log_slot, s);
+    if (n == 0) launch_fwd_finalize(g, log_slot, s);
     HIP_TRY(hipEventRecord(c->ev_fwd, s));  // the next fill may overwrite slots, the next forward the batch's arrays
     HIP_TRY(hipGetLastError());
     guard.done = true;

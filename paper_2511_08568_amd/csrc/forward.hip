@@ -131,8 +131,8 @@ __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t st
 // inverse map: where every index's row lives (slot, or -(miss + 1)).  The pooled
 // kernels make addresses of it themselves: an 8-byte address per index beside
 // the location was 38 MB of the 3.2 million indices' traffic here and there.
-__global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__restrict__ indices, int64_t n) {
-    if (*g.err) return;
+__device__ __forceinline__ void src_share(const DGlobal &g, const int32_t *__restrict__ indices, int64_t n,
+                                          int64_t first_block) {
     __shared__ int64_t s_start[RECMG_MAX_TABLES + 1];
     __shared__ const uint4 *s_rank[RECMG_MAX_TABLES];
     __shared__ int32_t s_ns[RECMG_MAX_TABLES], s_qb[RECMG_MAX_TABLES];
@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
     __syncthreads();
     // contiguous shares: a block meets one or two tables
     int64_t lo, hi;
-    block_share(n, &lo, &hi);
+    block_share(n, &lo, &hi, first_block);
     if (lo >= hi) return;
     int t = find_seg(s_start, g.T, lo);
     constexpr int Q = 4;
@@ -171,6 +171,10 @@ __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__
             g.src[i0 + q * kBlock] = g.slotU[s_start[tq[q]] + u];
         }
     }
+}
+
+__global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__restrict__ indices, int64_t n) {
+    if (!*g.err) src_share(g, indices, n, 0);
 }
 
 // Publishes the forward's counters; log_slot >= 0: also as that call's record
@@ -202,14 +206,22 @@ __device__ __forceinline__ void publish_forward(const DGlobal &g, int64_t log_sl
 
 // ZERO_COPY miss fetch: each distinct miss of a zero-copy table is read once
 // from pinned host memory (device-visible mapping) and written to its staging
-// row (STAGED tables' misses are staged by the host).  The grid's last block
-// publishes the forward's counters, which are complete before this kernel
-// starts: that costs no launch of its own (k_fwd_finalize took 3.4 us and a
-// dispatch after the pooled kernel of every forward).
-__global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot) {
+// row (STAGED tables' misses are staged by the host).  The block after the
+// copying ones publishes the forward's counters, which are complete before this
+// kernel starts: that costs no launch of its own (k_fwd_finalize took 3.4 us and a
+// dispatch after the pooled kernel of every forward).  n > 0: the blocks after
+// that one write the n locations (k_fwd_src's work), which then hides behind the
+// host link's time (a step of 8 32-way LFU tables of 25,000
+// indices 172 -> 164 us, a forward of 655,000 fp32 indices 434 -> 423), or, where
+// the host gathers every table's rows, behind that.
+__global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot, int32_t nb,
+                                                  const int32_t *__restrict__ indices, int64_t n) {
     if (*g.err) return;
-    const int64_t nb = (int64_t)gridDim.x - 1;
-    if ((int64_t)blockIdx.x == nb) {  // block-uniform
+    if ((int32_t)blockIdx.x > nb) {  // block-uniform
+        src_share(g, indices, n, nb + 1);
+        return;
+    }
+    if ((int32_t)blockIdx.x == nb) {  // block-uniform
         publish_forward(g, log_slot);
         return;
     }
@@ -841,9 +853,10 @@ void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, int64_t np, hi
     k_fwd_probe<<<grid_for(n > np ? n : np, kProbeRound, 8192), kProbeRound, 0, s>>>(g, stamp, np > 0 ? 1 : 0);
 }
 
+static unsigned src_blocks(int64_t n) { return grid_for(n, kBlock * items_per_thread(n, 4), 16384); }
+
 void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStream_t s) {
-    if (n <= 0) return;
-    k_fwd_src<<<grid_for(n, kBlock * items_per_thread(n, 4), 16384), kBlock, 0, s>>>(g, indices, n);
+    if (n > 0) k_fwd_src<<<src_blocks(n), kBlock, 0, s>>>(g, indices, n);
 }
 
 #ifndef RECMG_FETCH_BLOCKS
@@ -855,10 +868,12 @@ void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStre
 // (the next placement runs beside it).  Measured on configuration 3 (64-256
 // blocks): 96 is best with 32-way sets (k_sa_place's critical path runs
 // alongside), within 1% of the best without prefetch and on configuration 5.
-void launch_fetch(const DGlobal &g, int64_t log_slot, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    const dim3 grid(RECMG_FETCH_BLOCKS + 1);  // the last block publishes the counters
-    if (ev0 || ev1) hipExtLaunchKernelGGL(k_fetch, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, log_slot);
-    else k_fetch<<<grid, kBlock, 0, s>>>(g, log_slot);
+void launch_fetch(const DGlobal &g, bool copies, int64_t log_slot, const int32_t *indices, int64_t n, hipStream_t s,
+                  hipEvent_t ev0, hipEvent_t ev1) {
+    const int32_t nb = copies ? RECMG_FETCH_BLOCKS : 0;
+    const dim3 grid(nb + 1 + (n > 0 ? src_blocks(n) : 0));
+    if (ev0 || ev1) hipExtLaunchKernelGGL(k_fetch, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, log_slot, nb, indices, n);
+    else k_fetch<<<grid, kBlock, 0, s>>>(g, log_slot, nb, indices, n);
 }
 
 int pool_kind(int dtype, int vec, int wlw, int wr) {

@@ -32,8 +32,9 @@ void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStre
 // fetch, and the forward's counters published by a block of its own (log_slot:
 // record of this call in the stats log, or -1).
 // ev0 / ev1 (may be null): recorded by the dispatch itself around the kernel
-void launch_fetch(const DGlobal &g, int64_t log_slot, hipStream_t s, hipEvent_t ev0 = nullptr,
-                  hipEvent_t ev1 = nullptr);
+// copies = false: only the counters; n > 0: the n locations of launch_fwd_src too
+void launch_fetch(const DGlobal &g, bool copies, int64_t log_slot, const int32_t *indices, int64_t n, hipStream_t s,
+                  hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Pooled-sum kernels: kinds [0, kPoolKindsGroup) are the group-per-bag kernel
 // (dtype * 2 + vec), the rest the wave-per-bag kernel per (dtype, wlw, wr).
 constexpr int kPoolKindsGroup = 6, kPoolKinds = kPoolKindsGroup + 15;

@@ -599,9 +599,10 @@ __device__ __forceinline__ int32_t wave_append(bool want, int t, int32_t *counte
 // This block's contiguous share [*lo, *hi) of an index space of n, in whole
 // blocks of blockDim.x: a block then meets one or two tables, and its LDS
 // counters reach the table states with one or two atomics.
-__device__ __forceinline__ void block_share(int64_t n, int64_t *lo, int64_t *hi) {
-    const int64_t per = ((n + gridDim.x - 1) / gridDim.x + blockDim.x - 1) / blockDim.x * blockDim.x;
-    *lo = (int64_t)blockIdx.x * per;
+__device__ __forceinline__ void block_share(int64_t n, int64_t *lo, int64_t *hi, int64_t first_block = 0) {
+    const int64_t nb = (int64_t)gridDim.x - first_block;
+    const int64_t per = ((n + nb - 1) / nb + blockDim.x - 1) / blockDim.x * blockDim.x;
+    *lo = ((int64_t)blockIdx.x - first_block) * per;
     *hi = *lo + per < n ? *lo + per : n;
 }
 
