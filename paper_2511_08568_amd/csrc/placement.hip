@@ -315,8 +315,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_evict(DGlobal g, PlcParams p, in
             wb = __shfl(wb, 0);
             if (ev) s_free[wb + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)k;
         }
-        __syncthreads();
-        if (s_n > kEvictBuf - 4 * (int)blockDim.x) flush();  // room for one more pass of the block
+        if (list_past(&s_n, kEvictBuf - 4 * (int)blockDim.x)) flush();  // room for one more pass of the block
     }
     __syncthreads();
     flush();

@@ -266,6 +266,20 @@ __device__ __forceinline__ void last_batch_share(const DGlobal &g, const uint8_t
     }
 }
 
+// ----------------------------------------------------------------- freed slots
+
+// Whether a block's LDS list has grown past `limit`, the same answer in every
+// thread: the count is read between two barriers, so no wave appends to it again
+// before the slowest has read it.  (With the first barrier alone a fast wave's
+// next append can fall between two waves' reads; they would then part ways in
+// front of the flush, which has barriers of its own.)  Every thread calls.
+__device__ __forceinline__ bool list_past(const int *s_n, int limit) {
+    __syncthreads();
+    const bool past = *s_n > limit;
+    __syncthreads();
+    return past;
+}
+
 // ----------------------------------------------------------------- map upkeep
 
 // A map of many deleted entries is rebuilt in the placement after the one that

@@ -338,8 +338,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
         const int hn = block_sum(here, tmp);
         if (threadIdx.x == 0 && hn) atomicSub(&tb.rcnt[cur][ch], hn);
         nring += here;
-        __syncthreads();
-        if (s_n > kRingEvictBuf - 4 * (int)blockDim.x) flush();
+        if (list_past(&s_n, kRingEvictBuf - 4 * (int)blockDim.x)) flush();
     }
     if (compact) {  // the other buffer's chunk counts: [0, moved) live
         const int32_t nchunks = tb.ring_cap / kRingChunk;
@@ -373,8 +372,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
                 ev[q] = sl[q] >= 0;
             }
             evict(ev, sl, r);
-            __syncthreads();
-            if (s_n > kRingEvictBuf - Q * (int)blockDim.x) flush();
+            if (list_past(&s_n, kRingEvictBuf - Q * (int)blockDim.x)) flush();
         }
     }
     __syncthreads();
