@@ -212,22 +212,23 @@ __global__ void __launch_bounds__(kBlock) k_mark_resident(DGlobal g) {
     }
 }
 
-// The table of bitmap block blk (T <= blockDim.x): every table's bounds are
-// tested at once, where a binary search would chain its loads.  Ends with a
-// barrier.
+// The table of bitmap block blk (T <= blockDim.x), or -1 if the error word is set
+// (read once per block, see block_err): every table's bounds are tested at once,
+// where a binary search would chain its loads.  Ends with a barrier.
 __device__ __forceinline__ int block_table(const DGlobal &g, int blk) {
-    __shared__ int s_t;
+    __shared__ int s_t, s_err;
     const int t = threadIdx.x;
+    if (t == 0) s_err = *g.err;
     if (t < g.T && g.bm_block_start[t] <= blk && blk < g.bm_block_start[t + 1]) s_t = t;
     __syncthreads();
-    return s_t;
+    return s_err ? -1 : s_t;
 }
 
 __global__ void __launch_bounds__(kBlock) k_bm_count(DGlobal g) {
-    if (*g.err) return;
     __shared__ int tmp[16];
     const int blk = blockIdx.x;
     const int t = block_table(g, blk);
+    if (t < 0) return;  // block-uniform
     const DTable &tb = g.tabs[t];
     const int64_t w0 = (int64_t)(blk - tb.bm_block0) * kWordsPerBlock + threadIdx.x * kWordsPerThread;
     const uint4 w = *reinterpret_cast<const uint4 *>(tb.bitmap + w0);
@@ -239,10 +240,10 @@ __global__ void __launch_bounds__(kBlock) k_bm_count(DGlobal g) {
 // The parts' copies of a bitmap block put together: its non-zero words to the
 // (all-zero) bitmap, their popcount to blocksum.
 __global__ void __launch_bounds__(kBlock) k_bm_merge(DGlobal g, int parts) {
-    if (*g.err) return;
     __shared__ int tmp[16];
     const int blk = blockIdx.x;
     const int t = block_table(g, blk);
+    if (t < 0) return;  // block-uniform
     const DTable &tb = g.tabs[t];
     const int64_t words = (int64_t)g.total_bm_blocks * kWordsPerBlock;
     const uint32_t *src = g.part_bm + (int64_t)blk * kWordsPerBlock + threadIdx.x * kWordsPerThread;
@@ -262,7 +263,7 @@ __global__ void __launch_bounds__(kBlock) k_bm_merge(DGlobal g, int parts) {
 // One block per table: exclusive scan of the table's block counts (for tables
 // of more blocks than k_bm_emit adds up by itself).
 __global__ void __launch_bounds__(1024) k_bm_scan(DGlobal g) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int tmp[16];
     const int t = blockIdx.x;
     const int b0 = g.bm_block_start[t], nb = g.bm_block_start[t + 1] - b0;
@@ -286,10 +287,10 @@ __global__ void __launch_bounds__(1024) k_bm_scan(DGlobal g) {
 constexpr int kEmitThreads = kWordsPerBlock;
 template <int MODE, bool SCANNED>
 __global__ void __launch_bounds__(kEmitThreads) k_bm_emit(DGlobal g, int32_t *counts, int count_stride, int32_t stamp) {
-    if (*g.err) return;
     __shared__ int tmp[16];
     const int blk = blockIdx.x;
     const int t = block_table(g, blk);
+    if (t < 0) return;  // block-uniform
     const DTable &tb = g.tabs[t];
     const int b0 = tb.bm_block0, own = g.blocksum[blk];
     int first;

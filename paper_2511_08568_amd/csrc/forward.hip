@@ -43,7 +43,8 @@ __global__ void __launch_bounds__(kBlock) k_fwd_prep(DGlobal g, const int64_t *_
 // iff its rank word carries this forward's stamp and its bit.
 constexpr int kProbeRound = 256;
 __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t stamp, int cover) {
-    if (*g.err) return;
+    __shared__ int s_err;  // read once per block (block_err), behind the barriers of lay_tables
+    if (threadIdx.x == 0) s_err = *g.err;
     __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ int64_t s_ts[RECMG_MAX_TABLES];
     __shared__ int s_hits[RECMG_MAX_TABLES], s_hits_pf[RECMG_MAX_TABLES], s_miss[RECMG_MAX_TABLES];
@@ -53,6 +54,7 @@ __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t st
         s_ts[threadIdx.x] = g.tstart[threadIdx.x];
     }
     const int32_t n = lay_tables(g.T, [&](int t) { return g.st[t].ucount; }, s_pre, tmp);
+    if (s_err) return;  // block-uniform
     int32_t lo, hi;
     round_share(n, kProbeRound, &lo, &hi);
     for (int32_t base = lo; base < hi; base += kProbeRound) {  // block-uniform
@@ -174,7 +176,7 @@ __device__ __forceinline__ void src_share(const DGlobal &g, const int32_t *__res
 }
 
 __global__ void __launch_bounds__(kBlock) k_fwd_src(DGlobal g, const int32_t *__restrict__ indices, int64_t n) {
-    if (!*g.err) src_share(g, indices, n, 0);
+    if (!block_err(g)) src_share(g, indices, n, 0);
 }
 
 // Publishes the forward's counters; log_slot >= 0: also as that call's record
@@ -216,7 +218,7 @@ __device__ __forceinline__ void publish_forward(const DGlobal &g, int64_t log_sl
 // the host gathers every table's rows, behind that.
 __global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot, int32_t nb,
                                                   const int32_t *__restrict__ indices, int64_t n) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     if ((int32_t)blockIdx.x > nb) {  // block-uniform
         src_share(g, indices, n, nb + 1);
         return;
@@ -412,11 +414,14 @@ __global__ void __launch_bounds__(kBlock) k_pool(DGlobal g, const int64_t *__res
                                                  float *__restrict__ out, const int32_t *__restrict__ bstart,
                                                  const int32_t *__restrict__ btab, int32_t nt, int32_t boff,
                                                  int32_t nblk) {
-    if (*g.err) return;
     const int lb = boff + xcd_block(nblk);
-    __shared__ int s_k;
-    if (threadIdx.x == 0) s_k = find_seg32(bstart, nt, lb);
+    __shared__ int s_k, s_err;  // the error word is read once per block (block_err)
+    if (threadIdx.x == 0) {
+        s_err = *g.err;
+        s_k = find_seg32(bstart, nt, lb);
+    }
     __syncthreads();
+    if (s_err) return;  // block-uniform
     const int k = s_k, t = btab[k];
     pool_table<DT, VEC>(g, g.tabs[t], t, B, offsets, out, lb - bstart[k]);
 }
@@ -814,12 +819,13 @@ __global__ void __launch_bounds__(kBlock) k_pool_any(DGlobal g, const int64_t *_
                                                      const int32_t *__restrict__ src, int32_t B,
                                                      float *__restrict__ out, const int32_t *__restrict__ bstart,
                                                      const int32_t *__restrict__ btab, int32_t nt, int32_t nblk) {
-    if (*g.err) return;
     const int lb = xcd_block(nblk);
-    __shared__ int s_k;
+    __shared__ int s_k, s_err;  // the error word is read once per block (block_err)
+    if (threadIdx.x == 0) s_err = *g.err;
     // (blocks of the tables in btab order; a table without blocks matches none)
     if ((int)threadIdx.x < nt && bstart[threadIdx.x] <= lb && lb < bstart[threadIdx.x + 1]) s_k = threadIdx.x;
     __syncthreads();
+    if (s_err) return;  // block-uniform
     const int k = __builtin_amdgcn_readfirstlane(s_k);
     const int t = btab[k], blk = lb - bstart[k];
     const DTable &tb = g.tabs[t];

@@ -59,7 +59,8 @@ __global__ void __launch_bounds__(kBlock) k_plc_last(DGlobal g, const int64_t *_
 // last_n > 0: then the last batch's bits or counts.
 __global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last_stamp, const uint8_t *__restrict__ bits,
                                                          int64_t last_n) {
-    if (*g.err) return;
+    __shared__ int s_err;  // read once per block (block_err), behind the barriers of lay_tables
+    if (threadIdx.x == 0) s_err = *g.err;
     __shared__ int32_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ int64_t s_ps[RECMG_MAX_TABLES];
     __shared__ int s_res[RECMG_MAX_TABLES], s_new[RECMG_MAX_TABLES];
@@ -69,6 +70,7 @@ __global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last
         s_ps[threadIdx.x] = g.pstart[threadIdx.x];
     }
     const int32_t n = lay_tables(g.T, [&](int t) { return g.tabs[t].ways ? 0 : g.st[t].pcount; }, s_pre, tmp);
+    if (s_err) return;  // block-uniform
     int32_t lo, hi;
     round_share(n, kRound, &lo, &hi);
     for (int32_t base = lo; base < hi; base += kRound) {  // block-uniform
@@ -168,7 +170,7 @@ __device__ __forceinline__ uint64_t pass_threshold(const DGlobal &g, TState &st,
 
 // Scores of every candidate (written back) and the first select pass.
 __global__ void __launch_bounds__(kBlock) k_plc_update(DGlobal g, PlcParams p) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int s_hist[kRadix];
     const int t = blockIdx.y;
     const DTable &tb = g.tabs[t];
@@ -191,7 +193,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_update(DGlobal g, PlcParams p) {
 }
 
 __global__ void __launch_bounds__(kBlock) k_plc_select(DGlobal g, PlcParams p, int pass) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int s_hist[kRadix];
     const int t = blockIdx.y;
     const DTable &tb = g.tabs[t];
@@ -212,7 +214,7 @@ __global__ void __launch_bounds__(kBlock) k_plc_select(DGlobal g, PlcParams p, i
 // pass's histogram in LDS and its digit), one launch instead of 2 per pass.
 constexpr int kRankSmallThreads = 1024;
 __global__ void __launch_bounds__(kRankSmallThreads) k_plc_rank_small(DGlobal g, PlcParams p) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int s_hist[kRadix];
     __shared__ int tmp[16];
     const int t = blockIdx.x;
@@ -534,7 +536,7 @@ __device__ __forceinline__ void publish_placement(const DGlobal &g, int t, int64
 // k_plc_end) and the staging buffer of the forward before that placement,
 // which the next forward does not use.
 __global__ void __launch_bounds__(kBlock) k_plc_fill(DGlobal g, const int64_t *__restrict__ fdesc, int phase) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     // the blocks that copy: zero-copy fills as many as k_plc_end chose
     // (fdesc[3]), HBM-to-HBM copies of STAGED rows the whole grid
     const int64_t nb = phase == FILL_STAGED ? (int64_t)gridDim.x
@@ -584,7 +586,7 @@ constexpr int kFillGridBlocks = RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_SHARED
 // Table blocks also clear the radix select's histograms.
 __global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, int64_t log_slot, int32_t nfill,
                                                     int32_t nsa, int32_t passes) {
-    if (*g.err) return;  // set by earlier kernels only, but for broken ring counts (below)
+    if (block_err(g)) return;
     __shared__ long long tmp[16];
     if ((int)blockIdx.x < nfill) {  // block-uniform, as the other roles
         fill_rows(g, FILL_ZERO_COPY, nfill, [&](int t) { return g.ftstart[t] + g.pstart[t]; },

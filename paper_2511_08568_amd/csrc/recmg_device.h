@@ -653,9 +653,11 @@ __device__ __forceinline__ uint64_t make_key(int32_t score, int32_t row, int row
     return ((uint64_t)(uint32_t)score << rowbits) | (uint64_t)(uint32_t)row;
 }
 
-// The error word read once per block.  Evict and admit may set it (a broken
-// invariant) while other blocks of the same kernel start, and the waves of a
-// block must agree before the block's barriers.
+// The error word read once per block, for every kernel whose waves work on one
+// another's LDS or meet at barriers: blocks of the same kernel, or a call on
+// another stream, may set the word while the block starts, and a wave that left
+// alone would leave its part of the block's LDS (tables' starts, counts, a
+// table's number) unset for the waves that index with it.
 __device__ __forceinline__ bool block_err(const DGlobal &g) {
     __shared__ int s_err;
     if (threadIdx.x == 0) s_err = *g.err;

@@ -94,7 +94,7 @@ __device__ __forceinline__ int lds_bound(const int32_t *a, int n, int32_t v, boo
 // settled values.
 constexpr int kTileQ = 4, kTile = kTileQ * kBlock;
 __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int32_t s_row[kTile];  // the tile's pending rows, then its U rows
     __shared__ int32_t s_split[2];
     __shared__ int tmp[16];
@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_touch(DGlobal g, PlcParams p) {
 // One block per table: ring_cut, kept in the table's state for the kernels
 // that apply it.
 __global__ void __launch_bounds__(kRingThreads) k_ring_cut(DGlobal g, PlcParams p) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int tmp[16];
     const int t = blockIdx.x;
     const DTable &tb = g.tabs[t];
@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kBlock) k_ring_evict(DGlobal g, PlcParams p) {
 // their slots (-1 where not kept) to the pending list of buffer wr, the kept
 // residents losing F_INP.  Admitted candidates' slots come from admission.
 __global__ void __launch_bounds__(kBlock) k_ring_append(DGlobal g, PlcParams p, int wr) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ int tmp[16];
     const int t = blockIdx.y;
     const DTable &tb = g.tabs[t];

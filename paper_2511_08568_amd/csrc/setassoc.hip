@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(kSaBlock) k_sa_place(DGlobal g, PlcParams p, i
 // blockIdx.x is the table (in sa_btab order), blockIdx.y one of gridDim.y slices
 // of its blocks (tables of few blocks: one block of k_plc_end).
 __global__ void __launch_bounds__(1024) k_sa_sum(DGlobal g) {
-    if (*g.err) return;
+    if (block_err(g)) return;
     __shared__ long long tmp[16];
     sa_sum_records(g, blockIdx.x, blockIdx.y, gridDim.y, tmp);
 }
