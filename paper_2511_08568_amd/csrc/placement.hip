@@ -44,8 +44,9 @@ __global__ void k_plc_prep(DGlobal g, const int64_t *__restrict__ poff, int64_t 
 __global__ void __launch_bounds__(kBlock) k_plc_last(DGlobal g, const int64_t *__restrict__ poff, int64_t np,
                                                      const uint8_t *__restrict__ bits, int64_t n) {
     const bool err = block_err(g);
+    const bool bad = list_malformed(g, poff, np);  // a malformed call changes nothing
     if ((int)blockIdx.x < g.T) placement_prep(g, blockIdx.x, poff, np, 1);
-    if (!err) last_batch_share(g, bits, n);
+    if (!err && !bad) last_batch_share(g, bits, n);
 }
 
 // Classify every distinct prefetch row of the fully associative tables (Alg.

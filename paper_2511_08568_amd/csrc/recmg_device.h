@@ -717,6 +717,19 @@ __device__ __forceinline__ void forward_prep(const DGlobal &g, int t, const int6
     if (bad) atomicOr(g.err, ERR_OFFSETS);
 }
 
+// Whether a prefetch list's offsets are malformed, for blocks that change the
+// cache before the next kernel could see the error word that placement_prep
+// raises.  A wave looks at every table, so all waves know it without a barrier.
+__device__ __forceinline__ bool list_malformed(const DGlobal &g, const int64_t *__restrict__ poff, int64_t np) {
+    uint64_t bad = 0;
+    for (int t0 = 0; t0 < g.T; t0 += 64) {
+        const int t = t0 + (int)(threadIdx.x & 63);
+        const int64_t v = t < g.T ? poff[t] : 0, e = t < g.T ? poff[t + 1] : 0;
+        bad |= __ballot(v > e || v < 0 || e > np || (t == 0 && v != 0) || (t == g.T - 1 && e != np));
+    }
+    return bad != 0;
+}
+
 // Start of a placement for table t, by thread 0 of one block: the prefetch
 // list's offsets checked, the table's range and accumulators set.
 __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const int64_t *__restrict__ poff, int64_t np,

@@ -47,7 +47,8 @@ namespace recmg {
 __global__ void __launch_bounds__(kBlock) k_sa_heads(DGlobal g, int64_t nu, int64_t np, int32_t have_fwd,
                                                      int32_t last_stamp, const int64_t *__restrict__ poff,
                                                      const uint8_t *__restrict__ bits, int64_t last_n) {
-    const bool err = block_err(g);
+    bool err = block_err(g);
+    if (poff) err |= list_malformed(g, poff, np);  // a malformed call changes nothing
     if (poff && (int)blockIdx.x < g.T) placement_prep(g, blockIdx.x, poff, np, have_fwd);
     if (err) return;
     __shared__ int64_t s_ts[RECMG_MAX_TABLES + 1], s_ps[RECMG_MAX_TABLES + 1];
@@ -407,8 +408,8 @@ __global__ void __launch_bounds__(kSaBlock) k_sa_place(DGlobal g, PlcParams p, i
         // the other counts go to this block's record (plain stores: atomics from
         // every block would queue on the table state's few lines), added up per
         // table by k_sa_sum
-        if (lane < 7) g.sa_part[(int64_t)bid * 8 + lane] = pick_lane_tot(tot, lane + 1);
-        if (lane == 7) g.sa_part[(int64_t)bid * 8 + 7] = (int64_t)d;  // the digest's bits
+        if (lane < 7 && !err) g.sa_part[(int64_t)bid * 8 + lane] = pick_lane_tot(tot, lane + 1);
+        if (lane == 7 && !err) g.sa_part[(int64_t)bid * 8 + 7] = (int64_t)d;  // the digest's bits
     }
     __syncthreads();
     if (changed) {

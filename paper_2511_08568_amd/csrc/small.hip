@@ -276,10 +276,51 @@ __device__ __forceinline__ void lds_sum(int v, int *counter) {
     if ((threadIdx.x & 63) == 0 && v) atomicAdd(counter, v);
 }
 
+// Whether every id of a list lies in its table, whose first ids s_po gives: a
+// wave takes a contiguous share, its lanes neighbouring ids.  The loads of the
+// first kCheck of a thread's ids may be issued well before they are looked at.
+constexpr int kCheck = 8;
+struct IdCheck {
+    int64_t lo, hi;
+    uint32_t r[kCheck];
+    __device__ void load(const int32_t *__restrict__ keys, int64_t i0) {
+#pragma unroll
+        for (int q = 0; q < kCheck; ++q) r[q] = i0 + q * 64 < hi ? (uint32_t)keys[i0 + q * 64] : 0u;
+    }
+    __device__ void start(const int32_t *__restrict__ keys, int64_t n) {
+        const int64_t per = ((n + kSmallThreads - 1) / kSmallThreads) * 64;
+        lo = ((int64_t)threadIdx.x >> 6) * per;
+        hi = lo + per < n ? lo + per : n;
+        lo += threadIdx.x & 63;
+        load(keys, lo);
+    }
+    // true in every thread that met no bad id
+    __device__ bool finish(const int32_t *__restrict__ keys, int T, const int64_t *s_po, const uint32_t *s_rows) {
+        if (lo >= hi) return true;
+        int t = find_seg(s_po, T, lo);
+        bool ok = true;
+        for (int64_t i0 = lo;;) {
+#pragma unroll
+            for (int q = 0; q < kCheck; ++q) {
+                if (i0 + q * 64 >= hi) continue;
+                while (i0 + q * 64 >= s_po[t + 1]) ++t;
+                ok &= r[q] < s_rows[t];  // negative ids too
+            }
+            i0 += kCheck * 64;
+            if (i0 >= hi) return ok;
+            load(keys, i0);
+        }
+    }
+};
+
 // Everything of a placement but the sets of set-associative tables, the fill
 // and the published counters, for one table per block.  Same results as the
 // general sequence (placement.hip, ring.hip, k_sa_heads); what k_plc_end reads
 // from the table's state is written once, by thread 0, at the end.
+// Every block checks the whole list, its other tables' ids too (at most some ten
+// thousand, read beside its own), before it changes anything: no launch comes
+// between the check and the change, so a block that looked at its own table alone
+// would change the cache in a call that another table's ids make void.
 //   all tables   list offsets checked, caching bits or batch counts of the last
 //                batch, set(P) sorted (PU)
 //   set-assoc.   each set's event segments and the prefetch rows' staging rows
@@ -304,6 +345,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
     __shared__ int s_c[C_N], s_ch[Q];
     __shared__ int s_err, s_bad_id;
     __shared__ unsigned long long s_dig;
+    __shared__ int64_t s_po[RECMG_MAX_TABLES + 1];
+    __shared__ uint32_t s_rows[RECMG_MAX_TABLES];
     static_assert(sizeof(bz.w4) >= kRadix * sizeof(int), "the ranking's histogram takes a bitmap's place");
     const int t = blockIdx.x, tid = threadIdx.x;
     const DTable tb = g.tabs[t];
@@ -312,22 +355,51 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
         s_err = *g.err;  // read once: another block may set it meanwhile
         s_bad_id = 0;
         s_dig = 0;
+        s_po[g.T] = np;
+    }
+    if (tid < g.T) {
+        s_po[tid] = poff[tid];
+        s_rows[tid] = (uint32_t)g.tabs[tid].rows;
     }
     if (tid < C_N) s_c[tid] = 0;
     if (tid < Q) s_ch[tid] = 0;
     const int nw = tb.bm_words;
     bm.clear(nw);
     const int64_t lo = poff[t], hi = poff[t + 1];
+    const bool bad_off = list_malformed(g, poff, np);
     __syncthreads();
     if (s_err) return;  // block-uniform
-    if (lo < 0 || hi < lo || hi > np || (t == 0 && lo != 0) || (t == g.T - 1 && hi != np)) {  // block-uniform
+    if (bad_off) {      // block-uniform
         if (tid == 0) atomicOr(g.err, ERR_OFFSETS);
         return;
     }
+    // what the last batch brings (a thread's first Q of it) is read beside the
+    // ids, and applied once they are known to be good
     const int64_t ts = g.tstart[t], te = g.tstart[t + 1], fts = p.have_fwd ? ts : 0;
     const int32_t nu = p.have_fwd ? st.ucount : 0, nm = p.have_fwd ? st.mcount : 0;
     const int32_t n_res = st.n_res;
-    const bool reb = st.rebuild_next != 0;
+    const bool reb = st.rebuild_next != 0, or_bits = p.prio && bits && p.have_fwd;
+    int32_t lv[Q], lw[Q];  // PRIORITY: caching bit, location; LFU_BATCH: row, its count
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int64_t i = ts + q * kSmallThreads + tid;
+        lv[q] = lw[q] = 0;
+        if (or_bits && i < te) lv[q] = bits[i], lw[q] = (int32_t)gload4(g.src + i);
+        if (p.lfu && i - ts < nu) lv[q] = (int32_t)gload4(g.U + i);
+    }
+    IdCheck check;
+    if (g.T > 1) check.start(rows, np);
+    if (p.lfu)
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q * kSmallThreads + tid < nu) lw[q] = (int32_t)gload4(tb.freq + lv[q]);
+    if (!mark_ids(bm, tb, rows, lo, hi)) s_bad_id = 1;
+    if (g.T > 1 && !check.finish(rows, g.T, s_po, s_rows)) s_bad_id = 1;
+    __syncthreads();
+    if (s_bad_id) {  // block-uniform
+        if (tid == 0) atomicOr(g.err, ERR_RANGE);
+        return;
+    }
     if (tid == 0) {
         g.pstart[t] = lo;
         g.ftstart[t] = fts;
@@ -336,22 +408,23 @@ __global__ void __launch_bounds__(kSmallThreads) k_plc_small(DGlobal g, PlcParam
             g.ftstart[g.T] = p.have_fwd ? te : 0;
         }
     }
-    if (p.prio && bits && p.have_fwd) {
+    if (or_bits) {
         // OR of the caching bits per row; every writer stores the same value
-        for (int64_t i = ts + tid; i < te; i += kSmallThreads) {
-            if (!bits[i]) continue;
-            const int32_t s = g.src[i];
+        auto set_bit = [&](int32_t s) {
             uint8_t *f = s >= 0 ? tb.slot_cbit + s : g.mcbit + ts + (-(int64_t)s - 1);
             if (!*f) *f = 1;
-        }
+        };
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (lv[q]) set_bit(lw[q]);
+        for (int64_t i = ts + Q * kSmallThreads + tid; i < te; i += kSmallThreads)
+            if (bits[i]) set_bit(g.src[i]);
     }
-    if (p.lfu)
-        for (int32_t u = tid; u < nu; u += kSmallThreads) tb.freq[g.U[ts + u]] += 1;  // distinct rows
-    if (!mark_ids(bm, tb, rows, lo, hi)) s_bad_id = 1;
-    __syncthreads();
-    if (s_bad_id) {  // block-uniform
-        if (tid == 0) atomicOr(g.err, ERR_RANGE);
-        return;
+    if (p.lfu) {  // distinct rows
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q * kSmallThreads + tid < nu) tb.freq[lv[q]] = lw[q] + 1;
+        for (int32_t u = Q * kSmallThreads + tid; u < nu; u += kSmallThreads) tb.freq[g.U[ts + u]] += 1;
     }
     const int32_t pc = bm.scan(nw, tmp);
     int32_t *PU = g.PU + lo;

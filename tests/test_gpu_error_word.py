@@ -71,3 +71,45 @@ def test_malformed_placement_beside_a_forward(rows, bags, policy, ways, what):
             assert bool((out == 7.0).all()), "a call after the error wrote its output"
         finally:
             g.close()
+
+
+@pytest.mark.parametrize("what", ["row past the end", "negative row", "offsets decrease", "offsets end short",
+                                  "empty list, offsets malformed"])
+@pytest.mark.parametrize("policy,ways", [("lru", 0), ("priority", 0), ("lfu", 0), ("priority", 5), ("lfu", 5)])
+def test_malformed_small_placement_changes_nothing(policy, ways, what):
+    """One malformed table between good ones, in the kernel that runs a whole
+    placement per table: no block may change its table's cache for a call that
+    another table makes void.  The caller's workspace shows it: after the call
+    only the error word differs."""
+    w, tabs, batches = _case([3000, 700, 2000], 60, 5, 20, policy=policy, ways=ways)
+    P = np.concatenate([np.arange(0, tb.rows, 3) for tb in w.tables]).astype(np.int32)
+    poff = np.concatenate([[0], np.cumsum([len(range(0, tb.rows, 3)) for tb in w.tables])]).astype(np.int64)
+    idx, off = batches[0]
+    bits = (np.arange(idx.size) % 3 == 0).astype(np.uint8) if policy == "priority" else None
+    g = GpuRunner(w, tabs, max_indices=idx.size, max_prefetch=P.size)
+    try:
+        g.placement(P, poff)
+        g.forward(idx, off)
+        _, total, code = g.cache.stats(strict=False)
+        assert code == bd.RECMG_OK
+        bad, boff = (P + 1) % 700, poff.copy()
+        if what == "row past the end":
+            bad[poff[2] - 1] = 700
+        elif what == "negative row":
+            bad[poff[1]] = -1
+        elif what == "offsets decrease":
+            boff[2] = boff[1] - 1
+        elif what == "offsets end short":
+            boff[3] -= 1
+        else:
+            bad, boff = bad[:0], np.array([0, 0, 1, 0], np.int64)
+        d = g.to_dev(bad) if bad.size else None, g.to_dev(boff), None if bits is None else g.to_dev(bits)
+        torch.cuda.synchronize()
+        before = g.cache.workspace.clone()
+        g.cache.placement(*d)
+        _, after, code = g.cache.stats(strict=False)
+        assert code == bd.RECMG_E_RANGE and after == total
+        at = torch.nonzero(before != g.cache.workspace).flatten()
+        assert 1 <= at.numel() <= 4 and int(at[-1]) - int(at[0]) < 4, f"{at.numel()} bytes of the workspace changed"
+    finally:
+        g.close()
