@@ -201,8 +201,10 @@ int32_t recmg_cache_init(const recmg_config_t *cfg, recmg_cache_t **out);
  * device until the process ends); cfg->device_workspace and
  * device_workspace_bytes are ignored.  Nothing is allocated on the device.
  * The host staging buffer (STAGED) still comes from the caller.
- *   RECMG_E_NOMEM   the configuration's workspace (recmg_query_workspace) is
- *                   larger than 32 MiB;
+ *   RECMG_E_NOMEM   the configuration's workspace is larger than 32 MiB
+ *                   (recmg_query_workspace, less the memory that only makes
+ *                   large placements and batches faster: a handle goes without
+ *                   that where the array would not hold it);
  *   RECMG_E_STATE   another live handle of this device holds the array (at
  *                   most one at a time; recmg_cache_destroy releases it).
  * The array keeps what the last handle left in it; init clears everything a

@@ -82,6 +82,7 @@ struct Layout {
     int32_t total_bm_blocks = 0;
     int32_t mark_parts = 1;
     size_t part_bm = 0;
+    int32_t hist_sets = 0;  // histograms of the radix select: one per pass, 0 where one block ranks every table
 };
 
 int32_t check_config(const recmg_config_t *cfg, std::vector<Geom> *geo) {
@@ -179,7 +180,19 @@ bool any_staged(const std::vector<Geom> &geo) {
     return false;
 }
 
-void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout *L) {
+// Passes of the radix select over the longest key that a table without a ring can get.
+int32_t most_passes(const recmg_config_t *cfg, const std::vector<Geom> &geo) {
+    int64_t rows = 1;
+    for (const Geom &g : geo) rows = std::max(rows, g.rows);
+    const int bits = bitlen(cfg->policy == RECMG_PRIORITY ? (uint64_t)cfg->eviction_speed + 1 : (uint64_t)INT32_MAX) +
+                     std::max(1, bitlen((uint64_t)(rows - 1)));
+    return (bits + kRadixBits - 1) / kRadixBits;
+}
+
+// tight: without the memory that only makes calls faster (the copies that many
+// ids are marked in, the histograms that let several blocks rank a table), for
+// a configuration that fits the static workspace only so.
+void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout *L, bool tight = false) {
     const int T = (int)geo.size();
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -240,7 +253,18 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     L->fill_src = take(4 * 2 * (mi + mp));   // two fill lists: a placement's fill may still
     L->fill_slot = take(4 * 2 * (mi + mp));  // read one while the next placement writes the other
     L->fdesc = take(8 * 4 * 2 * (size_t)T);
-    L->hist = take(4 * (size_t)kRadix * T * kMaxPasses);
+    // Several blocks rank a table only where slots and candidates pass what one
+    // block takes (launch_plc_rank), and tables with a ring, sets or no slot are
+    // never ranked: no histogram otherwise (six for each of 256 tables were 12.6 MB)
+    int64_t most_cap = 0;
+    bool ranked = false;
+    for (const Geom &g : geo) {
+        most_cap = std::max<int64_t>(most_cap, g.cap);
+        ranked = ranked || (!g.ways && !g.ring_cap && g.cap > 0);
+    }
+    if (ranked && !tight && most_cap + (cfg->max_indices + cfg->max_prefetch + T - 1) / T > kRankSmallItems)
+        L->hist_sets = most_passes(cfg, geo);
+    L->hist = take(4 * (size_t)kRadix * T * L->hist_sets);
     L->dump = take(4 * (size_t)L->sum_cap);
     L->dump_count = take(4 * T);
     L->pool_bstart = take(4 * (T + 1));
@@ -272,7 +296,7 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
     }
     if (all_owned) L->mark_parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMarkMaxParts, kMarkBlocks / slices));
     const bool many = std::max(cfg->max_indices, cfg->max_prefetch) / T >= kMarkSplitIds;
-    if (!many) L->mark_parts = 1;
+    if (!many || tight) L->mark_parts = 1;
     L->part_bm = take(L->mark_parts > 1 ? (size_t)L->mark_parts * L->total_bm_blocks * kWordsPerBlock * 4 : 0);
     L->staging[0] = take(mi * (size_t)L->stage_stride);
     L->staging[1] = take(mi * (size_t)L->stage_stride);
@@ -775,7 +799,7 @@ std::mutex g_static_mu;
 void *g_static_ptr[kMaxDevices];              // device address of `scratch` per device, set on first use
 recmg_cache_t *g_static_owner[kMaxDevices];   // the live handle that holds it, if any
 
-int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out);
+int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out, bool tight);
 
 }  // namespace
 
@@ -794,15 +818,17 @@ int32_t recmg_query_workspace(const recmg_config_t *cfg, size_t *device_bytes, s
     return RECMG_OK;
 }
 
-int32_t recmg_cache_init(const recmg_config_t *cfg, recmg_cache_t **out) { return cache_init(cfg, out); }
+int32_t recmg_cache_init(const recmg_config_t *cfg, recmg_cache_t **out) { return cache_init(cfg, out, false); }
 
 int32_t recmg_cache_init_static(const recmg_config_t *cfg, recmg_cache_t **out) {
     if (!out) return fail(RECMG_E_INVALID, "out is NULL");
     std::vector<Geom> geo;
     int32_t rc = check_config(cfg, &geo);
     if (rc) return rc;
-    Layout L;
-    make_layout(cfg, geo, &L);
+    Layout full, L;
+    make_layout(cfg, geo, &full);
+    const bool tight = full.total > kStaticWorkspaceBytes;
+    make_layout(cfg, geo, &L, tight);
     if (L.total > kStaticWorkspaceBytes)
         return fail(RECMG_E_NOMEM, "the configuration needs a " + std::to_string(L.total) +
                                        "-byte workspace; the static workspace holds " +
@@ -822,7 +848,7 @@ int32_t recmg_cache_init_static(const recmg_config_t *cfg, recmg_cache_t **out) 
     c2.device_workspace = g_static_ptr[dev];
     c2.device_workspace_bytes = kStaticWorkspaceBytes;
     recmg_cache_t *h = nullptr;
-    if ((rc = cache_init(&c2, &h))) return rc;
+    if ((rc = cache_init(&c2, &h, tight))) return rc;
     h->static_ws = true;
     g_static_owner[dev] = h;
     *out = h;
@@ -833,13 +859,13 @@ int32_t recmg_cache_init_static(const recmg_config_t *cfg, recmg_cache_t **out) 
 
 namespace {
 
-int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
+int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out, bool tight) {
     if (!out) return fail(RECMG_E_INVALID, "out is NULL");
     std::vector<Geom> geo;
     int32_t rc = check_config(cfg, &geo);
     if (rc) return rc;
     Layout L;
-    make_layout(cfg, geo, &L);
+    make_layout(cfg, geo, &L, tight);
     if (!cfg->device_workspace || cfg->device_workspace_bytes < L.total)
         return fail(RECMG_E_NOMEM, "device workspace smaller than recmg_query_workspace");
     if (reinterpret_cast<uintptr_t>(cfg->device_workspace) & 255)
@@ -917,6 +943,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     g.own_tables = 0;
     g.own_slices = 0;
     g.mark_parts = L.mark_parts;
+    g.hist_sets = L.hist_sets;
     g.part_bm = reinterpret_cast<uint32_t *>(ws + L.part_bm);
     g.stat_log = reinterpret_cast<int64_t *>(ws + L.stat_log);
     g.sa_bstart = reinterpret_cast<int32_t *>(ws + L.sa_bstart);
@@ -1051,7 +1078,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out) {
     HIP_TRY(hipMemsetAsync(ws + L.pstart, 0, 8 * (T + 1), s0));
     HIP_TRY(hipMemsetAsync(ws + L.ftstart, 0, 8 * (T + 1), s0));
     HIP_TRY(hipMemsetAsync(ws + L.err, 0, 4, s0));
-    HIP_TRY(hipMemsetAsync(ws + L.hist, 0, 4 * (size_t)kRadix * T * kMaxPasses, s0));
+    HIP_TRY(hipMemsetAsync(ws + L.hist, 0, 4 * (size_t)kRadix * T * L.hist_sets, s0));
     HIP_TRY(hipMemcpy(ws + L.tabs, tabs.data(), sizeof(DTable) * T, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ws + L.bm_block_start, bstart.data(), 4 * (T + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ws + L.pool_btab, c->pool_order.data(), 4 * T, hipMemcpyHostToDevice));
@@ -1196,7 +1223,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
                             num_prefetch == 0 && !c->has_fa ? prefetch_offsets : nullptr, last_bits, heads_last, s);
     }
     const int32_t end_nsa = c->sa_max_blocks <= kSaSumInEnd ? c->nsa : 0;
-    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, c->has_scan_fa ? p.passes : 0, s);
+    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, c->has_scan_fa && g.hist_sets ? p.passes : 0, s);
     if (!small) HIP_TRY(hipEventRecord(c->ev_plc, s));
     hipStream_t fs = c->copy_stream && !small ? c->copy_stream : s;
     if (early) {

@@ -657,10 +657,12 @@ void launch_plc_classify(const DGlobal &g, int32_t last_stamp, int64_t np, const
     k_plc_classify<<<grid_for(np > last_n / 4 ? np : last_n / 4, kRound, 1024), kRound, 0, s>>>(g, last_stamp, bits, last_n);
 }
 
-bool rank_in_block(int64_t item_bound) { return item_bound <= kRankSmallItems; }
+static bool rank_in_block(const DGlobal &g, int64_t item_bound) {
+    return g.hist_sets == 0 || item_bound <= kRankSmallItems;
+}
 
 void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, hipStream_t s) {
-    if (rank_in_block(item_bound)) {  // a table's slots and candidates fit one block's loop
+    if (rank_in_block(g, item_bound)) {  // a table's slots and candidates fit one block's loop
         k_plc_rank_small<<<g.T, kRankSmallThreads, 0, s>>>(g, p);
         return;
     }
@@ -676,7 +678,7 @@ void launch_plc_rank(const DGlobal &g, const PlcParams &p, int64_t item_bound, h
 }
 
 void launch_plc_evict(const DGlobal &g, const PlcParams &p, int32_t max_cap, int64_t item_bound, hipStream_t s) {
-    const int last = rank_in_block(item_bound) ? -1 : p.passes - 1;
+    const int last = rank_in_block(g, item_bound) ? -1 : p.passes - 1;
     // each block picks the last digit for itself (2 us), so it takes four rounds
     // of slots where there are that many
     k_plc_evict<<<dim3(grid_for(max_cap, kBlock * (max_cap > 1 << 16 ? 16 : 4), 2048), g.T), kBlock, 0, s>>>(g, p, last);

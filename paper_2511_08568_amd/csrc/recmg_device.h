@@ -183,7 +183,7 @@ struct DGlobal {
     int32_t *fill_src;        // [max_indices + max_prefetch] admitted row's source: staging row (>= 0)
                               // or -(host row + 1); table t at ftstart[t] + pstart[t]
     int32_t *fill_slot;       // [max_indices + max_prefetch] its slot
-    int32_t *hist;            // [kMaxPasses][T][kRadix], zero between placements
+    int32_t *hist;            // [hist_sets][T][kRadix], zero between placements
     int32_t *dump;            // [sum cap] sorted resident rows
     int32_t *dump_count;      // [T]
     char *staging;            // [max_indices][stage_stride] miss rows of the latest forward
@@ -199,6 +199,7 @@ struct DGlobal {
     int32_t total_bm_blocks;
     int32_t own_tables;  // tables with owns_bitmap(bm_nblk)
     int32_t own_slices;  // the most LDS slices of such a table
+    int32_t hist_sets;   // passes of the radix select that have histograms (all, or 0: one block ranks a table)
     int32_t mark_parts;  // parts that a table's ids may be marked in (1: never split)
     uint32_t *part_bm;   // [mark_parts][total_bm_blocks * kWordsPerBlock] each part's bitmap words
     int32_t *sa_bstart;  // [nsa + 1] first placement block of each set-associative table

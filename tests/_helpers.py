@@ -81,7 +81,8 @@ class GpuRunner:
     """Drives the HIP path through a workload (test helper; marshalling only)."""
 
     def __init__(self, w, tabs, miss_mode="zero_copy", validate=False, max_indices=None, max_prefetch=None,
-                 nbatches=None, pin=True, pipeline=False, stats_log_calls=0, overlap=True):
+                 nbatches=None, pin=True, pipeline=False, stats_log_calls=0, overlap=True,
+                 static_workspace=False):
         import torch
         from paper_2511_08568_amd import TieredEmbeddingCache
         self.torch = torch
@@ -100,7 +101,8 @@ class GpuRunner:
                                           policy=w.policy, eviction_speed=w.eviction_speed, miss_mode=miss_mode,
                                           max_bags_per_table=w.bags, max_indices=max_indices,
                                           max_prefetch=max_prefetch, validate=validate, ways=w.ways,
-                                          stats_log_calls=stats_log_calls, overlap=overlap)
+                                          stats_log_calls=stats_log_calls, overlap=overlap,
+                                          static_workspace=static_workspace)
         # pipelined placement: placements on a stream of their own, whose
         # inputs are copied on that stream too
         self.pstream = torch.cuda.Stream(device=self.dev) if pipeline else None

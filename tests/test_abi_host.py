@@ -114,6 +114,37 @@ def test_set_associative_slots():
     assert q(31) == q(0)
 
 
+# (rows, dim, cached rows, tables, policy, ways, max_indices, max_prefetch)
+STATIC_FITS = [(20000, 16, 400, 256, 1, 0, 8192, 8192), (14, 1, 1, 256, 1, 0, 213297, 111),
+               (15063, 2, 150, 256, 2, 0, 155, 2068), (13483, 64, 0, 256, 2, 0, 1512, 83573),
+               (888, 64, 266, 200, 0, 0, 570, 200), (3921, 16, 392, 256, 0, 0, 47, 21),
+               (90000, 9, 67380, 4, 1, 0, 100, 100), (100000, 64, 10000, 1, 0, 0, 5120, 5120)]
+
+
+@pytest.mark.parametrize("rows,dim,cap,T,policy,ways,mi,mp", STATIC_FITS)
+def test_static_workspace_takes_what_it_took(rows, dim, cap, T, policy, ways, mi, mp):
+    """Configurations that recmg_cache_init_static takes by its 32 MiB: memory
+    that only makes calls faster, or that no call of the configuration uses,
+    does not count against them (the next error is the missing device, or the
+    tables that are not pinned)."""
+    cfg = _cfg(rows=(rows,) * T, dims=(dim,) * T, dtypes=(0,) * T, caps=(cap,) * T, policy=policy, ways=ways,
+               max_idx=mi, max_pf=mp) if rows * dim * T < 1 << 24 else None
+    if cfg is None:  # the tables' bytes are never read: one address does for all
+        cfg = _cfg(rows=(1,) * T, dims=(dim,) * T, dtypes=(0,) * T, caps=(cap,) * T, policy=policy, ways=ways,
+                   max_idx=mi, max_pf=mp)
+        cfg._rows = (ctypes.c_int64 * T)(*[rows] * T)
+        cfg.rows = cfg._rows
+    h = ctypes.c_void_p(0)
+    code = pk.load_library().recmg_cache_init_static(ctypes.byref(cfg), ctypes.byref(h))
+    assert code in (bd.RECMG_E_HIP, bd.RECMG_E_INVALID) and not h.value, pk.recmg_last_error()
+
+
+def test_static_workspace_refuses_what_it_refused():
+    cfg = _cfg(rows=(200000,), dims=(2,), caps=(0,), max_idx=1 << 20, max_pf=1 << 20)
+    h = ctypes.c_void_p(0)
+    assert pk.load_library().recmg_cache_init_static(ctypes.byref(cfg), ctypes.byref(h)) == bd.RECMG_E_NOMEM
+
+
 def test_null_handle_is_rejected():
     lib = pk.load_library()
     assert lib.recmg_embbag_forward(None, None, None, 0, 0, None, None) == bd.RECMG_E_INVALID

@@ -115,3 +115,45 @@ def test_many_evictions_per_block(policy):
     # a list of 2,048 slots is emptied past 1,024.  PRIORITY and LFU: 4,096 slots per block (LFU frees fewer of
     # them); LRU: a ring's chunk per iteration, in at most 130,000 / 8 / 1,024 + 1 blocks
     assert most > (24 * 1024 if policy != "lfu" else 10_000) and (policy != "lru" or past > 2)
+
+
+@pytest.mark.parametrize("policy", ["priority", "lru"])
+def test_static_workspace_without_the_optional_memory(policy):
+    """A configuration that the library's 32 MiB array holds only without the
+    memory that makes calls faster: PRIORITY ranks 100,000 slots in one block
+    where several blocks would have their histograms, LRU marks 60,000 ids of
+    a table in one part.  The same counters and sums."""
+    from paper_2511_08568_amd import binding as bd
+    lru = policy == "lru"
+    rows, caps = ([300_000], [100_000]) if not lru else ([1_000_000], [10_000])
+    w = _workload(rows, caps, policy)
+    w.tables[0].dim = 32 if not lru else 8
+    full = 32 << 20
+    mi, step = (20_000, 50) if not lru else (60_000, 1_000)
+    query = lambda n: bd.recmg_query_workspace(_cfg_of(w, n))[0]
+    while query(mi) <= full:
+        mi += step
+    rng = np.random.default_rng(8)
+    with Against(w, mi, mi, static_workspace=True) as a:
+        last = None
+        for k in range(6):
+            P, poff = _list(rng, w, [(mi, mi // 2, 100)[k % 3]], 20_000)
+            a.placement(P, poff, (rng.random(last) < 0.4).astype(np.uint8) if last and not lru else None)
+            idx, off = _batch(rng, w, [(mi, 500)[k % 2]], 9_000)
+            a.forward(idx, off)
+            last = idx.size
+
+
+def _cfg_of(w, n):
+    """The configuration that `Against` makes for a one-table workload, to ask for its workspace."""
+    import ctypes
+    from paper_2511_08568_amd import binding as bd
+    tb = w.tables[0]
+    cfg = bd.recmg_config_t()
+    cfg._keep = [(ctypes.c_int64 * 1)(tb.rows), (ctypes.c_int32 * 1)(tb.dim), (ctypes.c_int32 * 1)(bd.RECMG_F32),
+                 (ctypes.c_void_p * 1)(4096), (ctypes.c_int64 * 1)(tb.cap)]
+    cfg.num_tables = 1
+    cfg.rows, cfg.dims, cfg.dtypes, cfg.host_tables, cfg.cache_rows = cfg._keep
+    cfg.policy, cfg.eviction_speed = bd.POLICY_CODES[w.policy], w.eviction_speed
+    cfg.max_bags_per_table, cfg.max_indices, cfg.max_prefetch = w.bags, n, n
+    return cfg
