@@ -1335,6 +1335,7 @@ int32_t recmg_embbag_forward(recmg_cache_t *c, const int32_t *indices, const int
     {
         StageTimer tm(c, RECMG_STAGE_FWD_DEDUP, s);
         const bool small = n > 0 && small_batch(c->T, n, c->max_nblk);
+        launch_bag_offsets(g, offsets, (int32_t)B, s);
         if (small) launch_fwd_small(g, indices, offsets, (int32_t)B, n, stamp, c->plc_np > 0, c->max_nblk, s);
         else if (n == 0) launch_fwd_prep(g, offsets, (int32_t)B, n, s);
         else {

@@ -28,6 +28,15 @@ __global__ void __launch_bounds__(kBlock) k_fwd_prep(DGlobal g, const int64_t *_
     forward_prep(g, blockIdx.x, offsets, B, n);
 }
 
+// Many bags: their offsets are checked over the whole chip, before the forward's
+// first kernel (one block per table took 70 us for 262,144).
+__global__ void __launch_bounds__(kBlock) k_bag_offsets(DGlobal g, const int64_t *__restrict__ offsets, int64_t bags) {
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < bags; i += (int64_t)gridDim.x * kBlock)
+        bad |= offsets[i] > offsets[i + 1];
+    if (bad) atomicOr(g.err, ERR_OFFSETS);
+}
+
 // Cache probe of every distinct row (row -> slot map, or a scan of the row's
 // set in a set-associative table): hits are stamped and counted, misses are
 // numbered (their staging row).  The tables' distinct rows are laid end to end
@@ -848,6 +857,11 @@ static inline unsigned grid_for(int64_t n, int per_block, unsigned cap) {
     if (b < 1) b = 1;
     if (b > (int64_t)cap) b = cap;
     return (unsigned)b;
+}
+
+void launch_bag_offsets(const DGlobal &g, const int64_t *offsets, int32_t B, hipStream_t s) {
+    const int64_t bags = (int64_t)g.T * B;
+    if (B > kPrepBags) k_bag_offsets<<<grid_for(bags, kBlock * 4, 4096), kBlock, 0, s>>>(g, offsets, bags);
 }
 
 void launch_fwd_prep(const DGlobal &g, const int64_t *offsets, int32_t B, int64_t n, hipStream_t s) {

@@ -25,6 +25,8 @@ void launch_dedup(const DGlobal &g, int mode, int32_t *counts, int count_stride,
                   hipStream_t s);
 
 // forward.hip
+// before a forward's first kernel, where that leaves the bag offsets to a check over the whole chip
+void launch_bag_offsets(const DGlobal &g, const int64_t *offsets, int32_t B, hipStream_t s);
 void launch_fwd_prep(const DGlobal &g, const int64_t *offsets, int32_t B, int64_t n, hipStream_t s);
 // np: prefetch ids of the placement just before this forward (0: none)
 void launch_fwd_probe(const DGlobal &g, int32_t stamp, int64_t n, int64_t np, hipStream_t s);

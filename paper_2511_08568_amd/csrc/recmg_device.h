@@ -695,13 +695,22 @@ __device__ __forceinline__ float f16_to_f32(uint32_t bits16) {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
 }
 
-// Start of a forward for table t, by one block: bag offsets checked, the
-// table's index range and counters set.  Every thread of the block calls.
+// Bags per table up to which the block that starts a table's forward checks their
+// offsets itself (1,024 of them take it 0.27 us); more are checked by a kernel of
+// its own before it (some 5 us).  Forwards of one id per 100 bags, 1 and 8 tables:
+// 262,144 bags 122.7 and 417.6 us in the block, 68.4 and 353.6 apart; 32,768 bags
+// 27.1 and 63.1 against 30.1 and 63.2.
+constexpr int32_t kPrepBags = 16384;
+
+// Start of a forward for table t, by one block: bag offsets checked (up to
+// kPrepBags; k_bag_offsets has checked more), the table's index range and counters
+// set.  Every thread of the block calls.
 __device__ __forceinline__ void forward_prep(const DGlobal &g, int t, const int64_t *__restrict__ offsets, int32_t B,
                                              int64_t n) {
     const int64_t *ob = offsets + (int64_t)t * B;
     bool bad = false;
-    for (int32_t j = threadIdx.x; j < B; j += blockDim.x) bad |= ob[j] > ob[j + 1];
+    const int32_t nb = B <= kPrepBags ? B : 0;
+    for (int32_t j = threadIdx.x; j < nb; j += blockDim.x) bad |= ob[j] > ob[j + 1];
     if (threadIdx.x == 0) {
         const int64_t lo = ob[0], hi = ob[B];
         // the last two hold in every table of a well-formed call

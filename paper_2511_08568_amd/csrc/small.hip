@@ -163,7 +163,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(DGlobal g, const in
     const int64_t *ob = offsets + (int64_t)t * B;
     const int64_t lo = ob[0], hi = ob[B];
     bool bad = lo < 0 || hi < lo || hi > n || (t == 0 && lo != 0) || (t == g.T - 1 && hi != n);
-    for (int j = threadIdx.x; j < B; j += kSmallThreads) bad |= ob[j] > ob[j + 1];
+    const int nb = B <= kPrepBags ? B : 0;  // more: k_bag_offsets
+    for (int j = threadIdx.x; j < nb; j += kSmallThreads) bad |= ob[j] > ob[j + 1];
     if (bad) s_bad_off = 1;
     __syncthreads();
     if (s_bad_off) {  // block-uniform

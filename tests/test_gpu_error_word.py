@@ -113,3 +113,35 @@ def test_malformed_small_placement_changes_nothing(policy, ways, what):
         assert 1 <= at.numel() <= 4 and int(at[-1]) - int(at[0]) < 4, f"{at.numel()} bytes of the workspace changed"
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("n", ["none", "few", "many"])
+@pytest.mark.parametrize("bags", [16384, 16385, 40000])
+def test_offsets_of_many_bags(bags, n):
+    """Bag counts on both sides of the line past which a kernel of its own
+    checks the offsets: a good call is served, one that decreases in the last
+    table's last bags is found, whatever the number of indices."""
+    w = tg.Workload(92, "bags", [tg.Table(500, 4, "f32", 50, 1.0, ("fixed", 1)) for _ in range(3)], batches=1, bags=bags)
+    tabs = [w.table_values(t) for t in range(3)]
+    rng = np.random.default_rng(6)
+    total = {"none": 0, "few": 900, "many": 60000}[n]
+    idx = rng.integers(0, 500, total).astype(np.int32)
+    off = np.concatenate([[0], np.sort(rng.integers(0, total + 1, 3 * bags - 1)), [total]]).astype(np.int64)
+    off[:3 * bags - 1] = np.minimum(off[:3 * bags - 1], max(total - 2, 0))
+    off[3 * bags - 1] = total  # the last bag but one ends the batch
+    g = GpuRunner(w, tabs, max_indices=max(total, 1), max_prefetch=1)
+    try:
+        call = lambda o: g.cache.forward(g.to_dev(idx) if total else g.to_dev(np.zeros(1, np.int32))[:0], g.to_dev(o), bags)
+        out = call(off).cpu().numpy().reshape(3, bags, 4)
+        g.cache.stats()
+        ref = np.stack([np.concatenate([np.zeros((1, 4)), np.cumsum(tabs[t][idx].astype(np.float64), 0)]) for t in range(3)])
+        for t in range(3):
+            o = off[t * bags:(t + 1) * bags + 1]
+            assert np.abs(out[t] - (ref[t][o[1:]] - ref[t][o[:-1]])).max() <= 1e-3
+        bad = off.copy()
+        bad[3 * bags - 1] = bad[3 * bags] + 1  # past the end, then back
+        out = call(bad)
+        _, _, code = g.cache.stats(strict=False)
+        assert code == bd.RECMG_E_RANGE
+    finally:
+        g.close()
