@@ -336,6 +336,7 @@ struct recmg_cache {
     int64_t sa_blocks1 = 0;  // the first of them, over the tables of one set per wave
     int64_t sa_max_blocks = 0;  // the most blocks of one table
     bool has_fa = false, has_sa = false;  // tables of each form present
+    bool has_fa_slots = false;            // some fully associative table has slots
     bool has_ring = false, has_scan_fa = false;  // fully associative tables with and without a resident ring
     int32_t max_ring_chunks = 0;
     bool has_zc = false, has_staged = false;  // tables of each miss mode present
@@ -1017,6 +1018,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out, bool tight) {
         }
         if (ge.ways) c->has_sa = true;
         else c->has_fa = true;
+        if (!ge.ways && ge.cap > 0) c->has_fa_slots = true;
 
         bstart[t + 1] = bstart[t] + ge.bm_nblk;
         out_off += ge.dim;
@@ -1165,7 +1167,8 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // Small batches: one kernel for all but the sets, and the fill beside the
     // published counters on this stream (a fill of some hundred rows takes a few
     // microseconds, the waits of another stream for it longer).
-    const bool small = !c->has_staged && small_placement(c->T, last_n, num_prefetch, c->max_nblk, max_fa_cap);
+    const bool small = !c->has_staged && small_placement(c->T, last_n, num_prefetch, c->max_nblk, max_fa_cap,
+                                                          c->has_fa_slots && !p.lfu);
     const uint8_t *last_bits = p.prio ? cache_bits : nullptr;
     const int64_t want_last = (p.prio && cache_bits) || p.lfu ? last_n : 0;
     int64_t heads_last = want_last;  // ... of these, what k_sa_heads takes care of

@@ -61,8 +61,9 @@ void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *o
                       int32_t stamp, bool cover, int32_t max_nblk, hipStream_t s);
 
 // a placement's kernels up to (not with) launch_sa_place and launch_plc_end; last_n: ids of
-// the last forward (0: none), max_fa_cap: the most slots of a fully associative table
-bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap);
+// the last forward (0: none), max_fa_cap: the most slots of a fully associative table,
+// dear: some such table has slots, under LRU_BATCH or PRIORITY
+bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap, bool dear);
 void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,
                       const uint8_t *bits, int wr, int32_t max_nblk, hipStream_t s);
 

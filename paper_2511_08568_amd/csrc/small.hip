@@ -923,20 +923,31 @@ void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *o
 }
 
 // The same for a placement, by the mean of its two lists (the last batch's ids,
-// the prefetch ids).  It saves eight to eleven launches, 60 .. 100 us: steps of 1
-// and 8 tables of 20,000 and 200,000 rows, cached tenth, take 52 .. 79 us at 300
-// ids per table where the general sequence takes 98 .. 157, 69 .. 116 against
-// 116 .. 207 at 2,500, and about the same at 6,000 in 8 tables.  A table's rows
-// cost its CU more here than in a forward, so the total that bounds the loss
-// of a batch with nearly all ids in one table is half as large; tables with
-// more slots than one block ranks take the general sequence too.
+// the prefetch ids).  It saves six to nine launches, 40 .. 60 us.  A table's rows
+// cost its CU more here than in a forward, so the total that bounds the loss of a
+// batch with nearly all ids in one table is half as large; tables with more slots
+// than one block ranks take the general sequence too.  What a row costs goes by
+// its new slot, map entry and ring entry, so it is dear in fully associative
+// tables whose rows change at every batch.  Steps of 1 table (40,000 x 64 fp32, half of each
+// list of m distinct rows new, as many ids in the batch), here and in the general
+// sequence, placements on the forward's stream and on one of their own:
+//           LRU                        PRIORITY                   32-way LRU
+//   m 2,000  82, 96    122, 136         75, 89    104, 112         70, 82   85, 98
+//     5,000  131, 153  132, 157        117, 138   126, 151         94, 110  102, 127
+//     6,000  153, 177  140, 165        134, 157   133, 162         99, 117  105, 130
+//    10,000  219, 254  161, 169        189, 221   158, 194        126, 147  118, 155
+// Zipf-distributed ids repeat (8,000 ids and a list of 3,067: LRU 127, 143 against
+// 155, 144).  So LRU and PRIORITY keep to kSmallFaIds per table where one is fully
+// associative; sets and LFU_BATCH (10,000: 170, 187 against 187, 201) need no line
+// of their own.
 #ifndef RECMG_SMALL_PLC_MAX
 #define RECMG_SMALL_PLC_MAX (RECMG_SMALL_MAX / 2)
 #endif
-bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap) {
+constexpr int64_t kSmallFaIds = 5500;
+bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap, bool dear) {
     const int64_t n = (last_n + np + 1) / 2;
     return last_n + np > 0 && n <= RECMG_SMALL_PLC_MAX && max_nblk <= kSmallBlocksPlc && max_fa_cap <= kRankSmallItems &&
-           small_batch(T, n, max_nblk);
+           (!dear || n <= kSmallFaIds * T) && small_batch(T, n, max_nblk);
 }
 
 void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,

@@ -117,6 +117,23 @@ def test_many_evictions_per_block(policy):
     assert most > (24 * 1024 if policy != "lfu" else 10_000) and (policy != "lru" or past > 2)
 
 
+@pytest.mark.parametrize("policy,ways", [("lru", 0), ("priority", 0), ("lfu", 0), ("lru", 8)])
+def test_both_sides_of_the_ids_per_table(policy, ways):
+    """Placements whose lists mean 5,500 and 5,501 ids (the line of fully
+    associative LRU and PRIORITY tables), and far apart, in turn on one cache."""
+    w = _workload([60_000], [9_000], policy, ways=ways)
+    rng = np.random.default_rng(9)
+    with Against(w, 9_000, 9_000) as a:
+        last = None
+        for pc, n in ((5_500, 5_500), (5_500, 5_501), (5_501, 5_500), (2_000, 9_000), (2_001, 9_000), (9_000, 40), (9_000, 9_000),
+                      (1, 2_000), (9_000, 5_500)):
+            P, poff = _list(rng, w, [pc], 9_000)
+            a.placement(P, poff, (rng.random(last) < 0.4).astype(np.uint8) if policy == "priority" and last else None)
+            idx, off = _batch(rng, w, [n], 9_000)
+            a.forward(idx, off)
+            last = n
+
+
 @pytest.mark.parametrize("policy", ["priority", "lru"])
 def test_static_workspace_without_the_optional_memory(policy):
     """A configuration that the library's 32 MiB array holds only without the
