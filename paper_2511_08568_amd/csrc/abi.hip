@@ -331,6 +331,7 @@ struct recmg_cache {
     Layout L;
     DGlobal g{};
     std::vector<const char *> host;  // host tables (host pointers)
+    int64_t row_bytes = 0;  // of one row of every table
     int32_t max_cap = 0, max_units = 0, rowbits = 1, nsa = 0, max_nblk = 0;
     int64_t sa_blocks = 0;   // blocks of the set-associative placement kernel
     int64_t sa_blocks1 = 0;  // the first of them, over the tables of one set per wave
@@ -1026,6 +1027,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out, bool tight) {
         c->max_cap = std::max(c->max_cap, ge.cap);
         c->max_units = std::max(c->max_units, ge.row_bytes / ge.copy_unit);
         c->max_rows = std::max(c->max_rows, ge.rows);
+        c->row_bytes += ge.row_bytes;
         c->max_nblk = std::max(c->max_nblk, ge.bm_nblk);
         if (owns_bitmap(ge.bm_nblk)) {
             g.own_tables += 1;
@@ -1164,11 +1166,12 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     const int64_t last_n = c->have_fwd ? c->last_n : 0;
     const int64_t log_slot = c->cfg.stats_log_calls ? c->calls % c->cfg.stats_log_calls : -1;
     const int32_t max_fa_cap = c->has_fa ? c->max_cap : 0;
-    // Small batches: one kernel for all but the sets, and the fill beside the
-    // published counters on this stream (a fill of some hundred rows takes a few
-    // microseconds, the waits of another stream for it longer).
+    // Small batches: one kernel for all but the sets, and a fill of few bytes
+    // beside the published counters on this stream (fill_in_end).
     const bool small = !c->has_staged && small_placement(c->T, last_n, num_prefetch, c->max_nblk, max_fa_cap,
                                                           c->has_fa_slots && !p.lfu);
+    const bool fill_here = small && fill_in_end(num_prefetch * c->row_bytes / c->T, c->copy_stream != nullptr,
+                                                c->fwd_ev && c->fwd_stream != s);
     const uint8_t *last_bits = p.prio ? cache_bits : nullptr;
     const int64_t want_last = (p.prio && cache_bits) || p.lfu ? last_n : 0;
     int64_t heads_last = want_last;  // ... of these, what k_sa_heads takes care of
@@ -1226,9 +1229,10 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
                             num_prefetch == 0 && !c->has_fa ? prefetch_offsets : nullptr, last_bits, heads_last, s);
     }
     const int32_t end_nsa = c->sa_max_blocks <= kSaSumInEnd ? c->nsa : 0;
-    if (!small) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, c->has_scan_fa && g.hist_sets ? p.passes : 0, s);
-    if (!small) HIP_TRY(hipEventRecord(c->ev_plc, s));
-    hipStream_t fs = c->copy_stream && !small ? c->copy_stream : s;
+    const int32_t end_passes = !small && c->has_scan_fa && g.hist_sets ? p.passes : 0;
+    if (!fill_here) launch_plc_end(g, fdesc, log_slot, false, max_fa_cap, end_nsa, end_passes, s);
+    if (!fill_here) HIP_TRY(hipEventRecord(c->ev_plc, s));
+    hipStream_t fs = c->copy_stream && !fill_here ? c->copy_stream : s;
     if (early) {
         // the host gathers while the kernels above run; the copies go on the
         // fill stream ahead of the fill (the last fill to read fstage has
@@ -1249,7 +1253,7 @@ int32_t recmg_apply_placement(recmg_cache_t *c, const int32_t *prefetch_rows, co
     // different streams) this fill waits for it, and so does every forward
     // that waits for this fill.
     if (c->fill_rec[q ^ 1] && c->fill_stream[q ^ 1] != fs) HIP_TRY(hipStreamWaitEvent(fs, c->ev_fill[q ^ 1], 0));
-    if (small) {
+    if (fill_here) {
         StageTimer tm(c, RECMG_STAGE_PLC_FILL, s);
         DispatchTimer dt(c, RECMG_STAGE_PLC_FILL, true);
         launch_plc_end(g, nullptr, log_slot, true, max_fa_cap, end_nsa, 0, s, dt.a, dt.b);

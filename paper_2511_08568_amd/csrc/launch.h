@@ -64,6 +64,9 @@ void launch_fwd_small(const DGlobal &g, const int32_t *indices, const int64_t *o
 // the last forward (0: none), max_fa_cap: the most slots of a fully associative table,
 // dear: some such table has slots, under LRU_BATCH or PRIORITY
 bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, int32_t max_fa_cap, bool dear);
+// whether the end of a small placement copies its prefetch rows too; bytes: the most they may be,
+// own_stream: the placement runs on another stream than the last forward
+bool fill_in_end(int64_t bytes, bool copy_stream, bool own_stream);
 void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,
                       const uint8_t *bits, int wr, int32_t max_nblk, hipStream_t s);
 

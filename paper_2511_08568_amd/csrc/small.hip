@@ -950,6 +950,31 @@ bool small_placement(int32_t T, int64_t last_n, int64_t np, int32_t max_nblk, in
            (!dear || n <= kSmallFaIds * T) && small_batch(T, n, max_nblk);
 }
 
+// Where a small placement's last kernel copies the prefetch rows too.  With a copy
+// stream that saves a launch and two streams' waits for one another, some 15 us,
+// and the next forward's dedup and a placement on a stream of its own wait for the
+// rows: worth it up to some 16 MiB of list (a bound of the rows that it brings;
+// 300 us of host link).  Without one there is no stream to wait for: a fill apart
+// lets the next forward's dedup start where the placement is on another stream,
+// and gains nothing where it is not.  Steps with half of each list new, in that
+// kernel | apart; in each: on the forward's stream and on one of its own with a copy
+// stream, on one of its own without:
+//   1 x   300 rows of   64 B (0.02 MiB)  56  67  67     77  68  64
+//   4 x 1,000 rows of  256 B (0.98 MiB)  80  92  91    105 119  90
+//   1 x 3,000 rows of 1 KiB  (2.9 MiB)  127 142 142    141 134 129
+//   3 x 2,000 rows of 1 KiB  (5.9 MiB)  151 166 166    174 190 158
+//   4 x 3,000 rows of 1 KiB  (11.7 MiB) 232 247 248    253 276 236
+//   1 x 5,000 rows of 4 KiB  (19.5 MiB) 351 358 357    355 377 330
+//   3 x 3,000 rows of 4 KiB  (35.2 MiB) 508 511 512    523 431 497
+// (apart, a placement on its own stream now and then settles a whole step ahead,
+// as in the 431.)
+#ifndef RECMG_SMALL_FILL_BYTES
+#define RECMG_SMALL_FILL_BYTES (16 << 20)
+#endif
+bool fill_in_end(int64_t bytes, bool copy_stream, bool own_stream) {
+    return copy_stream ? bytes <= RECMG_SMALL_FILL_BYTES : !own_stream;
+}
+
 void launch_plc_small(const DGlobal &g, const PlcParams &p, const int32_t *rows, const int64_t *poff, int64_t np,
                       const uint8_t *bits, int wr, int32_t max_nblk, hipStream_t s) {
     if (max_nblk <= kSmallBlocksLow)
