@@ -33,6 +33,7 @@ int32_t fail(int32_t code, const std::string &msg) {
 constexpr uint32_t kMagic = 0x52434d47u;  // "RCMG"
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+char *align_to(char *p, size_t a) { return p + (-reinterpret_cast<uintptr_t>(p) & (a - 1)); }
 
 int bitlen(uint64_t x) {
     int b = 0;
@@ -315,7 +316,7 @@ void make_layout(const recmg_config_t *cfg, const std::vector<Geom> &geo, Layout
         L->h_fsrc = htake(4 * (mi + mp));
         L->h_frows = htake(mp * (size_t)L->stage_stride);
         L->h_np = htake(4 * mp);
-        L->h_back = htake(L->back_bytes);
+        L->h_back = htake(L->back_bytes + alignof(TState));  // aligned where the caller's staging lies
         L->host_total = h;
     }
 }
@@ -516,7 +517,7 @@ hipError_t sync_all(recmg_cache_t *c) {
 
 // A host copy of the table states, the error word and the list starts, which
 // lie side by side in the workspace: one copy brings them all (a copy of a few
-// bytes costs its 5 to 10 us whatever its size).
+// bytes costs its 5 to 10 us whatever its size).  `host` is aligned as TState is.
 struct Back {
     const TState *st;
     const int64_t *tstart, *pstart, *ftstart;
@@ -1102,7 +1103,7 @@ int32_t cache_init(const recmg_config_t *cfg, recmg_cache_t **out, bool tight) {
         c->h_fsrc = reinterpret_cast<int32_t *>(hs + L.h_fsrc);
         c->h_frows = hs + L.h_frows;
         c->h_np = reinterpret_cast<int32_t *>(hs + L.h_np);
-        c->h_back = hs + L.h_back;
+        c->h_back = align_to(hs + L.h_back, alignof(TState));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_ready, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_copied, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&c->ev_np, hipEventDisableTiming));
@@ -1419,9 +1420,9 @@ int32_t recmg_stats(recmg_cache_t *c, recmg_table_stats_t *last, recmg_table_sta
     hipStream_t s = c->last_stream;
     HIP_TRY(sync_all(c));
     const int T = c->T;
-    std::vector<char> host(c->L.back_bytes);
-    HIP_TRY(hipMemcpy(host.data(), c->g.st, host.size(), hipMemcpyDeviceToHost));
-    const Back back(c->L, host.data());
+    std::vector<TState> host((c->L.back_bytes + sizeof(TState) - 1) / sizeof(TState));
+    HIP_TRY(hipMemcpy(host.data(), c->g.st, c->L.back_bytes, hipMemcpyDeviceToHost));
+    const Back back(c->L, reinterpret_cast<const char *>(host.data()));
     const TState *st = back.st;
     const int32_t err = back.err;
     for (int t = 0; t < T; ++t) {

@@ -180,3 +180,38 @@ def test_init_rejects_small_workspace_and_pageable_tables():
     with pytest.raises(ValueError):
         TieredEmbeddingCache([pinned], ["f32"], [10], max_bags_per_table=8, max_indices=64, max_prefetch=64,
                              workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("shift", [4, 8, 16, 72])
+def test_staging_of_any_alignment(shift):
+    """Host staging needs no alignment beyond its int32 arrays': what the host
+    reads back of the table states finds its own."""
+    import ctypes
+    import oracle
+    w = tg.scaled_config(3, row_scale=0.01, batches=3, bags=64, max_tables=3)
+    tabs = [w.table_values(t) for t in range(3)]
+    g = GpuRunner(w, tabs, miss_mode="staged")
+    o = oracle.for_workload(w, tabs)
+    try:
+        cfg = g.cache.cfg
+        need = cfg.host_staging_bytes
+        pinned = torch.empty(need + 128, dtype=torch.uint8, pin_memory=True)
+        assert bd.recmg_cache_destroy(g.cache.handle) == bd.RECMG_OK
+        g.cache.handle = 0
+        cfg.host_staging = pinned.data_ptr() + shift
+        g.cache.handle = bd.recmg_cache_init(cfg)
+        for b in range(3):
+            P, poff = w.prefetch_list(b)
+            bits = w.cache_bits(b - 1) if b else None
+            g.placement(P, poff, bits)
+            assert o.placement(P, poff, bits) == 0
+            idx, off = w.batch(b)
+            g.forward(idx, off)
+            assert o.forward(idx, off, w.bags)[0] == 0
+            last, _ = g.cache.stats()
+            for t in range(3):
+                for k in ("hits", "misses", "resident", "prefetch_fill", "digest"):
+                    assert last[t][k] == o.stats(t)[k], (b, t, k)
+    finally:
+        g.close()
+        o.close()
