@@ -66,10 +66,10 @@ __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t st
     if (s_err) return;  // block-uniform
     int32_t lo, hi;
     round_share(n, kProbeRound, &lo, &hi);
-    for (int32_t base = lo; base < hi; base += kProbeRound) {  // block-uniform
-        const int32_t i = base + (int32_t)threadIdx.x;
-        const bool in = i < hi;
-        int t = find_seg32(s_pre, g.T, in ? i : base);
+    for (int64_t base = lo; base < hi; base += kProbeRound) {  // block-uniform; 64 bits: hi may be 2^31 - 1
+        const bool in = base + threadIdx.x < hi;
+        const int32_t i = in ? (int32_t)(base + threadIdx.x) : (int32_t)base;
+        int t = find_seg32(s_pre, g.T, i);
         int64_t at = 0;
         int32_t row = 0, m = -1;
         // rows of one table (nearly every wave): its descriptor is read through scalar loads
@@ -122,11 +122,11 @@ __global__ void __launch_bounds__(kProbeRound) k_fwd_probe(DGlobal g, int32_t st
     }
     const int32_t np = lay_tables(g.T, [&](int t) { return g.st[t].pcount; }, s_pre, tmp);
     round_share(np, kProbeRound, &lo, &hi);
-    for (int32_t base = lo; base < hi; base += kProbeRound) {
-        const int32_t i = base + (int32_t)threadIdx.x;
+    for (int64_t base = lo; base < hi; base += kProbeRound) {
         int t = 0;
         bool hit = false;
-        if (i < hi) {
+        if (base + threadIdx.x < hi) {
+            const int32_t i = (int32_t)(base + threadIdx.x);
             t = find_seg32(s_pre, g.T, i);
             const DTable &tb = g.tabs[t];
             const uint32_t pos = bm_pos(tb, g.PU[s_ts[t] + (i - s_pre[t])]);

@@ -74,10 +74,10 @@ __global__ void __launch_bounds__(kRound) k_plc_classify(DGlobal g, int32_t last
     if (s_err) return;  // block-uniform
     int32_t lo, hi;
     round_share(n, kRound, &lo, &hi);
-    for (int32_t base = lo; base < hi; base += kRound) {  // block-uniform
-        const int32_t i = base + (int32_t)threadIdx.x;
-        const bool in = i < hi;
-        const int t = find_seg32(s_pre, g.T, in ? i : base);
+    for (int64_t base = lo; base < hi; base += kRound) {  // block-uniform; 64 bits: hi may be 2^31 - 1
+        const bool in = base + threadIdx.x < hi;
+        const int32_t i = in ? (int32_t)(base + threadIdx.x) : (int32_t)base;
+        const int t = find_seg32(s_pre, g.T, i);
         int64_t at = 0;
         int32_t row = 0, k = -1;
         // rows of one table (nearly every wave): its descriptor is read through scalar loads
