@@ -121,3 +121,75 @@ def test_wide_rows_in_small_placements(policy, ways, overlap):
             else:
                 q.forward(*args, None, dev)
         q.check()
+
+
+def _counts(kind, n, T):
+    """n ids over T tables: evenly, or nearly all in the first."""
+    return [n // T + (t < n % T) for t in range(T)] if kind == "even" else [n - 3 * (T - 1)] + [3] * (T - 1)
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+@pytest.mark.parametrize("policy,ways", [("lru", 0), ("priority", 0), ("lfu", 0), ("lru", 4), ("lfu", 32)])
+@pytest.mark.parametrize("big", [False, True])
+def test_random_sequences_across_the_line(big, policy, ways, overlap):
+    """Random placements and forwards, two of a kind in a row among them, small
+    and general ones in turn.  The first calls share one stream, the later ones
+    come on three, placements and forwards apart: the first placement on another
+    stream follows a general forward, whose locations are written beside its
+    fetch.  big: a table past the small kernels' bitmaps, so every call takes the
+    general sequence, whatever its size."""
+    rows = [(1 << 20) + 77, 5000, 300] if big else [60_000, 5000, 300]
+    tabs = [tg.Table(n, (16, 64, 9)[t], ("f32", "f16", "bf16")[t], max(ways, n // 25 if t else 4000), 1.0, ("fixed", 1))
+            for t, n in enumerate(rows)]
+    w = tg.Workload(96, "across", tabs, batches=1, bags=BAGS, policy=policy, ways=ways, eviction_speed=2)
+    rng = np.random.default_rng(60 + 7 * big + 3 * ways + overlap)
+    sizes = (40, 900, 12_000, 34_000)
+    calls, last = [], None
+    for k in range(36):
+        # one stream; from call 12 on placements on two others, forwards on two
+        kind = "f" if k in (5, 11) else "p" if k == 12 else ("p", "f")[int(rng.integers(2))]
+        n = 34_000 if k in (11, 12) else int(rng.choice(sizes))
+        c = _counts("even" if rng.random() < 0.6 else "skew", n, 3)
+        s = 0 if k < 12 else 1 + int(rng.integers(2)) if kind == "p" else 2 * int(rng.integers(2))
+        if kind == "p":
+            P, poff = _list(rng, w, c) if rng.random() < 0.85 or k == 12 else (np.zeros(0, np.int32), np.zeros(4, np.int64))
+            bits = (rng.random(last) < 0.4).astype(np.uint8) if policy == "priority" and last else None
+            calls.append(("p", (P, poff, bits), s))
+            last = None
+        else:
+            calls.append(("f", _batch(rng, w, c), s))
+            last = calls[-1][1][0].size
+    with Sequence(w, 34_000, len(calls), overlap=overlap) as q:
+        streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+        dev = [q.inputs(*args) for _, args, _ in calls]
+        for (kind, args, s), d in zip(calls, dev):
+            (q.placement if kind == "p" else q.forward)(*args, streams[s], d)
+        q.check()
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+@pytest.mark.parametrize("policy", ["lru", "priority"])
+def test_general_placements_in_a_row_on_streams(policy, overlap):
+    """Two general placements in a row, each on a stream other than the last
+    call's, then a forward on a third: the second frees slots that the first
+    one's fill may still be writing.  A small one follows now and then, whose
+    fill runs in its last kernel."""
+    w = tg.Workload(97, "row", [tg.Table(600_000, 32, "f32", 12_000, 1.0, ("fixed", 1)),
+                                tg.Table(4000, 32, "f16", 600, 1.0, ("fixed", 1))], batches=1, bags=BAGS,
+                    policy=policy, eviction_speed=2)
+    v = tg.Workload(98, "row", [tg.Table(200_000, 32, "f32", 12_000, 1.0, ("fixed", 1)),
+                                tg.Table(4000, 32, "f16", 600, 1.0, ("fixed", 1))], batches=1, bags=BAGS,
+                    policy=policy, eviction_speed=2)
+    rng = np.random.default_rng(19)
+    for x, lists in ((w, (9_000, 12_500, 300)), (v, (20_000, 24_000, 300))):
+        with Sequence(x, 26_000, 64, overlap=overlap) as q:
+            streams = [torch.cuda.Stream() for _ in range(3)]
+            calls = []
+            for b in range(6):
+                for rep in range(3 if b % 2 else 2):
+                    calls.append(("p", (*_list(rng, x, [lists[rep], 200]), None), rep % 2))
+                calls.append(("f", _batch(rng, x, [(6_000, 300)[b % 2], 200]), 2))
+            dev = [q.inputs(*args) for _, args, _ in calls]
+            for (kind, args, s), d in zip(calls, dev):
+                (q.placement if kind == "p" else q.forward)(*args, streams[s], d)
+            q.check()
