@@ -225,6 +225,13 @@ __device__ __forceinline__ void publish_forward(const DGlobal &g, int64_t log_sl
 // host link's time (a step of 8 32-way LFU tables of 25,000
 // indices 172 -> 164 us, a forward of 655,000 fp32 indices 434 -> 423), or, where
 // the host gathers every table's rows, behind that.
+#ifndef RECMG_FETCH_BLOCKS
+#define RECMG_FETCH_BLOCKS 96
+#endif
+#ifndef RECMG_FETCH_BLOCKS_HUGE
+#define RECMG_FETCH_BLOCKS_HUGE 160
+#endif
+constexpr int64_t kHugeFetchUnits = int64_t(1) << 25;  // 512 MiB in 16-byte units
 __global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot, int32_t nb,
                                                   const int32_t *__restrict__ indices, int64_t n) {
     if (block_err(g)) return;
@@ -237,7 +244,8 @@ __global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot, i
         return;
     }
     copy_flat(
-        g, [&](int t) { return g.tabs[t].staged ? 0 : g.st[t].mcount; }, nb,
+        g, [&](int t) { return g.tabs[t].staged ? 0 : g.st[t].mcount; },
+        [&](int64_t units) { return units >= kHugeFetchUnits ? nb : nb < RECMG_FETCH_BLOCKS ? nb : RECMG_FETCH_BLOCKS; },
         [&](int t, const DTable &tb, int64_t j) {
             return tb.host + (int64_t)g.M[g.tstart[t] + j] * tb.row_bytes;
         },
@@ -879,18 +887,19 @@ void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStre
     if (n > 0) k_fwd_src<<<src_blocks(n), kBlock, 0, s>>>(g, indices, n);
 }
 
-#ifndef RECMG_FETCH_BLOCKS
-#define RECMG_FETCH_BLOCKS 96
-#endif
-
 // As for the prefetch fill, which runs at the same time on the copy stream: a
 // modest grid fills the host link and leaves most CUs' L1s to other kernels
 // (the next placement runs beside it).  Measured on configuration 3 (64-256
 // blocks): 96 is best with 32-way sets (k_sa_place's critical path runs
-// alongside), within 1% of the best without prefetch and on configuration 5.
+// alongside) and within 1% of the best without prefetch.  From 512 MiB on the
+// fetch shares the link with a large fill for most of a step and takes
+// RECMG_FETCH_BLOCKS_HUGE: configuration 5 (750 MB), 768 fill blocks: 96 blocks
+// 83.4 ms per step, 112 82.5, 128 82.2, 160 82.2, 192 82.3, 256 82.4 (a step that
+// fetches some 270 MB: 7.49 ms with the two larger counts, 7.31 without).  The
+// kernel knows how much it copies; the grid holds the larger count.
 void launch_fetch(const DGlobal &g, bool copies, int64_t log_slot, const int32_t *indices, int64_t n, hipStream_t s,
                   hipEvent_t ev0, hipEvent_t ev1) {
-    const int32_t nb = copies ? RECMG_FETCH_BLOCKS : 0;
+    const int32_t nb = copies ? RECMG_FETCH_BLOCKS_HUGE : 0;
     const dim3 grid(nb + 1 + (n > 0 ? src_blocks(n) : 0));
     if (ev0 || ev1) hipExtLaunchKernelGGL(k_fetch, grid, dim3(kBlock), 0, s, ev0, ev1, 0, g, log_slot, nb, indices, n);
     else k_fetch<<<grid, kBlock, 0, s>>>(g, log_slot, nb, indices, n);

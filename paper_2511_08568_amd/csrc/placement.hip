@@ -451,7 +451,7 @@ __device__ __forceinline__ void fill_rows(const DGlobal &g, int phase, int64_t n
             const bool mine = (g.tabs[t].staged != 0) == (phase == FILL_STAGED);
             return mine && base >= 0 && n >= 0 && base + n <= g.fill_cap ? (int32_t)n : 0;
         },
-        nb,
+        [&](int64_t) { return nb; },
         [&](int t, const DTable &tb, int64_t j) -> const char * {
             const int32_t src = g.fill_src[first_of(t) + j];
             if (src >= 0) return g.staging + (miss0_of(t) + src) * g.stage_stride;  // admitted miss
@@ -554,18 +554,22 @@ __global__ void __launch_bounds__(kBlock) k_plc_fill(DGlobal g, const int64_t *_
 #define RECMG_FILL_BLOCKS_SHARED 256  // zero-copy fill beside the next forward's on-demand fetch
 #endif
 #ifndef RECMG_FILL_BLOCKS_BIG
-#define RECMG_FILL_BLOCKS_BIG 512  // zero-copy fill beside a fetch of hundreds of MB
+#define RECMG_FILL_BLOCKS_BIG 512  // zero-copy fill beside a fetch of a few hundred MB
+#endif
+#ifndef RECMG_FILL_BLOCKS_HUGE
+#define RECMG_FILL_BLOCKS_HUGE 768  // ... and of more
 #endif
 constexpr int kStagedFillBlocks = 1024;
 // on-demand fetch bytes above which the next fetch is taken to share the link
 // with the fill (below it, the fetch takes a few microseconds of link time)
 constexpr unsigned long long kSharedFetchBytes = 1ull << 20;
-// ... and above which the two hold the link together for tens of milliseconds
+// ... above which the two hold the link together for milliseconds
 constexpr unsigned long long kBigFetchBytes = 1ull << 28;
-constexpr int kFillGridBlocks = RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_SHARED
-                                    ? (RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_BIG ? RECMG_FILL_BLOCKS : RECMG_FILL_BLOCKS_BIG)
-                                    : (RECMG_FILL_BLOCKS_SHARED > RECMG_FILL_BLOCKS_BIG ? RECMG_FILL_BLOCKS_SHARED
-                                                                                       : RECMG_FILL_BLOCKS_BIG);
+// ... and for most of the step
+constexpr unsigned long long kHugeFetchBytes = 1ull << 29;
+constexpr int max_of(int a, int b) { return a > b ? a : b; }
+constexpr int kFillGridBlocks = max_of(max_of(RECMG_FILL_BLOCKS, RECMG_FILL_BLOCKS_SHARED),
+                                       max_of(RECMG_FILL_BLOCKS_BIG, RECMG_FILL_BLOCKS_HUGE));
 
 // The end of a placement.  Blocks by role:
 //   [0, nfill)         the fill, where it runs with the placement (small batches:
@@ -580,9 +584,9 @@ constexpr int kFillGridBlocks = RECMG_FILL_BLOCKS > RECMG_FILL_BLOCKS_SHARED
 // number of blocks such a fill copies with: zero-copy fills take more when the
 // last forward fetched at least 1 MB on demand, since the next forward's fetch
 // will then share the host link (with fewer waves of its own the fill gets less
-// of it), more still when it fetched at least 256 MB (the two then hold the
-// link for tens of milliseconds, and the kernels beside them are a small part
-// of the step), and fewer when the fill has the link to itself, so that it
+// of it), more still when it fetched at least 256 MB or 512 MB (the two then
+// hold the link for milliseconds or tens of them, and the kernels beside them
+// are a small part of the step), and fewer when the fill has the link to itself, so that it
 // takes no more CUs than it needs from the kernels beside it.
 // Table blocks also clear the radix select's histograms.
 __global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, int64_t log_slot, int32_t nfill,
@@ -617,7 +621,8 @@ __global__ void __launch_bounds__(kBlock) k_plc_end(DGlobal g, int64_t *fdesc, i
         }
         (void)block_excl_scan64(mb, tmp, &tot);
         if (threadIdx.x == 0)
-            fdesc[3] = (unsigned long long)tot >= kBigFetchBytes      ? RECMG_FILL_BLOCKS_BIG
+            fdesc[3] = (unsigned long long)tot >= kHugeFetchBytes     ? RECMG_FILL_BLOCKS_HUGE
+                       : (unsigned long long)tot >= kBigFetchBytes    ? RECMG_FILL_BLOCKS_BIG
                        : (unsigned long long)tot >= kSharedFetchBytes ? RECMG_FILL_BLOCKS_SHARED
                                                                       : RECMG_FILL_BLOCKS;
     }
@@ -701,8 +706,9 @@ void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStrea
     // runs beside the fill (192: -8% lookups/s).  On configuration 3 the fill
     // shares the link with the next forward's fetch of about 330,000 misses
     // (85 MB), and 256 blocks gave +4% (512: -6%).  On configuration 5 the
-    // fetch moves about 750 MB per batch beside a 3.8 GB fill, and 512 blocks
-    // gave +2.7% against 256 (768 and 1024: the same as 512).  The grid holds
+    // fetch moves about 750 MB per batch beside a 3.8 GB fill for most of the
+    // step: 768 blocks with the fetch's 160 (see launch_fetch) 82.2 ms per step,
+    // 512 and 96 blocks 83.7, 256 and 96 85.9, 1,024 and 96 84.0.  The grid holds
     // the largest count; k_plc_end writes how many of its blocks copy.
     // STAGED fills copy within HBM and take a full grid.
     const int blocks = phase == FILL_STAGED ? kStagedFillBlocks : kFillGridBlocks;

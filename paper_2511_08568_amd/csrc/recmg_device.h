@@ -777,11 +777,11 @@ __device__ __forceinline__ void placement_prep(const DGlobal &g, int t, const in
 }
 
 // Copy count_of(t) rows of every table in 16/4/2-byte units, the tables' work
-// laid end to end so every table gets its share of the first `nblocks` blocks
-// of the grid (the others copy nothing).  src_of / dst_of give the byte
+// laid end to end so every table gets its share of the first blocks_of(units)
+// blocks of the grid (the others copy nothing).  src_of / dst_of give the byte
 // addresses of item j of table t.
-template <class Count, class Src, class Dst>
-__device__ __forceinline__ void copy_flat(const DGlobal &g, Count count_of, int64_t nblocks, Src src_of, Dst dst_of) {
+template <class Count, class Blocks, class Src, class Dst>
+__device__ __forceinline__ void copy_flat(const DGlobal &g, Count count_of, Blocks blocks_of, Src src_of, Dst dst_of) {
     __shared__ int64_t s_pre[RECMG_MAX_TABLES + 1];
     __shared__ long long tmp[16];
     // per-table unit counts, scanned (T <= 256 = blockDim)
@@ -793,6 +793,7 @@ __device__ __forceinline__ void copy_flat(const DGlobal &g, Count count_of, int6
     if (t0 < g.T) s_pre[t0] = ex;
     if (t0 == 0) s_pre[g.T] = tot;
     __syncthreads();
+    const int64_t nblocks = blocks_of(s_pre[g.T]);
     const int64_t items = (int64_t)blockIdx.x < nblocks ? s_pre[g.T] : 0;
     const int64_t S = nblocks * blockDim.x;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; base < items; base += 4 * S) {
