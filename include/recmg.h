@@ -122,7 +122,10 @@ typedef struct {
     void *host_staging;                 /* caller-owned pinned host memory, STAGED only */
     size_t host_staging_bytes;
     void *copy_stream;                  /* hipStream_t for STAGED copies and the placement's
-                                           fill; NULL = the stream of each call */
+                                           fill; NULL = the stream of each call.  A short
+                                           zero-copy fill (a list of at most 16 MiB in a
+                                           placement of few ids) runs in the placement's last
+                                           kernel, on the call's stream, also where there is one */
     int32_t timing;                     /* initial timing level (see recmg_set_timing): 0 none,
                                            1 the pooled, fetch and fill kernels, 2 every stage */
     int32_t ways;                       /* 0: fully associative caches.  1 .. 64: W-way
@@ -139,15 +142,20 @@ typedef struct {
 /* Stages timed at timing level 2 (at level 1: the kernels named in
  * recmg_set_timing). */
 typedef enum {
-    RECMG_STAGE_FWD_DEDUP = 0,  /* offsets check, dedup + sort, map probe, inverse map */
-    RECMG_STAGE_FWD_FETCH = 1,  /* on-demand miss fetch (zero-copy kernel or staged copy) */
+    RECMG_STAGE_FWD_DEDUP = 0,  /* offsets check, dedup + sort, map probe; in forwards of few ids, and
+                                   once placements have come on another stream, the inverse map */
+    RECMG_STAGE_FWD_FETCH = 1,  /* on-demand miss fetch (zero-copy kernel or staged copy); the same
+                                   kernel writes the counters and, where FWD_DEDUP does not, the
+                                   inverse map */
     RECMG_STAGE_FWD_POOL = 2,   /* pooled gather + sum */
-    RECMG_STAGE_PLC_CLASSIFY = 3, /* caching bits, prefetch dedup + classification */
+    RECMG_STAGE_PLC_CLASSIFY = 3, /* caching bits, prefetch dedup + classification (in placements of few
+                                     ids one kernel does this, PLC_RANK and PLC_APPLY: counted there) */
     RECMG_STAGE_PLC_RANK = 4,   /* scoring + radix select of the kept keys (LRU_BATCH fully
                                    associative tables: new scores, zones and the cut of the
                                    resident ring) */
     RECMG_STAGE_PLC_APPLY = 5,  /* evict, map maintenance, admit, counters */
-    RECMG_STAGE_PLC_FILL = 6,   /* copy of admitted rows into slots (host link for prefetch) */
+    RECMG_STAGE_PLC_FILL = 6,   /* copy of admitted rows into slots (host link for prefetch); where the
+                                   placement's last kernel does it, with the counters */
     RECMG_STAGE_HOST_LINK = 7,  /* union of the FWD_FETCH and PLC_FILL intervals: the time the host
                                    link was in use (the two can overlap on different streams) */
     RECMG_NUM_STAGES = 8
@@ -275,7 +283,8 @@ int32_t recmg_stage_times(recmg_cache_t *c, double *ms, int64_t *calls, int32_t 
 /* Timing level for later calls:
  *   0  none;
  *   1  the kernels of the pooled sum, of the zero-copy miss fetch and of the
- *      placement's fill (RECMG_STAGE_FWD_POOL, _FWD_FETCH, _PLC_FILL, and
+ *      placement's fill, with what else those kernels do (see the stages)
+ *      (RECMG_STAGE_FWD_POOL, _FWD_FETCH, _PLC_FILL, and
  *      their host-link union), by events their own dispatches record (no
  *      command is added to the stream; such a dispatch starts a little later,
  *      by a few microseconds);

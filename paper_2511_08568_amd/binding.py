@@ -219,7 +219,7 @@ class TieredEmbeddingCache:
         self._modes = (ctypes.c_int32 * self.T)(*[MISS_CODES[m] for m in modes])
         cfg.miss_modes = self._modes
         cfg.validate = int(bool(validate))
-        cfg.timing = 2 if timing is True else int(timing)  # 0 off, 1 pooled kernel, 2 every stage
+        cfg.timing = 2 if timing is True else int(timing)  # 0 off, 1 pooled, fetch and fill kernels, 2 every stage
         cfg.ways = int(ways)  # 0 fully associative, W > 0 W-way set-associative
         cfg.stats_log_calls = int(stats_log_calls)  # counters of the latest calls, kept on the device
         cfg.max_bags_per_table = int(max_bags_per_table)
@@ -310,7 +310,7 @@ class TieredEmbeddingCache:
         return [[conv(buf[k * self.T + t]) for t in range(self.T)] for k in range(n_calls)]
 
     def set_timing(self, level: int):
-        """0 off, 1 the pooled kernel only (no stream commands added), 2 every stage."""
+        """0 off, 1 the pooled, fetch and fill kernels (no stream commands added), 2 every stage."""
         _check(recmg_set_timing(self.handle, int(level)), "recmg_set_timing")
 
     def stage_times(self, reset: bool = True):

@@ -1,6 +1,6 @@
 // C ABI of include/recmg.h: configuration checks, workspace carving, launch
 // order, the STAGED miss path and counter readback.  All arithmetic of the
-// lookup runs in the kernels of dedup.hip, forward.hip and placement.hip.
+// lookup runs in the kernels of the other files.
 #include <algorithm>
 #include <atomic>
 #include <cstddef>

@@ -4,12 +4,13 @@
 //   k_mark_own (and k_mark), k_bm_emit   bag offsets checked, each table's
 //                index range recorded, distinct rows sorted
 //   k_fwd_probe  map probe of the distinct rows, prefetch coverage
-//   k_fwd_src    per index: where its row lives (slot or staging row),
-//                through the rank of the row among the distinct rows
 //   k_fetch      ZERO_COPY: copy each distinct missing row once from pinned
-//                host memory to HBM staging (GPU reads over the host link); its
-//                last block publishes the counters (k_fwd_finalize where no
-//                fetch is launched)
+//                host memory to HBM staging (GPU reads over the host link); one
+//                block publishes the counters, further blocks write per index
+//                where its row lives (slot or staging row), through the rank of
+//                the row among the distinct rows.  (k_fwd_src writes the
+//                locations ahead of it where a placement on another stream may
+//                want them; k_fwd_finalize publishes a forward of no indices.)
 //   k_pool       per bag, sum of its rows in fp32 (Sec. II, pooling by sum)
 // A forward of few ids per table runs the part before the fetch in one kernel
 // (k_fwd_small, small.hip).
@@ -447,7 +448,7 @@ __global__ void __launch_bounds__(kBlock) k_pool(DGlobal g, const int64_t *__res
 //
 // One wave sums kWaveBags consecutive bags, one bag at a time.  Each lane
 // adds its LW-byte slice of every row; a row's address comes from its index's
-// location, written by k_fwd_src, so the kernel does no lookups.
+// location, written before it, so the kernel does no lookups.
 //   R == 1 (rows of 1024 bytes or whole multiples): all lanes read the same
 //     row, so its address is wave-uniform and comes in through scalar loads.
 //   R > 1 (shorter rows): the wave splits into R groups of 64 / R lanes that
@@ -851,8 +852,7 @@ __global__ void __launch_bounds__(kBlock) k_pool_any(DGlobal g, const int64_t *_
     else pool_any<RECMG_BF16>(g, tb, t, B, offsets, src, out, blk);
 }
 
-// The counters of a forward that fetches nothing from the host itself (no
-// indices, or every table STAGED).
+// The counters of a forward of no indices (others publish in k_fetch).
 __global__ void k_fwd_finalize(DGlobal g, int64_t log_slot) {
     if (*g.err) return;
     publish_forward(g, log_slot);

@@ -51,7 +51,7 @@ struct PoolLaunch {
 void launch_pool(const DGlobal &g, const int64_t *offsets, int32_t B, float *out, const int32_t *bstart,
                  const int32_t *btab, int32_t nt, const PoolLaunch *ls, int nl, hipEvent_t ev0, hipEvent_t ev1,
                  hipStream_t s);
-// the counters alone, for a forward that launches no fetch
+// the counters alone, for a forward of no indices
 void launch_fwd_finalize(const DGlobal &g, int64_t log_slot, hipStream_t s);
 
 // small.hip: forwards of few ids per table, one block per table.

@@ -33,7 +33,6 @@ constexpr int kMaxPasses = 6;                       // a key has at most 32 + 31
 static_assert(kMaxPasses * kRadixBits >= 63, "passes for the longest key");
 constexpr int32_t kEmpty = -1;                      // map key of a never-used entry
 constexpr int32_t kTomb = -2;                       // map key of a deleted entry
-constexpr int32_t kPending = INT32_MIN;             // probe result before miss numbering
 
 // per-slot flag bits
 constexpr uint32_t F_PF = 1u;    // admitted by a prefetch and not accessed since
@@ -375,22 +374,8 @@ __device__ __forceinline__ int map_insert_n(const DTable &tb, const int32_t (&ro
 }
 static_assert(kEmpty == -1, "an empty map entry is all ones");
 
-// Delete a present row (distinct rows may be deleted concurrently).
-__device__ __forceinline__ void map_delete(const DTable &tb, int32_t row) {
-    const int32_t mask = tb.map_mask;
-    uint32_t i = hash_row(row) & (uint32_t)mask;
-    for (int32_t n = 0; n <= mask; ++n) {
-        int32_t k = tb.map[i].x;
-        if (k == row) {
-            tb.map[i].x = kTomb;
-            return;
-        }
-        if (k == kEmpty) return;
-        i = (i + 1) & (uint32_t)mask;
-    }
-}
-
-// The same for the Q rows with `want`, their first probes in flight together.
+// Delete the Q present rows with `want` (distinct rows may be deleted
+// concurrently), their first probes in flight together.
 template <int Q>
 __device__ __forceinline__ void map_delete_n(const DTable &tb, const int32_t (&row)[Q], const bool (&want)[Q]) {
     const int32_t mask = tb.map_mask;

@@ -900,12 +900,17 @@ constexpr int kSmallBlocksLow = 8, kSmallBlocksHigh = kOwnSliceBlocks;  // bitma
 constexpr int kSmallBlocksPlc = 16;  // a placement's two bitmaps
 
 // Where one block per table is the faster form.  It saves the launches of three
-// kernels, about 12 us per forward, and pays for doing a table's work on one
-// CU: about 1.4 us per 1,000 ids of a table and 0.4 us per bitmap block more
-// than the general sequence (1, 8 and 26 tables of 10,000 .. 1,000,000 rows,
-// 2,000 .. 64,000 ids each: 8 tables of 100,000 rows take 26.4 against 39.7 us
-// at 2,000 ids each, 42.9 against 45.9 at 8,000, 62 against 50 at 16,000).  The
-// host knows only the mean of the tables' ids, and one table may hold nearly
+// kernels, 6 to 8 us per forward, and pays for doing a table's work on one CU.
+// Forwards of Zipf-distributed ids, 64 fp32 values per row, here and in the
+// general sequence:
+//   100,000 rows, 1 table: 2,000 ids 21 and 27 us, 4,000 28 and 29, 6,000 34 and 32,
+//     8,000 40 and 35
+//   100,000 rows, 8 tables: 2,000 each 25 and 31, 3,000 37 and 42, 4,000 49 and 51
+//   500,000 rows, 1 table: 1,000 24 and 27, 3,000 28 and 28, 6,000 34 and 28
+//   20,000 rows, 26 tables: 1,000 each 39 and 46
+// So one table crosses at some 4,500 ids (3,000 with 16 bitmap blocks) and the line
+// below lies past it, at a cost of up to 6 us: it was drawn when the general
+// sequence took longer.  The host knows only the mean of the tables' ids, and one table may hold nearly
 // all of them: the bound on the total keeps that case's loss to some 30 us.
 #ifndef RECMG_SMALL_MAX
 #define RECMG_SMALL_MAX 32768
