@@ -230,7 +230,7 @@ __device__ __forceinline__ void publish_forward(const DGlobal &g, int64_t log_sl
 #define RECMG_FETCH_BLOCKS 96
 #endif
 #ifndef RECMG_FETCH_BLOCKS_HUGE
-#define RECMG_FETCH_BLOCKS_HUGE 160
+#define RECMG_FETCH_BLOCKS_HUGE 288
 #endif
 constexpr int64_t kHugeFetchUnits = int64_t(1) << 25;  // 512 MiB in 16-byte units
 __global__ void __launch_bounds__(kBlock) k_fetch(DGlobal g, int64_t log_slot, int32_t nb,
@@ -893,9 +893,11 @@ void launch_fwd_src(const DGlobal &g, const int32_t *indices, int64_t n, hipStre
 // blocks): 96 is best with 32-way sets (k_sa_place's critical path runs
 // alongside) and within 1% of the best without prefetch.  From 512 MiB on the
 // fetch shares the link with a large fill for most of a step and takes
-// RECMG_FETCH_BLOCKS_HUGE: configuration 5 (750 MB), 768 fill blocks: 96 blocks
-// 83.4 ms per step, 112 82.5, 128 82.2, 160 82.2, 192 82.3, 256 82.4 (a step that
-// fetches some 270 MB: 7.49 ms with the two larger counts, 7.31 without).  The
+// RECMG_FETCH_BLOCKS_HUGE.  Configuration 5 with 768 fill blocks, ms per step, fully
+// associative (750 MB fetched beside a 3.8 GB fill) and with 32-way sets (more
+// fetched than filled): 96 blocks 83.4 and 42.2, 112 82.4 .. 84.6 and 42.7, 160 82.2
+// and 43.5, 224 82.4 and 42.5, 256 82.4 .. 82.9 and 42.0, 288 82.4 and 41.7.  (A step
+// that fetches some 270 MB: 7.49 ms with larger counts, 7.31 with 96 and 512.)  The
 // kernel knows how much it copies; the grid holds the larger count.
 void launch_fetch(const DGlobal &g, bool copies, int64_t log_slot, const int32_t *indices, int64_t n, hipStream_t s,
                   hipEvent_t ev0, hipEvent_t ev1) {

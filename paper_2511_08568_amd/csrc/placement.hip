@@ -707,8 +707,9 @@ void launch_plc_fill(const DGlobal &g, const int64_t *fdesc, int phase, hipStrea
     // shares the link with the next forward's fetch of about 330,000 misses
     // (85 MB), and 256 blocks gave +4% (512: -6%).  On configuration 5 the
     // fetch moves about 750 MB per batch beside a 3.8 GB fill for most of the
-    // step: 768 blocks with the fetch's 160 (see launch_fetch) 82.2 ms per step,
-    // 512 and 96 blocks 83.7, 256 and 96 85.9, 1,024 and 96 84.0.  The grid holds
+    // step: 768 blocks with the fetch's 288 (see launch_fetch) 82.4 ms per step,
+    // 512 and 96 blocks 83.7, 256 and 96 85.9, 1,024 and 96 84.0; with 32-way sets
+    // 41.7, 43.6 with 512 and 96.  The grid holds
     // the largest count; k_plc_end writes how many of its blocks copy.
     // STAGED fills copy within HBM and take a full grid.
     const int blocks = phase == FILL_STAGED ? kStagedFillBlocks : kFillGridBlocks;
